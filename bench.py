@@ -17,7 +17,8 @@ timed on a bounded sample of the same workload, and the parity of one GPU iterat
 roofline.frac is the fraction of the resource that binds: for the memory-bound kernels the bytes HBM really moved per
 launch (rocprofv3 FETCH_SIZE + WRITE_SIZE of the same kernel and work split, profiles/hbm_traffic.json) over the
 kernel's time, against 8 TB/s; the algorithmic bytes (every holder's read of a row charged) are reported beside it as
-algorithmic_GBps / algorithmic_ratio and exceed the peak where holders share one fetch.
+algorithmic_GBps / algorithmic_ratio and exceed the peak where holders share a row's fetch and its sums.  What stage 1 takes when
+every holder does its own arithmetic is in config.stage1_every_holder_ms.
 """
 from __future__ import annotations
 
@@ -54,9 +55,12 @@ def log(msg: str) -> None:
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
+SPLITS = ["equal_ranges", "row_cells", "shared_cells", "rows_once"]
+
+
 def split_signature(info) -> str:
     """What identifies the kernel and work split a traffic record belongs to."""
-    kind = ["equal_ranges", "row_cells", "shared_cells"][info.split_kind] if info.split_kind >= 0 else "none"
+    kind = SPLITS[info.split_kind] if info.split_kind >= 0 else "none"
     return f"{kind}:{info.split_value}:team{info.stage1_team_size}x{info.stage1_teams_per_group}:staged{info.stage1_staged}"
 
 
@@ -131,6 +135,27 @@ def cpu_baseline_aggregation(cfg, slabs_host_cols, cols, mask, g_gpu_cols, d):
     return {"value": (len(cols) / d) / elapsed, "unit": "iterations/s", "cores": 1, "kind": "oracle",
             "sample": f"{len(cols)} of {d} columns of one encode+decode (all {len(slabs)} slabs, every message), scaled to one iteration",
             "seconds": elapsed}, parity
+
+
+def every_holder_ms(cfg, X_dev, y_dev, w_dev) -> float:
+    """Stage-1 milliseconds (median of 5 launches) when every holder of a row does its own arithmetic on it (row cells): what the
+    redundancy of the scheme costs, where the default split forms the holders' common sums once."""
+    import paper_1902_01981_amd as cr
+
+    plan = cr.cr_plan_ex(cfg["L"], cfg["n"], cfg["s"], cfg["m"], cfg["d"], model=cfg["model"], x_dtype=cfg["x_dtype"])
+    row_bytes = cfg["d"] * (2 if cfg["x_dtype"] else 4)
+    visits = cr.cr_plan_info(plan).row_visits
+    cell = min(min(512, max(96, ((2 << 20) // row_bytes + 16) // 32 * 32)), max(16, (visits // 2048 + 15) // 16 * 16))
+    cr.cr_plan_set_split(plan, cr.CR_SPLIT_ROW_CELLS, cell)
+    ws = cr.Workspace(plan)
+    cr.cr_partial_grads(plan, X_dev, y_dev, w_dev)
+    cr.cr_profile_enable(plan, 1 << cr.CR_K_PARTIAL_GRADS)
+    for _ in range(5):
+        cr.cr_partial_grads(plan, X_dev, y_dev, w_dev)
+    ms = float(np.median(cr.cr_profile_samples(plan, cr.CR_K_PARTIAL_GRADS)))
+    cr.cr_plan_destroy(plan)
+    del ws
+    return ms
 
 
 _DATA_CACHE = {}
@@ -252,6 +277,7 @@ def run_workload(name: str, steps: int, warmup: int, cpu_budget: float, args) ->
     avg_s = dk["ms"]["avg"] * 1e-3
     signature = split_signature(info) if not aggregate else "encode"
     traffic, traffic_source = load_traffic(name, signature)
+    holder_ms = every_holder_ms(cfg, X_dev, y_dev, w_dev) if not aggregate and s > 0 else None
     # yardstick: what a plain streaming read of the same buffer reaches on this device right now
     big = G_dev if aggregate else X_dev
     sink = torch.empty(16384, dtype=torch.float32, device="cuda")
@@ -265,8 +291,8 @@ def run_workload(name: str, steps: int, warmup: int, cpu_budget: float, args) ->
            "stream_read_GBps": stream_gbps}
     common = {"kernel": dominant, "kernel_ms": dk["ms"], "algorithmic_bytes_per_launch": dk["algorithmic_bytes_per_launch"],
               "algorithmic_GBps": dk["algorithmic_GBps"], "algorithmic_ratio": dk["algorithmic_GBps"] / HBM_PEAK_GBPS}
-    if not aggregate and cfg["x_dtype"] == wl.BF16:
-        # bf16 rows: stage 1 is bound by vector-ALU issue (a widening operation and two multiply-adds per element), not by memory:
+    if not aggregate and cfg["x_dtype"] == wl.BF16 and info.split_kind in (cr.CR_SPLIT_EQUAL_RANGES, cr.CR_SPLIT_ROW_CELLS) and s > 0:
+        # bf16 rows, every holder's arithmetic done separately (--teams, --cell-rows): stage 1 is bound by vector-ALU issue (a widening operation and two multiply-adds per element), not by memory:
         # 4 flop per element of X visited, against the vector peak of the instructions this build issues
         flops = 4.0 * info.row_visits * d
         achieved = flops / avg_s / 1e12
@@ -324,8 +350,11 @@ def run_workload(name: str, steps: int, warmup: int, cpu_budget: float, args) ->
                    "workers": info.num_workers, "slabs": info.num_slabs, "row_visits": info.row_visits,
                    "computation_load": info.r_cr, "rows_per_worker": [info.min_rows, info.max_rows],
                    "stage1_teams": info.num_teams, "stage1_pieces": info.num_pieces, "code_gamma": info.gamma,
-                   "stage1_split": ["equal_ranges", "row_cells", "shared_cells"][info.split_kind] if info.split_kind >= 0 else None,
-                   "stage1_split_value": info.split_value, "stage1_team_size": info.stage1_team_size,
+                   "stage1_split": SPLITS[info.split_kind] if info.split_kind >= 0 else None,
+                   "stage1_split_value": info.split_value,
+                   "stage1_arithmetic": None if aggregate else "every holder" if s > 0 and info.split_kind in (cr.CR_SPLIT_EQUAL_RANGES, cr.CR_SPLIT_ROW_CELLS)
+                   else "every row once, for all its holders",
+                   "stage1_every_holder_ms": holder_ms, "stage1_team_size": info.stage1_team_size,
                    "stage1_holders_per_workgroup": info.stage1_teams_per_group if info.stage1_staged else 1,
                    "l2_domains": info.l2_domains, "l2_sharing_checked": info.l2_sharing, "split_signature": signature},
         "roofline": roofline,
@@ -409,7 +438,7 @@ def main() -> int:
         # Section III-C's comparison of computation loads on configuration 2's data (20 workers, one straggler in four tolerated)
         out["computation_load_comparison"] = {
             k: {"scheme": label, "load_r": records[k]["config"]["computation_load"], "iterations_per_s": records[k]["value"],
-                "stage1_ms": records[k]["roofline"]["kernel_ms"]["avg"], "algorithmic_bytes_per_launch": records[k]["roofline"]["algorithmic_bytes_per_launch"],
+                "stage1_ms": records[k]["roofline"]["kernel_ms"]["avg"], "stage1_every_holder_ms": records[k]["config"]["stage1_every_holder_ms"], "algorithmic_bytes_per_launch": records[k]["roofline"]["algorithmic_bytes_per_launch"],
                 "traffic_frac_of_peak": records[k]["roofline"].get("traffic_frac_of_peak")}
             for k, label in (("umw20", "uncoded master-worker, r = 1/N"), ("cfg2", "CodedReduce (4,2) tree, r = r_CR"), ("gc20", "gradient coding, r = (S+1)/N"))
             if k in records}

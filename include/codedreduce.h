@@ -67,15 +67,15 @@ typedef struct cr_plan_info {
     int32_t num_decode_rows; /* F = C(n,s) */
     int32_t code_candidate;  /* index of the winning candidate of the code search; -1 if B was supplied; -2 fractional repetition */
     int32_t num_teams;       /* stage-1 work split (0 until known, see cr_plan_set_split) */
-    int32_t num_pieces;      /* stage-1 partial rows (0 until the split is known) */
+    int32_t num_pieces;      /* entries of cr_plan_get_pieces (0 until the split is known) */
     int32_t split_kind;      /* enum cr_split of the split in force; -1 until it is known */
     int32_t stage1_team_size;       /* threads that share one row in the stage-1 kernel in force; 0: two-pass path for very wide rows */
-    int32_t stage1_teams_per_group; /* teams (holders) per workgroup of that kernel */
-    int32_t stage1_staged;   /* 1 if that kernel fetches rows once per workgroup into LDS */
+    int32_t stage1_teams_per_group; /* teams per workgroup; shared cells: holders of a cell that a workgroup serves */
+    int32_t stage1_staged;   /* 1 under shared cells: rows are fetched once per workgroup for all the holders it serves */
     int64_t m, d;
     int64_t row_visits;      /* sum over workers of allocated rows */
     int64_t min_rows, max_rows; /* smallest / largest per-worker load; both equal r_CR m up to integer cuts (Theorem 1) */
-    int64_t split_value;     /* teams (equal ranges) or rows per cell (row cells, shared cells); 0 until the split is known */
+    int64_t split_value;     /* teams (equal ranges), rows per cell (row cells, shared cells) or rows per fp32 sum (rows once); 0 until the split is known */
     double gamma;            /* max_f sum_i |a_fi| ||b_i||_2 / sqrt(n): rounding amplification of one decode.  Messages are fp32, so
                               * a decoded gradient carries a relative rounding error of about gamma^L * 2^-24 (see code_warning) */
     double r_cr;             /* computation load of Theorem 1 */
@@ -117,26 +117,30 @@ int cr_plan_get_segments(const cr_plan_t *plan, int64_t *row_begin, int64_t *row
 /* decode row for one sibling group (Section III-A, CR.Execute step 3): flags[j] != 0 marks child j a straggler.  With fewer than
  * s stragglers the set is padded with the highest-index survivors.  a: host, n doubles.  CR_E_UNDECODABLE if more than s are set. */
 int cr_plan_decode_row(const cr_plan_t *plan, const uint8_t *flags /* host, n */, double *a);
-/* Stage-1 work split into pieces (a piece = a run of one slab's rows handled by one team; it owns one d-float partial row).
+/* Stage-1 work split into pieces (a piece = a run of one slab's rows handled by one team).
  *   CR_SPLIT_EQUAL_RANGES  value = teams: the row visits of all slabs, slab-major, are cut into `teams` equal contiguous ranges,
  *                          cut again at slab boundaries.
  *   CR_SPLIT_ROW_CELLS     value = rows per cell: every slab is cut on one global grid of that many rows, one piece per team, teams
  *                          ordered by cell so that the holders of the same rows run at the same time.
  *   CR_SPLIT_SHARED_CELLS  value = most rows per cell: the grid is laid between slab boundaries, so every holder of a cell holds
- *                          all of it; 2, 3, 4 or 8 holders (by row width and by (s+1)^L, the most holders a row can have) share a
- *                          workgroup, which fetches each row once into LDS for all of them; each still does all of its own
- *                          arithmetic.  One workgroup per compute unit works through a queue of cells (a team then runs
- *                          several pieces).  fp32 rows of 257 to 3072 16-byte chunks with s > 0 only, else CR_E_INVAL.  Rows of
- *                          1537 to 2558 whole chunks (d a multiple of 4) held by 3 or more workers go straight from HBM into LDS
- *                          (no registers on the way in), 3, 4 or 6 holders per workgroup.  Rows that a single workgroup reads are
- *                          fetched with the non-temporal hint (they stream past the caches) when X has 1 GiB or more.
- * Default (when this is never called): with s = 0 (no row is held twice) equal ranges, one per resident workgroup; else shared
- * cells where that kernel exists and the problem has at least 16 rows per compute unit and workgroup, with the cell height
- * (16 to 1024 rows) that gives the shortest longest queue; else row cells of about 2 MB of X (96 to 512 rows, fewer for
- * small problems).  CR_E_STATE once a workspace is bound. */
-enum cr_split { CR_SPLIT_EQUAL_RANGES = 0, CR_SPLIT_ROW_CELLS = 1, CR_SPLIT_SHARED_CELLS = 2 };
+ *                          all of it; a workgroup works through a queue of cells (one queue per compute unit, two for rows of at
+ *                          most 8 KB) and forms every row of a cell once for the 2, 3, 4, 6 or 8 holders it serves
+ *                          (stage1_teams_per_group, by row width and by (s+1)^L, the most holders a row can have) -- and for the
+ *                          others, if a cell has more.  fp32 rows of 257 to 3072 16-byte chunks with s > 0 only, else CR_E_INVAL.
+ *   CR_SPLIT_ROWS_ONCE     value = most rows in one fp32 sum, rounded up to an even number of the kernel's steps (sums are added up in fp64): X is
+ *                          cut into one or two contiguous parts per compute unit, a part into runs at slab boundaries; a workgroup
+ *                          forms every row of its part once, for all slabs that hold it.  Rows that fit the registers of a
+ *                          workgroup (d <= 24576), else CR_E_INVAL.
+ * With the first two every holder of a row does its own arithmetic on it, as separate workers would: they are there to measure what
+ * the redundancy of a scheme costs.  With the other two the holders' identical sums are formed once and handed to every slab they
+ * belong to.  The slab gradients agree to rounding under every split.
+ * Default (when this is never called): rows once, or, for the smallest problems, a workgroup per distinct slab range.  With X of 1 GiB
+ * and more: equal ranges of the rows when s = 0 (no row is held twice), shared cells where one workgroup serves all holders of a
+ * row, with the cell height (16 to 1024 rows) that gives the shortest longest queue.  Rows wider than 24576 columns: row cells. */
+enum cr_split { CR_SPLIT_EQUAL_RANGES = 0, CR_SPLIT_ROW_CELLS = 1, CR_SPLIT_SHARED_CELLS = 2, CR_SPLIT_ROWS_ONCE = 3 };
 int cr_plan_set_split(cr_plan_t *plan, int kind, int64_t value);
-/* pieces in execution order: piece i is rows [row_begin[i], row_end[i]) of slab[i], run by team[i]; num_pieces entries each, any may be NULL */
+/* pieces in execution order: piece i is rows [row_begin[i], row_end[i]) of slab[i], run by team[i] (rows once: by workgroup team[i],
+ * one piece for every slab the rows belong to); num_pieces entries each, any may be NULL */
 int cr_plan_get_pieces(const cr_plan_t *plan, int32_t *slab, int64_t *row_begin, int64_t *row_end, int32_t *team);
 
 /* ---- run-time model (host only; Section III-C "Latency Performance", eq. (5), Theorem 2) ------------------------------------
@@ -152,7 +156,7 @@ int cr_simulate_iteration(const cr_plan_t *plan, double a, double mu, double t_c
                           uint8_t *mask, double *ready, double *total);
 
 /* ---- device binding --------------------------------------------------------------------------------------------
- * The workspace holds the device tables, 16 encode programs, the stage-1 piece partials, the slab gradients
+ * The workspace holds the device tables, 16 encode programs, the stage-1 partial rows, the slab gradients
  * G[S][d] (not for CR_AGGREGATE_ONLY) and the messages M[N][d], all fp32 rows of d floats.  dev_ptr must be 256-byte aligned and stay valid while the plan
  * is used; hip_stream is a hipStream_t (NULL = the default stream).  cr_bind_workspace copies the tables synchronously. */
 int cr_workspace_bytes(cr_plan_t *plan, size_t *bytes);
@@ -161,10 +165,9 @@ int cr_bind_workspace(cr_plan_t *plan, void *dev_ptr, size_t bytes, void *hip_st
 /* ---- the hot path ------------------------------------------------------------------------------------------------
  * cr_partial_grads (CR.Execute step 1): for every slab p,  G[p] = X[b:e]^T (phi(X[b:e] w) - y[b:e]),  phi = identity or sigmoid.
  *   X_dev  m x d row-major, contiguous, fp32 or bf16 per the plan, 16-byte aligned;  y_dev m floats;  w_dev d floats.
- *   Every holder of a row does all of its own arithmetic on it (the redundancy is the method) in one pass over its rows, as long
- *   as a row fits the registers of one team (d <= 24576, whether or not d is a multiple of the 16-byte chunk); wider rows take
- *   two passes.  Holders of the same rows are scheduled together, so that one fetch from HBM serves them all: through the L2
- *   (row cells) or, with shared cells, once per workgroup through LDS (see cr_plan_set_split).
+ *   One pass over X as long as a row fits the registers of a workgroup (d <= 24576, whether or not d is a multiple of the 16-byte
+ *   chunk); wider rows take two passes.  Every slab of every worker is written; what the workers that hold a row have in common is
+ *   formed once for all of them unless the split says otherwise (see cr_plan_set_split).
  * cr_load_partial_grads: use caller-supplied slab gradients G_dev[S][d] (fp32, 16-byte aligned) in place of stage 1;
  *   the buffer is read in place by cr_encode_tree and must stay valid until then.
  * cr_encode_tree (CR.Execute steps 2-5): mask is HOST memory, N bytes, non-zero = straggler.  For every non-straggler node,

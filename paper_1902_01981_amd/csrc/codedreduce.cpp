@@ -63,11 +63,16 @@ struct cr_plan_s {
     std::vector<cr::Slab> slabs;
     std::vector<int32_t> node_slab_begin;          // N+1
     int64_t row_visits = 0, min_rows = 0, max_rows = 0;
+    int64_t max_holders = 1;                       // most workers that hold a row: (s+1)^L, capped at 64
     mutable std::unordered_map<uint64_t, std::vector<double>> row_cache;   // padded straggler bitmask -> decode row
 
     // stage-1 split
-    const cr::Stage1Variant *variant = nullptr;        // the stage-1 kernel in use (nullptr: two-pass path for very wide rows)
-    const cr::Stage1Variant *variant_regs = nullptr, *variant_staged = nullptr;   // what exists for (x_dtype, d)
+    const cr::OnceVariant *once = nullptr;             // the stage-1 kernel in use: every row once ...
+    const cr::Stage1Variant *variant = nullptr;        // ... or, where this is not null, every holder's rows (both null: two-pass path)
+    const cr::OnceVariant *once_variant = nullptr;     // what exists for (x_dtype, d)
+    const cr::Stage1Variant *variant_regs = nullptr;
+    int cell_holders = 0;            // holders a workgroup of the shared-cells split serves; 0: no such split for this type and width
+    cr::OnceWork work;               // `once`: the runs and sums behind the split
     bool rows_as_buffers = false;    // every row starts on a 4-byte boundary and every piece has fewer than 2^31 bytes
     int split_kind = -1;                            // -1: choose from the device when the workspace is sized
     int64_t split_value = 0;
@@ -83,12 +88,15 @@ struct cr_plan_s {
     char *ws = nullptr;
     size_t ws_bytes = 0;
     cr::DevPiece *d_pieces = nullptr;
-    int32_t *d_team_piece_begin = nullptr, *d_slab_piece_begin = nullptr, *d_slab_pieces = nullptr;
-    int32_t *d_group_item_begin = nullptr, *d_item_pieces = nullptr;   // shared queues only
+    int32_t *d_team_piece_begin = nullptr;
+    cr::DevRun *d_parts = nullptr, *d_runs = nullptr;
+    cr::DevSum *d_sums = nullptr;
+    int32_t *d_dst = nullptr;
+    int num_sums = 0;
     uint32_t *d_placement = nullptr;               // kPlacementSlots words: where the workgroups of a probe launch ran
     char *d_program = nullptr;                     // kProgramSlots encode programs (each with its root decode terms)
     size_t program_bytes = 0;                      // size of one
-    float *d_partial = nullptr, *d_G = nullptr, *d_M = nullptr, *d_residuals = nullptr;   // residuals: wide-row path only
+    float *d_G = nullptr, *d_M = nullptr, *d_residuals = nullptr;   // d_G: the output table, slabs then partial rows; residuals: wide-row path only
     const float *G_src = nullptr;                  // slabs the encode reads: d_G or the caller's buffer
     char *h_staging = nullptr;                     // pinned, kStagingHalves * kProgramSlots * program_bytes
     hipEvent_t staging_done[kStagingHalves] = {};
@@ -96,6 +104,9 @@ struct cr_plan_s {
     int staging_next = 0;
     int dec_slot = 0;                              // program slot whose decode terms cr_decode_root uses
     // layout of the program block (offsets in bytes, fixed per plan)
+    // layout of the workspace (offsets in bytes)
+    size_t at_pieces = 0, at_team_piece_begin = 0, at_parts = 0, at_runs = 0, at_sums = 0, at_dst = 0, at_placement = 0, at_program = 0,
+           at_G = 0, at_residuals = 0, at_M = 0;
     size_t off_slab = 0, off_level = 0, off_row = 0, off_coef = 0, off_acoef = 0, off_sub = 0, off_dec = 0;
     size_t max_terms = 0;
     int num_dec_terms = 0;
@@ -115,7 +126,12 @@ struct cr_plan_s {
 namespace {
 
 int64_t elem_size(const cr_plan_t *p) { return p->x_dtype == CR_BF16 ? 2 : 4; }
-constexpr int64_t kStreamFromBytes = int64_t(1) << 30;      // four times the last-level cache: nothing of X survives an iteration
+// X is read past the caches (non-temporal hint) from the size of the last-level cache on.  Below it X may survive there from one
+// iteration to the next if its lines are allowed to (200 MB read again and again: 31.0 us with plain loads, 32.6 with the hint);
+// above it the hint wins either way (300 MB: 49.6 against 46.8 us, 800 MB: 136 against 118).
+constexpr int64_t kStreamFromBytes = int64_t(256) << 20;
+// The default splits of large data (see ensure_split)
+constexpr int64_t kLargeBytes = int64_t(1) << 30;
 
 // decode row for one group under rule "pad with the highest-index survivors"; returns CR_E_UNDECODABLE if more than s flags are set
 int group_decode_row(const cr_plan_t *p, const uint8_t *flags, const double **row)
@@ -152,23 +168,70 @@ int query_l2_domains()
     return kDefaultL2Domains;
 }
 
-// Workgroup slots of a staged kernel: one per compute unit of the current device (a multiple of the L2 domains; MI355X's 256
-// without a device).  Rows of at most 8 KB get two per unit where registers and LDS let two workgroups stay resident: their steps
-// are short, and the second workgroup fills the gaps around the first one's barriers (measured +10 to +16 % at 2048 columns;
-// longer rows gain nothing).
-int unit_slots(const cr::Stage1Variant *v, int64_t row_bytes, int64_t d, int domains)
+// Compute units of the current device (MI355X's 256 without one).
+int query_units()
 {
-    int dev = 0, cus = 0, resident = 0;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus >= domains) {
-        int slots = cus / domains * domains;
-        if (v && row_bytes <= 8192 && cr::prepare_stage1(*v, d) == hipSuccess &&
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, v->fn[0], v->block(), v->lds_bytes(d)) == hipSuccess && resident >= 2)
-            slots *= 2;
-        (void)hipGetLastError();
-        return slots;
-    }
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) return cus;
     (void)hipGetLastError();
-    return kDefaultUnits / domains * domains;
+    return kDefaultUnits;
+}
+
+// Workgroup slots of the shared-cells split: one per compute unit of the current device (a multiple of the L2 domains), two for rows
+// of at most 8 KB (MI355X's 256 without a device).
+int unit_slots(int64_t row_bytes, int domains)
+{
+    int count = 0;
+    const bool device = hipGetDeviceCount(&count) == hipSuccess && count > 0;
+    (void)hipGetLastError();
+    const int slots = std::max(query_units(), domains) / domains * domains;
+    return device && row_bytes <= 8192 ? 2 * slots : slots;
+}
+
+// Shared cells group the holders of a row by workgroup: how many of the up to max_holders (s+1)^L holders one workgroup serves.
+// fp32 rows of 257 to 3072 chunks; 0 where there is no such split.
+int shared_cell_holders(int x_dtype, int64_t d, int64_t max_holders)
+{
+    const int64_t nq = (d + 3) / 4;
+    if (x_dtype != CR_F32 || nq <= 256 || nq > 3072) return 0;
+    if (nq > 1536 && nq <= 2558 && d % 4 == 0 && max_holders >= 3) {
+        if ((max_holders == 5 || max_holders == 6) && nq <= 2557) return 6;
+        return (max_holders + 3) / 4 < (max_holders + 2) / 3 ? 4 : 3;      // whichever takes fewer workgroups per row
+    }
+    if (max_holders >= 5 && nq <= 1024) return 8;
+    return max_holders >= 3 && nq <= 1536 ? 4 : 2;
+}
+
+// rows added up in fp32, per accumulator at most `rows_per_sum`: an even number of the kernel's steps
+int32_t chunk_rows(const cr::OnceVariant *v, int64_t rows_per_sum)
+{
+    const int64_t rows = std::min<int64_t>(rows_per_sum * v->sums_per_workgroup(), int64_t(1) << 30), steps = 2 * v->rows_per_step;
+    return static_cast<int32_t>((rows + steps - 1) / steps * steps);
+}
+
+// Rows one after the other along X, every row once, on every compute unit: the parts of the default split.
+void make_rows_once(cr_plan_t *p, int64_t rows_per_sum, bool may_take_whole_ranges)
+{
+    const cr::OnceVariant *v = p->once_variant;
+    if (may_take_whole_ranges) {
+        // Small problems: a workgroup per distinct slab range forms its gradient whole, which saves the launch that adds up partial
+        // rows.  The line is where the two take the same time, at about 48 Ki elements in the longest range (fp32, a (3,2) tree, us
+        // whole / parts and sum: 200 x 100 elements 5.6 / 7.5, 667 x 100 9.0 / 8.2; 67 x 1000 6.3 / 7.5, 200 x 1000 12.2 / 7.8).
+        const cr::OnceVariant *whole = cr::select_once_whole(p->x_dtype, p->d);
+        int64_t longest = 0;
+        for (const cr::Slab &sl : p->slabs) longest = std::max(longest, sl.row_end - sl.row_begin);
+        if (longest * p->d <= 48 * 1024 && longest <= chunk_rows(whole, rows_per_sum)) {
+            p->once = whole;
+            cr::once_whole_ranges(p->slabs, chunk_rows(whole, rows_per_sum), p->work);
+            return;
+        }
+    }
+    p->once = v;
+    // small problems: no fewer rows per part than a workgroup takes in a step, two where the whole workgroup shares a row (the
+    // partial rows of shorter parts cost more than the extra workgroups bring)
+    const int64_t least = v->threads_per_row <= 64 ? std::min(v->rows_per_step, 128) : 2;
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(static_cast<int64_t>(query_units()) * v->parts_per_unit, p->m / least));
+    cr::once_equal_parts(p->slabs, p->m, parts, chunk_rows(v, rows_per_sum), p->work);
 }
 
 int ensure_split(cr_plan_t *p)
@@ -176,88 +239,73 @@ int ensure_split(cr_plan_t *p)
     if (!p->split.pieces.empty() || p->model == CR_AGGREGATE_ONLY) return CR_OK;
     int kind = p->split_kind;
     int64_t value = p->split_value;
-    p->variant = p->variant_regs;
+    p->variant = nullptr;
+    p->once = nullptr;
+    p->work = cr::OnceWork();
     const int domains = query_l2_domains();
     p->l2_domains = domains;
     p->unit_slots = 0;
     p->l2_sharing = -1;
-    if (kind < 0 && p->s == 0) {
-        // no redundancy (every row has one holder): nothing to share, so one contiguous range per resident workgroup streams best
-        int dev = 0, cus = 0, per_cu = 0;
-        int slots = 2 * 256;                                // MI355X: 256 CUs, two resident workgroups each; refined if a device is present
-        if (p->variant && hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, p->variant->fn[0], p->variant->block(), 0) == hipSuccess && cus > 0 && per_cu > 0)
-            slots = cus * per_cu;
-        else
-            (void)hipGetLastError();                        // no device: keep the default and clear the error
-        kind = CR_SPLIT_EQUAL_RANGES;
-        value = static_cast<int64_t>(slots) * (p->variant ? p->variant->teams_per_block() : 1);
+    const bool chosen_here = kind < 0;
+    const bool large = p->m * p->d * elem_size(p) >= kLargeBytes;
+    if (kind < 0 && !p->once_variant) {
+        // rows too wide for the single-pass kernels: cells of about 2 MB of X, at most 512 rows, at least 16 so that there are a few
+        // thousand pieces to spread over the chip
+        kind = CR_SPLIT_ROW_CELLS;
+        value = std::min<int64_t>(96, std::max<int64_t>(16, (p->row_visits / 2048 + 15) / 16 * 16));
     }
-    // small problems (under 16 rows per compute unit and workgroup) do not repay the staged kernel's start-up: row cells below
-    if (kind < 0 && p->variant_staged && p->row_visits / p->variant_staged->teams_per_block() >= 256 * 16) {
-        // Rows staged through LDS: one workgroup per compute unit, each with a queue of cells (see split_shared_queues); the
-        // launch lasts as long as the longest queue.  Take the cell height, 16 to 1024 rows in steps of 8, that makes it
-        // shortest; ties go to the taller cell (fewer partial rows).
+    if (kind < 0 && large && p->s == 0) {
+        // no row is held twice: equal ranges of the rows are equal ranges of the row visits
+        kind = CR_SPLIT_EQUAL_RANGES;
+        value = static_cast<int64_t>(query_units()) * p->once_variant->parts_per_unit;
+    }
+    if (kind < 0 && large && p->cell_holders >= p->max_holders) {
+        // All holders of a cell in one workgroup, cells between slab boundaries, one queue of cells per compute unit.  The launch
+        // lasts as long as the longest queue: take the cell height, 16 to 1024 rows in steps of 8, that makes it shortest; ties go
+        // to the taller cell (fewer partial rows).
         kind = CR_SPLIT_SHARED_CELLS;
-        const int tpb = p->variant_staged->teams_per_block();
-        const int slots = unit_slots(p->variant_staged, p->d * elem_size(p), p->d, domains);
+        const int slots = unit_slots(p->d * elem_size(p), domains);
         value = 512;
-        if (p->row_visits / tpb / 64 <= (int64_t(1) << 16)) {       // with longer queues than that the last round no longer matters
+        if (p->row_visits / p->cell_holders / 64 <= (int64_t(1) << 16)) {       // with longer queues than that the last round no longer matters
             int64_t best = -1;
             cr::Split trial;
             for (int64_t c = 16; c <= 1024; c += 8) {
-                cr::split_shared_queues(p->slabs, c, domains, tpb, slots / domains, trial);
+                cr::split_shared_queues(p->slabs, c, domains, p->cell_holders, slots / domains, trial);
                 if (best < 0 || trial.makespan <= best) { best = trial.makespan; value = c; }
             }
         }
     }
     if (kind < 0) {
-        // default: row cells of about 2 MB of X, between 96 and 512 rows, a multiple of 32.  Long enough that the d-float partial
-        // row each piece writes is about a percent of what it reads, short enough that the holders of a cell stay in step and
-        // that the last cells do not leave the chip half empty (measured on configurations 2, 3 and 5).
-        kind = CR_SPLIT_ROW_CELLS;
-        const int64_t row_bytes = p->d * elem_size(p);
-        value = std::min<int64_t>(512, std::max<int64_t>(96, ((int64_t(2) << 20) / row_bytes + 16) / 32 * 32));
-        // small problems: shorter cells, so that there are a few thousand pieces to spread over the chip
-        value = std::min<int64_t>(value, std::max<int64_t>(16, (p->row_visits / 2048 + 15) / 16 * 16));
+        kind = CR_SPLIT_ROWS_ONCE;
+        value = p->once_variant->rows_per_sum;
     }
-    if (kind == CR_SPLIT_SHARED_CELLS) {
-        if (!p->variant_staged) return fail(CR_E_INVAL, "no kernel stages rows of this width and type through LDS");
-        p->variant = p->variant_staged;
-    }
-    const int teams_per_block = p->variant ? p->variant->teams_per_block() : 1;     // wide rows: one workgroup per piece
     p->split_kind_used = kind;
     p->split_value_used = value;
-    if (kind == CR_SPLIT_SHARED_CELLS) {
+    if (kind == CR_SPLIT_ROWS_ONCE) {
+        if (!p->once_variant) return fail(CR_E_INVAL, "rows of this width do not fit the single-pass kernels");
+        if (p->m / value + 2 * static_cast<int64_t>(p->slabs.size()) > (int64_t(1) << 26)) return fail(CR_E_INVAL, "too many partial rows");
+        make_rows_once(p, value, chosen_here);
+        cr::once_as_split(p->slabs, p->work, p->split);
+    } else if (kind == CR_SPLIT_SHARED_CELLS) {
+        if (!p->cell_holders) return fail(CR_E_INVAL, "no shared cells for rows of this width and type");
         if (p->row_visits / value + 2 * static_cast<int64_t>(p->slabs.size()) > (int64_t(1) << 26)) return fail(CR_E_INVAL, "too many row cells");
-        p->unit_slots = unit_slots(p->variant, p->d * elem_size(p), p->d, domains);
-        cr::split_shared_queues(p->slabs, value, domains, teams_per_block, p->unit_slots / domains, p->split);
-        // what the staged kernel relies on: every piece of an item covers the same rows
-        const cr::Split &sp = p->split;
-        for (size_t it = 0; it * teams_per_block < sp.item_pieces.size(); ++it) {
-            const cr::Piece *first = nullptr;
-            for (int t = 0; t < teams_per_block; ++t) {
-                const int32_t pi = sp.item_pieces[it * teams_per_block + t];
-                if (pi < 0) continue;
-                const cr::Piece &pc = sp.pieces[pi];
-                if (first && (first->row_begin != pc.row_begin || first->row_end != pc.row_end)) {
-                    p->split = cr::Split();
-                    return fail(CR_E_STATE, "shared cells: the teams of a workgroup do not hold the same rows");
-                }
-                if (!first) first = &pc;
-            }
-        }
-    } else if (kind == CR_SPLIT_ROW_CELLS) {
-        if (p->row_visits / value + static_cast<int64_t>(p->slabs.size()) > (int64_t(1) << 26)) return fail(CR_E_INVAL, "too many row cells");
-        cr::split_row_cells(p->slabs, value, domains, teams_per_block, p->split);
-        if (!p->variant) {                                  // the wide-row kernels index pieces directly: no empty teams
-            cr::Split compact;
-            cr::split_row_cells(p->slabs, value, 1, 1, compact);
-            p->split = compact;
-        }
+        p->unit_slots = unit_slots(p->d * elem_size(p), domains);
+        cr::split_shared_queues(p->slabs, value, domains, p->cell_holders, p->unit_slots / domains, p->split);
+        p->once = p->once_variant;
+        cr::once_of_queues(p->slabs, p->split, p->cell_holders, chunk_rows(p->once, p->once->rows_per_sum), p->work);
+    } else if (kind == CR_SPLIT_EQUAL_RANGES && chosen_here) {
+        make_rows_once(p, p->once_variant->rows_per_sum, false);
+        cr::once_as_split(p->slabs, p->work, p->split);
     } else {
-        const int teams = static_cast<int>(std::min<int64_t>(value, std::max<int64_t>(1, p->row_visits)));
-        cr::split_equal_ranges(p->slabs, teams, p->split);
+        p->variant = p->variant_regs;
+        const int teams_per_block = p->variant ? p->variant->teams_per_block() : 1;     // wide rows: one workgroup per piece
+        if (kind == CR_SPLIT_ROW_CELLS) {
+            if (p->row_visits / value + static_cast<int64_t>(p->slabs.size()) > (int64_t(1) << 26)) return fail(CR_E_INVAL, "too many row cells");
+            // the wide-row kernels index pieces directly: no empty teams
+            cr::split_row_cells(p->slabs, value, p->variant ? domains : 1, teams_per_block, p->split);
+        } else {
+            cr::split_equal_ranges(p->slabs, static_cast<int>(std::min<int64_t>(value, std::max<int64_t>(1, p->row_visits))), p->split);
+        }
     }
     return CR_OK;
 }
@@ -265,6 +313,8 @@ int ensure_split(cr_plan_t *p)
 void compute_layout(cr_plan_t *p, size_t *total)
 {
     const size_t S = p->slabs.size(), N = p->tree.N, P = p->split.pieces.size();
+    const size_t runs = p->work.runs.size(), parts = p->work.part_run_begin.empty() ? 0 : p->work.part_run_begin.size() - 1;
+    const size_t sums = p->once ? p->work.sums.size() : S, dst = p->once ? p->work.dst.size() : S;
     // worst case: one term per slab plus one dummy per node, each sub-program padded to the unroll
     p->max_terms = align_up(S + N + static_cast<size_t>(p->n) * cr::kEncodeUnroll, cr::kEncodeUnroll);
     size_t off = 0;
@@ -278,21 +328,21 @@ void compute_layout(cr_plan_t *p, size_t *total)
     p->program_bytes = off;
 
     size_t w = 0;
-    w = align_up(w + P * sizeof(cr::DevPiece), 256);
-    w = align_up(w + (p->split.teams + 1) * sizeof(int32_t), 256);
-    w = align_up(w + (S + 1) * sizeof(int32_t), 256);
-    w = align_up(w + P * sizeof(int32_t), 256);
-    w = align_up(w + p->split.group_item_begin.size() * sizeof(int32_t), 256);
-    w = align_up(w + p->split.item_pieces.size() * sizeof(int32_t), 256);
-    w = align_up(w + kPlacementSlots * sizeof(uint32_t), 256);
-    w = align_up(w + kProgramSlots * p->program_bytes, 256);
+    auto take = [&](size_t bytes) { const size_t at = w; w = align_up(w + bytes, 256); return at; };
+    p->at_pieces = take(p->once ? 0 : P * sizeof(cr::DevPiece));
+    p->at_team_piece_begin = take(p->once ? 0 : (p->split.teams + 1) * sizeof(int32_t));
+    p->at_parts = take(parts * sizeof(cr::DevRun));
+    p->at_runs = take(runs * sizeof(cr::DevRun));
+    p->at_sums = take(p->model == CR_AGGREGATE_ONLY ? 0 : sums * sizeof(cr::DevSum));
+    p->at_dst = take(p->model == CR_AGGREGATE_ONLY ? 0 : dst * sizeof(int32_t));
+    p->at_placement = take(kPlacementSlots * sizeof(uint32_t));
+    p->at_program = take(kProgramSlots * p->program_bytes);
     const size_t row = static_cast<size_t>(p->d) * sizeof(float);
     if (p->model != CR_AGGREGATE_ONLY) {
-        w = align_up(w + P * row, 256);
-        w = align_up(w + S * row, 256);
-        if (!p->variant) w = align_up(w + static_cast<size_t>(p->row_visits) * sizeof(float), 256);
+        p->at_G = take((S + (p->once ? p->work.partials : P)) * row);
+        p->at_residuals = take(p->once || p->variant ? 0 : static_cast<size_t>(p->row_visits) * sizeof(float));
     }
-    w = align_up(w + N * row, 256);
+    p->at_M = take(N * row);
     *total = w;
 }
 
@@ -416,10 +466,9 @@ int cr_plan_ex(int L, int n, int s, int64_t m, int64_t d, int model, int x_dtype
         if (p->slabs.size() > (size_t(1) << 30)) { delete p; return fail(CR_E_INVAL, "too many slabs"); }
         if (model != CR_AGGREGATE_ONLY) {
             p->variant_regs = cr::select_stage1(x_dtype, d);          // nullptr: rows too wide for one team's registers, two-pass path
-            int64_t max_holders = 1;                                  // a leaf's rows sit in s+1 workers of every level above it
-            for (int l = 0; l < L && max_holders < 64; ++l) max_holders *= s + 1;
-            p->variant_staged = s > 0 ? cr::select_stage1_staged(x_dtype, d, max_holders) : nullptr;   // nullptr: no such kernel for this width
-            p->variant = p->variant_regs;
+            p->once_variant = cr::select_once(x_dtype, d);
+            for (int l = 0; l < L && p->max_holders < 64; ++l) p->max_holders *= s + 1;     // a leaf's rows sit in s+1 workers of every level above it
+            p->cell_holders = s > 0 ? shared_cell_holders(x_dtype, d, p->max_holders) : 0;
         }
     } catch (const std::bad_alloc &) {
         delete p;
@@ -456,9 +505,11 @@ int cr_plan_info(const cr_plan_t *p, cr_plan_info_t *info)
     const bool split_known = !p->split.pieces.empty();
     info->split_kind = split_known ? p->split_kind_used : -1;
     info->split_value = split_known ? p->split_value_used : 0;
-    info->stage1_team_size = p->variant ? p->variant->team_size : 0;
-    info->stage1_teams_per_group = p->variant ? p->variant->teams_per_block() : 1;
-    info->stage1_staged = p->variant && p->variant->staged ? 1 : 0;
+    const bool cells = split_known && p->split_kind_used == CR_SPLIT_SHARED_CELLS;
+    const cr::OnceVariant *once = p->once ? p->once : split_known ? nullptr : p->once_variant;
+    info->stage1_team_size = once ? once->threads_per_row : p->variant ? p->variant->team_size : 0;
+    info->stage1_teams_per_group = cells ? p->cell_holders : once ? once->block / once->threads_per_row : p->variant ? p->variant->teams_per_block() : 1;
+    info->stage1_staged = cells ? 1 : 0;
     info->m = p->m; info->d = p->d;
     info->row_visits = p->row_visits;
     info->min_rows = p->min_rows; info->max_rows = p->max_rows;
@@ -516,7 +567,7 @@ int cr_plan_decode_row(const cr_plan_t *p, const uint8_t *flags, double *a)
 int cr_plan_set_split(cr_plan_t *p, int kind, int64_t value)
 {
     if (!p) return fail(CR_E_INVAL, "NULL plan");
-    if (kind != CR_SPLIT_EQUAL_RANGES && kind != CR_SPLIT_ROW_CELLS && kind != CR_SPLIT_SHARED_CELLS) return fail(CR_E_INVAL, "unknown split kind");
+    if (kind < CR_SPLIT_EQUAL_RANGES || kind > CR_SPLIT_ROWS_ONCE) return fail(CR_E_INVAL, "unknown split kind");
     if (value < 1) return fail(CR_E_INVAL, "split value must be >= 1");
     if (kind == CR_SPLIT_EQUAL_RANGES && value > (int64_t(1) << 24)) return fail(CR_E_INVAL, "too many teams");
     if (p->bound) return fail(CR_E_STATE, "the work split cannot change once a workspace is bound");
@@ -570,61 +621,65 @@ int cr_bind_workspace(cr_plan_t *p, void *dev_ptr, size_t bytes, void *hip_strea
     compute_layout(p, &need);
     if (bytes < need) return fail(CR_E_INVAL, "workspace too small");
     if (p->bound) CR_HIP(hipStreamSynchronize(p->stream));
-    if (p->variant) {
-        int dev = 0, lds = 0;
-        CR_HIP(hipGetDevice(&dev));
-        CR_HIP(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-        if (p->variant->lds_bytes(p->d) > static_cast<size_t>(lds)) return fail(CR_E_INVAL, "the stage-1 kernel needs more LDS per workgroup than this device has");
-        CR_HIP(cr::prepare_stage1(*p->variant, p->d));
-    }
     p->stream = static_cast<hipStream_t>(hip_stream);
     p->ws = static_cast<char *>(dev_ptr);
     p->ws_bytes = bytes;
 
-    const size_t S = p->slabs.size(), N = p->tree.N, P = p->split.pieces.size();
-    const size_t row = static_cast<size_t>(p->d) * sizeof(float);
-    size_t w = 0;
-    p->d_pieces = reinterpret_cast<cr::DevPiece *>(p->ws + w);             w = align_up(w + P * sizeof(cr::DevPiece), 256);
-    p->d_team_piece_begin = reinterpret_cast<int32_t *>(p->ws + w);        w = align_up(w + (p->split.teams + 1) * sizeof(int32_t), 256);
-    p->d_slab_piece_begin = reinterpret_cast<int32_t *>(p->ws + w);        w = align_up(w + (S + 1) * sizeof(int32_t), 256);
-    p->d_slab_pieces = reinterpret_cast<int32_t *>(p->ws + w);             w = align_up(w + P * sizeof(int32_t), 256);
-    p->d_group_item_begin = reinterpret_cast<int32_t *>(p->ws + w);        w = align_up(w + p->split.group_item_begin.size() * sizeof(int32_t), 256);
-    p->d_item_pieces = reinterpret_cast<int32_t *>(p->ws + w);             w = align_up(w + p->split.item_pieces.size() * sizeof(int32_t), 256);
-    p->d_placement = reinterpret_cast<uint32_t *>(p->ws + w);              w = align_up(w + kPlacementSlots * sizeof(uint32_t), 256);
-    p->d_program = p->ws + w;                                              w = align_up(w + kProgramSlots * p->program_bytes, 256);
-    p->d_partial = nullptr; p->d_G = nullptr;
-    if (p->model != CR_AGGREGATE_ONLY) {
-        p->d_partial = reinterpret_cast<float *>(p->ws + w);               w = align_up(w + P * row, 256);
-        p->d_G = reinterpret_cast<float *>(p->ws + w);                     w = align_up(w + S * row, 256);
-        if (!p->variant) { p->d_residuals = reinterpret_cast<float *>(p->ws + w); w = align_up(w + static_cast<size_t>(p->row_visits) * sizeof(float), 256); }
-    }
-    p->d_M = reinterpret_cast<float *>(p->ws + w);                         w = align_up(w + N * row, 256);
+    const int32_t S = static_cast<int32_t>(p->slabs.size()), P = static_cast<int32_t>(p->split.pieces.size());
+    p->d_pieces = reinterpret_cast<cr::DevPiece *>(p->ws + p->at_pieces);
+    p->d_team_piece_begin = reinterpret_cast<int32_t *>(p->ws + p->at_team_piece_begin);
+    p->d_parts = reinterpret_cast<cr::DevRun *>(p->ws + p->at_parts);
+    p->d_runs = reinterpret_cast<cr::DevRun *>(p->ws + p->at_runs);
+    p->d_sums = reinterpret_cast<cr::DevSum *>(p->ws + p->at_sums);
+    p->d_dst = reinterpret_cast<int32_t *>(p->ws + p->at_dst);
+    p->d_placement = reinterpret_cast<uint32_t *>(p->ws + p->at_placement);
+    p->d_program = p->ws + p->at_program;
+    const bool stage1 = p->model != CR_AGGREGATE_ONLY;
+    p->d_G = stage1 ? reinterpret_cast<float *>(p->ws + p->at_G) : nullptr;
+    p->d_residuals = stage1 ? reinterpret_cast<float *>(p->ws + p->at_residuals) : nullptr;
+    p->d_M = reinterpret_cast<float *>(p->ws + p->at_M);
     p->G_src = p->d_G;
 
-    if (P > 0) {
+    std::vector<cr::DevSum> sums;
+    std::vector<int32_t> dst;
+    if (p->once) {
+        std::vector<cr::DevRun> runs, parts;
+        for (const cr::RowRun &r : p->work.runs) runs.push_back({r.row_begin, static_cast<int32_t>(r.row_end - r.row_begin), r.dst_begin, r.dst_end, 0, 0, 0});
+        for (size_t b = 0; b + 1 < p->work.part_run_begin.size(); ++b) {
+            cr::DevRun part = runs[p->work.part_run_begin[b]];           // the part's first run, so that one load starts a workgroup
+            part.more_begin = p->work.part_run_begin[b] + 1;
+            part.more_end = p->work.part_run_begin[b + 1];
+            parts.push_back(part);
+        }
+        for (const cr::RowSum &sum : p->work.sums) sums.push_back({sum.row_begin, sum.row_end, sum.dst_begin, sum.dst_end});
+        dst = p->work.dst;
+        CR_HIP(hipMemcpy(p->d_parts, parts.data(), parts.size() * sizeof(cr::DevRun), hipMemcpyHostToDevice));
+        CR_HIP(hipMemcpy(p->d_runs, runs.data(), runs.size() * sizeof(cr::DevRun), hipMemcpyHostToDevice));
+    } else if (stage1) {
+        // every piece's partial row lies where its slab's sum reads it: slab by slab, in row order
+        std::vector<int32_t> out_row(P);
+        for (int32_t i = 0; i < P; ++i) out_row[p->split.slab_pieces[i]] = S + i;
         std::vector<cr::DevPiece> hp(P);
         int64_t visit = 0, longest = 0;
-        for (size_t i = 0; i < P; ++i) longest = std::max(longest, p->split.pieces[i].row_end - p->split.pieces[i].row_begin);
+        for (int32_t i = 0; i < P; ++i) longest = std::max(longest, p->split.pieces[i].row_end - p->split.pieces[i].row_begin);
         p->rows_as_buffers = (p->d * elem_size(p)) % 4 == 0 && longest * p->d * elem_size(p) < (int64_t(1) << 31);
-        for (size_t i = 0; i < P; ++i) {
+        // a row that several holders fetch is left in the caches for them; with no redundancy a large X streams past
+        const int32_t shared = p->s > 0 || p->m * p->d * elem_size(p) < kStreamFromBytes ? 1 : 0;
+        for (int32_t i = 0; i < P; ++i) {
             const int64_t rows = p->split.pieces[i].row_end - p->split.pieces[i].row_begin;
-            // shared cells know which of them several workgroups fetch; under the other splits a row is fetched by each of its holders
-            // ... and a data matrix of a few hundred megabytes stays in the last-level cache (256 MB on MI355X) from one iteration
-            // to the next if its lines are allowed to: only larger ones are streamed past the caches
-            const bool streams = p->m * p->d * elem_size(p) >= kStreamFromBytes;
-            const int32_t shared = !streams ? 1 : p->split_kind_used == CR_SPLIT_SHARED_CELLS ? p->split.pieces[i].shared : (p->s > 0 ? 1 : 0);
-            hp[i] = {p->split.pieces[i].row_begin, visit, static_cast<int32_t>(rows), p->split.pieces[i].slab, shared, 0};
+            hp[i] = {p->split.pieces[i].row_begin, visit, static_cast<int32_t>(rows), p->split.pieces[i].slab, shared, out_row[i]};
             visit += rows;
+        }
+        for (int32_t q = 0; q < S; ++q) {
+            sums.push_back({S + p->split.slab_piece_begin[q], S + p->split.slab_piece_begin[q + 1], q, q + 1});
+            dst.push_back(q);
         }
         CR_HIP(hipMemcpy(p->d_pieces, hp.data(), P * sizeof(cr::DevPiece), hipMemcpyHostToDevice));
         CR_HIP(hipMemcpy(p->d_team_piece_begin, p->split.team_piece_begin.data(), (p->split.teams + 1) * sizeof(int32_t), hipMemcpyHostToDevice));
-        CR_HIP(hipMemcpy(p->d_slab_piece_begin, p->split.slab_piece_begin.data(), (S + 1) * sizeof(int32_t), hipMemcpyHostToDevice));
-        CR_HIP(hipMemcpy(p->d_slab_pieces, p->split.slab_pieces.data(), P * sizeof(int32_t), hipMemcpyHostToDevice));
-        if (!p->split.item_pieces.empty()) {
-            CR_HIP(hipMemcpy(p->d_group_item_begin, p->split.group_item_begin.data(), p->split.group_item_begin.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-            CR_HIP(hipMemcpy(p->d_item_pieces, p->split.item_pieces.data(), p->split.item_pieces.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-        }
     }
+    p->num_sums = static_cast<int>(sums.size());
+    if (!sums.empty()) CR_HIP(hipMemcpy(p->d_sums, sums.data(), sums.size() * sizeof(cr::DevSum), hipMemcpyHostToDevice));
+    if (!dst.empty()) CR_HIP(hipMemcpy(p->d_dst, dst.data(), dst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     p->l2_sharing = -1;
     if (P > 0 && (p->split_kind_used == CR_SPLIT_ROW_CELLS || p->split_kind_used == CR_SPLIT_SHARED_CELLS)) {
         int rc = check_l2_sharing(p);
@@ -647,27 +702,26 @@ int cr_partial_grads(cr_plan_t *p, const void *X, const float *y, const float *w
     if (p->model == CR_AGGREGATE_ONLY) return fail(CR_E_STATE, "aggregation-only plan: use cr_load_partial_grads");
     if (reinterpret_cast<uintptr_t>(X) % 16 != 0) return fail(CR_E_INVAL, "X must be 16-byte aligned");
     const int64_t S = static_cast<int64_t>(p->slabs.size()), P = static_cast<int64_t>(p->split.pieces.size());
+    const int logistic = p->model == CR_LOGISTIC ? 1 : 0;
     {
         // what the method must move: every holder reads its rows and targets once, each slab gradient is written once
         const int64_t bytes = p->row_visits * p->d * elem_size(p) + p->row_visits * 4 + S * p->d * 4 + p->d * 4;
         LaunchTimer t(p, CR_K_PARTIAL_GRADS, bytes);
-        if (p->variant && p->variant->staged) {
-            CR_HIP(cr::launch_partial_grads_staged(*p->variant, X, y, w, p->d_pieces, p->d_group_item_begin, p->d_item_pieces,
-                                                   static_cast<int>(p->split.group_item_begin.size()) - 1, p->d_partial, p->d,
-                                                   p->model == CR_LOGISTIC ? 1 : 0, p->stream));
+        if (p->once) {
+            CR_HIP(cr::launch_rows_once(*p->once, X, y, w, p->d_parts, static_cast<int>(p->work.part_run_begin.size()) - 1, p->d_runs, p->d_dst,
+                                        p->d_G, p->d, p->work.chunk, logistic, p->m * p->d * elem_size(p) >= kStreamFromBytes, p->stream));
         } else if (p->variant) {
-            CR_HIP(cr::launch_partial_grads(*p->variant, X, y, w, p->d_pieces, p->d_team_piece_begin, p->split.teams, p->d_partial, p->d,
-                                            p->model == CR_LOGISTIC ? 1 : 0, p->rows_as_buffers, p->stream));
+            CR_HIP(cr::launch_partial_grads(*p->variant, X, y, w, p->d_pieces, p->d_team_piece_begin, p->split.teams, p->d_G, p->d, logistic,
+                                            p->rows_as_buffers, p->stream));
         } else {
-            CR_HIP(cr::launch_residuals(p->x_dtype, X, y, w, p->d_pieces, static_cast<int>(P), p->d_residuals, p->d,
-                                        p->model == CR_LOGISTIC ? 1 : 0, p->stream));
-            CR_HIP(cr::launch_xt_residuals(p->x_dtype, X, p->d_pieces, static_cast<int>(P), p->d_residuals, p->d_partial, p->d, p->stream));
+            CR_HIP(cr::launch_residuals(p->x_dtype, X, y, w, p->d_pieces, static_cast<int>(P), p->d_residuals, p->d, logistic, p->stream));
+            CR_HIP(cr::launch_xt_residuals(p->x_dtype, X, p->d_pieces, static_cast<int>(P), p->d_residuals, p->d_G, p->d, p->stream));
         }
         t.done();
     }
-    {
-        LaunchTimer t(p, CR_K_REDUCE_PIECES, (P + S) * p->d * 4);
-        CR_HIP(cr::launch_reduce_pieces(p->d_partial, p->d_slab_piece_begin, p->d_slab_pieces, static_cast<int>(S), p->d_G, p->d, p->stream));
+    if (p->num_sums > 0) {
+        LaunchTimer t(p, CR_K_REDUCE_PIECES, ((p->once ? p->work.partials : P) + S) * p->d * 4);
+        CR_HIP(cr::launch_sum_rows(p->d_G, p->d_sums, p->num_sums, p->d_dst, p->d, p->stream));
         t.done();
     }
     p->G_src = p->d_G;

@@ -12,7 +12,21 @@ struct DevPiece {            // one stage-1 work item: rows [row_begin, row_begi
     int32_t nrows;
     int32_t slab;
     int32_t shared;          // 1: other workgroups fetch these rows at the same time, so the fetch should leave them in the L2
-    int32_t reserved;
+    int32_t out_row;         // row of the output table that receives the piece's gradient
+};
+
+// Output table of stage 1: rows of d floats, first the slab gradients G[0 .. S), then the partial rows.
+struct DevRun {              // rows [row_begin, row_begin + nrows) of X, formed once; the result goes to rows dst[dst_begin .. dst_end)
+    int64_t row_begin;
+    int32_t nrows;
+    int32_t dst_begin, dst_end;
+    int32_t more_begin, more_end;   // in the part table: the part's further runs, runs[more_begin .. more_end)
+    int32_t pad;
+};
+
+struct DevSum {              // rows dst[dst_begin .. dst_end) = sum of rows [row_begin, row_end)
+    int32_t row_begin, row_end;
+    int32_t dst_begin, dst_end;
 };
 
 // Encode program: a post-order list of terms, stored as parallel arrays so that a wavefront fetches kEncodeUnroll terms with a few
@@ -37,52 +51,51 @@ struct DecTerm {             // g += coef * M[row]
 constexpr int kEncodeUnroll = 8;   // encode sub-programs are padded to a multiple of this many terms
 constexpr int kMaxLevels = 8;
 
-// Stage-1 kernel variant chosen for (x_dtype, d): team size, chunks per thread, rows per step, teams per workgroup.
-// A `staged` variant fetches each row once per workgroup into LDS, from where all its teams (holders of the same rows) read it.
+// Stage-1 kernels that do every holder's work separately: team size, chunks per thread, rows per step, teams per workgroup.
 struct Stage1Variant {
     int xd, vec, team_size, k, rows, tpb;
-    bool staged;
     const void *fn[2];               // phi = identity, phi = sigmoid
-    int ring = 0;                    // > 0: rows reach LDS by direct global-to-LDS loads into a ring of `ring` rows
-    int w_in_lds = 0;                // 1: the weights sit in LDS behind the ring (one more row of LDS)
     const void *fn_buffers[2] = {nullptr, nullptr};   // the same kernel fetching rows with buffer loads (see launch_partial_grads)
-    int holders_per_team = 1;        // 2: every team of threads works for two of the tpb holders of an item, one after the other
-    int block() const { return team_size * tpb / holders_per_team; }
+    int block() const { return team_size * tpb; }
     int teams_per_block() const { return tpb; }
-    // dynamic LDS the launch needs for rows of d columns (0 for variants that keep rows in registers only)
-    size_t lds_bytes(int64_t d) const;
 };
-
-constexpr size_t kLdsPerWorkgroup = 160 * 1024;   // gfx950
-
 // Returns nullptr if (x_dtype, d) is outside what the single-pass register kernels cover.
 const Stage1Variant *select_stage1(int x_dtype, int64_t d);
-// The LDS-staged kernel for rows held by up to max_holders workers each, or nullptr if there is none for this type and width.
-// Rows of 1537 to 2558 whole 16-byte chunks (fp32, d a multiple of 4) held by three or more workers get the kernel that loads
-// straight into LDS, three or four holders per workgroup.
-const Stage1Variant *select_stage1_staged(int x_dtype, int64_t d, int64_t max_holders);
-// Once per variant and device before the first launch (raises the kernel's dynamic LDS limit where needed).
-hipError_t prepare_stage1(const Stage1Variant &v, int64_t d);
+
+// Stage-1 kernels that form every row once.
+struct OnceVariant {
+    int xd, vec, threads_per_row, k;
+    int rows_per_step;               // rows a workgroup takes per step
+    int block;                       // threads per workgroup
+    int parts_per_unit;              // contiguous parts of X per compute unit (see the kernels)
+    int rows_per_sum;                // most rows in one fp32 sum
+    const void *fn[2];               // plain loads, loads with the non-temporal hint
+    // fp32 accumulators per column that share the rows of a workgroup
+    int sums_per_workgroup() const { return threads_per_row <= 64 ? block / threads_per_row : 1; }
+};
+// For (x_dtype, d), or nullptr if the row is too wide for the registers of a workgroup.
+const OnceVariant *select_once(int x_dtype, int64_t d);
+// The same with as many wavefronts per workgroup as there are for rows this narrow, for launches of a few workgroups.
+const OnceVariant *select_once_whole(int x_dtype, int64_t d);
+// Workgroup b runs parts[b], then runs[parts[b].more_begin .. more_end).  rows: the output table.  chunk: an even number of steps; a
+// run of more rows has one destination per chunk of that many.
+hipError_t launch_rows_once(const OnceVariant &v, const void *X, const float *y, const float *w, const DevRun *parts, int num_parts,
+                            const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int chunk, int logistic,
+                            bool stream_past_caches, hipStream_t stream);
 
 // rows_as_buffers: every row starts on a 4-byte boundary and every piece has fewer than 2^31 bytes; variants that have a
 // buffer-load twin (bf16 rows, one wavefront per team) then run it
 hipError_t launch_partial_grads(const Stage1Variant &v, const void *X, const float *y, const float *w, const DevPiece *pieces,
-                                const int32_t *team_piece_begin, int num_teams, float *partial, int64_t d, int logistic,
+                                const int32_t *team_piece_begin, int num_teams, float *rows, int64_t d, int logistic,
                                 bool rows_as_buffers, hipStream_t stream);
-// Staged variants: workgroup g works through items [group_item_begin[g], group_item_begin[g+1]); item i hands team t of the
-// workgroup the piece item_pieces[i * teams_per_block + t] (or -1); all pieces of an item cover the same rows.
-hipError_t launch_partial_grads_staged(const Stage1Variant &v, const void *X, const float *y, const float *w, const DevPiece *pieces,
-                                       const int32_t *group_item_begin, const int32_t *item_pieces, int num_groups, float *partial,
-                                       int64_t d, int logistic, hipStream_t stream);
 // Wide rows (a row does not fit the registers of one team): two passes.  launch_residuals writes phi(x.w) - y for every row visit,
 // launch_xt_residuals forms X^T r per piece and block of 256*kWideChunks*vec columns.  X is read twice on this path.
 constexpr int kWideChunks = 8;
 hipError_t launch_residuals(int x_dtype, const void *X, const float *y, const float *w, const DevPiece *pieces, int num_pieces,
                             float *residuals, int64_t d, int logistic, hipStream_t stream);
-hipError_t launch_xt_residuals(int x_dtype, const void *X, const DevPiece *pieces, int num_pieces, const float *residuals, float *partial,
+hipError_t launch_xt_residuals(int x_dtype, const void *X, const DevPiece *pieces, int num_pieces, const float *residuals, float *rows,
                                int64_t d, hipStream_t stream);
-hipError_t launch_reduce_pieces(const float *partial, const int32_t *slab_piece_begin, const int32_t *slab_pieces, int num_slabs, float *G, int64_t d,
-                                hipStream_t stream);
+hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, const int32_t *dst, int64_t d, hipStream_t stream);
 hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int num_sub, int L, int64_t d, hipStream_t stream);
 // w != nullptr: also steps w <- w - lr g (g as stored, rounded to fp32) in the same launch
 hipError_t launch_decode(const float *M, float *g, const DecTerm *terms, int nterms, int64_t d, float *w, float lr, hipStream_t stream);

@@ -1,11 +1,11 @@
 // HIP kernels of the CodedReduce hot path for gfx950 (64-wide wavefronts).  Everything here is bandwidth bound (stage 1 on bf16
 // rows: bound by vector-ALU issue): plain vector FMAs, 16-byte coalesced loads, no matrix cores.
 //
-//   partial_grads_kernel   CR.Execute step 1: G_piece = X[b:e]^T (phi(X[b:e] w) - y[b:e]) in ONE pass over the rows
-//   partial_grads_staged_kernel   the same, with the rows fetched once per workgroup into LDS for several holders of those rows
-//   partial_grads_dma_kernel      the same, with the rows loaded from global memory straight into LDS (no registers on the way)
+//   rows_once_kernel, rows_once_team_kernel   CR.Execute step 1: X[b:e]^T (phi(X[b:e] w) - y[b:e]) in ONE pass over X, every row's
+//                          contribution formed once for all workers that hold it
+//   partial_grads_kernel   the same for every holder separately (the splits that lay out every holder's own work)
 //   residuals_kernel, xt_residuals_kernel   the same in two passes, for rows too wide for one team's registers
-//   reduce_pieces_kernel   sums the pieces of each slab (fixed order, so results are reproducible bit for bit)
+//   sum_rows_kernel        sums of partial rows (fixed order, so results are reproducible bit for bit)
 //   encode_kernel          CR.Execute steps 2-5: every node's message, children folded into parents in registers
 //   decode_kernel          the master's decode  g = sum_j a_j m_(1,j), optionally followed by w <- w - lr g in the same launch
 //   update_kernel, update_metrics_kernel    w <- w - lr g, optionally with the convergence measures of eq. (6) and (8)
@@ -21,6 +21,7 @@
 
 #include <atomic>
 #include <cstring>
+#include <iterator>
 #include <type_traits>
 
 namespace cr {
@@ -196,7 +197,7 @@ template <int XD, int VEC, int TS, int K, int R, bool LOGISTIC, bool BUF = false
 __global__ void __launch_bounds__((TS < 256 ? 256 : TS))
 partial_grads_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w,
                      const DevPiece *__restrict__ pieces, const int32_t *__restrict__ team_piece_begin, int num_teams,
-                     float *__restrict__ partial, int d, int nq)
+                     float *__restrict__ rows, int d, int nq)
 {
     using C = Chunk<XD, VEC>;
     using raw_t = typename C::raw_t;
@@ -347,422 +348,343 @@ partial_grads_kernel(const void *__restrict__ X, const float *__restrict__ y, co
                 }
             }
         }
-        float *out = partial + static_cast<int64_t>(p) * d;
+        float *out = rows + static_cast<int64_t>(pc.out_row) * d;
 #pragma unroll
         for (int k = 0; k < K; ++k)
             if (tl + k * TS < nq) store_row<VEC>(out + off[k], acc[k]);
     }
 }
 
-// ---- stage 1 with rows staged through LDS -----------------------------------------------------------------------------
-// The holders of a cell run the same rows.  Here H of them share a workgroup: its H*TS threads fetch every row once, pass it
-// through registers into LDS, and each team then reads the row from LDS and does its own dot product, residual and rank-1 update
-// exactly as above.  The L2 therefore serves a row once per workgroup instead of once per holder.
-// Software pipeline, one barrier per step of R rows: while step s is computed from one LDS buffer, step s+1 moves from registers
-// into the other buffer and the global loads of steps s+2 and s+3 are in flight in two register sets.
-// One workgroup per compute unit works through a queue of items (an item = one cell for up to H of its holders); all pieces of
-// an item must cover the same rows (cells cut at slab boundaries).  The weights are loaded once per workgroup.
-template <int XD, int VEC, int TS, int K, int R, int H, bool LOGISTIC>
-__global__ void __launch_bounds__(TS * H)
-partial_grads_staged_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w,
-                            const DevPiece *__restrict__ pieces, const int32_t *__restrict__ group_item_begin,
-                            const int32_t *__restrict__ item_pieces, float *__restrict__ partial, int d, int nq)
+// ---- stage 1, every row once ------------------------------------------------------------------------------------------
+// All holders of a row need the same thing of it, (phi(x.w) - y) x, so here it is formed once.  A *run* is a contiguous range of
+// rows that no slab begins or ends inside; its gradient goes to every row of the output table its destination list names: straight
+// into the slabs that consist of just this run, and into a partial row where larger slabs are summed from several runs
+// (sum_rows_kernel).  A workgroup owns one contiguous *part* of X -- in the default split the chip's compute units take one or two
+// parts each, so X is read as a few hundred long sequential streams with one wave of workgroups and few partial rows.
+// What bounds it is the read of X: 256 parts of one 4-wavefront workgroup each reach 7.0 to 7.1 TB/s on 3 GB of rows of 4096 to 10000
+// fp32 or 8192 bf16 values (a plain streaming read of the same buffer: 7.06), 512 parts 6.4 to 6.9, 768 parts and more 6.4 to 6.6;
+// rows of at most 256 chunks, one row per wavefront or less, do best with 512 (7.0 to 7.1 on 1000 fp32 or 1024 bf16 columns).
+// The rows of the next step are loaded before the current step is computed (two register sets).
+// NT: rows fetched with the non-temporal hint, for matrices larger than the last-level cache.
+
+// The plan's tables are written before the launch: read through the scalar cache, whatever the kernel stores meanwhile.
+template <typename T> using table_t = const __attribute__((address_space(4))) T *;
+template <typename T> __device__ __forceinline__ table_t<T> table(const T *p) { return (table_t<T>)(p); }
+struct Run { int64_t row_begin; int nrows, dst_begin, dst_end; };
+__device__ __forceinline__ Run read_run(table_t<DevRun> r) { return {r->row_begin, r->nrows, r->dst_begin, r->dst_end}; }
+
+// No more than this many rows are added up one by one in an fp32 accumulator; such sums are then added to each other (in fp32, up to
+// kFolds of them) or to other partial rows (in fp64).  Folding costs a second set of accumulators and nothing else; handing the
+// partial row over after 512 rows instead stalls all workgroups at once (252 000 x 4096 fp32: 611 us against 584).
+constexpr int kFoldRows = 512, kFolds = 8;
+
+// phi(z) - y; the choice is the same for the whole launch
+__device__ __forceinline__ float residual(float z, float y, int logistic) { return (logistic ? sigmoid(z) : z) - y; }
+
+// Sum over aligned groups of LPR lanes, delivered to every lane of the group, in vector operations only (no LDS round trip).
+template <int LPR> __device__ __forceinline__ float group_sum(float v)
 {
+    if constexpr (LPR >= 2) v = dpp_add<0xB1>(v);       // quad_perm [1,0,3,2]
+    if constexpr (LPR >= 4) v = dpp_add<0x4E>(v);       // quad_perm [2,3,0,1]
+    if constexpr (LPR >= 8) v = dpp_add<0x141>(v);      // row_half_mirror
+    if constexpr (LPR >= 16) v = dpp_add<0x140>(v);     // row_mirror
+    if constexpr (LPR >= 32) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(v), __float_as_int(v), false, false);
+        v = __int_as_float(r[0]) + __int_as_float(r[1]);
+    }
+    if constexpr (LPR >= 64) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(v), __float_as_int(v), false, false);
+        v = __int_as_float(r[0]) + __int_as_float(r[1]);
+    }
+    return v;
+}
+
+// Rows of at most 256 chunks.  LPR lanes share a row (64 / LPR rows side by side in a wavefront), lane t of them holding chunks t,
+// t + LPR, ... (K > 1 only with LPR = 64); a wavefront takes R such sets of rows per step.  No barrier until the sums of a run -- or
+// of `chunk` rows of a longer one -- are done; then the accumulators of the whole workgroup meet in LDS and are added up in fp64 and
+// rounded once.
+template <int XD, int VEC, int LPR, int K, int R, int WAVES, bool NT>
+__global__ void __launch_bounds__(WAVES * 64)
+rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w, const DevRun *__restrict__ parts,
+                 const DevRun *__restrict__ runs, const int32_t *__restrict__ dst, float *__restrict__ rows, int d, int nq, int chunk, int logistic)
+{
+    static_assert(K == 1 || LPR == 64, "several chunks per lane only for rows of more than 64 chunks");
+    static_assert(kFoldRows % (2 * R) == 0, "sums are folded after an even number of steps");
     using C = Chunk<XD, VEC>;
-    using raw_t = typename C::raw_t;
-    using lds_t = typename C::lds_t;
-    constexpr int BT = TS * H, WAVES = TS / 64, LPT = (K + H - 1) / H, ROW = LPT * BT;   // ROW chunks of LDS per staged row
-    extern __shared__ __align__(16) unsigned char smem[];
-    lds_t *stage = reinterpret_cast<lds_t *>(smem);                                       // [2][R][ROW]
-    float *red = reinterpret_cast<float *>(smem + sizeof(lds_t) * 2 * R * ROW);           // [H][2][R][WAVES]
-    const int tl = threadIdx.x % TS;
-    const int tib = __builtin_amdgcn_readfirstlane(threadIdx.x / TS);
-    const int wave = tl / 64;
+    constexpr int RPW = 64 / LPR, STEP = WAVES * R * RPW, THREADS = WAVES * 64;
+    // SETS sets of COLS accumulators each; where there are fewer columns than threads, GROUPS threads share a column
+    constexpr int SETS = WAVES * RPW, COLS = K * LPR * VEC, GROUPS = COLS < THREADS ? THREADS / COLS : 1;
+    __shared__ __align__(16) float comb[SETS][COLS];
+    __shared__ double comb2[GROUPS > 1 ? GROUPS : 1][GROUPS > 1 ? COLS : 1];
+    const int lane = threadIdx.x & 63, sub = lane / LPR, tl = lane % LPR;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const table_t<DevRun> part = table(parts) + blockIdx.x;
+    const int more = part->more_end;
+    int next = part->more_begin;
+    Run run = read_run(part);
 
-    // what the item in hand is: set at the top of the item loop below, read by the pipeline stages
-    DevPiece pc = {};                                   // the rows of the item (every team's piece of it has the same rows)
-    int my_piece = -1;                                  // this team's piece of the item, or -1: it then only helps to fetch
-    bool active = false;
-    int nsteps = 0;
-
-    // fetch role: thread g of the workgroup brings chunks g, g+BT, ... of every row
-    unsigned goff[LPT];
-#pragma unroll
-    for (int j = 0; j < LPT; ++j) goff[j] = chunk_offset<VEC>(threadIdx.x + j * BT, nq, d);
-    // compute role: as in the register-only kernel
+    unsigned off[K];                                     // first element of the lane's chunks
     float wv[K][VEC];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const int q = tl + k * TS;
-        const int o = chunk_offset<VEC>(q, nq, d);
+        const int q = tl + k * LPR;
+        off[k] = chunk_offset<VEC>(q, nq, d);
+        load_row<VEC>(w + off[k], wv[k]);
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            const float t = w[o + v];
-            wv[k][v] = chunk_owns<VEC>(q, v, nq, d) ? t : 0.f;
-        }
+        for (int v = 0; v < VEC; ++v) wv[k][v] = chunk_owns<VEC>(q, v, nq, d) ? wv[k][v] : 0.f;
     }
-    float acc[K][VEC];
 
-    // rows that other workgroups fetch as well are left in the L2 for them; rows only this workgroup reads stream past it
-    auto fetch = [&](raw_t (&P)[R][LPT], int step) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int rr = min(step * R + r, pc.nrows - 1);
-            const void *row = row_ptr<XD>(X, pc.row_begin + rr, d);
-            if (pc.shared) {
-#pragma unroll
-                for (int j = 0; j < LPT; ++j) P[r][j] = C::load(row, goff[j]);
-            } else {
-                asm volatile("; rows read once" ::: "memory");       // (the markers keep the two kinds of load from being merged into one)
-#pragma unroll
-                for (int j = 0; j < LPT; ++j) P[r][j] = C::load_once(row, goff[j]);
-                asm volatile("; rows read once" ::: "memory");
-            }
-        }
+    struct Step {
+        typename C::raw_t x[R][K];
+        float yy[R];
     };
-    auto park = [&](const raw_t (&P)[R][LPT], int buf) {
+    for (;;) {
+        const void *base = row_ptr<XD>(X, run.row_begin, d);
+        const float *yb = y + run.row_begin;
+        const int n = run.nrows;
+        float acc[K][VEC];
+        auto clear = [&](float (&s)[K][VEC]) {
 #pragma unroll
-        for (int r = 0; r < R; ++r)
+            for (int k = 0; k < K; ++k)
 #pragma unroll
-            for (int j = 0; j < LPT; ++j) stage[(buf * R + r) * ROW + threadIdx.x + j * BT] = __builtin_bit_cast(lds_t, P[r][j]);
-    };
-    // one step: rows step*R .. step*R+R-1 are in LDS buffer `cur`; `next` holds the rows of step+1 (loaded or still in flight)
-    auto step_fn = [&](int step, raw_t (&next)[R][LPT], int cur) {
-        park(next, cur ^ 1);
-        fetch(next, step + 3);                          // unconditional: the load queue then has a known depth at every wait
-        float pd[R], yy[R];
-        lds_t xr[R][K];
-        if (active) {
+                for (int v = 0; v < VEC; ++v) s[k][v] = 0.f;
+        };
+        auto fold = [&](float (&s)[K][VEC]) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) yy[r] = y[pc.row_begin + min(step * R + r, pc.nrows - 1)];   // asked for early, used after the barrier
+            for (int k = 0; k < K; ++k)
 #pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int k = 0; k < K; ++k) xr[r][k] = stage[(cur * R + r) * ROW + tl + k * TS];
+                for (int v = 0; v < VEC; ++v) s[k][v] += acc[k][v];
+        };
+        // rows past the end of the run re-read its last row; they count for nothing
+        auto load = [&](Step &s, int r0) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                float s[4] = {0.f, 0.f, 0.f, 0.f};       // four chains: a sum need not wait for the one before it
+                const int first = min(r0 + (wave * R + r) * RPW, n - 1);
+                const void *row = row_ptr<XD>(base, first, d);
+                const int mine = RPW == 1 ? first : min(first + sub, n - 1);
+                const unsigned rel = RPW == 1 ? 0u : static_cast<unsigned>(mine - first) * static_cast<unsigned>(d);
+                s.yy[r] = yb[mine];
+#pragma unroll
+                for (int k = 0; k < K; ++k) s.x[r][k] = NT ? C::load_once(row, rel + off[k]) : C::load(row, rel + off[k]);
+            }
+        };
+        auto compute = [&](const Step &s, int r0) {
+            float z[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float t = 0.f;
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     float xv[VEC];
-                    C::widen(__builtin_bit_cast(raw_t, xr[r][k]), xv);
+                    C::widen(s.x[r][k], xv);
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) s[k & 3] = fmaf(xv[v], wv[k][v], s[k & 3]);
+                    for (int v = 0; v < VEC; ++v) t = fmaf(xv[v], wv[k][v], t);
                 }
-                pd[r] = wave_sum<XD == 1>((s[0] + s[1]) + (s[2] + s[3]));
+                z[r] = group_sum<LPR>(t);
             }
-            if constexpr (WAVES > 1) {
-                if ((tl & 63) == 0) {
-#pragma unroll
-                    for (int r = 0; r < R; ++r) red[((tib * 2 + cur) * R + r) * WAVES + wave] = pd[r];
-                }
-            }
-        }
-        __syncthreads();
-        if (active) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                float z = pd[r];
-                if constexpr (WAVES > 1) {
-                    z = 0.f;
-#pragma unroll
-                    for (int i = 0; i < WAVES; ++i) z += red[((tib * 2 + cur) * R + r) * WAVES + i];
-                }
-                const int rr = step * R + r;
-                const float ph = LOGISTIC ? sigmoid(z) : z;
-                const float res = (rr < pc.nrows) ? ph - yy[r] : 0.f;
+                const int at = r0 + (wave * R + r) * RPW + (RPW == 1 ? 0 : sub);
+                const float res = at < n ? residual(z[r], s.yy[r], logistic) : 0.f;
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     float xv[VEC];
-                    C::widen(__builtin_bit_cast(raw_t, xr[r][k]), xv);
+                    C::widen(s.x[r][k], xv);
 #pragma unroll
                     for (int v = 0; v < VEC; ++v) acc[k][v] = fmaf(res, xv[v], acc[k][v]);
                 }
             }
-        }
-    };
-
-    // The workgroup works through its queue of items.  The last barrier of an item is behind every LDS read of it, so the next
-    // item's first buffer can be filled at once; loads still in flight for steps past its end land in registers nobody reads.
-    raw_t P0[R][LPT], P1[R][LPT];
-    const int item_end = group_item_begin[blockIdx.x + 1];
-    for (int item = group_item_begin[blockIdx.x]; item < item_end; ++item) {
-        int ref_piece = -1;
-        my_piece = -1;
+        };
+        auto store = [&](const float (&s)[K][VEC], int dst_begin, int dst_end) {
+            __syncthreads();                             // the sums stored before these have been read
 #pragma unroll
-        for (int t = 0; t < H; ++t) {
-            const int pi = item_pieces[item * H + t];
-            if (pi >= 0) {
-                if (ref_piece < 0) ref_piece = pi;
-                if (t == tib) my_piece = pi;
-            }
-        }
-        if (ref_piece < 0) continue;                    // a gap in the queue (the same for the whole workgroup)
-        pc = pieces[ref_piece];
-        active = my_piece >= 0;
-        nsteps = (pc.nrows + R - 1) / R;
+            for (int k = 0; k < K; ++k)
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[k][v] = 0.f;
-
-        fetch(P0, 0);
-        fetch(P1, 1);                                   // steps past the end re-read the last row; nothing is computed from them
-        park(P0, 0);
-        fetch(P0, 2);
-        __syncthreads();
-        int step = 0;
-        for (; step + 1 < nsteps; step += 2) {          // two steps per trip, so that register sets and LDS buffers are fixed at compile time
-            step_fn(step, P1, 0);
-            step_fn(step + 1, P0, 1);
-        }
-        if (step < nsteps) step_fn(step, P1, 0);
-        if (active) {
-            float *out = partial + static_cast<int64_t>(my_piece) * d;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int q = tl + k * TS;
-                if (q < nq) store_row<VEC>(out + chunk_offset<VEC>(q, nq, d), acc[k]);
-            }
-        }
-    }
-}
-
-// ---- stage 1 with rows loaded straight into LDS ------------------------------------------------------------------------
-// The same sharing for rows that start on 16-byte boundaries (fp32, d a multiple of 4), with the fetch done by the load-to-LDS form
-// of the global load (global_load_lds_dwordx4: lane l of a wavefront writes 16 bytes at LDS offset M0 + 16 l).  Nothing passes
-// through registers on its way in, which leaves room for a third holder per workgroup at 10 chunks per thread (168 registers at
-// 768 threads), and the depth of the prefetch is set by LDS alone: a ring of NB rows, one being computed, the others landed or in
-// flight.  One barrier per row:
-//     read row b from its ring slot into registers, dot products, park the partial dots in LDS
-//     wait until this wavefront's loads of row b+1 have landed (rows b+2 .. b+NB-1 stay in flight), barrier
-//     aim the loads of row b+NB at the slot of row b            (every team holds row b in registers)
-//     residuals and rank-1 updates of row b
-// The loads are written as inline assembly so that the compiler neither knows nor guesses which LDS bytes they touch: every wait is
-// written out with the number of loads that may stay in flight.  That count must be exact, so every wavefront issues the same
-// number of loads for every row, also past the end of its queue (it then re-fetches its last row into a slot nobody reads), and
-// the wavefront has no other vector loads in flight while the ring runs.  The fetch cursor runs through the whole queue of the
-// workgroup, so the pipeline does not drain between items.
-__device__ __forceinline__ void load_to_lds_16(const void *gptr, unsigned lds_offset)
-{
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_offset) : "memory", "m0");
-}
-// the same with the non-temporal hint: for rows that no other workgroup asks for, which then stream past the caches (a plain
-// read of a large buffer reaches 7.0 TB/s that way on this machine, 6.0 to 6.3 without the hint)
-__device__ __forceinline__ void load_to_lds_16_nt(const void *gptr, unsigned lds_offset)
-{
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gptr), "s"(lds_offset) : "memory", "m0");
-}
-// wait until at most N of this wavefront's vector memory loads are in flight (the other counters are left alone)
-template <int N> __device__ __forceinline__ void wait_loads()
-{
-    static_assert(N >= 0 && N < 64, "the counter has six bits");
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
-template <int TS, int K, int H, int NB, bool WL, int HPT, bool LOGISTIC>
-__global__ void __launch_bounds__(TS * H)
-partial_grads_dma_kernel(const void *__restrict__ Xv, const float *__restrict__ y, const float *__restrict__ w,
-                         const DevPiece *__restrict__ pieces, const int32_t *__restrict__ group_item_begin,
-                         const int32_t *__restrict__ item_pieces, float *__restrict__ partial, int d, int nq)
-{
-    constexpr int BT = TS * H, WAVES = TS / 64, LPT = (K + H - 1) / H;     // LPT loads per thread and row; (LPT - 1) * BT < nq always
-    static_assert((NB - 1) * LPT < 64, "the loads in flight per wavefront must fit the hardware counter");
-    static_assert(NB >= 2 && WAVES > 1, "a ring of at least two rows; teams of several wavefronts");
-    static_assert(HPT == 1 || (HPT == 2 && WL), "a team that works for two holders keeps two sets of accumulators: the weights must be in LDS");
-    constexpr int SLOTS = H * HPT;                          // holders per workgroup: team t works for holders t * HPT ... of an item
-    const float *X = static_cast<const float *>(Xv);
-    extern __shared__ __align__(16) unsigned char smem[];
-    f4a *ring = reinterpret_cast<f4a *>(smem);                                          // [NB][nq] chunks
-    f4a *wl = ring + NB * nq;                                                           // WL: the weights, [nq] chunks
-    float *red = reinterpret_cast<float *>(smem + sizeof(f4a) * (NB + (WL ? 1 : 0)) * nq);   // [SLOTS][2][WAVES]
-    const unsigned ring_lds = static_cast<unsigned>(reinterpret_cast<size_t>((__attribute__((address_space(3))) unsigned char *)smem));
-    const int tl = threadIdx.x % TS;
-    const int tib = __builtin_amdgcn_readfirstlane(threadIdx.x / TS);
-    const int wave = tl / 64;
-    const int wgwave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-
-    const int item_begin = group_item_begin[blockIdx.x], item_end = group_item_begin[blockIdx.x + 1];
-
-    // compute role, as in the kernels above: chunks tl, tl + TS, ... of a row; a chunk index past the row reads the row's last chunk
-    // with zero weights (K = ceil(nq / TS), so only a thread's last chunk can lie past the row)
-    // WL (1024 threads, so 128 registers each): the weights live in LDS behind the ring and are read per row like the row itself;
-    // only a thread's last chunk, the one that may need masking, keeps its weights in registers (wv[0])
-    constexpr int KW = WL ? 1 : K;
-    float wv[KW][4];
-    const int qlast = min(tl + (K - 1) * TS, nq - 1);
-#pragma unroll
-    for (int k = WL ? K - 1 : 0; k < K; ++k) {
-        const int q = k < K - 1 ? tl + k * TS : qlast;
-        const f4u t = *reinterpret_cast<const f4u *>(w + 4 * q);
-        const bool own = tl + k * TS < nq;
-        float(&dst)[4] = wv[WL ? 0 : k];
-        dst[0] = own ? t.x : 0.f; dst[1] = own ? t.y : 0.f; dst[2] = own ? t.z : 0.f; dst[3] = own ? t.w : 0.f;
-    }
-    if constexpr (WL) {
-        for (int q = threadIdx.x; q < nq; q += BT) {
-            const f4u t = *reinterpret_cast<const f4u *>(w + 4 * q);
-            f4a v; v.x = t.x; v.y = t.y; v.z = t.z; v.w = t.w;
-            wl[q] = v;                   // visible to the others after the barrier that follows the first fetches
-        }
-    }
-    float acc[HPT][K][4];
-#pragma unroll
-    for (int h = 0; h < HPT; ++h)
-#pragma unroll
-        for (int k = 0; k < K; ++k) acc[h][k][0] = acc[h][k][1] = acc[h][k][2] = acc[h][k][3] = 0.f;
-    __builtin_amdgcn_s_waitcnt(0);       // the weights are in: from here on the only vector loads of this wavefront are the ring's
-
-    // fetch role: thread t brings chunks t, t + BT, ... of every row.  Only the last of them can lie outside the row, and a whole
-    // wavefront may then have nothing to bring: it skips that load and counts one load fewer per row when it waits.
-    const bool last_any = (LPT - 1) * BT + wgwave * 64 < nq;                 // the same for the whole wavefront
-    const bool last_mine = (LPT - 1) * BT + static_cast<int>(threadIdx.x) < nq;
-
-    // cursors over the workgroup's queue: the fetch cursor runs NB rows ahead of the compute cursor
-    struct Cursor {
-        int item;           // index into the queue; item_end: past the end
-        int rows_left;      // rows of the current item not yet passed
-        int piece[HPT];     // compute cursor: this team's pieces of the item (-1: none); fetch cursor: [0] = any piece of the item
-        int shared;         // fetch cursor: do other workgroups fetch the item's rows too?
-        int64_t row;        // current row of X
-    };
-    auto enter = [&](Cursor &c, bool for_compute) {     // settle on the first item at or after c.item that has pieces
-        for (; c.item < item_end; ++c.item) {
-            int ref = -1, mine[HPT];
-#pragma unroll
-            for (int h = 0; h < HPT; ++h) mine[h] = -1;
-#pragma unroll
-            for (int t = 0; t < SLOTS; ++t) {
-                const int pi = item_pieces[c.item * SLOTS + t];
-                if (pi >= 0) {
-                    if (ref < 0) ref = pi;
-                    if (t / HPT == tib) mine[t % HPT] = pi;
-                }
-            }
-            if (ref < 0) continue;                          // a gap in the queue
-            const DevPiece pc = pieces[ref];                // every piece of an item covers the same rows
-            c.row = pc.row_begin;
-            c.rows_left = pc.nrows;
-#pragma unroll
-            for (int h = 0; h < HPT; ++h) c.piece[h] = for_compute ? mine[h] : ref;
-            c.shared = pc.shared;
-            return;
-        }
-    };
-    Cursor F, C;
-    F.item = C.item = item_begin;
-    F.rows_left = C.rows_left = 0;
-#pragma unroll
-    for (int h = 0; h < HPT; ++h) F.piece[h] = C.piece[h] = -1;
-    F.shared = C.shared = 1;
-    F.row = C.row = 0;
-    enter(F, false);
-    enter(C, true);
-    if (C.item >= item_end) return;                        // nothing queued (the same for the whole workgroup)
-
-    // loads of the row under the fetch cursor into ring slot `slot`; then the cursor moves on, staying on its last row once the
-    // queue is exhausted.  Rows that other workgroups fetch as well are left in the L2 for them; rows that only this workgroup
-    // reads stream past it.
-    auto issue = [&](int slot) {
-        const float *row = X + F.row * d;
-        const unsigned dst = ring_lds + 16u * static_cast<unsigned>(slot * nq + wgwave * 64);
-        if (F.shared) {
-#pragma unroll
-            for (int j = 0; j < LPT - 1; ++j) load_to_lds_16(row + 4 * (threadIdx.x + j * BT), dst + 16u * (j * BT));
-            if (last_any) {
-                if (last_mine) load_to_lds_16(row + 4 * (threadIdx.x + (LPT - 1) * BT), dst + 16u * ((LPT - 1) * BT));
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < LPT - 1; ++j) load_to_lds_16_nt(row + 4 * (threadIdx.x + j * BT), dst + 16u * (j * BT));
-            if (last_any) {
-                if (last_mine) load_to_lds_16_nt(row + 4 * (threadIdx.x + (LPT - 1) * BT), dst + 16u * ((LPT - 1) * BT));
-            }
-        }
-        if (F.rows_left > 1) { --F.rows_left; ++F.row; }
-        else {
-            Cursor N = F;
-            ++N.item;
-            enter(N, false);
-            if (N.item < item_end) F = N;
-        }
-    };
-    // wait until at most B of this wavefront's rows are still in flight
-    auto wait_for = [&](auto tag) {
-        constexpr int B = decltype(tag)::value;
-        if (last_any) wait_loads<B * LPT>(); else wait_loads<B * (LPT - 1)>();
-    };
-
-#pragma unroll
-    for (int i = 0; i < NB; ++i) issue(i);
-    wait_for(std::integral_constant<int, NB - 1>{});
-    __syncthreads();
-    int slot = 0, par = 0;
-    while (C.item < item_end) {                            // the items of the queue ...
-        bool has[HPT];
-        bool active = false;
-#pragma unroll
-        for (int h = 0; h < HPT; ++h) { has[h] = C.piece[h] >= 0; active = active || has[h]; }
-        int64_t row = C.row;
-        for (int left = C.rows_left; left > 0; --left, ++row) {         // ... and the rows of an item
-            float yy = 0.f;
-            f4a xr[K];
-            if (active) {
-                yy = y[row];
-#pragma unroll
-                for (int k = 0; k < K; ++k) xr[k] = ring[slot * nq + (k < K - 1 ? tl + k * TS : qlast)];
-#pragma unroll
-                for (int h = 0; h < HPT; ++h) {            // every holder forms its own dot product
-                    if (!has[h]) continue;
-                    float s = 0.f, s1 = 0.f;
-#pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        f4a wk;
-                        if (WL && k < K - 1) wk = wl[tl + k * TS];
-                        else { const float(&r)[4] = wv[WL ? 0 : k]; wk.x = r[0]; wk.y = r[1]; wk.z = r[2]; wk.w = r[3]; }
-                        if (k & 1) { s1 = fmaf(xr[k].x, wk.x, s1); s1 = fmaf(xr[k].y, wk.y, s1); s1 = fmaf(xr[k].z, wk.z, s1); s1 = fmaf(xr[k].w, wk.w, s1); }
-                        else { s = fmaf(xr[k].x, wk.x, s); s = fmaf(xr[k].y, wk.y, s); s = fmaf(xr[k].z, wk.z, s); s = fmaf(xr[k].w, wk.w, s); }
-                    }
-                    const float pd = wave_sum<false>(s + s1);
-                    if ((tl & 63) == 0) red[((tib * HPT + h) * 2 + par) * WAVES + wave] = pd;
-                }
-            }
-            wait_for(std::integral_constant<int, NB - 2>{});      // my part of the next row has landed; the barrier covers the others'
+                for (int v = 0; v < VEC; ++v) comb[wave * RPW + sub][(k * LPR + tl) * VEC + v] = s[k][v];
             __syncthreads();
-            issue(slot);                                         // every team holds this row in registers: its slot is free
-            if (active) {
+            auto put = [&](int c, double t) {
+                const float out = static_cast<float>(t);
+                const int col = chunk_offset<VEC>(c / VEC, nq, d) + c % VEC;
+                for (int j = dst_begin; j < dst_end; ++j) rows[static_cast<int64_t>(table(dst)[j]) * d + col] = out;
+            };
+            if constexpr (GROUPS > 1) {
+                const int c = threadIdx.x % COLS, g = threadIdx.x / COLS;
+                double t = 0.0;
 #pragma unroll
-                for (int h = 0; h < HPT; ++h) {
-                    if (!has[h]) continue;
-                    float z = 0.f;
+                for (int i = 0; i < (SETS + GROUPS - 1) / GROUPS; ++i)
+                    if (g + i * GROUPS < SETS) t += static_cast<double>(comb[g + i * GROUPS][c]);
+                comb2[g][c] = t;
+                __syncthreads();
+                if (g == 0 && c < nq * VEC) {
 #pragma unroll
-                    for (int i = 0; i < WAVES; ++i) z += red[((tib * HPT + h) * 2 + par) * WAVES + i];
-                    const float res = (LOGISTIC ? sigmoid(z) : z) - yy;
+                    for (int i = 1; i < GROUPS; ++i) t += comb2[i][c];
+                    put(c, t);
+                }
+            } else {
+                for (int c = threadIdx.x; c < nq * VEC; c += THREADS) {
+                    double t = 0.0;
 #pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        acc[h][k][0] = fmaf(res, xr[k].x, acc[h][k][0]); acc[h][k][1] = fmaf(res, xr[k].y, acc[h][k][1]);
-                        acc[h][k][2] = fmaf(res, xr[k].z, acc[h][k][2]); acc[h][k][3] = fmaf(res, xr[k].w, acc[h][k][3]);
-                    }
+                    for (int i = 0; i < SETS; ++i) t += static_cast<double>(comb[i][c]);
+                    put(c, t);
                 }
             }
-            slot = slot + 1 == NB ? 0 : slot + 1;
-            par ^= 1;
-        }
-#pragma unroll
-        for (int h = 0; h < HPT; ++h) {
-            if (!has[h]) continue;                         // the item is done: this holder's partial row is complete
-            float *out = partial + static_cast<int64_t>(C.piece[h]) * d;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int q = tl + k * TS;
-                if (q < nq) { f4u t; t.x = acc[h][k][0]; t.y = acc[h][k][1]; t.z = acc[h][k][2]; t.w = acc[h][k][3]; *reinterpret_cast<f4u *>(out + 4 * q) = t; }
-                acc[h][k][0] = acc[h][k][1] = acc[h][k][2] = acc[h][k][3] = 0.f;
+        };
+        // chunk is an even number of steps; the chunks of a run that has several go to one row each
+        Step a, b;
+        load(a, 0);
+        for (int r0 = 0, to = run.dst_begin; r0 < n; ++to) {
+            const int stop = min(r0 + chunk, n);
+            float sum[K][VEC];
+            clear(sum);
+            while (r0 < stop) {
+                const int end = min(r0 + kFoldRows / R * STEP, stop);
+                clear(acc);
+                for (;;) {
+                    load(b, r0 + STEP);
+                    compute(a, r0);
+                    if ((r0 += STEP) >= end) break;
+                    load(a, r0 + STEP);
+                    compute(b, r0);
+                    if ((r0 += STEP) >= end) break;
+                }
+                fold(sum);
             }
+            store(sum, to, r0 < n ? to + 1 : run.dst_end);
         }
-        ++C.item;
-        enter(C, true);
+        if (next >= more) break;
+        run = read_run(table(runs) + next++);
     }
-    wait_loads<0>();                      // the re-fetches past the end of the queue land before the workgroup gives its LDS back
+}
+
+// Wider rows: the TS threads of the workgroup share every row, thread t holding chunks t, t + TS, ..., R rows per step.  One barrier
+// per step exchanges the wavefronts' parts of the dot products (double buffered in LDS).  PF: the next step's rows are loaded before
+// the current step is computed; beyond 9 chunks per thread the second register set costs more than it hides (a row is then long
+// enough: 12 chunks, 24576 columns, 200 MB: 43.4 us without, 45.8 with it).  FOLD: there are registers for a second set of sums.
+template <int XD, int VEC, int TS, int K, int R, bool PF, bool FOLD, bool NT>
+__global__ void __launch_bounds__(TS)
+rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w, const DevRun *__restrict__ parts,
+                      const DevRun *__restrict__ runs, const int32_t *__restrict__ dst, float *__restrict__ rows, int d, int nq, int chunk, int logistic)
+{
+    static_assert(kFoldRows % (2 * R) == 0, "sums are folded after an even number of steps");
+    using C = Chunk<XD, VEC>;
+    constexpr int WAVES = TS / 64;
+    __shared__ float red[2][R][WAVES];
+    const int tl = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const table_t<DevRun> part = table(parts) + blockIdx.x;
+    const int more = part->more_end;
+    int next = part->more_begin;
+    Run run = read_run(part);
+
+    unsigned off[K];
+    float wv[K][VEC];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int q = tl + k * TS;
+        off[k] = chunk_offset<VEC>(q, nq, d);
+        load_row<VEC>(w + off[k], wv[k]);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) wv[k][v] = chunk_owns<VEC>(q, v, nq, d) ? wv[k][v] : 0.f;
+    }
+
+    struct Step {
+        typename C::raw_t x[R][K];
+        float yy[R];
+    };
+    int buf = 0;
+    for (;;) {
+        const void *base = row_ptr<XD>(X, run.row_begin, d);
+        const float *yb = y + run.row_begin;
+        const int n = run.nrows;
+        float acc[K][VEC];
+        auto clear = [&](float (&s)[K][VEC]) {
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) s[k][v] = 0.f;
+        };
+        auto fold = [&](float (&s)[K][VEC]) {
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) s[k][v] += acc[k][v];
+        };
+        auto load = [&](Step &s, int r0) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int at = min(r0 + r, n - 1);
+                const void *row = row_ptr<XD>(base, at, d);
+                s.yy[r] = yb[at];
+#pragma unroll
+                for (int k = 0; k < K; ++k) s.x[r][k] = NT ? C::load_once(row, off[k]) : C::load(row, off[k]);
+            }
+        };
+        auto compute = [&](const Step &s, int r0) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float t[2] = {0.f, 0.f};                 // two chains: a multiply-add need not wait for the one before it
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    float xv[VEC];
+                    C::widen(s.x[r][k], xv);
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) t[k & 1] = fmaf(xv[v], wv[k][v], t[k & 1]);
+                }
+                const float dot = group_sum<64>(t[0] + t[1]);
+                if ((tl & 63) == 0) red[buf][r][wave] = dot;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float z = 0.f;
+#pragma unroll
+                for (int i = 0; i < WAVES; ++i) z += red[buf][r][i];
+                const float res = r0 + r < n ? residual(z, s.yy[r], logistic) : 0.f;
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    float xv[VEC];
+                    C::widen(s.x[r][k], xv);
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) acc[k][v] = fmaf(res, xv[v], acc[k][v]);
+                }
+            }
+            buf ^= 1;
+        };
+        auto store = [&](const float (&s)[K][VEC], int dst_begin, int dst_end) {
+            for (int j = dst_begin; j < dst_end; ++j) {
+                float *out = rows + static_cast<int64_t>(table(dst)[j]) * d;
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    if (tl + k * TS < nq) store_row<VEC>(out + off[k], s[k]);
+            }
+        };
+        Step a, b;
+        if constexpr (PF) load(a, 0);
+        for (int r0 = 0, to = run.dst_begin; r0 < n; ++to) {
+            const int stop = min(r0 + chunk, n);
+            float sum[K][VEC];
+            clear(sum);
+            while (r0 < stop) {
+                const int end = FOLD ? min(r0 + kFoldRows, stop) : stop;
+                clear(acc);
+                for (;;) {
+                    if constexpr (PF) load(b, r0 + R);
+                    else load(a, r0);
+                    compute(a, r0);
+                    if ((r0 += R) >= end) break;
+                    if constexpr (PF) {
+                        load(a, r0 + R);
+                        compute(b, r0);
+                        if ((r0 += R) >= end) break;
+                    }
+                }
+                if constexpr (FOLD) fold(sum);
+            }
+            store(FOLD ? sum : acc, to, r0 < n ? to + 1 : run.dst_end);
+        }
+        if (next >= more) break;
+        run = read_run(table(runs) + next++);
+    }
 }
 
 // ---- stage 1 for wide rows -----------------------------------------------------------------------------------------
@@ -812,7 +734,7 @@ residuals_kernel(const void *__restrict__ X, const float *__restrict__ y, const 
 template <int XD, int VEC>
 __global__ void __launch_bounds__(256)
 xt_residuals_kernel(const void *__restrict__ X, const DevPiece *__restrict__ pieces, const float *__restrict__ residuals,
-                    float *__restrict__ partial, int d, int nq)
+                    float *__restrict__ rows, int d, int nq)
 {
     using C = Chunk<XD, VEC>;
     using raw_t = typename C::raw_t;
@@ -841,62 +763,56 @@ xt_residuals_kernel(const void *__restrict__ X, const DevPiece *__restrict__ pie
             for (int v = 0; v < VEC; ++v) acc[k][v] = fmaf(res, xv[v], acc[k][v]);
         }
     }
-    float *out = partial + static_cast<int64_t>(blockIdx.y) * d;
+    float *out = rows + static_cast<int64_t>(pc.out_row) * d;
 #pragma unroll
     for (int k = 0; k < K; ++k)
         if (qbase + k * 256 < nq) store_row<VEC>(out + off[k], acc[k]);
 }
 
-// ---- piece reduction ------------------------------------------------------------------------------------------------
-// G[slab] = sum of the slab's pieces.  A workgroup covers 64 chunks of columns of one slab; its four wavefronts each add up every
-// fourth piece (eight loads in flight per lane), then the four partial sums are combined through LDS.  The order of the
-// additions is fixed by the piece list alone, so the result is the same bits on every run; the sums are carried in fp64.
+// ---- sums of partial rows ---------------------------------------------------------------------------------------------
+// Slabs that several runs make up: the sum of consecutive partial rows, written to every slab that covers the same rows (so the
+// partial rows are read once per distinct slab range, not once per slab).  A workgroup covers 64 chunks of columns of one sum; its
+// eight wavefronts each add every eighth row (eight loads in flight per lane), the eight partial sums meet in LDS, and the
+// wavefronts share out the destinations.  fp64 throughout, in an order fixed by the tables alone: the same bits on every run.
 template <int VEC>
-__global__ void __launch_bounds__(256)
-reduce_pieces_kernel(const float *__restrict__ partial, const int32_t *__restrict__ slab_piece_begin, const int32_t *__restrict__ slab_pieces,
-                     float *__restrict__ G, int64_t d, int nq)
+__global__ void __launch_bounds__(512)
+sum_rows_kernel(float *__restrict__ rows, const DevSum *__restrict__ sums, const int32_t *__restrict__ dst, int64_t d, int nq)
 {
-    constexpr int WAVES = 4;
-    constexpr int U = 8;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int WAVES = 8, U = 8;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int q = min(static_cast<int>(blockIdx.x) * 64 + lane, nq - 1);     // lanes past the row repeat its last chunk and do not store
     const int64_t col = chunk_offset<VEC>(q, nq, static_cast<int>(d));
-    const int slab = blockIdx.y;
-    const int pb = slab_piece_begin[slab], pe = slab_piece_begin[slab + 1];
+    const table_t<DevSum> s = table(sums) + blockIdx.y;
+    const int row_begin = s->row_begin, row_end = s->row_end;
     double acc[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
-    for (int j0 = pb + wave; j0 < pe; j0 += WAVES * U) {
+    for (int j0 = row_begin + wave; j0 < row_end; j0 += WAVES * U) {
         float xv[U][VEC];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int j = min(j0 + u * WAVES, pe - 1);
-            load_row<VEC>(partial + static_cast<int64_t>(slab_pieces[j]) * d + col, xv[u]);
-        }
+        for (int u = 0; u < U; ++u) load_row<VEC>(rows + static_cast<int64_t>(min(j0 + u * WAVES, row_end - 1)) * d + col, xv[u]);
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (j0 + u * WAVES < pe) {
+            if (j0 + u * WAVES < row_end) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) acc[v] += static_cast<double>(xv[u][v]);
             }
     }
-    __shared__ double part[WAVES - 1][VEC][64];
-    if (wave > 0) {
+    __shared__ double part[WAVES][VEC][64];
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) part[wave - 1][v][lane] = acc[v];
-    }
+    for (int v = 0; v < VEC; ++v) part[wave][v][lane] = acc[v];
     __syncthreads();
-    if (wave == 0 && static_cast<int>(blockIdx.x) * 64 + lane < nq) {
-        float out[VEC];
+    if (static_cast<int>(blockIdx.x) * 64 + lane >= nq) return;
+    float out[VEC];
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            double t = acc[v];
+    for (int v = 0; v < VEC; ++v) {
+        double t = 0.0;
 #pragma unroll
-            for (int k = 0; k < WAVES - 1; ++k) t += part[k][v][lane];
-            out[v] = static_cast<float>(t);
-        }
-        store_row<VEC>(G + static_cast<int64_t>(slab) * d + col, out);
+        for (int i = 0; i < WAVES; ++i) t += part[i][v][lane];
+        out[v] = static_cast<float>(t);
     }
+    for (int j = s->dst_begin + wave; j < s->dst_end; j += WAVES) store_row<VEC>(rows + static_cast<int64_t>(table(dst)[j]) * d + col, out);
 }
 
 // ---- encode ---------------------------------------------------------------------------------------------------------
@@ -1072,31 +988,15 @@ update_metrics_kernel(float *__restrict__ w, const float *__restrict__ g, float 
 // each variant is built twice, for phi = identity and phi = sigmoid: every lane forms the residual of every row, and the kernels
 // bound by vector-ALU issue would pay for evaluating both forms and selecting one
 #define CR_V(XD, VEC, TS, K, R)                                                                         \
-    {XD, VEC, TS, K, R, (TS < 256 ? 256 / TS : 1), false,                                               \
+    {XD, VEC, TS, K, R, (TS < 256 ? 256 / TS : 1),                                                      \
      {reinterpret_cast<const void *>(&partial_grads_kernel<XD, VEC, TS, K, R, false>),                  \
       reinterpret_cast<const void *>(&partial_grads_kernel<XD, VEC, TS, K, R, true>)}}
 #define CR_VB(XD, VEC, TS, K, R)                                                                        \
-    {XD, VEC, TS, K, R, (TS < 256 ? 256 / TS : 1), false,                                               \
+    {XD, VEC, TS, K, R, (TS < 256 ? 256 / TS : 1),                                                      \
      {reinterpret_cast<const void *>(&partial_grads_kernel<XD, VEC, TS, K, R, false>),                  \
-      reinterpret_cast<const void *>(&partial_grads_kernel<XD, VEC, TS, K, R, true>)}, 0, 0,            \
+      reinterpret_cast<const void *>(&partial_grads_kernel<XD, VEC, TS, K, R, true>)},                  \
      {reinterpret_cast<const void *>(&partial_grads_kernel<XD, VEC, TS, K, R, false, true>),            \
       reinterpret_cast<const void *>(&partial_grads_kernel<XD, VEC, TS, K, R, true, true>)}}
-#define CR_S(XD, VEC, TS, K, R, H)                                                                      \
-    {XD, VEC, TS, K, R, H, true,                                                                        \
-     {reinterpret_cast<const void *>(&partial_grads_staged_kernel<XD, VEC, TS, K, R, H, false>),        \
-      reinterpret_cast<const void *>(&partial_grads_staged_kernel<XD, VEC, TS, K, R, H, true>)}}
-#define CR_D(TS, K, NB, H)                                                                             \
-    {0, 4, TS, K, 1, H, true,                                                                          \
-     {reinterpret_cast<const void *>(&partial_grads_dma_kernel<TS, K, H, NB, false, 1, false>),           \
-      reinterpret_cast<const void *>(&partial_grads_dma_kernel<TS, K, H, NB, false, 1, true>)}, NB, 0}
-#define CR_DW2(TS, K, NB, H)                                                                           \
-    {0, 4, TS, K, 1, 2 * H, true,                                                                      \
-     {reinterpret_cast<const void *>(&partial_grads_dma_kernel<TS, K, H, NB, true, 2, false>),         \
-      reinterpret_cast<const void *>(&partial_grads_dma_kernel<TS, K, H, NB, true, 2, true>)}, NB, 1, {nullptr, nullptr}, 2}
-#define CR_DW(TS, K, NB, H)                                                                            \
-    {0, 4, TS, K, 1, H, true,                                                                          \
-     {reinterpret_cast<const void *>(&partial_grads_dma_kernel<TS, K, H, NB, true, 1, false>),            \
-      reinterpret_cast<const void *>(&partial_grads_dma_kernel<TS, K, H, NB, true, 1, true>)}, NB, 1}
 // one variant per exact chunk count K = ceil(row chunks / team size); R rows in flight chosen so a thread holds about 16-24 chunks
 const Stage1Variant kVariants[] = {
     // fp32, chunks of 4 columns (4 registers per chunk)
@@ -1112,23 +1012,46 @@ const Stage1Variant kVariants[] = {
     CR_V(1, 8, 256, 6, 2), CR_V(1, 8, 1024, 2, 2), CR_V(1, 8, 1024, 3, 1),
     // rows shorter than one wide chunk: one column per lane
     CR_V(0, 1, 64, 1, 8), CR_V(1, 1, 64, 1, 8),
-    // fp32 rows of 1537 to 2558 whole 16-byte chunks (up to 40 KB) loaded straight into LDS.  Four holders per workgroup (1024
-    // threads, 128 registers each: the weights move to LDS, behind a ring of three rows) where the holder counts make that fewer
-    // workgroups per row; else three holders per workgroup (768 threads) and a ring of four rows.  Listed before the
-    // register-staged kernels of two holders that cover the same widths.
-    CR_DW2(256, 7, 3, 3), CR_DW2(256, 8, 3, 3), CR_DW2(256, 9, 3, 3), CR_DW2(256, 10, 3, 3),
-    CR_DW(256, 7, 3, 4), CR_DW(256, 8, 3, 4), CR_DW(256, 9, 3, 4), CR_DW(256, 10, 3, 4),
-    CR_D(256, 7, 4, 3), CR_D(256, 8, 4, 3), CR_D(256, 9, 4, 3), CR_D(256, 10, 4, 3),
-    // fp32 rows staged through LDS by way of registers (any width).  Eight holders per workgroup, one wavefront each, for rows of up to 1024 chunks ...
-    CR_S(0, 4, 64, 5, 1, 8), CR_S(0, 4, 64, 6, 1, 8), CR_S(0, 4, 64, 7, 1, 8), CR_S(0, 4, 64, 8, 1, 8), CR_S(0, 4, 64, 9, 1, 8),
-    CR_S(0, 4, 64, 10, 1, 8), CR_S(0, 4, 64, 11, 1, 8), CR_S(0, 4, 64, 12, 1, 8), CR_S(0, 4, 64, 13, 1, 8), CR_S(0, 4, 64, 14, 1, 8),
-    CR_S(0, 4, 64, 15, 1, 8), CR_S(0, 4, 64, 16, 1, 8),
-    // ... four holders of four wavefronts (1024 threads, so at most 128 registers each) up to 1536 chunks ...
-    CR_S(0, 4, 256, 2, 2, 4), CR_S(0, 4, 256, 3, 2, 4), CR_S(0, 4, 256, 4, 2, 4), CR_S(0, 4, 256, 5, 1, 4), CR_S(0, 4, 256, 6, 1, 4),
-    // ... two holders up to 3072 chunks; R is limited by the two LDS buffers of R rows each
-    CR_S(0, 4, 256, 2, 4, 2), CR_S(0, 4, 256, 3, 2, 2), CR_S(0, 4, 256, 4, 2, 2), CR_S(0, 4, 256, 5, 2, 2), CR_S(0, 4, 256, 6, 2, 2),
-    CR_S(0, 4, 256, 7, 1, 2), CR_S(0, 4, 256, 8, 1, 2), CR_S(0, 4, 256, 9, 1, 2), CR_S(0, 4, 256, 10, 1, 2),
-    CR_S(0, 4, 256, 11, 1, 2), CR_S(0, 4, 256, 12, 1, 2),
+};
+
+// every-row-once kernels: threads that share a row, chunks per thread, rows per step, threads per workgroup
+#define CR_O(XD, VEC, LPR, K, R, WAVES)                                                                 \
+    {XD, VEC, LPR, K, WAVES * R * (64 / LPR), WAVES * 64, 2, kFolds * kFoldRows,                        \
+     {reinterpret_cast<const void *>(&rows_once_kernel<XD, VEC, LPR, K, R, WAVES, false>),              \
+      reinterpret_cast<const void *>(&rows_once_kernel<XD, VEC, LPR, K, R, WAVES, true>)}}
+#define CR_OT(XD, VEC, TS, K, R, PF, FOLD)                                                              \
+    {XD, VEC, TS, K, R, TS, XD == 1 && TS == 128 ? 2 : 1, FOLD ? kFolds * kFoldRows : kFoldRows,        \
+     {reinterpret_cast<const void *>(&rows_once_team_kernel<XD, VEC, TS, K, R, PF, FOLD, false>),       \
+      reinterpret_cast<const void *>(&rows_once_team_kernel<XD, VEC, TS, K, R, PF, FOLD, true>)}}
+const OnceVariant kOnceVariants[] = {
+    // fp32: up to 256 chunks (1024 columns) a wavefront or a part of one per row ...
+    CR_O(0, 4, 2, 1, 4, 4), CR_O(0, 4, 4, 1, 4, 4), CR_O(0, 4, 8, 1, 4, 4), CR_O(0, 4, 16, 1, 4, 4), CR_O(0, 4, 32, 1, 4, 4),
+    CR_O(0, 4, 64, 1, 4, 4), CR_O(0, 4, 64, 2, 4, 4), CR_O(0, 4, 64, 3, 2, 4), CR_O(0, 4, 64, 4, 2, 4),
+    // ... then two wavefronts up to 512, four up to 1792, eight up to 6144 chunks (more chunks per thread would leave no room for the
+    // next step; 1500 columns, 3 GB: 423 us with two wavefronts, 444 with four, a quarter of whose second chunks lie past the row)
+    CR_OT(0, 4, 128, 3, 4, true, true), CR_OT(0, 4, 128, 4, 4, true, true), CR_OT(0, 4, 256, 3, 4, true, true), CR_OT(0, 4, 256, 4, 2, true, true),
+    CR_OT(0, 4, 256, 5, 2, true, true), CR_OT(0, 4, 256, 6, 2, true, true), CR_OT(0, 4, 256, 7, 2, true, false),
+    CR_OT(0, 4, 512, 4, 2, true, true), CR_OT(0, 4, 512, 5, 2, true, true), CR_OT(0, 4, 512, 6, 1, true, true),
+    CR_OT(0, 4, 512, 7, 1, true, true), CR_OT(0, 4, 512, 8, 1, true, true), CR_OT(0, 4, 512, 9, 1, true, false),
+    CR_OT(0, 4, 512, 10, 1, false, false), CR_OT(0, 4, 512, 11, 1, false, false), CR_OT(0, 4, 512, 12, 1, false, false),
+    // bf16: the same, a chunk widening to eight accumulators
+    CR_O(1, 8, 2, 1, 4, 4), CR_O(1, 8, 4, 1, 4, 4), CR_O(1, 8, 8, 1, 4, 4), CR_O(1, 8, 16, 1, 4, 4), CR_O(1, 8, 32, 1, 4, 4),
+    CR_O(1, 8, 64, 1, 4, 4), CR_O(1, 8, 64, 2, 2, 4), CR_O(1, 8, 64, 3, 2, 4), CR_O(1, 8, 64, 4, 2, 4),
+    // (rows of an odd number of columns start on any 2-byte boundary, where 16-byte loads take two trips: two smaller workgroups per
+    // unit hide that better, 3 GB of 3001 columns 466 against 527 us)
+    CR_OT(1, 8, 128, 3, 4, true, true), CR_OT(1, 8, 128, 4, 2, true, true), CR_OT(1, 8, 128, 5, 2, true, true),
+    CR_OT(1, 8, 128, 6, 2, true, true),
+    CR_OT(1, 8, 256, 2, 4, true, true), CR_OT(1, 8, 256, 3, 2, true, true), CR_OT(1, 8, 256, 4, 2, true, true),
+    CR_OT(1, 8, 512, 3, 1, true, true), CR_OT(1, 8, 512, 4, 1, true, true), CR_OT(1, 8, 512, 5, 1, true, true),
+    CR_OT(1, 8, 512, 6, 1, true, false),
+    // rows shorter than one wide chunk: one column per lane
+    CR_O(0, 1, 4, 1, 4, 4), CR_O(1, 1, 8, 1, 4, 4),
+};
+// one row per wavefront or less, sixteen wavefronts: for launches of a few workgroups that each have a whole slab range to do
+const OnceVariant kOnceVariants16[] = {
+    CR_O(0, 4, 2, 1, 4, 16), CR_O(0, 4, 4, 1, 4, 16), CR_O(0, 4, 8, 1, 4, 16), CR_O(0, 4, 16, 1, 4, 16), CR_O(0, 4, 32, 1, 4, 16),
+    CR_O(0, 4, 64, 1, 4, 16), CR_O(1, 8, 2, 1, 4, 16), CR_O(1, 8, 4, 1, 4, 16), CR_O(1, 8, 8, 1, 4, 16), CR_O(1, 8, 16, 1, 4, 16),
+    CR_O(1, 8, 32, 1, 4, 16), CR_O(1, 8, 64, 1, 4, 16), CR_O(0, 1, 4, 1, 4, 16), CR_O(1, 1, 8, 1, 4, 16),
 };
 
 // columns per chunk: the 16-byte width unless the row is shorter than that
@@ -1140,17 +1063,6 @@ int stage1_chunk_width(int x_dtype, int64_t d)
 
 }  // namespace
 
-size_t Stage1Variant::lds_bytes(int64_t d) const
-{
-    if (!staged) return 0;
-    if (ring > 0) {        // ring of whole rows, then the partial dot products of the teams' wavefronts
-        const size_t nq = static_cast<size_t>((d + vec - 1) / vec);
-        return 16 * static_cast<size_t>(ring + w_in_lds) * nq + sizeof(float) * tpb * 2 * (team_size / 64);
-    }
-    const size_t row_chunks = static_cast<size_t>((k + tpb - 1) / tpb) * block();
-    return 16 * 2 * rows * row_chunks + sizeof(float) * tpb * 2 * rows * (team_size / 64);
-}
-
 const Stage1Variant *select_stage1(int x_dtype, int64_t d)
 {
     const int vec = stage1_chunk_width(x_dtype, d);
@@ -1159,85 +1071,76 @@ const Stage1Variant *select_stage1(int x_dtype, int64_t d)
     for (int ts : {64, 256, 1024}) {
         const int64_t k = (nq + ts - 1) / ts;
         for (const Stage1Variant &v : kVariants)
-            if (!v.staged && v.xd == x_dtype && v.vec == vec && v.team_size == ts && v.k == k) return &v;
+            if (v.xd == x_dtype && v.vec == vec && v.team_size == ts && v.k == k) return &v;
     }
     return nullptr;
 }
 
-const Stage1Variant *select_stage1_staged(int x_dtype, int64_t d, int64_t max_holders)
+namespace {
+const OnceVariant *find_once(const OnceVariant *begin, const OnceVariant *end, int x_dtype, int64_t d)
 {
     const int vec = stage1_chunk_width(x_dtype, d);
     const int64_t nq = (d + vec - 1) / vec;
-    // the widest workgroup that is not wider than the rows need: 8 holders for rows with 5 or more, 4 (3 for long rows) for 3 or 4,
-    // else 2.  The table lists wide workgroups before narrow ones; the kernel that loads straight into LDS needs rows of whole
-    // 16-byte chunks and a ring that fits LDS at this width.
-    const int widest = max_holders >= 5 ? 8 : max_holders >= 3 ? 4 : 2;
-    for (const Stage1Variant &v : kVariants) {
-        if (!v.staged || v.xd != x_dtype || v.vec != vec || v.k != (nq + v.team_size - 1) / v.team_size || v.tpb > widest) continue;
-        if (v.ring > 0 && (d % vec != 0 || v.lds_bytes(d) > kLdsPerWorkgroup)) continue;
-        // four holders per workgroup (weights in LDS) only where that takes fewer workgroups per row than three do
-        if (v.w_in_lds && v.holders_per_team == 1 && (max_holders + 3) / 4 >= (max_holders + 2) / 3) continue;
-        // three teams that each work for two holders: rows with five or six holders in one workgroup
-        if (v.holders_per_team == 2 && max_holders != 5 && max_holders != 6) continue;
-        return &v;
+    for (const OnceVariant *v = begin; v != end; ++v) {
+        if (v->xd != x_dtype || v->vec != vec || (x_dtype == 1 && v->threads_per_row == 128 && d % 2 == 0)) continue;
+        // listed from narrow to wide: the first that covers the row.  K is exact, so that only a thread's last chunk can lie past it
+        if (v->threads_per_row <= 64 ? nq <= static_cast<int64_t>(v->threads_per_row) * v->k
+                                     : v->k == (nq + v->threads_per_row - 1) / v->threads_per_row) return v;
     }
     return nullptr;
 }
+}  // namespace
 
-hipError_t prepare_stage1(const Stage1Variant &v, int64_t d)
+const OnceVariant *select_once(int x_dtype, int64_t d) { return find_once(std::begin(kOnceVariants), std::end(kOnceVariants), x_dtype, d); }
+const OnceVariant *select_once_whole(int x_dtype, int64_t d)
 {
-    if (v.lds_bytes(d) <= 48 * 1024) return hipSuccess;
-    for (const void *fn : v.fn) {
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(v.lds_bytes(d)));
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    const OnceVariant *v = find_once(std::begin(kOnceVariants16), std::end(kOnceVariants16), x_dtype, d);
+    return v ? v : select_once(x_dtype, d);
+}
+
+hipError_t launch_rows_once(const OnceVariant &v, const void *X, const float *y, const float *w, const DevRun *parts, int num_parts,
+                            const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int chunk, int logistic,
+                            bool stream_past_caches, hipStream_t stream)
+{
+    int di = static_cast<int>(d);
+    int nq = static_cast<int>((d + v.vec - 1) / v.vec);
+    void *args[] = {&X, &y, &w, &parts, &runs, &dst, &rows, &di, &nq, &chunk, &logistic};
+    return hipLaunchKernel(v.fn[stream_past_caches ? 1 : 0], dim3(num_parts), dim3(v.block), args, 0, stream);
 }
 
 hipError_t launch_partial_grads(const Stage1Variant &v, const void *X, const float *y, const float *w, const DevPiece *pieces,
-                                const int32_t *team_piece_begin, int num_teams, float *partial, int64_t d, int logistic,
+                                const int32_t *team_piece_begin, int num_teams, float *rows, int64_t d, int logistic,
                                 bool rows_as_buffers, hipStream_t stream)
 {
     int di = static_cast<int>(d);
     int nq = static_cast<int>((d + v.vec - 1) / v.vec);
-    void *args[] = {&X, &y, &w, &pieces, &team_piece_begin, &num_teams, &partial, &di, &nq};
+    void *args[] = {&X, &y, &w, &pieces, &team_piece_begin, &num_teams, &rows, &di, &nq};
     const int tpb = v.teams_per_block();
     dim3 grid((num_teams + tpb - 1) / tpb), block(v.block());
     const void *fn = rows_as_buffers && v.fn_buffers[0] ? v.fn_buffers[logistic ? 1 : 0] : v.fn[logistic ? 1 : 0];
     return hipLaunchKernel(fn, grid, block, args, 0, stream);
 }
 
-hipError_t launch_partial_grads_staged(const Stage1Variant &v, const void *X, const float *y, const float *w, const DevPiece *pieces,
-                                       const int32_t *group_item_begin, const int32_t *item_pieces, int num_groups, float *partial,
-                                       int64_t d, int logistic, hipStream_t stream)
-{
-    int di = static_cast<int>(d);
-    int nq = static_cast<int>((d + v.vec - 1) / v.vec);
-    void *args[] = {&X, &y, &w, &pieces, &group_item_begin, &item_pieces, &partial, &di, &nq};
-    dim3 grid(num_groups), block(v.block());
-    return hipLaunchKernel(v.fn[logistic ? 1 : 0], grid, block, args, v.lds_bytes(d), stream);
-}
-
 namespace {
 template <int XD, int VEC>
 hipError_t launch_wide(const void *X, const float *y, const float *w, const DevPiece *pieces, int num_pieces, float *residuals,
-                       float *partial, int64_t d, int logistic, hipStream_t stream)
+                       float *rows, int64_t d, int logistic, hipStream_t stream)
 {
     const int nq = static_cast<int>((d + VEC - 1) / VEC);
     const int di = static_cast<int>(d);
-    if (partial == nullptr)
+    if (rows == nullptr)
         residuals_kernel<XD, VEC><<<num_pieces, 256, 0, stream>>>(X, y, w, pieces, residuals, di, nq, logistic);
     else
         xt_residuals_kernel<XD, VEC><<<dim3((nq + 256 * kWideChunks - 1) / (256 * kWideChunks), num_pieces), 256, 0, stream>>>(
-            X, pieces, residuals, partial, di, nq);
+            X, pieces, residuals, rows, di, nq);
     return hipGetLastError();
 }
 
 hipError_t dispatch_wide(int x_dtype, const void *X, const float *y, const float *w, const DevPiece *pieces, int num_pieces,
-                         float *residuals, float *partial, int64_t d, int logistic, hipStream_t stream)
+                         float *residuals, float *rows, int64_t d, int logistic, hipStream_t stream)
 {
-    if (x_dtype == 0) return launch_wide<0, 4>(X, y, w, pieces, num_pieces, residuals, partial, d, logistic, stream);
-    return launch_wide<1, 8>(X, y, w, pieces, num_pieces, residuals, partial, d, logistic, stream);
+    if (x_dtype == 0) return launch_wide<0, 4>(X, y, w, pieces, num_pieces, residuals, rows, d, logistic, stream);
+    return launch_wide<1, 8>(X, y, w, pieces, num_pieces, residuals, rows, d, logistic, stream);
 }
 }  // namespace
 
@@ -1247,21 +1150,20 @@ hipError_t launch_residuals(int x_dtype, const void *X, const float *y, const fl
     return dispatch_wide(x_dtype, X, y, w, pieces, num_pieces, residuals, nullptr, d, logistic, stream);
 }
 
-hipError_t launch_xt_residuals(int x_dtype, const void *X, const DevPiece *pieces, int num_pieces, const float *residuals, float *partial,
+hipError_t launch_xt_residuals(int x_dtype, const void *X, const DevPiece *pieces, int num_pieces, const float *residuals, float *rows,
                                int64_t d, hipStream_t stream)
 {
-    return dispatch_wide(x_dtype, X, nullptr, nullptr, pieces, num_pieces, const_cast<float *>(residuals), partial, d, 0, stream);
+    return dispatch_wide(x_dtype, X, nullptr, nullptr, pieces, num_pieces, const_cast<float *>(residuals), rows, d, 0, stream);
 }
 
-hipError_t launch_reduce_pieces(const float *partial, const int32_t *slab_piece_begin, const int32_t *slab_pieces, int num_slabs, float *G,
-                                int64_t d, hipStream_t stream)
+hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, const int32_t *dst, int64_t d, hipStream_t stream)
 {
-    if (d >= 4) {
-        const int nq = static_cast<int>((d + 3) / 4);
-        reduce_pieces_kernel<4><<<dim3((nq + 63) / 64, num_slabs), 256, 0, stream>>>(partial, slab_piece_begin, slab_pieces, G, d, nq);
-    } else {
-        const int nq = static_cast<int>(d);
-        reduce_pieces_kernel<1><<<dim3((nq + 63) / 64, num_slabs), 256, 0, stream>>>(partial, slab_piece_begin, slab_pieces, G, d, nq);
+    constexpr int kMaxGridY = 65535;
+    const int nq = static_cast<int>(d >= 4 ? (d + 3) / 4 : d);
+    for (int lo = 0; lo < num_sums; lo += kMaxGridY) {
+        const dim3 grid((nq + 63) / 64, num_sums - lo < kMaxGridY ? num_sums - lo : kMaxGridY);
+        if (d >= 4) sum_rows_kernel<4><<<grid, 512, 0, stream>>>(rows, sums + lo, dst, d, nq);
+        else sum_rows_kernel<1><<<grid, 512, 0, stream>>>(rows, sums + lo, dst, d, nq);
     }
     return hipGetLastError();
 }

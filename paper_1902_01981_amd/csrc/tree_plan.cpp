@@ -162,16 +162,23 @@ void split_equal_ranges(const std::vector<Slab> &slabs, int teams, Split &out)
 namespace {
 struct Unit { int64_t cell; int32_t slab; int64_t row_begin, row_end; };
 
-// Cells that every holder holds whole: the row axis is first cut wherever any slab begins or ends (between two such cuts the set of
-// holders does not change), then every stretch is cut into near-equal cells of at most cell_rows rows.  Units sorted by cell.
-std::vector<Unit> whole_cell_units(const std::vector<Slab> &slabs, int64_t cell_rows)
+// every row at which some slab begins or ends
+std::vector<int64_t> slab_cuts(const std::vector<Slab> &slabs)
 {
-    std::vector<Unit> units;
     std::vector<int64_t> cuts;
     cuts.reserve(2 * slabs.size());
     for (const Slab &sl : slabs) { cuts.push_back(sl.row_begin); cuts.push_back(sl.row_end); }
     std::sort(cuts.begin(), cuts.end());
     cuts.erase(std::unique(cuts.begin(), cuts.end()), cuts.end());
+    return cuts;
+}
+
+// Cells that every holder holds whole: the row axis is first cut wherever any slab begins or ends (between two such cuts the set of
+// holders does not change), then every stretch is cut into near-equal cells of at most cell_rows rows.  Units sorted by cell.
+std::vector<Unit> whole_cell_units(const std::vector<Slab> &slabs, int64_t cell_rows)
+{
+    std::vector<Unit> units;
+    const std::vector<int64_t> cuts = slab_cuts(slabs);
     std::vector<int64_t> first_cell(cuts.size(), 0);     // index of the first cell of the stretch that starts at cuts[i]
     for (size_t i = 0; i + 1 < cuts.size(); ++i) first_cell[i + 1] = first_cell[i] + (cuts[i + 1] - cuts[i] + cell_rows - 1) / cell_rows;
     for (size_t q = 0; q < slabs.size(); ++q) {
@@ -261,6 +268,156 @@ void split_shared_queues(const std::vector<Slab> &slabs, int64_t cell_rows, int 
         out.group_item_begin[g + 1] = out.group_item_begin[g] + static_cast<int32_t>(queue[g].size());
         out.item_pieces.insert(out.item_pieces.end(), piece_of[g].begin(), piece_of[g].end());
     }
+    index_slab_pieces(slabs.size(), out);
+}
+
+namespace {
+// Given the runs of `out` (part-major, disjoint, covering every slab in whole runs): who receives what.
+void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
+{
+    const int32_t S = static_cast<int32_t>(slabs.size());
+    std::vector<int32_t> by_row(out.runs.size());
+    for (size_t i = 0; i < by_row.size(); ++i) by_row[i] = static_cast<int32_t>(i);
+    std::sort(by_row.begin(), by_row.end(), [&](int32_t a, int32_t b) { return out.runs[a].row_begin < out.runs[b].row_begin; });
+    std::vector<int64_t> begins(by_row.size());
+    for (size_t i = 0; i < by_row.size(); ++i) begins[i] = out.runs[by_row[i]].row_begin;
+
+    std::vector<int32_t> order(S);                       // slabs, those of one range next to each other
+    for (int32_t p = 0; p < S; ++p) order[p] = p;
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+        return slabs[a].row_begin != slabs[b].row_begin ? slabs[a].row_begin < slabs[b].row_begin : slabs[a].row_end < slabs[b].row_end;
+    });
+    auto chunks = [&](size_t i) { const RowRun &r = out.runs[by_row[i]]; return (r.row_end - r.row_begin + out.chunk - 1) / out.chunk; };
+    struct Range { size_t ob, oe, rb, re; };             // slabs order[ob .. oe), runs by_row[rb .. re)
+    std::vector<Range> ranges;
+    std::vector<char> partial(by_row.size(), 0);
+    for (size_t i = 0; i < order.size();) {
+        const Slab &sl = slabs[order[i]];
+        size_t k = i;
+        while (k < order.size() && slabs[order[k]].row_begin == sl.row_begin && slabs[order[k]].row_end == sl.row_end) ++k;
+        const size_t rb = static_cast<size_t>(std::lower_bound(begins.begin(), begins.end(), sl.row_begin) - begins.begin());
+        const size_t re = static_cast<size_t>(std::lower_bound(begins.begin(), begins.end(), sl.row_end) - begins.begin());
+        ranges.push_back({i, k, rb, re});
+        if (re - rb > 1 || chunks(rb) > 1) std::fill(partial.begin() + rb, partial.begin() + re, 1);
+        i = k;
+    }
+    std::vector<int32_t> partial_row(by_row.size() + 1);             // first partial row of a run that has any
+    std::vector<std::vector<int32_t>> to(by_row.size());
+    out.partials = 0;
+    for (size_t i = 0; i < by_row.size(); ++i) {
+        partial_row[i] = S + out.partials;
+        if (partial[i])
+            for (int64_t c = chunks(i); c > 0; --c) to[i].push_back(S + out.partials++);
+    }
+    partial_row[by_row.size()] = S + out.partials;
+    for (const Range &r : ranges)
+        if (r.re - r.rb == 1 && chunks(r.rb) == 1) to[r.rb].insert(to[r.rb].end(), order.begin() + r.ob, order.begin() + r.oe);
+    for (size_t i = 0; i < by_row.size(); ++i) {
+        RowRun &run = out.runs[by_row[i]];
+        run.dst_begin = static_cast<int32_t>(out.dst.size());
+        out.dst.insert(out.dst.end(), to[i].begin(), to[i].end());
+        run.dst_end = static_cast<int32_t>(out.dst.size());
+    }
+    for (const Range &r : ranges)
+        if (r.re - r.rb > 1 || chunks(r.rb) > 1) {
+            const int32_t begin = static_cast<int32_t>(out.dst.size());
+            out.dst.insert(out.dst.end(), order.begin() + r.ob, order.begin() + r.oe);
+            out.sums.push_back({partial_row[r.rb], partial_row[r.re], begin, static_cast<int32_t>(out.dst.size())});
+        }
+}
+}  // namespace
+
+void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, int32_t chunk, OnceWork &out)
+{
+    out = OnceWork();
+    out.chunk = chunk;
+    const std::vector<int64_t> cuts = slab_cuts(slabs);
+    out.part_run_begin.push_back(0);
+    for (int64_t b = 0; b < parts; ++b) {
+        int64_t lo = static_cast<int64_t>(static_cast<__int128>(m) * b / parts);
+        const int64_t hi = static_cast<int64_t>(static_cast<__int128>(m) * (b + 1) / parts);
+        while (lo < hi) {
+            const int64_t stop = std::min(hi, *std::upper_bound(cuts.begin(), cuts.end(), lo));
+            out.runs.push_back({lo, stop, 0, 0});
+            lo = stop;
+        }
+        out.part_run_begin.push_back(static_cast<int32_t>(out.runs.size()));
+    }
+    assign_outputs(slabs, out);
+}
+
+void once_whole_ranges(const std::vector<Slab> &slabs, int32_t chunk, OnceWork &out)
+{
+    out = OnceWork();
+    out.chunk = chunk;
+    std::vector<int32_t> order(slabs.size());
+    for (size_t p = 0; p < order.size(); ++p) order[p] = static_cast<int32_t>(p);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+        return slabs[a].row_begin != slabs[b].row_begin ? slabs[a].row_begin < slabs[b].row_begin : slabs[a].row_end < slabs[b].row_end;
+    });
+    out.dst = order;
+    out.part_run_begin.push_back(0);
+    for (size_t i = 0; i < order.size();) {
+        const Slab &sl = slabs[order[i]];
+        size_t k = i;
+        while (k < order.size() && slabs[order[k]].row_begin == sl.row_begin && slabs[order[k]].row_end == sl.row_end) ++k;
+        out.runs.push_back({sl.row_begin, sl.row_end, static_cast<int32_t>(i), static_cast<int32_t>(k)});
+        out.part_run_begin.push_back(static_cast<int32_t>(out.runs.size()));
+        i = k;
+    }
+}
+
+void once_of_queues(const std::vector<Slab> &slabs, const Split &split, int teams_per_group, int32_t chunk, OnceWork &out)
+{
+    out = OnceWork();
+    out.chunk = chunk;
+    std::vector<int64_t> taken;                          // first rows of the cells some workgroup already has
+    for (const Piece &pc : split.pieces) taken.push_back(pc.row_begin);
+    std::sort(taken.begin(), taken.end());
+    taken.erase(std::unique(taken.begin(), taken.end()), taken.end());
+    std::vector<char> is_taken(taken.size(), 0);
+    out.part_run_begin.push_back(0);
+    for (size_t g = 0; g + 1 < split.group_item_begin.size(); ++g) {
+        for (int32_t it = split.group_item_begin[g]; it < split.group_item_begin[g + 1]; ++it) {
+            int32_t pi = -1;
+            for (int t = 0; t < teams_per_group && pi < 0; ++t) pi = split.item_pieces[static_cast<size_t>(it) * teams_per_group + t];
+            if (pi < 0) continue;
+            const Piece &pc = split.pieces[pi];
+            char &seen = is_taken[std::lower_bound(taken.begin(), taken.end(), pc.row_begin) - taken.begin()];
+            if (!seen) out.runs.push_back({pc.row_begin, pc.row_end, 0, 0});
+            seen = 1;
+        }
+        // a workgroup whose cells all went to others has no part
+        if (static_cast<int32_t>(out.runs.size()) > out.part_run_begin.back()) out.part_run_begin.push_back(static_cast<int32_t>(out.runs.size()));
+    }
+    assign_outputs(slabs, out);
+}
+
+void once_as_split(const std::vector<Slab> &slabs, const OnceWork &work, Split &out)
+{
+    out = Split();
+    const int32_t S = static_cast<int32_t>(slabs.size());
+    out.teams = static_cast<int>(work.part_run_begin.size()) - 1;
+    std::vector<std::vector<int32_t>> slabs_of(work.partials);      // which slabs a partial row goes into
+    for (const RowSum &sum : work.sums)
+        for (int32_t r = sum.row_begin; r < sum.row_end; ++r)
+            slabs_of[r - S].insert(slabs_of[r - S].end(), work.dst.begin() + sum.dst_begin, work.dst.begin() + sum.dst_end);
+    for (int b = 0; b < out.teams; ++b) {
+        out.team_piece_begin.push_back(static_cast<int32_t>(out.pieces.size()));
+        for (int32_t i = work.part_run_begin[b]; i < work.part_run_begin[b + 1]; ++i) {
+            const RowRun &run = work.runs[i];
+            auto add = [&](int32_t slab) { out.pieces.push_back({slab, b, run.row_begin, run.row_end}); };
+            bool partial = false;                        // the run's partial rows all go into the same slabs
+            for (int32_t j = run.dst_begin; j < run.dst_end; ++j) {
+                if (work.dst[j] < S) add(work.dst[j]);
+                else if (!partial) {
+                    for (int32_t slab : slabs_of[work.dst[j] - S]) add(slab);
+                    partial = true;
+                }
+            }
+        }
+    }
+    out.team_piece_begin.push_back(static_cast<int32_t>(out.pieces.size()));
     index_slab_pieces(slabs.size(), out);
 }
 
