@@ -129,14 +129,14 @@ int cr_plan_decode_row(const cr_plan_t *plan, const uint8_t *flags /* host, n */
  *                          others, if a cell has more.  fp32 rows of 257 to 3072 16-byte chunks with s > 0 only, else CR_E_INVAL.
  *   CR_SPLIT_ROWS_ONCE     value = most rows in one fp32 sum, rounded up to an even number of the kernel's steps (sums are added up in fp64): X is
  *                          cut into one or two contiguous parts per compute unit, a part into runs at slab boundaries; a workgroup
- *                          forms every row of its part once, for all slabs that hold it.  Rows that fit the registers of a
- *                          workgroup (d <= 24576), else CR_E_INVAL.
+ *                          forms every row of its part once, for all slabs that hold it.  Rows too wide for the registers of a
+ *                          workgroup (d > 24576) take two passes over X, the second cut into parts of rows and blocks of columns.
  * With the first two every holder of a row does its own arithmetic on it, as separate workers would: they are there to measure what
  * the redundancy of a scheme costs.  With the other two the holders' identical sums are formed once and handed to every slab they
  * belong to.  The slab gradients agree to rounding under every split.
  * Default (when this is never called): rows once, or, for the smallest problems, a workgroup per distinct slab range.  With X of 1 GiB
  * and more: equal ranges of the rows when s = 0 (no row is held twice), shared cells where one workgroup serves all holders of a
- * row, with the cell height (16 to 1024 rows) that gives the shortest longest queue.  Rows wider than 24576 columns: row cells. */
+ * row, with the cell height (16 to 1024 rows) that gives the shortest longest queue. */
 enum cr_split { CR_SPLIT_EQUAL_RANGES = 0, CR_SPLIT_ROW_CELLS = 1, CR_SPLIT_SHARED_CELLS = 2, CR_SPLIT_ROWS_ONCE = 3 };
 int cr_plan_set_split(cr_plan_t *plan, int kind, int64_t value);
 /* pieces in execution order: piece i is rows [row_begin[i], row_end[i]) of slab[i], run by team[i] (rows once: by workgroup team[i],

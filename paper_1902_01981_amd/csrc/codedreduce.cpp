@@ -67,12 +67,14 @@ struct cr_plan_s {
     mutable std::unordered_map<uint64_t, std::vector<double>> row_cache;   // padded straggler bitmask -> decode row
 
     // stage-1 split
-    const cr::OnceVariant *once = nullptr;             // the stage-1 kernel in use: every row once ...
-    const cr::Stage1Variant *variant = nullptr;        // ... or, where this is not null, every holder's rows (both null: two-pass path)
+    bool rows_once = false;                            // every row once (`work`), or every holder's rows (`split`)
+    const cr::OnceVariant *once = nullptr;             // the stage-1 kernel in use; null: the two-pass path of wide rows
+    const cr::Stage1Variant *variant = nullptr;        // ... of every holder's rows; the same
     const cr::OnceVariant *once_variant = nullptr;     // what exists for (x_dtype, d)
     const cr::Stage1Variant *variant_regs = nullptr;
     int cell_holders = 0;            // holders a workgroup of the shared-cells split serves; 0: no such split for this type and width
-    cr::OnceWork work;               // `once`: the runs and sums behind the split
+    cr::OnceWork work;               // `rows_once`: the runs and sums behind the split
+    int units = 0;                   // compute units the wide-row launches are sized for
     bool rows_as_buffers = false;    // every row starts on a 4-byte boundary and every piece has fewer than 2^31 bytes
     int split_kind = -1;                            // -1: choose from the device when the workspace is sized
     int64_t split_value = 0;
@@ -202,6 +204,9 @@ int shared_cell_holders(int x_dtype, int64_t d, int64_t max_holders)
     return max_holders >= 3 && nq <= 1536 ? 4 : 2;
 }
 
+// Bytes of X that the first pass over wide rows leaves in the 256 MB last-level cache for the second.
+constexpr int64_t kKeptBytes = int64_t(160) << 20;
+
 // rows added up in fp32, per accumulator at most `rows_per_sum`: an even number of the kernel's steps
 int32_t chunk_rows(const cr::OnceVariant *v, int64_t rows_per_sum)
 {
@@ -234,6 +239,16 @@ void make_rows_once(cr_plan_t *p, int64_t rows_per_sum, bool may_take_whole_rang
     cr::once_equal_parts(p->slabs, p->m, parts, chunk_rows(v, rows_per_sum), p->work);
 }
 
+// The same for wide rows: the parts of the second pass, each of which has one workgroup per block of columns.  Four workgroups per
+// compute unit, no fewer rows per part than a workgroup has in flight.
+void make_wide_once(cr_plan_t *p, int64_t rows_per_sum)
+{
+    const int64_t vec = p->x_dtype == CR_BF16 ? 8 : 4, blocks = ((p->d + vec - 1) / vec + cr::kWideColumnChunks - 1) / cr::kWideColumnChunks;
+    p->units = query_units();
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(4 * static_cast<int64_t>(p->units) / blocks, p->m / 16));
+    cr::once_equal_parts(p->slabs, p->m, parts, static_cast<int32_t>(std::min<int64_t>(rows_per_sum, int64_t(1) << 30)), p->work);
+}
+
 int ensure_split(cr_plan_t *p)
 {
     if (!p->split.pieces.empty() || p->model == CR_AGGREGATE_ONLY) return CR_OK;
@@ -241,6 +256,7 @@ int ensure_split(cr_plan_t *p)
     int64_t value = p->split_value;
     p->variant = nullptr;
     p->once = nullptr;
+    p->rows_once = false;
     p->work = cr::OnceWork();
     const int domains = query_l2_domains();
     p->l2_domains = domains;
@@ -248,13 +264,7 @@ int ensure_split(cr_plan_t *p)
     p->l2_sharing = -1;
     const bool chosen_here = kind < 0;
     const bool large = p->m * p->d * elem_size(p) >= kLargeBytes;
-    if (kind < 0 && !p->once_variant) {
-        // rows too wide for the single-pass kernels: cells of about 2 MB of X, at most 512 rows, at least 16 so that there are a few
-        // thousand pieces to spread over the chip
-        kind = CR_SPLIT_ROW_CELLS;
-        value = std::min<int64_t>(96, std::max<int64_t>(16, (p->row_visits / 2048 + 15) / 16 * 16));
-    }
-    if (kind < 0 && large && p->s == 0) {
+    if (kind < 0 && large && p->s == 0 && p->once_variant) {
         // no row is held twice: equal ranges of the rows are equal ranges of the row visits
         kind = CR_SPLIT_EQUAL_RANGES;
         value = static_cast<int64_t>(query_units()) * p->once_variant->parts_per_unit;
@@ -277,14 +287,15 @@ int ensure_split(cr_plan_t *p)
     }
     if (kind < 0) {
         kind = CR_SPLIT_ROWS_ONCE;
-        value = p->once_variant->rows_per_sum;
+        value = p->once_variant ? p->once_variant->rows_per_sum : cr::kWideSumRows;
     }
     p->split_kind_used = kind;
     p->split_value_used = value;
     if (kind == CR_SPLIT_ROWS_ONCE) {
-        if (!p->once_variant) return fail(CR_E_INVAL, "rows of this width do not fit the single-pass kernels");
         if (p->m / value + 2 * static_cast<int64_t>(p->slabs.size()) > (int64_t(1) << 26)) return fail(CR_E_INVAL, "too many partial rows");
-        make_rows_once(p, value, chosen_here);
+        if (p->once_variant) make_rows_once(p, value, chosen_here);
+        else make_wide_once(p, value);
+        p->rows_once = true;
         cr::once_as_split(p->slabs, p->work, p->split);
     } else if (kind == CR_SPLIT_SHARED_CELLS) {
         if (!p->cell_holders) return fail(CR_E_INVAL, "no shared cells for rows of this width and type");
@@ -292,9 +303,11 @@ int ensure_split(cr_plan_t *p)
         p->unit_slots = unit_slots(p->d * elem_size(p), domains);
         cr::split_shared_queues(p->slabs, value, domains, p->cell_holders, p->unit_slots / domains, p->split);
         p->once = p->once_variant;
+        p->rows_once = true;
         cr::once_of_queues(p->slabs, p->split, p->cell_holders, chunk_rows(p->once, p->once->rows_per_sum), p->work);
     } else if (kind == CR_SPLIT_EQUAL_RANGES && chosen_here) {
         make_rows_once(p, p->once_variant->rows_per_sum, false);
+        p->rows_once = true;
         cr::once_as_split(p->slabs, p->work, p->split);
     } else {
         p->variant = p->variant_regs;
@@ -314,7 +327,7 @@ void compute_layout(cr_plan_t *p, size_t *total)
 {
     const size_t S = p->slabs.size(), N = p->tree.N, P = p->split.pieces.size();
     const size_t runs = p->work.runs.size(), parts = p->work.part_run_begin.empty() ? 0 : p->work.part_run_begin.size() - 1;
-    const size_t sums = p->once ? p->work.sums.size() : S, dst = p->once ? p->work.dst.size() : S;
+    const size_t sums = p->rows_once ? p->work.sums.size() : S, dst = p->rows_once ? p->work.dst.size() : S;
     // worst case: one term per slab plus one dummy per node, each sub-program padded to the unroll
     p->max_terms = align_up(S + N + static_cast<size_t>(p->n) * cr::kEncodeUnroll, cr::kEncodeUnroll);
     size_t off = 0;
@@ -329,8 +342,8 @@ void compute_layout(cr_plan_t *p, size_t *total)
 
     size_t w = 0;
     auto take = [&](size_t bytes) { const size_t at = w; w = align_up(w + bytes, 256); return at; };
-    p->at_pieces = take(p->once ? 0 : P * sizeof(cr::DevPiece));
-    p->at_team_piece_begin = take(p->once ? 0 : (p->split.teams + 1) * sizeof(int32_t));
+    p->at_pieces = take(p->rows_once ? 0 : P * sizeof(cr::DevPiece));
+    p->at_team_piece_begin = take(p->rows_once ? 0 : (p->split.teams + 1) * sizeof(int32_t));
     p->at_parts = take(parts * sizeof(cr::DevRun));
     p->at_runs = take(runs * sizeof(cr::DevRun));
     p->at_sums = take(p->model == CR_AGGREGATE_ONLY ? 0 : sums * sizeof(cr::DevSum));
@@ -339,8 +352,8 @@ void compute_layout(cr_plan_t *p, size_t *total)
     p->at_program = take(kProgramSlots * p->program_bytes);
     const size_t row = static_cast<size_t>(p->d) * sizeof(float);
     if (p->model != CR_AGGREGATE_ONLY) {
-        p->at_G = take((S + (p->once ? p->work.partials : P)) * row);
-        p->at_residuals = take(p->once || p->variant ? 0 : static_cast<size_t>(p->row_visits) * sizeof(float));
+        p->at_G = take((S + (p->rows_once ? p->work.partials : P)) * row);
+        p->at_residuals = take(p->once || p->variant ? 0 : static_cast<size_t>(p->rows_once ? p->m : p->row_visits) * sizeof(float));
     }
     p->at_M = take(N * row);
     *total = w;
@@ -642,7 +655,7 @@ int cr_bind_workspace(cr_plan_t *p, void *dev_ptr, size_t bytes, void *hip_strea
 
     std::vector<cr::DevSum> sums;
     std::vector<int32_t> dst;
-    if (p->once) {
+    if (p->rows_once) {
         std::vector<cr::DevRun> runs, parts;
         for (const cr::RowRun &r : p->work.runs) runs.push_back({r.row_begin, static_cast<int32_t>(r.row_end - r.row_begin), r.dst_begin, r.dst_end, 0, 0, 0});
         for (size_t b = 0; b + 1 < p->work.part_run_begin.size(); ++b) {
@@ -710,6 +723,10 @@ int cr_partial_grads(cr_plan_t *p, const void *X, const float *y, const float *w
         if (p->once) {
             CR_HIP(cr::launch_rows_once(*p->once, X, y, w, p->d_parts, static_cast<int>(p->work.part_run_begin.size()) - 1, p->d_runs, p->d_dst,
                                         p->d_G, p->d, p->work.chunk, logistic, p->m * p->d * elem_size(p) >= kStreamFromBytes, p->stream));
+        } else if (p->rows_once) {
+            const int64_t cached_from = std::max<int64_t>(0, p->m - kKeptBytes / (p->d * elem_size(p)));
+            CR_HIP(cr::launch_wide_once(p->x_dtype, X, y, w, p->d_residuals, p->m, p->d_parts, static_cast<int>(p->work.part_run_begin.size()) - 1,
+                                        p->d_runs, p->d_dst, p->d_G, p->d, p->work.chunk, logistic, cached_from, p->units, p->stream));
         } else if (p->variant) {
             CR_HIP(cr::launch_partial_grads(*p->variant, X, y, w, p->d_pieces, p->d_team_piece_begin, p->split.teams, p->d_G, p->d, logistic,
                                             p->rows_as_buffers, p->stream));
@@ -720,7 +737,7 @@ int cr_partial_grads(cr_plan_t *p, const void *X, const float *y, const float *w
         t.done();
     }
     if (p->num_sums > 0) {
-        LaunchTimer t(p, CR_K_REDUCE_PIECES, ((p->once ? p->work.partials : P) + S) * p->d * 4);
+        LaunchTimer t(p, CR_K_REDUCE_PIECES, ((p->rows_once ? p->work.partials : P) + S) * p->d * 4);
         CR_HIP(cr::launch_sum_rows(p->d_G, p->d_sums, p->num_sums, p->d_dst, p->d, p->stream));
         t.done();
     }

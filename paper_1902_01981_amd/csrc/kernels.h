@@ -88,13 +88,19 @@ hipError_t launch_rows_once(const OnceVariant &v, const void *X, const float *y,
 hipError_t launch_partial_grads(const Stage1Variant &v, const void *X, const float *y, const float *w, const DevPiece *pieces,
                                 const int32_t *team_piece_begin, int num_teams, float *rows, int64_t d, int logistic,
                                 bool rows_as_buffers, hipStream_t stream);
-// Wide rows (a row does not fit the registers of one team): two passes.  launch_residuals writes phi(x.w) - y for every row visit,
+// Wide rows (a row does not fit the registers of one team), every holder separately: two passes.  launch_residuals writes phi(x.w) - y for every row visit,
 // launch_xt_residuals forms X^T r per piece and block of 256*kWideChunks*vec columns.  X is read twice on this path.
 constexpr int kWideChunks = 8;
 hipError_t launch_residuals(int x_dtype, const void *X, const float *y, const float *w, const DevPiece *pieces, int num_pieces,
                             float *residuals, int64_t d, int logistic, hipStream_t stream);
 hipError_t launch_xt_residuals(int x_dtype, const void *X, const DevPiece *pieces, int num_pieces, const float *residuals, float *rows,
                                int64_t d, hipStream_t stream);
+// The same with every row once, both passes: residuals has one entry per row of X; parts, runs, dst, rows and chunk as for launch_rows_once.
+// Rows from cached_from on are kept in the last-level cache between the passes.
+constexpr int kWideFoldRows = 64, kWideSumRows = 512, kWideColumnChunks = 256;
+hipError_t launch_wide_once(int x_dtype, const void *X, const float *y, const float *w, float *residuals, int64_t m, const DevRun *parts, int num_parts,
+                            const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int chunk, int logistic, int64_t cached_from, int units,
+                            hipStream_t stream);
 hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, const int32_t *dst, int64_t d, hipStream_t stream);
 hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int num_sub, int L, int64_t d, hipStream_t stream);
 // w != nullptr: also steps w <- w - lr g (g as stored, rounded to fp32) in the same launch

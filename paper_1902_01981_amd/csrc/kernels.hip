@@ -4,7 +4,8 @@
 //   rows_once_kernel, rows_once_team_kernel   CR.Execute step 1: X[b:e]^T (phi(X[b:e] w) - y[b:e]) in ONE pass over X, every row's
 //                          contribution formed once for all workers that hold it
 //   partial_grads_kernel   the same for every holder separately (the splits that lay out every holder's own work)
-//   residuals_kernel, xt_residuals_kernel   the same in two passes, for rows too wide for one team's registers
+//   wide_residuals_kernel, wide_xt_kernel   rows too wide for a workgroup's registers, every row once, in two passes
+//   residuals_kernel, xt_residuals_kernel   the same for every holder separately
 //   sum_rows_kernel        sums of partial rows (fixed order, so results are reproducible bit for bit)
 //   encode_kernel          CR.Execute steps 2-5: every node's message, children folded into parents in registers
 //   decode_kernel          the master's decode  g = sum_j a_j m_(1,j), optionally followed by w <- w - lr g in the same launch
@@ -687,7 +688,138 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
     }
 }
 
-// ---- stage 1 for wide rows -----------------------------------------------------------------------------------------
+// ---- stage 1 for wide rows, every row once ---------------------------------------------------------------------------
+// A row whose accumulators do not fit the registers of a workgroup is read twice: first the residuals phi(x.w) - y of every row
+// (R rows per workgroup, so that the weights, twice the size of a bf16 row, come out of the L2 once for R rows), then X^T r by
+// blocks of columns and parts of rows.  Both passes are bound by the read of X.  The rows from cached_from on are read with plain
+// loads and stay in the last-level cache for the second pass, which takes the parts from the end; the rest streams past (NT).
+// 4000 x 50008 bf16 (400 MB) on a (2,4) tree with s = 1: 61 and 70 us, the whole iteration 163 us; every holder's rows read for itself,
+// in cells of 16 rows, took 1683 us.
+template <int XD, int VEC, int R>
+__global__ void __launch_bounds__(512)
+wide_residuals_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w, float *__restrict__ residuals,
+                      int64_t m, int d, int nq, int logistic, int64_t cached_from)
+{
+    using C = Chunk<XD, VEC>;
+    constexpr int U = 8 / R, WAVES = 8;                  // eight row chunks in flight per thread
+    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * R;
+    float s[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) s[r] = 0.f;
+    auto pass = [&](auto nt) {
+        for (int b = 0; b < nq; b += 512 * U) {
+            typename C::raw_t x[U][R];
+            float wv[U][VEC];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int off = chunk_offset<VEC>(b + u * 512 + static_cast<int>(threadIdx.x), nq, d);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const void *row = row_ptr<XD>(X, min(r0 + r, m - 1), d);
+                    x[u][r] = decltype(nt)::value ? C::load_once(row, off) : C::load(row, off);
+                }
+                load_row<VEC>(w + off, wv[u]);
+            }
+            const bool whole = b + 512 * U < nq;         // no thread's chunk is the row's last one, which may overlap its neighbour
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    float xv[VEC];
+                    C::widen(x[u][r], xv);
+                    if (whole) {
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) s[r] = fmaf(xv[v], wv[u][v], s[r]);
+                    } else {
+                        const int q = b + u * 512 + static_cast<int>(threadIdx.x);
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v)
+                            if (chunk_owns<VEC>(q, v, nq, d)) s[r] = fmaf(xv[v], wv[u][v], s[r]);
+                    }
+                }
+        }
+    };
+    if (r0 >= cached_from) pass(std::false_type{});
+    else pass(std::true_type{});
+    __shared__ float red[R][WAVES];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const float t = group_sum<64>(s[r]);
+        if ((threadIdx.x & 63) == 0) red[r][threadIdx.x >> 6] = t;
+    }
+    __syncthreads();
+    const int r = threadIdx.x;
+    if (r >= R || r0 + r >= m) return;
+    float z = 0.f;
+#pragma unroll
+    for (int i = 0; i < WAVES; ++i) z += red[r][i];
+    residuals[r0 + r] = residual(z, y[r0 + r], logistic);
+}
+
+// Sums in fp32 over kWideFoldRows rows, added up in fp32 over a chunk of kWideSumRows.
+template <int XD, int VEC>
+__global__ void __launch_bounds__(256)
+wide_xt_kernel(const void *__restrict__ X, const float *__restrict__ residuals, const DevRun *__restrict__ parts, const DevRun *__restrict__ runs,
+               const int32_t *__restrict__ dst, float *__restrict__ rows, int d, int nq, int chunk, int64_t cached_from)
+{
+    using C = Chunk<XD, VEC>;
+    constexpr int U = 16;                                // rows in flight
+    static_assert(kWideFoldRows % U == 0, "whole steps per fold");
+    const table_t<DevRun> part = table(parts) + (gridDim.y - 1 - blockIdx.y);
+    const int more = part->more_end;
+    int next = part->more_begin;
+    Run run = read_run(part);
+    const int q = blockIdx.x * 256 + threadIdx.x;        // threads past the row repeat its last chunk and do not store
+    const int off = chunk_offset<VEC>(q, nq, d);
+    const bool cached = run.row_begin >= cached_from;
+    for (;;) {
+        const void *base = row_ptr<XD>(X, run.row_begin, d);
+        const float *res = residuals + run.row_begin;
+        const int n = run.nrows;
+        for (int r0 = 0, to = run.dst_begin; r0 < n; ++to) {
+            const int stop = min(r0 + chunk, n);
+            float sum[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) sum[v] = 0.f;
+            auto pass = [&](auto nt) {
+                while (r0 < stop) {
+                    const int end = min(r0 + kWideFoldRows, stop);
+                    float acc[VEC];
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
+                    for (; r0 < end; r0 += U) {
+                        typename C::raw_t x[U];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const void *row = row_ptr<XD>(base, min(r0 + u, end - 1), d);
+                            x[u] = decltype(nt)::value ? C::load_once(row, off) : C::load(row, off);
+                        }
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+                            if (r0 + u < end) {
+                                float xv[VEC];
+                                C::widen(x[u], xv);
+#pragma unroll
+                                for (int v = 0; v < VEC; ++v) acc[v] = fmaf(res[r0 + u], xv[v], acc[v]);
+                            }
+                    }
+                    r0 = end;
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) sum[v] += acc[v];
+                }
+            };
+            if (cached) pass(std::false_type{});
+            else pass(std::true_type{});
+            if (q < nq)
+                for (int j = to, je = r0 < n ? to + 1 : run.dst_end; j < je; ++j)
+                    store_row<VEC>(rows + static_cast<int64_t>(table(dst)[j]) * d + off, sum);
+        }
+        if (next >= more) break;
+        run = read_run(table(runs) + next++);
+    }
+}
+
+// ---- stage 1 for wide rows, every holder separately ----------------------------------------------------------------
 // When a row is too long for one team's registers the single pass is split in two: first the residuals r = phi(x.w) - y of every
 // row visit (one workgroup per piece, the row streamed in chunks), then G_piece = X^T r per piece and column block.
 template <int XD, int VEC>
@@ -1154,6 +1286,37 @@ hipError_t launch_xt_residuals(int x_dtype, const void *X, const DevPiece *piece
                                int64_t d, hipStream_t stream)
 {
     return dispatch_wide(x_dtype, X, nullptr, nullptr, pieces, num_pieces, const_cast<float *>(residuals), rows, d, 0, stream);
+}
+
+namespace {
+template <int XD, int VEC>
+hipError_t wide_once(const void *X, const float *y, const float *w, float *residuals, int64_t m, const DevRun *parts, int num_parts, const DevRun *runs,
+                     const int32_t *dst, float *rows, int64_t d, int chunk, int logistic, int64_t cached_from, int units, hipStream_t stream)
+{
+    const int nq = static_cast<int>((d + VEC - 1) / VEC), di = static_cast<int>(d);
+    auto residuals_of = [&](auto r) {
+        constexpr int R = decltype(r)::value;
+        wide_residuals_kernel<XD, VEC, R><<<static_cast<unsigned>((m + R - 1) / R), 512, 0, stream>>>(X, y, w, residuals, m, di, nq, logistic, cached_from);
+    };
+    // the most rows per workgroup that still leave the chip nearly two workgroups per compute unit
+    const int64_t enough = 2 * static_cast<int64_t>(units) * 7 / 8;
+    if (m >= 8 * enough) residuals_of(std::integral_constant<int, 8>{});
+    else if (m >= 4 * enough) residuals_of(std::integral_constant<int, 4>{});
+    else if (m >= 2 * enough) residuals_of(std::integral_constant<int, 2>{});
+    else residuals_of(std::integral_constant<int, 1>{});
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    wide_xt_kernel<XD, VEC><<<dim3((nq + 255) / 256, num_parts), 256, 0, stream>>>(X, residuals, parts, runs, dst, rows, di, nq, chunk, cached_from);
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_wide_once(int x_dtype, const void *X, const float *y, const float *w, float *residuals, int64_t m, const DevRun *parts, int num_parts,
+                            const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int chunk, int logistic, int64_t cached_from, int units,
+                            hipStream_t stream)
+{
+    if (x_dtype == 0) return wide_once<0, 4>(X, y, w, residuals, m, parts, num_parts, runs, dst, rows, d, chunk, logistic, cached_from, units, stream);
+    return wide_once<1, 8>(X, y, w, residuals, m, parts, num_parts, runs, dst, rows, d, chunk, logistic, cached_from, units, stream);
 }
 
 hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, const int32_t *dst, int64_t d, hipStream_t stream)

@@ -38,10 +38,14 @@ def test_rows_once_tables(value):
     rows = np.array([sum(end[b] - b for b in end if by[b] == t) for t in range(info.num_teams)])
     assert rows.max() - rows.min() <= 1 and rows.sum() == 4_003
     cr.cr_plan_destroy(p)
+    # rows too wide for one pass: every row once by default too, and what the plan reports can be set
     wide = cr.cr_plan_ex(2, 3, 1, 100, 24_577)
-    with pytest.raises(cr.CodedReduceError) as ei:
-        cr.cr_plan_set_split(wide, cr.CR_SPLIT_ROWS_ONCE, 64)
-    assert ei.value.status == cr.CR_E_INVAL
+    cr.cr_workspace_bytes(wide)
+    info = cr.cr_plan_info(wide)
+    assert (info.split_kind, info.stage1_team_size) == (cr.CR_SPLIT_ROWS_ONCE, 0)
+    pieces = cr.cr_plan_get_pieces(wide)
+    cr.cr_plan_set_split(wide, info.split_kind, info.split_value)
+    assert all(np.array_equal(a, b) for a, b in zip(pieces, cr.cr_plan_get_pieces(wide)))
     cr.cr_plan_destroy(wide)
 
 
@@ -93,3 +97,38 @@ def test_rows_once_streamed_past_the_caches():
             cr.cr_plan_destroy(plan)
         for q in range(len(out[0])):
             assert_close(out[0][q], out[1][q], 1e-5, gate_for(), ("slab", d, q))
+
+
+# rows per workgroup of the first pass 1, 2, 4 and 8 (from 448, 896, 1792 and 3584 rows on 256 compute units) and a ragged last one;
+# rows that end in a whole chunk, an overlapping one, a chunk of one column; more rows than are kept in the cache between the passes
+WIDE = [(24_577, 0, 13), (24_580, 1, 14), (30_003, 0, 897), (32_768, 1, 451), (24_583, 1, 1_801), (24_578, 0, 3_601)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,bf16,m", WIDE)
+def test_wide_rows_once(d, bf16, m):
+    """Two passes, every row once, against the row cells of every holder separately: the same sums over runs of up to 512 rows in
+    another order, so both lie within fp32 rounding of each other, well under the gate (1e-5); `value` 1 and 70 for sums of one row and
+    of one fold and a remainder."""
+    import torch
+
+    for logistic in (0, 1):
+        X = torch.empty(m, d, device="cuda", dtype=torch.bfloat16 if bf16 else torch.float32).normal_()
+        w = torch.randn(d, device="cuda") / d ** 0.5
+        y = (torch.rand(m, device="cuda") < 0.5).float()
+        out = []
+        for split in ((cr.CR_SPLIT_ROW_CELLS, 64), None, (cr.CR_SPLIT_ROWS_ONCE, 1), (cr.CR_SPLIT_ROWS_ONCE, 70)):
+            if split and split[1] == 1 and m > 1_000:
+                continue
+            plan = cr.cr_plan_ex(2, 3, 1, m, d, model=logistic, x_dtype=bf16)
+            if split:
+                cr.cr_plan_set_split(plan, *split)
+            ws = cr.Workspace(plan)
+            ws.slab_grads().fill_(float("nan"))
+            cr.cr_partial_grads(plan, X, y, w)
+            cr.cr_synchronize(plan)
+            out.append(ws.slab_grads().double().cpu().numpy())
+            cr.cr_plan_destroy(plan)
+        for G in out[1:]:
+            for q in range(len(G)):
+                assert_close(G[q], out[0][q], 1e-5, gate_for(), ("slab", d, q))
