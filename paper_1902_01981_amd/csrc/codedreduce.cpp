@@ -760,7 +760,7 @@ int cr_load_partial_grads(cr_plan_t *p, const float *G)
 
 namespace {
 
-struct ProgramCounts { int64_t active_slabs = 0, active_msgs = 0; int dec_terms = 0; };
+struct ProgramCounts { int64_t active_slabs = 0, active_msgs = 0; int terms = 0, dec_terms = 0; };
 
 // Turns a straggler mask into the encode program of one iteration, written into the host block h (program_bytes long, laid out
 // by compute_layout): the post-order term list of every level-1 sub-tree and the master's decode terms.  Any group beyond
@@ -829,8 +829,17 @@ int build_program(cr_plan_t *p, const uint8_t *mask, char *h, ProgramCounts *cou
     int ndec = 0;
     for (int j = 0; j < n; ++j)
         if (!mask[j] && rows[0][j] != 0.0) dec[ndec++] = {j, 0, rows[0][j]};
+    counts->terms = static_cast<int>(nt);                // padding included
     counts->dec_terms = ndec;
     return CR_OK;
+}
+
+// the program's arrays in a program block, in host or device memory
+cr::ProgramTables program_tables(const cr_plan_t *p, char *block)
+{
+    return {reinterpret_cast<int32_t *>(block + p->off_slab), reinterpret_cast<int32_t *>(block + p->off_level), reinterpret_cast<int32_t *>(block + p->off_row),
+            reinterpret_cast<double *>(block + p->off_coef), reinterpret_cast<double *>(block + p->off_acoef), reinterpret_cast<int32_t *>(block + p->off_sub),
+            reinterpret_cast<cr::DecTerm *>(block + p->off_dec)};
 }
 
 // the program's arrays as the encode kernel takes them, for a program block at device address d_program
@@ -1017,7 +1026,7 @@ int cr_aggregate_static(cr_plan_t *p, const float *G, const uint8_t *mask, float
     CR_HIP(cr::static_scratch(&base));                  // this device's copy of the array; never the array's name
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     float *M = reinterpret_cast<float *>(base + cr::kStaticProgramBytes);
-    CR_HIP(cr::launch_upload(base, p->static_program.data(), p->program_bytes, stream));
+    CR_HIP(cr::launch_program(program_tables(p, base), program_tables(p, p->static_program.data()), counts.terms, 2 * p->n, counts.dec_terms, stream));
     CR_HIP(cr::launch_encode(G, M, program_view(p, base), p->n, p->L, p->d, stream));
     CR_HIP(cr::launch_decode(M, g, reinterpret_cast<const cr::DecTerm *>(base + p->off_dec), counts.dec_terms, p->d, nullptr, 0.f, stream));
     return CR_OK;

@@ -115,9 +115,16 @@ hipError_t launch_stream_read(const void *src, size_t n16, float *sink, hipStrea
 constexpr size_t kStaticProgramBytes = size_t(64) << 10;                 // head of the array: one encode program
 constexpr size_t kStaticScratchBytes = size_t(96) << 20;                 // the whole array; messages follow the program
 hipError_t static_scratch(char **ptr);
-// copies `bytes` (a multiple of 4) from host memory to the device address dst through kernel arguments: launches only, no
-// staging buffer, no memcpy node; the host bytes are consumed before the call returns
-hipError_t launch_upload(char *dst, const char *src_host, size_t bytes, hipStream_t stream);
+// An encode program's tables, in device or in host memory; launch_program sends `terms` terms (at most 4096, of slabs and rows below
+// 4096), `subs` (an even number) sub-program words and `decs` decode terms of the host's through kernel arguments: launches only, no
+// staging buffer, no memcpy node; the host tables are consumed before the call returns
+struct ProgramTables {
+    int32_t *slab, *level, *row;
+    double *coef, *acoef;
+    int32_t *sub;
+    DecTerm *dec;
+};
+hipError_t launch_program(const ProgramTables &out, const ProgramTables &host, int terms, int subs, int decs, hipStream_t stream);
 
 // one wavefront per workgroup; out[workgroup id] = (die the workgroup ran on) << 16 | (shader engine and compute unit inside the die)
 hipError_t launch_placement_probe(uint32_t *out, int groups, hipStream_t stream);

@@ -1433,21 +1433,80 @@ hipError_t static_scratch(char **ptr)
     return hipSuccess;
 }
 
-// A block of host bytes travels as a kernel argument (kernel arguments are copied when the launch is enqueued) and one
-// workgroup writes it out with vector stores.
-struct UploadBlock { uint32_t word[960]; };
-__global__ void __launch_bounds__(256) upload_kernel(uint32_t *__restrict__ dst, UploadBlock block, int nwords)
+// An encode program travels as kernel arguments (copied when the launch is enqueued) and one workgroup writes it out with vector
+// stores.  What bounds it is the number of launches, 4 KB of arguments at most each, so a term of 28 bytes travels as 8: slab, row,
+// level and the places of its two coefficients in a table of the block's distinct ones.  Every block is complete in itself, and only
+// the terms that the mask leaves travel.  Ten vectors of 10 to 73728 entries on a tree of two levels of twelve with s = 2: 305 to
+// 340 us with the program's bytes as they are (six launches per vector), 155 us in this form (one).
+struct ProgramBlock {
+    static constexpr int kWords = 480;                   // 8-byte words: the coefficients, then the terms
+    int32_t first, terms, coefs, subs, decs, pad;        // subs / decs: words of the sub-program and decode tables, behind the terms
+    uint64_t word[kWords];
+};
+static_assert(sizeof(ProgramBlock) <= 4000, "kernel arguments");
+
+__global__ void __launch_bounds__(256) program_kernel(ProgramTables out, ProgramBlock block)
 {
-    for (int i = threadIdx.x; i < nwords; i += 256) dst[i] = block.word[i];
+    for (int i = threadIdx.x; i < block.terms; i += 256) {
+        const uint64_t t = block.word[block.coefs + i];
+        out.slab[block.first + i] = static_cast<int32_t>(t & 4095);
+        out.row[block.first + i] = static_cast<int32_t>(t >> 12 & 4095);
+        out.level[block.first + i] = static_cast<int32_t>(t >> 24 & 15);
+        out.coef[block.first + i] = __longlong_as_double(static_cast<int64_t>(block.word[t >> 28 & 4095]));
+        out.acoef[block.first + i] = __longlong_as_double(static_cast<int64_t>(block.word[t >> 40 & 4095]));
+    }
+    const int at = block.coefs + block.terms;
+    for (int i = threadIdx.x; i < block.subs; i += 256) reinterpret_cast<uint64_t *>(out.sub)[i] = block.word[at + i];
+    for (int i = threadIdx.x; i < block.decs; i += 256) reinterpret_cast<uint64_t *>(out.dec)[i] = block.word[at + block.subs + i];
 }
 
-hipError_t launch_upload(char *dst, const char *src_host, size_t bytes, hipStream_t stream)
+hipError_t launch_program(const ProgramTables &out, const ProgramTables &host, int terms, int subs, int decs, hipStream_t stream)
 {
-    for (size_t off = 0; off < bytes; off += sizeof(UploadBlock)) {
-        UploadBlock block;
-        const size_t len = bytes - off < sizeof(UploadBlock) ? bytes - off : sizeof(UploadBlock);
-        std::memcpy(block.word, src_host + off, len);
-        upload_kernel<<<1, 256, 0, stream>>>(reinterpret_cast<uint32_t *>(dst + off), block, static_cast<int>(len / 4));
+    constexpr int kSlots = 2048;                         // of the hash table; a block has fewer than 480 distinct coefficients
+    constexpr int kTailWords = 64 + 2 * 64;              // groups have at most 64 members: their tables leave room for terms
+    uint16_t slot[kSlots];
+    ProgramBlock block;
+    const int subs8 = subs / 2, decs8 = decs * 2;
+    static_assert(sizeof(DecTerm) == 16 && kTailWords < ProgramBlock::kWords, "tables in 8-byte words");
+    if (terms > 4096 || subs % 2 != 0 || subs8 + decs8 > kTailWords) return hipErrorInvalidValue;
+    bool tail = false;                                   // the sub-program and decode tables are on their way
+    for (int first = 0; first < terms || !tail;) {
+        std::memset(slot, 0xff, sizeof slot);
+        int coefs = 0, count = 0;
+        uint64_t packed[ProgramBlock::kWords];
+        auto place = [&](double c) {                     // the coefficient's place in the block's table
+            uint64_t bits;
+            std::memcpy(&bits, &c, 8);
+            unsigned h = static_cast<unsigned>((bits * 0x9E3779B97F4A7C15ull) >> 53);
+            while (slot[h] != 0xffff && block.word[slot[h]] != bits) h = (h + 1) % kSlots;
+            if (slot[h] == 0xffff) {
+                slot[h] = static_cast<uint16_t>(coefs);
+                block.word[coefs++] = bits;
+            }
+            return static_cast<uint64_t>(slot[h]);
+        };
+        while (first + count < terms && coefs + count + 3 <= ProgramBlock::kWords) {     // room for a term and two new coefficients
+            const int t = first + count;
+            if ((host.slab[t] | host.row[t]) >> 12 || host.level[t] >> 4) return hipErrorInvalidValue;
+            const uint64_t c = place(host.coef[t]), a = place(host.acoef[t]);
+            packed[count++] = static_cast<uint64_t>(host.slab[t]) | static_cast<uint64_t>(host.row[t]) << 12 |
+                              static_cast<uint64_t>(host.level[t]) << 24 | c << 28 | a << 40;
+        }
+        std::memcpy(block.word + coefs, packed, static_cast<size_t>(count) * 8);
+        block.first = first;
+        block.terms = count;
+        block.coefs = coefs;
+        block.subs = block.decs = block.pad = 0;
+        first += count;
+        const int used = coefs + count;
+        if (first == terms && used + subs8 + decs8 <= ProgramBlock::kWords) {
+            block.subs = subs8;
+            block.decs = decs8;
+            std::memcpy(block.word + used, host.sub, static_cast<size_t>(subs8) * 8);
+            std::memcpy(block.word + used + subs8, host.dec, static_cast<size_t>(decs8) * 8);
+            tail = true;
+        }
+        program_kernel<<<1, 256, 0, stream>>>(out, block);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
