@@ -291,6 +291,8 @@ int ensure_split(cr_plan_t *p)
     }
     p->split_kind_used = kind;
     p->split_value_used = value;
+    // more rows than there are mean all of them; the products and sums below then stay far inside 64 bits
+    if (kind != CR_SPLIT_EQUAL_RANGES) value = std::min(value, p->m);
     if (kind == CR_SPLIT_ROWS_ONCE) {
         if (p->m / value + 2 * static_cast<int64_t>(p->slabs.size()) > (int64_t(1) << 26)) return fail(CR_E_INVAL, "too many partial rows");
         if (p->once_variant) make_rows_once(p, value, chosen_here);
