@@ -75,7 +75,7 @@ typedef struct cr_plan_info {
     int64_t m, d;
     int64_t row_visits;      /* sum over workers of allocated rows */
     int64_t min_rows, max_rows; /* smallest / largest per-worker load; both equal r_CR m up to integer cuts (Theorem 1) */
-    int64_t split_value;     /* teams (equal ranges), rows per cell (row cells, shared cells) or rows per fp32 sum (rows once); 0 until the split is known */
+    int64_t split_value;     /* teams (equal ranges), rows per cell (row cells, shared cells) or rows per run (rows once); 0 until the split is known */
     double gamma;            /* max_f sum_i |a_fi| ||b_i||_2 / sqrt(n): rounding amplification of one decode.  Messages are fp32, so
                               * a decoded gradient carries a relative rounding error of about gamma^L * 2^-24 (see code_warning) */
     double r_cr;             /* computation load of Theorem 1 */
@@ -127,10 +127,11 @@ int cr_plan_decode_row(const cr_plan_t *plan, const uint8_t *flags /* host, n */
  *                          most 8 KB) and forms every row of a cell once for the 2, 3, 4, 6 or 8 holders it serves
  *                          (stage1_teams_per_group, by row width and by (s+1)^L, the most holders a row can have) -- and for the
  *                          others, if a cell has more.  fp32 rows of 257 to 3072 16-byte chunks with s > 0 only, else CR_E_INVAL.
- *   CR_SPLIT_ROWS_ONCE     value = most rows in one fp32 sum, rounded up to an even number of the kernel's steps (sums are added up in fp64): X is
- *                          cut into one or two contiguous parts per compute unit, a part into runs at slab boundaries; a workgroup
- *                          forms every row of its part once, for all slabs that hold it.  Rows too wide for the registers of a
- *                          workgroup (d > 24576) take two passes over X, the second cut into parts of rows and blocks of columns.
+ *   CR_SPLIT_ROWS_ONCE     value = most rows per run: X is cut into one or two contiguous parts per compute unit, a part into runs at
+ *                          slab boundaries and after `value` rows; a workgroup forms every row of its part once, for all slabs that
+ *                          hold it, and adds a run up in fp64 (all but the up to four rows it has in hand at a time).  Rows too wide
+ *                          for the registers of a workgroup (d > 24576) take two passes over X, the second cut into parts of rows
+ *                          and blocks of columns.
  * With the first two every holder of a row does its own arithmetic on it, as separate workers would: they are there to measure what
  * the redundancy of a scheme costs.  With the other two the holders' identical sums are formed once and handed to every slab they
  * belong to.  The slab gradients agree to rounding under every split.

@@ -207,27 +207,19 @@ int shared_cell_holders(int x_dtype, int64_t d, int64_t max_holders)
 // Bytes of X that the first pass over wide rows leaves in the 256 MB last-level cache for the second.
 constexpr int64_t kKeptBytes = int64_t(160) << 20;
 
-// rows added up in fp32, per accumulator at most `rows_per_sum`: an even number of the kernel's steps
-int32_t chunk_rows(const cr::OnceVariant *v, int64_t rows_per_sum)
-{
-    const int64_t rows = std::min<int64_t>(rows_per_sum * v->sums_per_workgroup(), int64_t(1) << 30), steps = 2 * v->rows_per_step;
-    return static_cast<int32_t>((rows + steps - 1) / steps * steps);
-}
-
 // Rows one after the other along X, every row once, on every compute unit: the parts of the default split.
-void make_rows_once(cr_plan_t *p, int64_t rows_per_sum, bool may_take_whole_ranges)
+void make_rows_once(cr_plan_t *p, int64_t rows_per_run, bool may_take_whole_ranges)
 {
     const cr::OnceVariant *v = p->once_variant;
     if (may_take_whole_ranges) {
         // Small problems: a workgroup per distinct slab range forms its gradient whole, which saves the launch that adds up partial
         // rows.  The line is where the two take the same time, at about 48 Ki elements in the longest range (fp32, a (3,2) tree, us
         // whole / parts and sum: 200 x 100 elements 5.6 / 7.5, 667 x 100 9.0 / 8.2; 67 x 1000 6.3 / 7.5, 200 x 1000 12.2 / 7.8).
-        const cr::OnceVariant *whole = cr::select_once_whole(p->x_dtype, p->d);
         int64_t longest = 0;
         for (const cr::Slab &sl : p->slabs) longest = std::max(longest, sl.row_end - sl.row_begin);
-        if (longest * p->d <= 48 * 1024 && longest <= chunk_rows(whole, rows_per_sum)) {
-            p->once = whole;
-            cr::once_whole_ranges(p->slabs, chunk_rows(whole, rows_per_sum), p->work);
+        if (longest * p->d <= 48 * 1024) {
+            p->once = cr::select_once_whole(p->x_dtype, p->d);
+            cr::once_whole_ranges(p->slabs, p->work);
             return;
         }
     }
@@ -236,17 +228,17 @@ void make_rows_once(cr_plan_t *p, int64_t rows_per_sum, bool may_take_whole_rang
     // partial rows of shorter parts cost more than the extra workgroups bring)
     const int64_t least = v->threads_per_row <= 64 ? std::min(v->rows_per_step, 128) : 2;
     const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(static_cast<int64_t>(query_units()) * v->parts_per_unit, p->m / least));
-    cr::once_equal_parts(p->slabs, p->m, parts, chunk_rows(v, rows_per_sum), p->work);
+    cr::once_equal_parts(p->slabs, p->m, parts, rows_per_run, p->work);
 }
 
 // The same for wide rows: the parts of the second pass, each of which has one workgroup per block of columns.  Four workgroups per
 // compute unit, no fewer rows per part than a workgroup has in flight.
-void make_wide_once(cr_plan_t *p, int64_t rows_per_sum)
+void make_wide_once(cr_plan_t *p, int64_t rows_per_run)
 {
     const int64_t vec = p->x_dtype == CR_BF16 ? 8 : 4, blocks = ((p->d + vec - 1) / vec + cr::kWideColumnChunks - 1) / cr::kWideColumnChunks;
     p->units = query_units();
     const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(4 * static_cast<int64_t>(p->units) / blocks, p->m / 16));
-    cr::once_equal_parts(p->slabs, p->m, parts, static_cast<int32_t>(std::min<int64_t>(rows_per_sum, int64_t(1) << 30)), p->work);
+    cr::once_equal_parts(p->slabs, p->m, parts, rows_per_run, p->work);
 }
 
 int ensure_split(cr_plan_t *p)
@@ -287,7 +279,7 @@ int ensure_split(cr_plan_t *p)
     }
     if (kind < 0) {
         kind = CR_SPLIT_ROWS_ONCE;
-        value = p->once_variant ? p->once_variant->rows_per_sum : cr::kWideSumRows;
+        value = p->m;
     }
     p->split_kind_used = kind;
     p->split_value_used = value;
@@ -306,9 +298,9 @@ int ensure_split(cr_plan_t *p)
         cr::split_shared_queues(p->slabs, value, domains, p->cell_holders, p->unit_slots / domains, p->split);
         p->once = p->once_variant;
         p->rows_once = true;
-        cr::once_of_queues(p->slabs, p->split, p->cell_holders, chunk_rows(p->once, p->once->rows_per_sum), p->work);
+        cr::once_of_queues(p->slabs, p->split, p->cell_holders, p->work);
     } else if (kind == CR_SPLIT_EQUAL_RANGES && chosen_here) {
-        make_rows_once(p, p->once_variant->rows_per_sum, false);
+        make_rows_once(p, p->m, false);
         p->rows_once = true;
         cr::once_as_split(p->slabs, p->work, p->split);
     } else {
@@ -724,11 +716,11 @@ int cr_partial_grads(cr_plan_t *p, const void *X, const float *y, const float *w
         LaunchTimer t(p, CR_K_PARTIAL_GRADS, bytes);
         if (p->once) {
             CR_HIP(cr::launch_rows_once(*p->once, X, y, w, p->d_parts, static_cast<int>(p->work.part_run_begin.size()) - 1, p->d_runs, p->d_dst,
-                                        p->d_G, p->d, p->work.chunk, logistic, p->m * p->d * elem_size(p) >= kStreamFromBytes, p->stream));
+                                        p->d_G, p->d, logistic, p->m * p->d * elem_size(p) >= kStreamFromBytes, p->stream));
         } else if (p->rows_once) {
             const int64_t cached_from = std::max<int64_t>(0, p->m - kKeptBytes / (p->d * elem_size(p)));
             CR_HIP(cr::launch_wide_once(p->x_dtype, X, y, w, p->d_residuals, p->m, p->d_parts, static_cast<int>(p->work.part_run_begin.size()) - 1,
-                                        p->d_runs, p->d_dst, p->d_G, p->d, p->work.chunk, logistic, cached_from, p->units, p->stream));
+                                        p->d_runs, p->d_dst, p->d_G, p->d, logistic, cached_from, p->units, p->stream));
         } else if (p->variant) {
             CR_HIP(cr::launch_partial_grads(*p->variant, X, y, w, p->d_pieces, p->d_team_piece_begin, p->split.teams, p->d_G, p->d, logistic,
                                             p->rows_as_buffers, p->stream));

@@ -68,20 +68,16 @@ struct OnceVariant {
     int rows_per_step;               // rows a workgroup takes per step
     int block;                       // threads per workgroup
     int parts_per_unit;              // contiguous parts of X per compute unit (see the kernels)
-    int rows_per_sum;                // most rows in one fp32 sum
     const void *fn[2];               // plain loads, loads with the non-temporal hint
-    // fp32 accumulators per column that share the rows of a workgroup
-    int sums_per_workgroup() const { return threads_per_row <= 64 ? block / threads_per_row : 1; }
 };
 // For (x_dtype, d), or nullptr if the row is too wide for the registers of a workgroup.
 const OnceVariant *select_once(int x_dtype, int64_t d);
 // The same with as many wavefronts per workgroup as there are for rows this narrow, for launches of a few workgroups.
 const OnceVariant *select_once_whole(int x_dtype, int64_t d);
-// Workgroup b runs parts[b], then runs[parts[b].more_begin .. more_end).  rows: the output table.  chunk: an even number of steps; a
-// run of more rows has one destination per chunk of that many.
+// Workgroup b runs parts[b], then runs[parts[b].more_begin .. more_end).  rows: the output table.
 hipError_t launch_rows_once(const OnceVariant &v, const void *X, const float *y, const float *w, const DevRun *parts, int num_parts,
-                            const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int chunk, int logistic,
-                            bool stream_past_caches, hipStream_t stream);
+                            const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int logistic, bool stream_past_caches,
+                            hipStream_t stream);
 
 // rows_as_buffers: every row starts on a 4-byte boundary and every piece has fewer than 2^31 bytes; variants that have a
 // buffer-load twin (bf16 rows, one wavefront per team) then run it
@@ -95,11 +91,11 @@ hipError_t launch_residuals(int x_dtype, const void *X, const float *y, const fl
                             float *residuals, int64_t d, int logistic, hipStream_t stream);
 hipError_t launch_xt_residuals(int x_dtype, const void *X, const DevPiece *pieces, int num_pieces, const float *residuals, float *rows,
                                int64_t d, hipStream_t stream);
-// The same with every row once, both passes: residuals has one entry per row of X; parts, runs, dst, rows and chunk as for launch_rows_once.
+// The same with every row once, both passes: residuals has one entry per row of X; parts, runs, dst and rows as for launch_rows_once.
 // Rows from cached_from on are kept in the last-level cache between the passes.
-constexpr int kWideFoldRows = 64, kWideSumRows = 512, kWideColumnChunks = 256;
+constexpr int kWideColumnChunks = 256;
 hipError_t launch_wide_once(int x_dtype, const void *X, const float *y, const float *w, float *residuals, int64_t m, const DevRun *parts, int num_parts,
-                            const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int chunk, int logistic, int64_t cached_from, int units,
+                            const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int logistic, int64_t cached_from, int units,
                             hipStream_t stream);
 hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, const int32_t *dst, int64_t d, hipStream_t stream);
 hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int num_sub, int L, int64_t d, hipStream_t stream);

@@ -374,10 +374,23 @@ template <typename T> __device__ __forceinline__ table_t<T> table(const T *p) { 
 struct Run { int64_t row_begin; int nrows, dst_begin, dst_end; };
 __device__ __forceinline__ Run read_run(table_t<DevRun> r) { return {r->row_begin, r->nrows, r->dst_begin, r->dst_end}; }
 
-// No more than this many rows are added up one by one in an fp32 accumulator; such sums are then added to each other (in fp32, up to
-// kFolds of them) or to other partial rows (in fp64).  Folding costs a second set of accumulators and nothing else; handing the
-// partial row over after 512 rows instead stalls all workgroups at once (252 000 x 4096 fp32: 611 us against 584).
-constexpr int kFoldRows = 512, kFolds = 8;
+// Sums over rows are kept in fp64 and rounded once per run; only the R <= 4 rows that a thread has in hand in one step are added in
+// fp32 first, which leaves one widening and one fp64 add per R rows.  (fp32 sums folded every 512 rows take the same registers and
+// were further from the exact slabs: 100 000 x 20 480 bf16 2.5e-7 against 0.7e-7.)
+template <int VEC, int R> __device__ __forceinline__ void add_rows(double (&acc)[VEC], const float (&res)[R], const float (&xv)[R][VEC])
+{
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+        if constexpr (R == 1) {
+            acc[v] = fma(static_cast<double>(res[0]), static_cast<double>(xv[0][v]), acc[v]);
+        } else {
+            float t = res[0] * xv[0][v];
+#pragma unroll
+            for (int r = 1; r < R; ++r) t = fmaf(res[r], xv[r][v], t);
+            acc[v] += static_cast<double>(t);
+        }
+    }
+}
 
 // phi(z) - y; the choice is the same for the whole launch
 __device__ __forceinline__ float residual(float z, float y, int logistic) { return (logistic ? sigmoid(z) : z) - y; }
@@ -401,21 +414,19 @@ template <int LPR> __device__ __forceinline__ float group_sum(float v)
 }
 
 // Rows of at most 256 chunks.  LPR lanes share a row (64 / LPR rows side by side in a wavefront), lane t of them holding chunks t,
-// t + LPR, ... (K > 1 only with LPR = 64); a wavefront takes R such sets of rows per step.  No barrier until the sums of a run -- or
-// of `chunk` rows of a longer one -- are done; then the accumulators of the whole workgroup meet in LDS and are added up in fp64 and
-// rounded once.
+// t + LPR, ... (K > 1 only with LPR = 64); a wavefront takes R such sets of rows per step.  No barrier until the sums of a run are
+// done; then the accumulators of the whole workgroup meet in LDS, are added up and rounded.
 template <int XD, int VEC, int LPR, int K, int R, int WAVES, bool NT>
 __global__ void __launch_bounds__(WAVES * 64)
 rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w, const DevRun *__restrict__ parts,
-                 const DevRun *__restrict__ runs, const int32_t *__restrict__ dst, float *__restrict__ rows, int d, int nq, int chunk, int logistic)
+                 const DevRun *__restrict__ runs, const int32_t *__restrict__ dst, float *__restrict__ rows, int d, int nq, int logistic)
 {
     static_assert(K == 1 || LPR == 64, "several chunks per lane only for rows of more than 64 chunks");
-    static_assert(kFoldRows % (2 * R) == 0, "sums are folded after an even number of steps");
     using C = Chunk<XD, VEC>;
     constexpr int RPW = 64 / LPR, STEP = WAVES * R * RPW, THREADS = WAVES * 64;
     // SETS sets of COLS accumulators each; where there are fewer columns than threads, GROUPS threads share a column
     constexpr int SETS = WAVES * RPW, COLS = K * LPR * VEC, GROUPS = COLS < THREADS ? THREADS / COLS : 1;
-    __shared__ __align__(16) float comb[SETS][COLS];
+    __shared__ __align__(16) double comb[SETS][COLS];
     __shared__ double comb2[GROUPS > 1 ? GROUPS : 1][GROUPS > 1 ? COLS : 1];
     const int lane = threadIdx.x & 63, sub = lane / LPR, tl = lane % LPR;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -443,19 +454,11 @@ rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const 
         const void *base = row_ptr<XD>(X, run.row_begin, d);
         const float *yb = y + run.row_begin;
         const int n = run.nrows;
-        float acc[K][VEC];
-        auto clear = [&](float (&s)[K][VEC]) {
+        double acc[K][VEC];
 #pragma unroll
-            for (int k = 0; k < K; ++k)
+        for (int k = 0; k < K; ++k)
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) s[k][v] = 0.f;
-        };
-        auto fold = [&](float (&s)[K][VEC]) {
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) s[k][v] += acc[k][v];
-        };
+            for (int v = 0; v < VEC; ++v) acc[k][v] = 0.0;
         // rows past the end of the run re-read its last row; they count for nothing
         auto load = [&](Step &s, int r0) {
 #pragma unroll
@@ -483,37 +486,38 @@ rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const 
                 }
                 z[r] = group_sum<LPR>(t);
             }
+            float res[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int at = r0 + (wave * R + r) * RPW + (RPW == 1 ? 0 : sub);
-                const float res = at < n ? residual(z[r], s.yy[r], logistic) : 0.f;
+                res[r] = at < n ? residual(z[r], s.yy[r], logistic) : 0.f;
+            }
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    float xv[VEC];
-                    C::widen(s.x[r][k], xv);
+            for (int k = 0; k < K; ++k) {
+                float xv[R][VEC];
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[k][v] = fmaf(res, xv[v], acc[k][v]);
-                }
+                for (int r = 0; r < R; ++r) C::widen(s.x[r][k], xv[r]);
+                add_rows<VEC, R>(acc[k], res, xv);
             }
         };
-        auto store = [&](const float (&s)[K][VEC], int dst_begin, int dst_end) {
+        auto store = [&] {
             __syncthreads();                             // the sums stored before these have been read
 #pragma unroll
             for (int k = 0; k < K; ++k)
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) comb[wave * RPW + sub][(k * LPR + tl) * VEC + v] = s[k][v];
+                for (int v = 0; v < VEC; ++v) comb[wave * RPW + sub][(k * LPR + tl) * VEC + v] = acc[k][v];
             __syncthreads();
             auto put = [&](int c, double t) {
                 const float out = static_cast<float>(t);
                 const int col = chunk_offset<VEC>(c / VEC, nq, d) + c % VEC;
-                for (int j = dst_begin; j < dst_end; ++j) rows[static_cast<int64_t>(table(dst)[j]) * d + col] = out;
+                for (int j = run.dst_begin; j < run.dst_end; ++j) rows[static_cast<int64_t>(table(dst)[j]) * d + col] = out;
             };
             if constexpr (GROUPS > 1) {
                 const int c = threadIdx.x % COLS, g = threadIdx.x / COLS;
                 double t = 0.0;
 #pragma unroll
                 for (int i = 0; i < (SETS + GROUPS - 1) / GROUPS; ++i)
-                    if (g + i * GROUPS < SETS) t += static_cast<double>(comb[g + i * GROUPS][c]);
+                    if (g + i * GROUPS < SETS) t += comb[g + i * GROUPS][c];
                 comb2[g][c] = t;
                 __syncthreads();
                 if (g == 0 && c < nq * VEC) {
@@ -525,33 +529,22 @@ rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const 
                 for (int c = threadIdx.x; c < nq * VEC; c += THREADS) {
                     double t = 0.0;
 #pragma unroll
-                    for (int i = 0; i < SETS; ++i) t += static_cast<double>(comb[i][c]);
+                    for (int i = 0; i < SETS; ++i) t += comb[i][c];
                     put(c, t);
                 }
             }
         };
-        // chunk is an even number of steps; the chunks of a run that has several go to one row each
         Step a, b;
         load(a, 0);
-        for (int r0 = 0, to = run.dst_begin; r0 < n; ++to) {
-            const int stop = min(r0 + chunk, n);
-            float sum[K][VEC];
-            clear(sum);
-            while (r0 < stop) {
-                const int end = min(r0 + kFoldRows / R * STEP, stop);
-                clear(acc);
-                for (;;) {
-                    load(b, r0 + STEP);
-                    compute(a, r0);
-                    if ((r0 += STEP) >= end) break;
-                    load(a, r0 + STEP);
-                    compute(b, r0);
-                    if ((r0 += STEP) >= end) break;
-                }
-                fold(sum);
-            }
-            store(sum, to, r0 < n ? to + 1 : run.dst_end);
+        for (int r0 = 0;;) {
+            load(b, r0 + STEP);
+            compute(a, r0);
+            if ((r0 += STEP) >= n) break;
+            load(a, r0 + STEP);
+            compute(b, r0);
+            if ((r0 += STEP) >= n) break;
         }
+        store();
         if (next >= more) break;
         run = read_run(table(runs) + next++);
     }
@@ -560,13 +553,12 @@ rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const 
 // Wider rows: the TS threads of the workgroup share every row, thread t holding chunks t, t + TS, ..., R rows per step.  One barrier
 // per step exchanges the wavefronts' parts of the dot products (double buffered in LDS).  PF: the next step's rows are loaded before
 // the current step is computed; beyond 9 chunks per thread the second register set costs more than it hides (a row is then long
-// enough: 12 chunks, 24576 columns, 200 MB: 43.4 us without, 45.8 with it).  FOLD: there are registers for a second set of sums.
-template <int XD, int VEC, int TS, int K, int R, bool PF, bool FOLD, bool NT>
+// enough: 12 chunks, 24576 columns, 200 MB: 43.4 us without, 45.8 with it).
+template <int XD, int VEC, int TS, int K, int R, bool PF, bool NT>
 __global__ void __launch_bounds__(TS)
 rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w, const DevRun *__restrict__ parts,
-                      const DevRun *__restrict__ runs, const int32_t *__restrict__ dst, float *__restrict__ rows, int d, int nq, int chunk, int logistic)
+                      const DevRun *__restrict__ runs, const int32_t *__restrict__ dst, float *__restrict__ rows, int d, int nq, int logistic)
 {
-    static_assert(kFoldRows % (2 * R) == 0, "sums are folded after an even number of steps");
     using C = Chunk<XD, VEC>;
     constexpr int WAVES = TS / 64;
     __shared__ float red[2][R][WAVES];
@@ -597,19 +589,11 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
         const void *base = row_ptr<XD>(X, run.row_begin, d);
         const float *yb = y + run.row_begin;
         const int n = run.nrows;
-        float acc[K][VEC];
-        auto clear = [&](float (&s)[K][VEC]) {
+        double acc[K][VEC];
 #pragma unroll
-            for (int k = 0; k < K; ++k)
+        for (int k = 0; k < K; ++k)
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) s[k][v] = 0.f;
-        };
-        auto fold = [&](float (&s)[K][VEC]) {
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) s[k][v] += acc[k][v];
-        };
+            for (int v = 0; v < VEC; ++v) acc[k][v] = 0.0;
         auto load = [&](Step &s, int r0) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -635,53 +619,45 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
                 if ((tl & 63) == 0) red[buf][r][wave] = dot;
             }
             __syncthreads();
+            float res[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 float z = 0.f;
 #pragma unroll
                 for (int i = 0; i < WAVES; ++i) z += red[buf][r][i];
-                const float res = r0 + r < n ? residual(z, s.yy[r], logistic) : 0.f;
+                res[r] = r0 + r < n ? residual(z, s.yy[r], logistic) : 0.f;
+            }
 #pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    float xv[VEC];
-                    C::widen(s.x[r][k], xv);
+            for (int k = 0; k < K; ++k) {
+                float xv[R][VEC];
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[k][v] = fmaf(res, xv[v], acc[k][v]);
-                }
+                for (int r = 0; r < R; ++r) C::widen(s.x[r][k], xv[r]);
+                add_rows<VEC, R>(acc[k], res, xv);
             }
             buf ^= 1;
         };
-        auto store = [&](const float (&s)[K][VEC], int dst_begin, int dst_end) {
-            for (int j = dst_begin; j < dst_end; ++j) {
-                float *out = rows + static_cast<int64_t>(table(dst)[j]) * d;
-#pragma unroll
-                for (int k = 0; k < K; ++k)
-                    if (tl + k * TS < nq) store_row<VEC>(out + off[k], s[k]);
-            }
-        };
         Step a, b;
         if constexpr (PF) load(a, 0);
-        for (int r0 = 0, to = run.dst_begin; r0 < n; ++to) {
-            const int stop = min(r0 + chunk, n);
-            float sum[K][VEC];
-            clear(sum);
-            while (r0 < stop) {
-                const int end = FOLD ? min(r0 + kFoldRows, stop) : stop;
-                clear(acc);
-                for (;;) {
-                    if constexpr (PF) load(b, r0 + R);
-                    else load(a, r0);
-                    compute(a, r0);
-                    if ((r0 += R) >= end) break;
-                    if constexpr (PF) {
-                        load(a, r0 + R);
-                        compute(b, r0);
-                        if ((r0 += R) >= end) break;
-                    }
-                }
-                if constexpr (FOLD) fold(sum);
+        for (int r0 = 0;;) {
+            if constexpr (PF) load(b, r0 + R);
+            else load(a, r0);
+            compute(a, r0);
+            if ((r0 += R) >= n) break;
+            if constexpr (PF) {
+                load(a, r0 + R);
+                compute(b, r0);
+                if ((r0 += R) >= n) break;
             }
-            store(FOLD ? sum : acc, to, r0 < n ? to + 1 : run.dst_end);
+        }
+        for (int j = run.dst_begin; j < run.dst_end; ++j) {
+            float *out = rows + static_cast<int64_t>(table(dst)[j]) * d;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                float sum[VEC];
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) sum[v] = static_cast<float>(acc[k][v]);
+                if (tl + k * TS < nq) store_row<VEC>(out + off[k], sum);
+            }
         }
         if (next >= more) break;
         run = read_run(table(runs) + next++);
@@ -756,15 +732,13 @@ wide_residuals_kernel(const void *__restrict__ X, const float *__restrict__ y, c
     residuals[r0 + r] = residual(z, y[r0 + r], logistic);
 }
 
-// Sums in fp32 over kWideFoldRows rows, added up in fp32 over a chunk of kWideSumRows.
 template <int XD, int VEC>
 __global__ void __launch_bounds__(256)
 wide_xt_kernel(const void *__restrict__ X, const float *__restrict__ residuals, const DevRun *__restrict__ parts, const DevRun *__restrict__ runs,
-               const int32_t *__restrict__ dst, float *__restrict__ rows, int d, int nq, int chunk, int64_t cached_from)
+               const int32_t *__restrict__ dst, float *__restrict__ rows, int d, int nq, int64_t cached_from)
 {
     using C = Chunk<XD, VEC>;
     constexpr int U = 16;                                // rows in flight
-    static_assert(kWideFoldRows % U == 0, "whole steps per fold");
     const table_t<DevRun> part = table(parts) + (gridDim.y - 1 - blockIdx.y);
     const int more = part->more_end;
     int next = part->more_begin;
@@ -776,44 +750,36 @@ wide_xt_kernel(const void *__restrict__ X, const float *__restrict__ residuals, 
         const void *base = row_ptr<XD>(X, run.row_begin, d);
         const float *res = residuals + run.row_begin;
         const int n = run.nrows;
-        for (int r0 = 0, to = run.dst_begin; r0 < n; ++to) {
-            const int stop = min(r0 + chunk, n);
-            float sum[VEC];
+        double acc[VEC];
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) sum[v] = 0.f;
-            auto pass = [&](auto nt) {
-                while (r0 < stop) {
-                    const int end = min(r0 + kWideFoldRows, stop);
-                    float acc[VEC];
+        for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
+        auto pass = [&](auto nt) {
+            for (int r0 = 0; r0 < n; r0 += U) {
+                typename C::raw_t x[U];
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
-                    for (; r0 < end; r0 += U) {
-                        typename C::raw_t x[U];
-#pragma unroll
-                        for (int u = 0; u < U; ++u) {
-                            const void *row = row_ptr<XD>(base, min(r0 + u, end - 1), d);
-                            x[u] = decltype(nt)::value ? C::load_once(row, off) : C::load(row, off);
-                        }
-#pragma unroll
-                        for (int u = 0; u < U; ++u)
-                            if (r0 + u < end) {
-                                float xv[VEC];
-                                C::widen(x[u], xv);
-#pragma unroll
-                                for (int v = 0; v < VEC; ++v) acc[v] = fmaf(res[r0 + u], xv[v], acc[v]);
-                            }
-                    }
-                    r0 = end;
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) sum[v] += acc[v];
+                for (int u = 0; u < U; ++u) {
+                    const void *row = row_ptr<XD>(base, min(r0 + u, n - 1), d);
+                    x[u] = decltype(nt)::value ? C::load_once(row, off) : C::load(row, off);
                 }
-            };
-            if (cached) pass(std::false_type{});
-            else pass(std::true_type{});
-            if (q < nq)
-                for (int j = to, je = r0 < n ? to + 1 : run.dst_end; j < je; ++j)
-                    store_row<VEC>(rows + static_cast<int64_t>(table(dst)[j]) * d + off, sum);
-        }
+#pragma unroll
+                for (int u = 0; u < U; u += 4) {
+                    float xv[4][VEC], rv[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        C::widen(x[u + i], xv[i]);
+                        rv[i] = r0 + u + i < n ? res[r0 + u + i] : 0.f;
+                    }
+                    add_rows<VEC, 4>(acc, rv, xv);
+                }
+            }
+        };
+        if (cached) pass(std::false_type{});
+        else pass(std::true_type{});
+        float sum[VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) sum[v] = static_cast<float>(acc[v]);
+        if (q < nq)
+            for (int j = run.dst_begin; j < run.dst_end; ++j) store_row<VEC>(rows + static_cast<int64_t>(table(dst)[j]) * d + off, sum);
         if (next >= more) break;
         run = read_run(table(runs) + next++);
     }
@@ -1148,34 +1114,34 @@ const Stage1Variant kVariants[] = {
 
 // every-row-once kernels: threads that share a row, chunks per thread, rows per step, threads per workgroup
 #define CR_O(XD, VEC, LPR, K, R, WAVES)                                                                 \
-    {XD, VEC, LPR, K, WAVES * R * (64 / LPR), WAVES * 64, 2, kFolds * kFoldRows,                        \
+    {XD, VEC, LPR, K, WAVES * R * (64 / LPR), WAVES * 64, 2,                                            \
      {reinterpret_cast<const void *>(&rows_once_kernel<XD, VEC, LPR, K, R, WAVES, false>),              \
       reinterpret_cast<const void *>(&rows_once_kernel<XD, VEC, LPR, K, R, WAVES, true>)}}
-#define CR_OT(XD, VEC, TS, K, R, PF, FOLD)                                                              \
-    {XD, VEC, TS, K, R, TS, XD == 1 && TS == 128 ? 2 : 1, FOLD ? kFolds * kFoldRows : kFoldRows,        \
-     {reinterpret_cast<const void *>(&rows_once_team_kernel<XD, VEC, TS, K, R, PF, FOLD, false>),       \
-      reinterpret_cast<const void *>(&rows_once_team_kernel<XD, VEC, TS, K, R, PF, FOLD, true>)}}
+#define CR_OT(XD, VEC, TS, K, R, PF)                                                                    \
+    {XD, VEC, TS, K, R, TS, XD == 1 && TS == 128 ? 2 : 1,                                               \
+     {reinterpret_cast<const void *>(&rows_once_team_kernel<XD, VEC, TS, K, R, PF, false>),             \
+      reinterpret_cast<const void *>(&rows_once_team_kernel<XD, VEC, TS, K, R, PF, true>)}}
 const OnceVariant kOnceVariants[] = {
     // fp32: up to 256 chunks (1024 columns) a wavefront or a part of one per row ...
     CR_O(0, 4, 2, 1, 4, 4), CR_O(0, 4, 4, 1, 4, 4), CR_O(0, 4, 8, 1, 4, 4), CR_O(0, 4, 16, 1, 4, 4), CR_O(0, 4, 32, 1, 4, 4),
     CR_O(0, 4, 64, 1, 4, 4), CR_O(0, 4, 64, 2, 4, 4), CR_O(0, 4, 64, 3, 2, 4), CR_O(0, 4, 64, 4, 2, 4),
     // ... then two wavefronts up to 512, four up to 1792, eight up to 6144 chunks (more chunks per thread would leave no room for the
     // next step; 1500 columns, 3 GB: 423 us with two wavefronts, 444 with four, a quarter of whose second chunks lie past the row)
-    CR_OT(0, 4, 128, 3, 4, true, true), CR_OT(0, 4, 128, 4, 4, true, true), CR_OT(0, 4, 256, 3, 4, true, true), CR_OT(0, 4, 256, 4, 2, true, true),
-    CR_OT(0, 4, 256, 5, 2, true, true), CR_OT(0, 4, 256, 6, 2, true, true), CR_OT(0, 4, 256, 7, 2, true, false),
-    CR_OT(0, 4, 512, 4, 2, true, true), CR_OT(0, 4, 512, 5, 2, true, true), CR_OT(0, 4, 512, 6, 1, true, true),
-    CR_OT(0, 4, 512, 7, 1, true, true), CR_OT(0, 4, 512, 8, 1, true, true), CR_OT(0, 4, 512, 9, 1, true, false),
-    CR_OT(0, 4, 512, 10, 1, false, false), CR_OT(0, 4, 512, 11, 1, false, false), CR_OT(0, 4, 512, 12, 1, false, false),
+    CR_OT(0, 4, 128, 3, 4, true), CR_OT(0, 4, 128, 4, 4, true), CR_OT(0, 4, 256, 3, 4, true), CR_OT(0, 4, 256, 4, 2, true),
+    CR_OT(0, 4, 256, 5, 2, true), CR_OT(0, 4, 256, 6, 2, true), CR_OT(0, 4, 256, 7, 2, true),
+    CR_OT(0, 4, 512, 4, 2, true), CR_OT(0, 4, 512, 5, 2, true), CR_OT(0, 4, 512, 6, 1, true),
+    CR_OT(0, 4, 512, 7, 1, true), CR_OT(0, 4, 512, 8, 1, true), CR_OT(0, 4, 512, 9, 1, true),
+    CR_OT(0, 4, 512, 10, 1, false), CR_OT(0, 4, 512, 11, 1, false), CR_OT(0, 4, 512, 12, 1, false),
     // bf16: the same, a chunk widening to eight accumulators
     CR_O(1, 8, 2, 1, 4, 4), CR_O(1, 8, 4, 1, 4, 4), CR_O(1, 8, 8, 1, 4, 4), CR_O(1, 8, 16, 1, 4, 4), CR_O(1, 8, 32, 1, 4, 4),
     CR_O(1, 8, 64, 1, 4, 4), CR_O(1, 8, 64, 2, 2, 4), CR_O(1, 8, 64, 3, 2, 4), CR_O(1, 8, 64, 4, 2, 4),
     // (rows of an odd number of columns start on any 2-byte boundary, where 16-byte loads take two trips: two smaller workgroups per
     // unit hide that better, 3 GB of 3001 columns 466 against 527 us)
-    CR_OT(1, 8, 128, 3, 4, true, true), CR_OT(1, 8, 128, 4, 2, true, true), CR_OT(1, 8, 128, 5, 2, true, true),
-    CR_OT(1, 8, 128, 6, 2, true, true),
-    CR_OT(1, 8, 256, 2, 4, true, true), CR_OT(1, 8, 256, 3, 2, true, true), CR_OT(1, 8, 256, 4, 2, true, true),
-    CR_OT(1, 8, 512, 3, 1, true, true), CR_OT(1, 8, 512, 4, 1, true, true), CR_OT(1, 8, 512, 5, 1, true, true),
-    CR_OT(1, 8, 512, 6, 1, true, false),
+    CR_OT(1, 8, 128, 3, 4, true), CR_OT(1, 8, 128, 4, 2, true), CR_OT(1, 8, 128, 5, 2, true),
+    CR_OT(1, 8, 128, 6, 2, true),
+    CR_OT(1, 8, 256, 2, 4, true), CR_OT(1, 8, 256, 3, 2, true), CR_OT(1, 8, 256, 4, 2, true),
+    CR_OT(1, 8, 512, 3, 1, true), CR_OT(1, 8, 512, 4, 1, true), CR_OT(1, 8, 512, 5, 1, true),
+    CR_OT(1, 8, 512, 6, 1, true),
     // rows shorter than one wide chunk: one column per lane
     CR_O(0, 1, 4, 1, 4, 4), CR_O(1, 1, 8, 1, 4, 4),
 };
@@ -1231,12 +1197,12 @@ const OnceVariant *select_once_whole(int x_dtype, int64_t d)
 }
 
 hipError_t launch_rows_once(const OnceVariant &v, const void *X, const float *y, const float *w, const DevRun *parts, int num_parts,
-                            const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int chunk, int logistic,
-                            bool stream_past_caches, hipStream_t stream)
+                            const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int logistic, bool stream_past_caches,
+                            hipStream_t stream)
 {
     int di = static_cast<int>(d);
     int nq = static_cast<int>((d + v.vec - 1) / v.vec);
-    void *args[] = {&X, &y, &w, &parts, &runs, &dst, &rows, &di, &nq, &chunk, &logistic};
+    void *args[] = {&X, &y, &w, &parts, &runs, &dst, &rows, &di, &nq, &logistic};
     return hipLaunchKernel(v.fn[stream_past_caches ? 1 : 0], dim3(num_parts), dim3(v.block), args, 0, stream);
 }
 
@@ -1291,7 +1257,7 @@ hipError_t launch_xt_residuals(int x_dtype, const void *X, const DevPiece *piece
 namespace {
 template <int XD, int VEC>
 hipError_t wide_once(const void *X, const float *y, const float *w, float *residuals, int64_t m, const DevRun *parts, int num_parts, const DevRun *runs,
-                     const int32_t *dst, float *rows, int64_t d, int chunk, int logistic, int64_t cached_from, int units, hipStream_t stream)
+                     const int32_t *dst, float *rows, int64_t d, int logistic, int64_t cached_from, int units, hipStream_t stream)
 {
     const int nq = static_cast<int>((d + VEC - 1) / VEC), di = static_cast<int>(d);
     auto residuals_of = [&](auto r) {
@@ -1306,17 +1272,17 @@ hipError_t wide_once(const void *X, const float *y, const float *w, float *resid
     else residuals_of(std::integral_constant<int, 1>{});
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    wide_xt_kernel<XD, VEC><<<dim3((nq + 255) / 256, num_parts), 256, 0, stream>>>(X, residuals, parts, runs, dst, rows, di, nq, chunk, cached_from);
+    wide_xt_kernel<XD, VEC><<<dim3((nq + 255) / 256, num_parts), 256, 0, stream>>>(X, residuals, parts, runs, dst, rows, di, nq, cached_from);
     return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_wide_once(int x_dtype, const void *X, const float *y, const float *w, float *residuals, int64_t m, const DevRun *parts, int num_parts,
-                            const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int chunk, int logistic, int64_t cached_from, int units,
+                            const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int logistic, int64_t cached_from, int units,
                             hipStream_t stream)
 {
-    if (x_dtype == 0) return wide_once<0, 4>(X, y, w, residuals, m, parts, num_parts, runs, dst, rows, d, chunk, logistic, cached_from, units, stream);
-    return wide_once<1, 8>(X, y, w, residuals, m, parts, num_parts, runs, dst, rows, d, chunk, logistic, cached_from, units, stream);
+    if (x_dtype == 0) return wide_once<0, 4>(X, y, w, residuals, m, parts, num_parts, runs, dst, rows, d, logistic, cached_from, units, stream);
+    return wide_once<1, 8>(X, y, w, residuals, m, parts, num_parts, runs, dst, rows, d, logistic, cached_from, units, stream);
 }
 
 hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, const int32_t *dst, int64_t d, hipStream_t stream)

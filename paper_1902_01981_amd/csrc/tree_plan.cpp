@@ -287,7 +287,6 @@ void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
         return slabs[a].row_begin != slabs[b].row_begin ? slabs[a].row_begin < slabs[b].row_begin : slabs[a].row_end < slabs[b].row_end;
     });
-    auto chunks = [&](size_t i) { const RowRun &r = out.runs[by_row[i]]; return (r.row_end - r.row_begin + out.chunk - 1) / out.chunk; };
     struct Range { size_t ob, oe, rb, re; };             // slabs order[ob .. oe), runs by_row[rb .. re)
     std::vector<Range> ranges;
     std::vector<char> partial(by_row.size(), 0);
@@ -298,20 +297,19 @@ void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
         const size_t rb = static_cast<size_t>(std::lower_bound(begins.begin(), begins.end(), sl.row_begin) - begins.begin());
         const size_t re = static_cast<size_t>(std::lower_bound(begins.begin(), begins.end(), sl.row_end) - begins.begin());
         ranges.push_back({i, k, rb, re});
-        if (re - rb > 1 || chunks(rb) > 1) std::fill(partial.begin() + rb, partial.begin() + re, 1);
+        if (re - rb > 1) std::fill(partial.begin() + rb, partial.begin() + re, 1);
         i = k;
     }
-    std::vector<int32_t> partial_row(by_row.size() + 1);             // first partial row of a run that has any
+    std::vector<int32_t> partial_row(by_row.size() + 1);             // partial row of a run that has one
     std::vector<std::vector<int32_t>> to(by_row.size());
     out.partials = 0;
     for (size_t i = 0; i < by_row.size(); ++i) {
         partial_row[i] = S + out.partials;
-        if (partial[i])
-            for (int64_t c = chunks(i); c > 0; --c) to[i].push_back(S + out.partials++);
+        if (partial[i]) to[i].push_back(S + out.partials++);
     }
     partial_row[by_row.size()] = S + out.partials;
     for (const Range &r : ranges)
-        if (r.re - r.rb == 1 && chunks(r.rb) == 1) to[r.rb].insert(to[r.rb].end(), order.begin() + r.ob, order.begin() + r.oe);
+        if (r.re - r.rb == 1) to[r.rb].insert(to[r.rb].end(), order.begin() + r.ob, order.begin() + r.oe);
     for (size_t i = 0; i < by_row.size(); ++i) {
         RowRun &run = out.runs[by_row[i]];
         run.dst_begin = static_cast<int32_t>(out.dst.size());
@@ -319,7 +317,7 @@ void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
         run.dst_end = static_cast<int32_t>(out.dst.size());
     }
     for (const Range &r : ranges)
-        if (r.re - r.rb > 1 || chunks(r.rb) > 1) {
+        if (r.re - r.rb > 1) {
             const int32_t begin = static_cast<int32_t>(out.dst.size());
             out.dst.insert(out.dst.end(), order.begin() + r.ob, order.begin() + r.oe);
             out.sums.push_back({partial_row[r.rb], partial_row[r.re], begin, static_cast<int32_t>(out.dst.size())});
@@ -327,17 +325,17 @@ void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
 }
 }  // namespace
 
-void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, int32_t chunk, OnceWork &out)
+void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, int64_t rows_per_run, OnceWork &out)
 {
+    rows_per_run = std::min<int64_t>(rows_per_run, int64_t(1) << 30);    // the kernels count a run's rows in 32 bits
     out = OnceWork();
-    out.chunk = chunk;
     const std::vector<int64_t> cuts = slab_cuts(slabs);
     out.part_run_begin.push_back(0);
     for (int64_t b = 0; b < parts; ++b) {
         int64_t lo = static_cast<int64_t>(static_cast<__int128>(m) * b / parts);
         const int64_t hi = static_cast<int64_t>(static_cast<__int128>(m) * (b + 1) / parts);
         while (lo < hi) {
-            const int64_t stop = std::min(hi, *std::upper_bound(cuts.begin(), cuts.end(), lo));
+            const int64_t stop = std::min({hi, lo + rows_per_run, *std::upper_bound(cuts.begin(), cuts.end(), lo)});
             out.runs.push_back({lo, stop, 0, 0});
             lo = stop;
         }
@@ -346,10 +344,9 @@ void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, 
     assign_outputs(slabs, out);
 }
 
-void once_whole_ranges(const std::vector<Slab> &slabs, int32_t chunk, OnceWork &out)
+void once_whole_ranges(const std::vector<Slab> &slabs, OnceWork &out)
 {
     out = OnceWork();
-    out.chunk = chunk;
     std::vector<int32_t> order(slabs.size());
     for (size_t p = 0; p < order.size(); ++p) order[p] = static_cast<int32_t>(p);
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
@@ -367,10 +364,9 @@ void once_whole_ranges(const std::vector<Slab> &slabs, int32_t chunk, OnceWork &
     }
 }
 
-void once_of_queues(const std::vector<Slab> &slabs, const Split &split, int teams_per_group, int32_t chunk, OnceWork &out)
+void once_of_queues(const std::vector<Slab> &slabs, const Split &split, int teams_per_group, OnceWork &out)
 {
     out = OnceWork();
-    out.chunk = chunk;
     std::vector<int64_t> taken;                          // first rows of the cells some workgroup already has
     for (const Piece &pc : split.pieces) taken.push_back(pc.row_begin);
     std::sort(taken.begin(), taken.end());
@@ -407,13 +403,9 @@ void once_as_split(const std::vector<Slab> &slabs, const OnceWork &work, Split &
         for (int32_t i = work.part_run_begin[b]; i < work.part_run_begin[b + 1]; ++i) {
             const RowRun &run = work.runs[i];
             auto add = [&](int32_t slab) { out.pieces.push_back({slab, b, run.row_begin, run.row_end}); };
-            bool partial = false;                        // the run's partial rows all go into the same slabs
             for (int32_t j = run.dst_begin; j < run.dst_end; ++j) {
                 if (work.dst[j] < S) add(work.dst[j]);
-                else if (!partial) {
-                    for (int32_t slab : slabs_of[work.dst[j] - S]) add(slab);
-                    partial = true;
-                }
+                else for (int32_t slab : slabs_of[work.dst[j] - S]) add(slab);
             }
         }
     }

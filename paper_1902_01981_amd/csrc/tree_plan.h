@@ -71,9 +71,8 @@ void split_row_cells(const std::vector<Slab> &slabs, int64_t cell_rows, int lane
 
 // Rows once: what stage 1 does when every row's contribution is formed a single time for all slabs that hold it.  A run is a range
 // of rows that no slab begins or ends inside; its gradient goes to the output rows dst[dst_begin .. dst_end).  Output row p < S is
-// slab p, output rows S, S + 1, ... are partial rows, in the order of the rows of X they stand for.  A slab that is one run of at
-// most `chunk` rows is written by that run; a longer run has one partial row per chunk of that many rows, and slabs of several
-// partial rows are sums of consecutive ones, one sum per distinct range.
+// slab p, output rows S, S + 1, ... are partial rows, in the order of the rows of X they stand for.  A slab that is one run is
+// written by that run; slabs of several runs are sums of consecutive partial rows, one sum per distinct range.
 struct RowRun { int64_t row_begin, row_end; int32_t dst_begin, dst_end; };
 struct RowSum { int32_t row_begin, row_end, dst_begin, dst_end; };        // output rows [row_begin, row_end) -> dst[dst_begin .. dst_end)
 struct OnceWork {
@@ -82,16 +81,14 @@ struct OnceWork {
     std::vector<RowSum> sums;
     std::vector<int32_t> dst;
     int32_t partials = 0;
-    int32_t chunk = 0;
 };
-// `parts` contiguous, near-equal parts of the rows [0, m), cut at slab boundaries.
-void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, int32_t chunk, OnceWork &out);
-// One part per distinct slab range, whole and at most `chunk` rows (ranges that overlap are then formed separately): no sums, no
-// partial rows.
-void once_whole_ranges(const std::vector<Slab> &slabs, int32_t chunk, OnceWork &out);
+// `parts` contiguous, near-equal parts of the rows [0, m), cut at slab boundaries and after every `rows_per_run` rows.
+void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, int64_t rows_per_run, OnceWork &out);
+// One part per distinct slab range, whole (ranges that overlap are then formed separately): no sums, no partial rows.
+void once_whole_ranges(const std::vector<Slab> &slabs, OnceWork &out);
 // The cells of a shared-queues split: part g = workgroup g with its queue; a cell that several workgroups are queued for is formed
 // by the first of them.
-void once_of_queues(const std::vector<Slab> &slabs, const Split &split, int teams_per_group, int32_t chunk, OnceWork &out);
+void once_of_queues(const std::vector<Slab> &slabs, const Split &split, int teams_per_group, OnceWork &out);
 // The (slab, rows, part) triples of `work` as pieces (slab_piece_begin and the rest as in Split).
 void once_as_split(const std::vector<Slab> &slabs, const OnceWork &work, Split &out);
 
