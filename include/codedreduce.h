@@ -133,7 +133,8 @@ int cr_plan_decode_row(const cr_plan_t *plan, const uint8_t *flags /* host, n */
  *                          for the registers of a workgroup (d > 24576) take two passes over X, the second cut into parts of rows
  *                          and blocks of columns.
  * With the first two every holder of a row does its own arithmetic on it, as separate workers would: they are there to measure what
- * the redundancy of a scheme costs.  With the other two the holders' identical sums are formed once and handed to every slab they
+ * the redundancy of a scheme costs (with s = 0 no row has a second holder, and equal ranges run the kernels of rows once, a
+ * workgroup per team).  With the other two the holders' identical sums are formed once and handed to every slab they
  * belong to.  The slab gradients agree to rounding under every split.
  * Default (when this is never called): rows once, or, for the smallest problems, a workgroup per distinct slab range.  With X of 1 GiB
  * and more: equal ranges of the rows when s = 0 (no row is held twice), shared cells where one workgroup serves all holders of a

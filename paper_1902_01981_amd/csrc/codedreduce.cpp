@@ -257,7 +257,7 @@ int ensure_split(cr_plan_t *p)
     const bool chosen_here = kind < 0;
     const bool large = p->m * p->d * elem_size(p) >= kLargeBytes;
     if (kind < 0 && large && p->s == 0 && p->once_variant) {
-        // no row is held twice: equal ranges of the rows are equal ranges of the row visits
+        // no row is held twice
         kind = CR_SPLIT_EQUAL_RANGES;
         value = static_cast<int64_t>(query_units()) * p->once_variant->parts_per_unit;
     }
@@ -299,10 +299,12 @@ int ensure_split(cr_plan_t *p)
         p->once = p->once_variant;
         p->rows_once = true;
         cr::once_of_queues(p->slabs, p->split, p->cell_holders, p->work);
-    } else if (kind == CR_SPLIT_EQUAL_RANGES && chosen_here) {
-        make_rows_once(p, p->m, false);
+    } else if (kind == CR_SPLIT_EQUAL_RANGES && p->s == 0 && p->once_variant) {
+        // no row is held twice: every holder's arithmetic is every row once
+        cr::split_equal_ranges(p->slabs, static_cast<int>(std::min<int64_t>(value, p->m)), p->split);
+        p->once = p->once_variant;
         p->rows_once = true;
-        cr::once_as_split(p->slabs, p->work, p->split);
+        cr::once_of_pieces(p->slabs, p->split, p->work);
     } else {
         p->variant = p->variant_regs;
         const int teams_per_block = p->variant ? p->variant->teams_per_block() : 1;     // wide rows: one workgroup per piece

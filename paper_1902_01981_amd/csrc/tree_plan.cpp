@@ -272,6 +272,8 @@ void split_shared_queues(const std::vector<Slab> &slabs, int64_t cell_rows, int 
 }
 
 namespace {
+constexpr int64_t kMaxRunRows = int64_t(1) << 30;       // the kernels count a run's rows in 32 bits
+
 // Given the runs of `out` (part-major, disjoint, covering every slab in whole runs): who receives what.
 void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
 {
@@ -327,7 +329,7 @@ void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
 
 void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, int64_t rows_per_run, OnceWork &out)
 {
-    rows_per_run = std::min<int64_t>(rows_per_run, int64_t(1) << 30);    // the kernels count a run's rows in 32 bits
+    rows_per_run = std::min(rows_per_run, kMaxRunRows);
     out = OnceWork();
     const std::vector<int64_t> cuts = slab_cuts(slabs);
     out.part_run_begin.push_back(0);
@@ -362,6 +364,20 @@ void once_whole_ranges(const std::vector<Slab> &slabs, OnceWork &out)
         out.part_run_begin.push_back(static_cast<int32_t>(out.runs.size()));
         i = k;
     }
+}
+
+void once_of_pieces(const std::vector<Slab> &slabs, const Split &split, OnceWork &out)
+{
+    out = OnceWork();
+    out.part_run_begin.push_back(0);
+    for (int t = 0; t < split.teams; ++t) {
+        for (int32_t i = split.team_piece_begin[t]; i < split.team_piece_begin[t + 1]; ++i) {
+            for (int64_t lo = split.pieces[i].row_begin, hi = split.pieces[i].row_end; lo < hi; lo += kMaxRunRows)
+                out.runs.push_back({lo, std::min(lo + kMaxRunRows, hi), 0, 0});
+        }
+        if (static_cast<int32_t>(out.runs.size()) > out.part_run_begin.back()) out.part_run_begin.push_back(static_cast<int32_t>(out.runs.size()));
+    }
+    assign_outputs(slabs, out);
 }
 
 void once_of_queues(const std::vector<Slab> &slabs, const Split &split, int teams_per_group, OnceWork &out)

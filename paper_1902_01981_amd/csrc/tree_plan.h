@@ -86,6 +86,8 @@ struct OnceWork {
 void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, int64_t rows_per_run, OnceWork &out);
 // One part per distinct slab range, whole (ranges that overlap are then formed separately): no sums, no partial rows.
 void once_whole_ranges(const std::vector<Slab> &slabs, OnceWork &out);
+// The pieces of a split of slabs that share no row: part t = team t.
+void once_of_pieces(const std::vector<Slab> &slabs, const Split &split, OnceWork &out);
 // The cells of a shared-queues split: part g = workgroup g with its queue; a cell that several workgroups are queued for is formed
 // by the first of them.
 void once_of_queues(const std::vector<Slab> &slabs, const Split &split, int teams_per_group, OnceWork &out);
