@@ -131,15 +131,16 @@ int cr_plan_decode_row(const cr_plan_t *plan, const uint8_t *flags /* host, n */
  *                          slab boundaries and after `value` rows; a workgroup forms every row of its part once, for all slabs that
  *                          hold it, and adds a run up in fp64 (all but the up to four rows it has in hand at a time).  Rows too wide
  *                          for the registers of a workgroup (d > 24576) take two passes over X, the second cut into parts of rows
- *                          and blocks of columns.
+ *                          and blocks of columns.  CR_ROWS_WHOLE_RANGES as value (d <= 24576): a workgroup per distinct slab range,
+ *                          which it adds up whole; rows of ranges that overlap are then formed once per range.
  * With the first two every holder of a row does its own arithmetic on it, as separate workers would: they are there to measure what
  * the redundancy of a scheme costs (with s = 0 no row has a second holder, and equal ranges run the kernels of rows once, a
  * workgroup per team).  With the other two the holders' identical sums are formed once and handed to every slab they
  * belong to.  The slab gradients agree to rounding under every split.
- * Default (when this is never called): rows once, or, for the smallest problems, a workgroup per distinct slab range.  With X of 1 GiB
- * and more: equal ranges of the rows when s = 0 (no row is held twice), shared cells where one workgroup serves all holders of a
+ * Default (when this is never called): rows once, for the smallest problems by whole ranges.  With X of 1 GiB and more: equal ranges of the rows when s = 0 (no row is held twice), shared cells where one workgroup serves all holders of a
  * row, with the cell height (16 to 1024 rows) that gives the shortest longest queue. */
 enum cr_split { CR_SPLIT_EQUAL_RANGES = 0, CR_SPLIT_ROW_CELLS = 1, CR_SPLIT_SHARED_CELLS = 2, CR_SPLIT_ROWS_ONCE = 3 };
+#define CR_ROWS_WHOLE_RANGES ((int64_t)1 << 62)
 int cr_plan_set_split(cr_plan_t *plan, int kind, int64_t value);
 /* pieces in execution order: piece i is rows [row_begin[i], row_end[i]) of slab[i], run by team[i] (rows once: by workgroup team[i],
  * one piece for every slab the rows belong to); num_pieces entries each, any may be NULL */

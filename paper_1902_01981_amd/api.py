@@ -21,6 +21,7 @@ CR_F32, CR_BF16 = 0, 1
 CR_K_PARTIAL_GRADS, CR_K_REDUCE_PIECES, CR_K_ENCODE, CR_K_DECODE, CR_K_UPDATE, CR_K_COUNT = 0, 1, 2, 3, 4, 5
 CR_PROFILE_ALL = (1 << CR_K_COUNT) - 1
 CR_SPLIT_EQUAL_RANGES, CR_SPLIT_ROW_CELLS, CR_SPLIT_SHARED_CELLS, CR_SPLIT_ROWS_ONCE = 0, 1, 2, 3
+CR_ROWS_WHOLE_RANGES = 1 << 62
 DEFAULT_SEED = 190201981
 
 EXPORTS = [

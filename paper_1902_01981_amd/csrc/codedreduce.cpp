@@ -207,23 +207,25 @@ int shared_cell_holders(int x_dtype, int64_t d, int64_t max_holders)
 // Bytes of X that the first pass over wide rows leaves in the 256 MB last-level cache for the second.
 constexpr int64_t kKeptBytes = int64_t(160) << 20;
 
-// Rows one after the other along X, every row once, on every compute unit: the parts of the default split.
-void make_rows_once(cr_plan_t *p, int64_t rows_per_run, bool may_take_whole_ranges)
+int64_t longest_range(const cr_plan_t *p)
 {
-    const cr::OnceVariant *v = p->once_variant;
-    if (may_take_whole_ranges) {
-        // Small problems: a workgroup per distinct slab range forms its gradient whole, which saves the launch that adds up partial
-        // rows.  The line is where the two take the same time, at about 48 Ki elements in the longest range (fp32, a (3,2) tree, us
-        // whole / parts and sum: 200 x 100 elements 5.6 / 7.5, 667 x 100 9.0 / 8.2; 67 x 1000 6.3 / 7.5, 200 x 1000 12.2 / 7.8).
-        int64_t longest = 0;
-        for (const cr::Slab &sl : p->slabs) longest = std::max(longest, sl.row_end - sl.row_begin);
-        if (longest * p->d <= 48 * 1024) {
-            p->once = cr::select_once_whole(p->x_dtype, p->d);
-            cr::once_whole_ranges(p->slabs, p->work);
-            return;
-        }
-    }
-    p->once = v;
+    int64_t longest = 0;
+    for (const cr::Slab &sl : p->slabs) longest = std::max(longest, sl.row_end - sl.row_begin);
+    return longest;
+}
+
+// Small problems: a workgroup per distinct slab range forms its gradient whole, which saves the launch that adds up partial rows.  The
+// line is where the two take the same time, at about 48 Ki elements in the longest range (fp32, us whole / parts and sum; a (3,2) tree:
+// 160 x 150 elements in the longest range 5.6 / 7.9, 320 x 150 7.4 / 8.0, 640 x 150 12.0 / 7.9; 54 x 900 6.1 / 8.1, 107 x 900 8.9 / 9.7;
+// 19 x 2500 7.9 / 8.0, 38 x 2500 13.4 / 8.3).  Ranges that overlap without being equal are formed one by one; on the trees measured that
+// costs less than the launch as long as about 25 MB are read in all (a (5,4) tree, where a row is in 4 ranges on average: 160 x 150
+// 8.9 / 9.2, 320 x 150 with 47 MB 13.6 / 10.0, but 54 x 900 with 52 MB 13.6 / 18.0, where parts have runs of less than one step).
+bool whole_ranges_pay(const cr_plan_t *p) { return p->once_variant && longest_range(p) * p->d <= 48 * 1024; }
+
+// Rows one after the other along X, every row once, on every compute unit: the parts of the default split.
+void make_rows_once(cr_plan_t *p, int64_t rows_per_run)
+{
+    const cr::OnceVariant *v = p->once = p->once_variant;
     // small problems: no fewer rows per part than a workgroup takes in a step, two where the whole workgroup shares a row (the
     // partial rows of shorter parts cost more than the extra workgroups bring)
     const int64_t least = v->threads_per_row <= 64 ? std::min(v->rows_per_step, 128) : 2;
@@ -254,7 +256,6 @@ int ensure_split(cr_plan_t *p)
     p->l2_domains = domains;
     p->unit_slots = 0;
     p->l2_sharing = -1;
-    const bool chosen_here = kind < 0;
     const bool large = p->m * p->d * elem_size(p) >= kLargeBytes;
     if (kind < 0 && large && p->s == 0 && p->once_variant) {
         // no row is held twice
@@ -279,15 +280,19 @@ int ensure_split(cr_plan_t *p)
     }
     if (kind < 0) {
         kind = CR_SPLIT_ROWS_ONCE;
-        value = p->m;
+        value = whole_ranges_pay(p) ? CR_ROWS_WHOLE_RANGES : p->m;
     }
     p->split_kind_used = kind;
     p->split_value_used = value;
     // more rows than there are mean all of them; the products and sums below then stay far inside 64 bits
+    const bool whole_ranges = kind == CR_SPLIT_ROWS_ONCE && value == CR_ROWS_WHOLE_RANGES && p->once_variant && longest_range(p) <= cr::kMaxRunRows;
     if (kind != CR_SPLIT_EQUAL_RANGES) value = std::min(value, p->m);
     if (kind == CR_SPLIT_ROWS_ONCE) {
         if (p->m / value + 2 * static_cast<int64_t>(p->slabs.size()) > (int64_t(1) << 26)) return fail(CR_E_INVAL, "too many partial rows");
-        if (p->once_variant) make_rows_once(p, value, chosen_here);
+        if (whole_ranges) {
+            p->once = cr::select_once_whole(p->x_dtype, p->d);
+            cr::once_whole_ranges(p->slabs, p->work);
+        } else if (p->once_variant) make_rows_once(p, value);
         else make_wide_once(p, value);
         p->rows_once = true;
         cr::once_as_split(p->slabs, p->work, p->split);

@@ -272,8 +272,6 @@ void split_shared_queues(const std::vector<Slab> &slabs, int64_t cell_rows, int 
 }
 
 namespace {
-constexpr int64_t kMaxRunRows = int64_t(1) << 30;       // the kernels count a run's rows in 32 bits
-
 // Given the runs of `out` (part-major, disjoint, covering every slab in whole runs): who receives what.
 void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
 {

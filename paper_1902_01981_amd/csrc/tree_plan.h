@@ -73,6 +73,7 @@ void split_row_cells(const std::vector<Slab> &slabs, int64_t cell_rows, int lane
 // of rows that no slab begins or ends inside; its gradient goes to the output rows dst[dst_begin .. dst_end).  Output row p < S is
 // slab p, output rows S, S + 1, ... are partial rows, in the order of the rows of X they stand for.  A slab that is one run is
 // written by that run; slabs of several runs are sums of consecutive partial rows, one sum per distinct range.
+constexpr int64_t kMaxRunRows = int64_t(1) << 30;       // the kernels count a run's rows in 32 bits
 struct RowRun { int64_t row_begin, row_end; int32_t dst_begin, dst_end; };
 struct RowSum { int32_t row_begin, row_end, dst_begin, dst_end; };        // output rows [row_begin, row_end) -> dst[dst_begin .. dst_end)
 struct OnceWork {
@@ -84,7 +85,8 @@ struct OnceWork {
 };
 // `parts` contiguous, near-equal parts of the rows [0, m), cut at slab boundaries and after every `rows_per_run` rows.
 void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, int64_t rows_per_run, OnceWork &out);
-// One part per distinct slab range, whole (ranges that overlap are then formed separately): no sums, no partial rows.
+// One part per distinct slab range, whole (ranges that overlap are then formed separately, none of more than kMaxRunRows rows): no
+// sums, no partial rows.
 void once_whole_ranges(const std::vector<Slab> &slabs, OnceWork &out);
 // The pieces of a split of slabs that share no row: part t = team t.
 void once_of_pieces(const std::vector<Slab> &slabs, const Split &split, OnceWork &out);

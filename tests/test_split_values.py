@@ -66,3 +66,46 @@ def test_equal_ranges_without_redundancy(teams):
         idx = np.nonzero(slab == q)[0]
         assert pb[idx[0]] == rb[q] and pe[idx[-1]] == re_[q] and np.array_equal(pb[idx[1:]], pe[idx[:-1]])
     cr.cr_plan_destroy(p)
+
+
+# one range per worker, ranges that overlap without being equal, more ranges than compute units; 1 to 1 870 columns
+@pytest.mark.parametrize("L,n,s,m,d,bf16", [(2, 3, 1, 1_200, 100, 0), (1, 10, 4, 253, 900, 0), (3, 4, 1, 328, 1_000, 0), (2, 12, 2, 312, 1_870, 1),
+                                             (3, 3, 1, 4_003, 64, 0), (2, 4, 1, 60, 1, 0), (2, 4, 0, 68, 200, 0), (2, 3, 1, 12, 2_500, 0), (2, 4, 1, 8_359, 71, 1),
+                                             (2, 4, 1, 60_000, 1_500, 0), (2, 4, 1, 4_000, 50_008, 1), (3, 4, 1, 252_000, 4_096, 0)])
+def test_default_runs_as_reported(L, n, s, m, d, bf16):
+    info = _runs_as_reported((L, n, s, m, d), bf16)
+    assert (info.split_value == cr.CR_ROWS_WHOLE_RANGES) == (info.split_kind == cr.CR_SPLIT_ROWS_ONCE and info.split_value != m)
+
+
+@pytest.mark.parametrize("L,n,s,m,d,bf16", [(2, 3, 1, 5_000, 64, 0), (3, 4, 1, 9_000, 700, 1), (2, 4, 1, 2_000, 5_000, 0)])
+def test_whole_ranges(L, n, s, m, d, bf16):
+    """A workgroup per distinct slab range, which it has whole: no partial rows, so the workspace has fewer rows than with parts."""
+    p, q = cr.cr_plan_ex(L, n, s, m, d, x_dtype=bf16), cr.cr_plan_ex(L, n, s, m, d, x_dtype=bf16)
+    cr.cr_plan_set_split(p, cr.CR_SPLIT_ROWS_ONCE, cr.CR_ROWS_WHOLE_RANGES)
+    cr.cr_plan_set_split(q, cr.CR_SPLIT_ROWS_ONCE, m)
+    rb, re_, _, _ = cr.cr_plan_get_segments(p)
+    slab, pb, pe, team = cr.cr_plan_get_pieces(p)
+    ranges = sorted(set(zip(rb.tolist(), re_.tolist())))
+    assert cr.cr_plan_info(p).num_teams == len(ranges) and len(slab) == len(rb)
+    assert sorted(zip(slab.tolist(), pb.tolist(), pe.tolist())) == sorted(zip(range(len(rb)), rb.tolist(), re_.tolist()))
+    assert [ranges[t] for t in team] == list(zip(pb.tolist(), pe.tolist()))
+    assert cr.cr_workspace_bytes(p) < cr.cr_workspace_bytes(q)
+    cr.cr_plan_destroy(p)
+    cr.cr_plan_destroy(q)
+    # rows in two passes have no such form: the value then is what any large one is, no limit
+    w, v = cr.cr_plan_ex(2, 3, 1, 100, 24_577), cr.cr_plan_ex(2, 3, 1, 100, 24_577)
+    cr.cr_plan_set_split(w, cr.CR_SPLIT_ROWS_ONCE, cr.CR_ROWS_WHOLE_RANGES)
+    cr.cr_plan_set_split(v, cr.CR_SPLIT_ROWS_ONCE, 100)
+    assert _pieces(w) == _pieces(v)
+    cr.cr_plan_destroy(w)
+    cr.cr_plan_destroy(v)
+
+
+def test_whole_ranges_of_more_rows_than_a_run_can_have():
+    """The kernels count a run's rows in 32 bits: longer ranges are cut into parts as under any large value."""
+    p, q = cr.cr_plan_ex(1, 4, 1, 1 << 34, 1), cr.cr_plan_ex(1, 4, 1, 1 << 34, 1)
+    cr.cr_plan_set_split(p, cr.CR_SPLIT_ROWS_ONCE, cr.CR_ROWS_WHOLE_RANGES)
+    cr.cr_plan_set_split(q, cr.CR_SPLIT_ROWS_ONCE, 1 << 34)
+    assert _pieces(p) == _pieces(q) and max(e - b for b, e in zip(*_pieces(p)[1:3])) <= 1 << 30
+    cr.cr_plan_destroy(p)
+    cr.cr_plan_destroy(q)
