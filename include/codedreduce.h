@@ -125,8 +125,9 @@ int cr_plan_decode_row(const cr_plan_t *plan, const uint8_t *flags /* host, n */
  *   CR_SPLIT_SHARED_CELLS  value = most rows per cell: the grid is laid between slab boundaries, so every holder of a cell holds
  *                          all of it; a workgroup works through a queue of cells (one queue per compute unit, two for rows of at
  *                          most 8 KB) and forms every row of a cell once for the 2, 3, 4, 6 or 8 holders it serves
- *                          (stage1_teams_per_group, by row width and by (s+1)^L, the most holders a row can have) -- and for the
- *                          others, if a cell has more.  fp32 rows of 257 to 3072 16-byte chunks with s > 0 only, else CR_E_INVAL.
+ *                          (stage1_teams_per_group, by row width and by (s+1)^L, the most holders a row can have); a cell with more
+ *                          holders is formed by several workgroups of one L2 domain, each for its own holders.  fp32 rows of 257 to
+ *                          3072 16-byte chunks with s > 0 only, else CR_E_INVAL.
  *   CR_SPLIT_ROWS_ONCE     value = most rows per run: X is cut into one or two contiguous parts per compute unit, a part into runs at
  *                          slab boundaries and after `value` rows; a workgroup forms every row of its part once, for all slabs that
  *                          hold it, and adds a run up in fp64 (all but the up to four rows it has in hand at a time).  Rows too wide
@@ -135,8 +136,8 @@ int cr_plan_decode_row(const cr_plan_t *plan, const uint8_t *flags /* host, n */
  *                          which it adds up whole; rows of ranges that overlap are then formed once per range.
  * With the first two every holder of a row does its own arithmetic on it, as separate workers would: they are there to measure what
  * the redundancy of a scheme costs (with s = 0 no row has a second holder, and equal ranges run the kernels of rows once, a
- * workgroup per team).  With the other two the holders' identical sums are formed once and handed to every slab they
- * belong to.  The slab gradients agree to rounding under every split.
+ * workgroup per team).  With the other two the holders' identical sums are formed once (per workgroup) and handed to
+ * every slab they belong to.  The slab gradients agree to rounding under every split.
  * Default (when this is never called): rows once, for the smallest problems by whole ranges.  With X of 1 GiB and more: equal ranges of the rows when s = 0 (no row is held twice), shared cells where one workgroup serves all holders of a
  * row, with the cell height (16 to 1024 rows) that gives the shortest longest queue. */
 enum cr_split { CR_SPLIT_EQUAL_RANGES = 0, CR_SPLIT_ROW_CELLS = 1, CR_SPLIT_SHARED_CELLS = 2, CR_SPLIT_ROWS_ONCE = 3 };

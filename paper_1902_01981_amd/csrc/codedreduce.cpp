@@ -75,6 +75,7 @@ struct cr_plan_s {
     int cell_holders = 0;            // holders a workgroup of the shared-cells split serves; 0: no such split for this type and width
     cr::OnceWork work;               // `rows_once`: the runs and sums behind the split
     int units = 0;                   // compute units the wide-row launches are sized for
+    bool streams = false;            // rows_once: X is read past the caches
     bool rows_as_buffers = false;    // every row starts on a 4-byte boundary and every piece has fewer than 2^31 bytes
     int split_kind = -1;                            // -1: choose from the device when the workspace is sized
     int64_t split_value = 0;
@@ -321,6 +322,10 @@ int ensure_split(cr_plan_t *p)
             cr::split_equal_ranges(p->slabs, static_cast<int>(std::min<int64_t>(value, std::max<int64_t>(1, p->row_visits))), p->split);
         }
     }
+    // rows that several workgroups read are left in the caches for each other
+    int64_t rows_read = 0;
+    for (const cr::RowRun &run : p->work.runs) rows_read += run.row_end - run.row_begin;
+    p->streams = p->m * p->d * elem_size(p) >= kStreamFromBytes && rows_read <= p->m;
     return CR_OK;
 }
 
@@ -723,7 +728,7 @@ int cr_partial_grads(cr_plan_t *p, const void *X, const float *y, const float *w
         LaunchTimer t(p, CR_K_PARTIAL_GRADS, bytes);
         if (p->once) {
             CR_HIP(cr::launch_rows_once(*p->once, X, y, w, p->d_parts, static_cast<int>(p->work.part_run_begin.size()) - 1, p->d_runs, p->d_dst,
-                                        p->d_G, p->d, logistic, p->m * p->d * elem_size(p) >= kStreamFromBytes, p->stream));
+                                        p->d_G, p->d, logistic, p->streams, p->stream));
         } else if (p->rows_once) {
             const int64_t cached_from = std::max<int64_t>(0, p->m - kKeptBytes / (p->d * elem_size(p)));
             CR_HIP(cr::launch_wide_once(p->x_dtype, X, y, w, p->d_residuals, p->m, p->d_parts, static_cast<int>(p->work.part_run_begin.size()) - 1,

@@ -2,6 +2,7 @@
 #include "tree_plan.h"
 
 #include <algorithm>
+#include <unordered_map>
 
 namespace cr {
 
@@ -381,26 +382,48 @@ void once_of_pieces(const std::vector<Slab> &slabs, const Split &split, OnceWork
 void once_of_queues(const std::vector<Slab> &slabs, const Split &split, int teams_per_group, OnceWork &out)
 {
     out = OnceWork();
-    std::vector<int64_t> taken;                          // first rows of the cells some workgroup already has
-    for (const Piece &pc : split.pieces) taken.push_back(pc.row_begin);
-    std::sort(taken.begin(), taken.end());
-    taken.erase(std::unique(taken.begin(), taken.end()), taken.end());
-    std::vector<char> is_taken(taken.size(), 0);
+    const int32_t S = static_cast<int32_t>(slabs.size());
+    const bool several = std::any_of(split.pieces.begin(), split.pieces.end(), [](const Piece &pc) { return pc.shared != 0; });
+    std::vector<int32_t> out_row(split.pieces.size());   // `several`: a piece's own row of the output table
+    if (several) {
+        for (int32_t q = 0; q < S; ++q) {
+            const int32_t b = split.slab_piece_begin[q], e = split.slab_piece_begin[q + 1];
+            for (int32_t i = b; i < e; ++i) out_row[split.slab_pieces[i]] = e - b == 1 ? q : S + i;
+        }
+        out.partials = static_cast<int32_t>(split.pieces.size());
+    }
     out.part_run_begin.push_back(0);
     for (size_t g = 0; g + 1 < split.group_item_begin.size(); ++g) {
-        for (int32_t it = split.group_item_begin[g]; it < split.group_item_begin[g + 1]; ++it) {
-            int32_t pi = -1;
-            for (int t = 0; t < teams_per_group && pi < 0; ++t) pi = split.item_pieces[static_cast<size_t>(it) * teams_per_group + t];
-            if (pi < 0) continue;
-            const Piece &pc = split.pieces[pi];
-            char &seen = is_taken[std::lower_bound(taken.begin(), taken.end(), pc.row_begin) - taken.begin()];
-            if (!seen) out.runs.push_back({pc.row_begin, pc.row_end, 0, 0});
-            seen = 1;
+        std::unordered_map<int64_t, size_t> mine;        // first row of a cell -> the workgroup's run
+        std::vector<std::vector<int32_t>> to;
+        for (int32_t it = split.group_item_begin[g]; it < split.group_item_begin[g + 1]; ++it)
+            for (int t = 0; t < teams_per_group; ++t) {
+                const int32_t pi = split.item_pieces[static_cast<size_t>(it) * teams_per_group + t];
+                if (pi < 0) continue;
+                const Piece &pc = split.pieces[pi];
+                const auto at = mine.emplace(pc.row_begin, to.size());
+                if (at.second) {
+                    out.runs.push_back({pc.row_begin, pc.row_end, 0, 0});
+                    to.emplace_back();
+                }
+                if (several) to[at.first->second].push_back(out_row[pi]);
+            }
+        if (to.empty()) continue;
+        for (size_t i = 0; several && i < to.size(); ++i) {
+            RowRun &run = out.runs[out.runs.size() - to.size() + i];
+            run.dst_begin = static_cast<int32_t>(out.dst.size());
+            out.dst.insert(out.dst.end(), to[i].begin(), to[i].end());
+            run.dst_end = static_cast<int32_t>(out.dst.size());
         }
-        // a workgroup whose cells all went to others has no part
-        if (static_cast<int32_t>(out.runs.size()) > out.part_run_begin.back()) out.part_run_begin.push_back(static_cast<int32_t>(out.runs.size()));
+        out.part_run_begin.push_back(static_cast<int32_t>(out.runs.size()));
     }
-    assign_outputs(slabs, out);
+    if (!several) return assign_outputs(slabs, out);
+    for (int32_t q = 0; q < S; ++q) {
+        const int32_t b = split.slab_piece_begin[q], e = split.slab_piece_begin[q + 1], at = static_cast<int32_t>(out.dst.size());
+        if (e - b == 1) continue;
+        out.dst.push_back(q);
+        out.sums.push_back({S + b, S + e, at, at + 1});
+    }
 }
 
 void once_as_split(const std::vector<Slab> &slabs, const OnceWork &work, Split &out)

@@ -20,7 +20,7 @@ struct Slab {             // one (worker, segment) pair: owns one d-float partia
 struct Piece {            // a contiguous run of one slab's rows handled by one stage-1 team
     int32_t slab, team;
     int64_t row_begin, row_end;
-    int32_t shared = 0;   // shared cells: 1 if other workgroups fetch the same rows at the same time (the cell has several items)
+    int32_t shared = 0;   // shared cells: 1 if other workgroups have the same rows (the cell has several items)
 };
 
 struct Tree {
@@ -72,7 +72,8 @@ void split_row_cells(const std::vector<Slab> &slabs, int64_t cell_rows, int lane
 // Rows once: what stage 1 does when every row's contribution is formed a single time for all slabs that hold it.  A run is a range
 // of rows that no slab begins or ends inside; its gradient goes to the output rows dst[dst_begin .. dst_end).  Output row p < S is
 // slab p, output rows S, S + 1, ... are partial rows, in the order of the rows of X they stand for.  A slab that is one run is
-// written by that run; slabs of several runs are sums of consecutive partial rows, one sum per distinct range.
+// written by that run; slabs of several runs are sums of consecutive partial rows, one sum per distinct range (once_of_queues may
+// have one per slab).
 constexpr int64_t kMaxRunRows = int64_t(1) << 30;       // the kernels count a run's rows in 32 bits
 struct RowRun { int64_t row_begin, row_end; int32_t dst_begin, dst_end; };
 struct RowSum { int32_t row_begin, row_end, dst_begin, dst_end; };        // output rows [row_begin, row_end) -> dst[dst_begin .. dst_end)
@@ -90,8 +91,8 @@ void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, 
 void once_whole_ranges(const std::vector<Slab> &slabs, OnceWork &out);
 // The pieces of a split of slabs that share no row: part t = team t.
 void once_of_pieces(const std::vector<Slab> &slabs, const Split &split, OnceWork &out);
-// The cells of a shared-queues split: part g = workgroup g with its queue; a cell that several workgroups are queued for is formed
-// by the first of them.
+// The cells of a shared-queues split: part g = the g-th workgroup that has any.  Where every cell belongs to one workgroup its partial
+// row serves all slabs; else each workgroup of a cell forms it for the holders it serves, and every piece has a row of its own.
 void once_of_queues(const std::vector<Slab> &slabs, const Split &split, int teams_per_group, OnceWork &out);
 // The (slab, rows, part) triples of `work` as pieces (slab_piece_begin and the rest as in Split).
 void once_as_split(const std::vector<Slab> &slabs, const OnceWork &work, Split &out);
