@@ -244,9 +244,8 @@ void make_wide_once(cr_plan_t *p, int64_t rows_per_run)
     cr::once_equal_parts(p->slabs, p->m, parts, rows_per_run, p->work);
 }
 
-int ensure_split(cr_plan_t *p)
+int make_split(cr_plan_t *p)
 {
-    if (!p->split.pieces.empty() || p->model == CR_AGGREGATE_ONLY) return CR_OK;
     int kind = p->split_kind;
     int64_t value = p->split_value;
     p->variant = nullptr;
@@ -327,6 +326,18 @@ int ensure_split(cr_plan_t *p)
     for (const cr::RowRun &run : p->work.runs) rows_read += run.row_end - run.row_begin;
     p->streams = p->m * p->d * elem_size(p) >= kStreamFromBytes && rows_read <= p->m;
     return CR_OK;
+}
+
+int ensure_split(cr_plan_t *p)
+{
+    if (!p->split.pieces.empty() || p->model == CR_AGGREGATE_ONLY) return CR_OK;
+    try {
+        return make_split(p);
+    } catch (const std::bad_alloc &) {
+        p->split = cr::Split();                          // half a split is none
+        p->work = cr::OnceWork();
+        return fail(CR_E_NOMEM, "out of host memory");
+    }
 }
 
 void compute_layout(cr_plan_t *p, size_t *total)
@@ -631,7 +642,7 @@ int cr_workspace_bytes(cr_plan_t *p, size_t *bytes)
 }
 
 int cr_bind_workspace(cr_plan_t *p, void *dev_ptr, size_t bytes, void *hip_stream)
-{
+try {
     if (!p || !dev_ptr) return fail(CR_E_INVAL, "NULL argument");
     if (reinterpret_cast<uintptr_t>(dev_ptr) % 256 != 0) return fail(CR_E_INVAL, "workspace must be 256-byte aligned");
     int rc = ensure_split(p);
@@ -640,6 +651,7 @@ int cr_bind_workspace(cr_plan_t *p, void *dev_ptr, size_t bytes, void *hip_strea
     compute_layout(p, &need);
     if (bytes < need) return fail(CR_E_INVAL, "workspace too small");
     if (p->bound) CR_HIP(hipStreamSynchronize(p->stream));
+    p->bound = false;                                    // until the new workspace has its tables
     p->stream = static_cast<hipStream_t>(hip_stream);
     p->ws = static_cast<char *>(dev_ptr);
     p->ws_bytes = bytes;
@@ -712,6 +724,8 @@ int cr_bind_workspace(cr_plan_t *p, void *dev_ptr, size_t bytes, void *hip_strea
     p->have_grads = false;
     p->have_messages = false;
     return CR_OK;
+} catch (const std::bad_alloc &) {
+    return fail(CR_E_NOMEM, "out of host memory");
 }
 
 int cr_partial_grads(cr_plan_t *p, const void *X, const float *y, const float *w)

@@ -109,3 +109,32 @@ def test_whole_ranges_of_more_rows_than_a_run_can_have():
     assert _pieces(p) == _pieces(q) and max(e - b for b, e in zip(*_pieces(p)[1:3])) <= 1 << 30
     cr.cr_plan_destroy(p)
     cr.cr_plan_destroy(q)
+
+
+@pytest.mark.parametrize("kind", [cr.CR_SPLIT_ROWS_ONCE, cr.CR_SPLIT_ROW_CELLS, cr.CR_SPLIT_SHARED_CELLS])
+def test_out_of_host_memory_is_an_error(kind):
+    """A split of tens of millions of pieces in a process that may not grow by that much: a status, and the plan can be used on."""
+    import os
+    import subprocess
+    import sys
+
+    code = f"""
+import resource
+import paper_1902_01981_amd as cr
+p = cr.cr_plan_ex(2, 3, 1, 12_000_000, 1_500)
+cr.cr_plan_set_split(p, cr.CR_SPLIT_EQUAL_RANGES, 100)
+size = int(open('/proc/self/statm').read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (size + (200 << 20), resource.RLIM_INFINITY))
+for _ in range(2):
+    try:
+        cr.cr_plan_set_split(p, {kind}, 1)
+        raise SystemExit('the split fits after all')
+    except cr.CodedReduceError as e:
+        assert e.status == cr.CR_E_NOMEM, e
+    assert cr.cr_plan_info(p).num_pieces == 0
+cr.cr_plan_set_split(p, cr.CR_SPLIT_ROWS_ONCE, 10_000)
+assert cr.cr_plan_info(p).num_pieces > 0 and cr.cr_workspace_bytes(p) > 0
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    res = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, (res.returncode, res.stderr[-400:])
