@@ -698,7 +698,7 @@ try {
         const int32_t shared = p->s > 0 || p->m * p->d * elem_size(p) < kStreamFromBytes ? 1 : 0;
         for (int32_t i = 0; i < P; ++i) {
             const int64_t rows = p->split.pieces[i].row_end - p->split.pieces[i].row_begin;
-            hp[i] = {p->split.pieces[i].row_begin, visit, static_cast<int32_t>(rows), p->split.pieces[i].slab, shared, out_row[i]};
+            hp[i] = {p->split.pieces[i].row_begin, visit, static_cast<int32_t>(rows), shared, out_row[i], 0};
             visit += rows;
         }
         for (int32_t q = 0; q < S; ++q) {

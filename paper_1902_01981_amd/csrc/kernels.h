@@ -10,9 +10,9 @@ struct DevPiece {            // one stage-1 work item: rows [row_begin, row_begi
     int64_t row_begin;
     int64_t visit_begin;     // index of the piece's first row among all row visits, piece-major (wide-row path: where its residuals live)
     int32_t nrows;
-    int32_t slab;
     int32_t shared;          // 1: other workgroups fetch these rows at the same time, so the fetch should leave them in the L2
     int32_t out_row;         // row of the output table that receives the piece's gradient
+    int32_t pad;
 };
 
 // Output table of stage 1: rows of d floats, first the slab gradients G[0 .. S), then the partial rows.

@@ -1,5 +1,5 @@
-// HIP kernels of the CodedReduce hot path for gfx950 (64-wide wavefronts).  Everything here is bandwidth bound (stage 1 on bf16
-// rows: bound by vector-ALU issue): plain vector FMAs, 16-byte coalesced loads, no matrix cores.
+// HIP kernels of the CodedReduce hot path for gfx950 (64-wide wavefronts).  Everything here is bandwidth bound (stage 1 with every
+// holder's bf16 rows done separately: bound by vector-ALU issue): plain vector multiply-adds, 16-byte coalesced loads, no matrix cores.
 //
 //   rows_once_kernel, rows_once_team_kernel   CR.Execute step 1: X[b:e]^T (phi(X[b:e] w) - y[b:e]) in ONE pass over X, every row's
 //                          contribution formed once for all workers that hold it
@@ -31,8 +31,7 @@ namespace {
 
 typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));       // four floats of an fp32 row
 typedef unsigned u4h __attribute__((ext_vector_type(4), aligned(2)));    // eight bf16 values of a bf16 row
-typedef float f4a __attribute__((ext_vector_type(4)));                   // the same chunks parked in LDS, 16-byte aligned there
-typedef unsigned u4a __attribute__((ext_vector_type(4)));
+typedef float f4a __attribute__((ext_vector_type(4)));                   // four floats on a 16-byte boundary
 
 // v + (v of the lane that the cross-lane pattern CTRL pairs this lane with, inside its row of 16 lanes)
 template <int CTRL> __device__ __forceinline__ float dpp_add(float v)
@@ -116,14 +115,12 @@ template <int XD> __device__ __forceinline__ const void *row_ptr(const void *X, 
 
 template <> struct Chunk<0, 4> {
     using raw_t = f4u;
-    using lds_t = f4a;
     static __device__ __forceinline__ raw_t load(const void *row, unsigned e) { return *reinterpret_cast<const f4u *>(static_cast<const char *>(row) + e * 4u); }
     static __device__ __forceinline__ raw_t load_once(const void *row, unsigned e) { return __builtin_nontemporal_load(reinterpret_cast<const f4u *>(static_cast<const char *>(row) + e * 4u)); }
     static __device__ __forceinline__ void widen(const raw_t &r, float (&v)[4]) { v[0] = r.x; v[1] = r.y; v[2] = r.z; v[3] = r.w; }
 };
 template <> struct Chunk<1, 8> {
     using raw_t = u4h;
-    using lds_t = u4a;
     static __device__ __forceinline__ raw_t load(const void *row, unsigned e) { return *reinterpret_cast<const u4h *>(static_cast<const char *>(row) + e * 2u); }
     static __device__ __forceinline__ raw_t load_once(const void *row, unsigned e) { return __builtin_nontemporal_load(reinterpret_cast<const u4h *>(static_cast<const char *>(row) + e * 2u)); }
     static __device__ __forceinline__ void widen(const raw_t &r, float (&v)[8])

@@ -483,7 +483,6 @@ void split_row_cells(const std::vector<Slab> &slabs, int64_t cell_rows, int lane
         }
         size_t deepest = 0;
         for (auto &c : cells) deepest = std::max(deepest, c.second - c.first);
-        const bool last_run = (j == units.size());
         for (size_t g = 0; g * teams_per_block < deepest; ++g)
             for (size_t c = 0; c < static_cast<size_t>(lanes); ++c)
                 for (int t = 0; t < teams_per_block; ++t) {
@@ -491,7 +490,6 @@ void split_row_cells(const std::vector<Slab> &slabs, int64_t cell_rows, int lane
                     if (c < cells.size() && cells[c].first + rank < cells[c].second) order.push_back(units[cells[c].first + rank]);
                     else if (lanes > 1 || teams_per_block > 1) order.push_back(none);
                 }
-        (void)last_run;
         i = j;
     }
     while (!order.empty() && order.back().slab < 0) order.pop_back();
