@@ -265,7 +265,8 @@ int make_split(cr_plan_t *p)
     if (kind < 0 && large && p->cell_holders >= p->max_holders) {
         // All holders of a cell in one workgroup, cells between slab boundaries, one queue of cells per compute unit.  The launch
         // lasts as long as the longest queue: take the cell height, 16 to 1024 rows in steps of 8, that makes it shortest; ties go
-        // to the taller cell (fewer partial rows).
+        // to the taller cell (fewer partial rows).  Against contiguous parts (rows once), stage 1 in us: 252 000 x 4 096 589 / 590,
+        // 100 000 x 10 000 on a (4,2) tree 578 / 578, with 20 workers in one layer 612 / 579, 366 000 x 2 048 464 / 428.
         kind = CR_SPLIT_SHARED_CELLS;
         const int slots = unit_slots(p->d * elem_size(p), domains);
         value = 512;

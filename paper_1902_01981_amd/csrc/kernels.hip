@@ -359,9 +359,11 @@ partial_grads_kernel(const void *__restrict__ X, const float *__restrict__ y, co
 // into the slabs that consist of just this run, and into a partial row where larger slabs are summed from several runs
 // (sum_rows_kernel).  A workgroup owns one contiguous *part* of X -- in the default split the chip's compute units take one or two
 // parts each, so X is read as a few hundred long sequential streams with one wave of workgroups and few partial rows.
-// What bounds it is the read of X: 256 parts of one 4-wavefront workgroup each reach 7.0 to 7.1 TB/s on 3 GB of rows of 4096 to 10000
-// fp32 or 8192 bf16 values (a plain streaming read of the same buffer: 7.06), 512 parts 6.4 to 6.9, 768 parts and more 6.4 to 6.6;
-// rows of at most 256 chunks, one row per wavefront or less, do best with 512 (7.0 to 7.1 on 1000 fp32 or 1024 bf16 columns).
+// What bounds it is the read of X (a plain streaming read: 7.06 TB/s).  One workgroup per compute unit for rows that a whole workgroup
+// shares: 252 000 x 4 096 and 100 000 x 10 000 fp32 7.0 and 6.9 TB/s.  It is slower where the parts' starts lie a large power of two
+// apart (196 608 x 4 096, parts of 12 MB: 6.25 with 256 workgroups, 6.80 with 512, 6.72 with 768; x 8 192 bf16 6.26, 6.59, 6.47) and
+// the same where they do not (80 530 x 10 000: 6.32, 6.36, 6.28).  Rows of at most 256 chunks, one row per wavefront or less, get two:
+// 805 306 x 1 000 fp32 6.45, 6.77, 6.87, 1 572 864 x 1 024 bf16 5.83, 6.77, 6.85.
 // The rows of the next step are loaded before the current step is computed (two register sets).
 // NT: rows fetched with the non-temporal hint, for matrices larger than the last-level cache.
 
@@ -550,7 +552,7 @@ rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const 
 // Wider rows: the TS threads of the workgroup share every row, thread t holding chunks t, t + TS, ..., R rows per step.  One barrier
 // per step exchanges the wavefronts' parts of the dot products (double buffered in LDS).  PF: the next step's rows are loaded before
 // the current step is computed; beyond 9 chunks per thread the second register set costs more than it hides (a row is then long
-// enough: 12 chunks, 24576 columns, 200 MB: 43.4 us without, 45.8 with it).
+// enough: 12 chunks, 24576 columns, 3.2 GB: 497 us without, 604 with it).
 template <int XD, int VEC, int TS, int K, int R, bool PF, bool NT>
 __global__ void __launch_bounds__(TS)
 rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w, const DevRun *__restrict__ parts,
@@ -1123,7 +1125,7 @@ const OnceVariant kOnceVariants[] = {
     CR_O(0, 4, 2, 1, 4, 4), CR_O(0, 4, 4, 1, 4, 4), CR_O(0, 4, 8, 1, 4, 4), CR_O(0, 4, 16, 1, 4, 4), CR_O(0, 4, 32, 1, 4, 4),
     CR_O(0, 4, 64, 1, 4, 4), CR_O(0, 4, 64, 2, 4, 4), CR_O(0, 4, 64, 3, 2, 4), CR_O(0, 4, 64, 4, 2, 4),
     // ... then two wavefronts up to 512, four up to 1792, eight up to 6144 chunks (more chunks per thread would leave no room for the
-    // next step; 1500 columns, 3 GB: 423 us with two wavefronts, 444 with four, a quarter of whose second chunks lie past the row)
+    // next step; 60 000 x 1500: 59 us with two wavefronts, 63 with four, a quarter of whose second chunks lie past the row)
     CR_OT(0, 4, 128, 3, 4, true), CR_OT(0, 4, 128, 4, 4, true), CR_OT(0, 4, 256, 3, 4, true), CR_OT(0, 4, 256, 4, 2, true),
     CR_OT(0, 4, 256, 5, 2, true), CR_OT(0, 4, 256, 6, 2, true), CR_OT(0, 4, 256, 7, 2, true),
     CR_OT(0, 4, 512, 4, 2, true), CR_OT(0, 4, 512, 5, 2, true), CR_OT(0, 4, 512, 6, 1, true),
@@ -1133,7 +1135,7 @@ const OnceVariant kOnceVariants[] = {
     CR_O(1, 8, 2, 1, 4, 4), CR_O(1, 8, 4, 1, 4, 4), CR_O(1, 8, 8, 1, 4, 4), CR_O(1, 8, 16, 1, 4, 4), CR_O(1, 8, 32, 1, 4, 4),
     CR_O(1, 8, 64, 1, 4, 4), CR_O(1, 8, 64, 2, 2, 4), CR_O(1, 8, 64, 3, 2, 4), CR_O(1, 8, 64, 4, 2, 4),
     // (rows of an odd number of columns start on any 2-byte boundary, where 16-byte loads take two trips: two smaller workgroups per
-    // unit hide that better, 3 GB of 3001 columns 466 against 527 us)
+    // unit hide that better, 3 GB of 3001 columns 509 against 785 us, of 6001 columns 517 against 662)
     CR_OT(1, 8, 128, 3, 4, true), CR_OT(1, 8, 128, 4, 2, true), CR_OT(1, 8, 128, 5, 2, true),
     CR_OT(1, 8, 128, 6, 2, true),
     CR_OT(1, 8, 256, 2, 4, true), CR_OT(1, 8, 256, 3, 2, true), CR_OT(1, 8, 256, 4, 2, true),

@@ -174,8 +174,8 @@ def test_cfg5_full():
 
 
 def test_four_holders_two_workgroups_per_unit_full():
-    """A (2,4,1) tree over 366 000 x 2 048 fp32 (3 GB): the staged kernel with four holders per workgroup and, rows being 8 KB,
-    two workgroups per compute unit."""
+    """A (2,4,1) tree over 366 000 x 2 048 fp32 (3 GB): shared cells of four holders and, rows being 8 KB, two
+    workgroups per compute unit."""
     cfg = wl.config("cfg2", m=366_000, d=2_048, lr=3e-7)
     data = wl.make_dataset(cfg, threads=16)
     hip = HipPath(cfg["L"], cfg["n"], cfg["s"], data["X"], data["y"], cr.CR_LINEAR, cr.CR_F32)
@@ -189,8 +189,8 @@ def test_four_holders_two_workgroups_per_unit_full():
 
 
 def test_gradient_coding_twenty_workers_full():
-    """One layer, 20 workers, 4 stragglers tolerated, on configuration 2's data: five holders per row, all in one workgroup of three
-    teams that work for two holders each, so that every row is fetched once and streamed."""
+    """One layer, 20 workers, 4 stragglers tolerated, on configuration 2's data: five holders per row, all served by one
+    workgroup, so that every row is formed once and streamed."""
     cfg = wl.config("gc20")
     data = wl.make_dataset(cfg, threads=16)
     hip = HipPath(cfg["L"], cfg["n"], cfg["s"], data["X"], data["y"], cr.CR_LINEAR, cr.CR_F32)
@@ -204,8 +204,8 @@ def test_gradient_coding_twenty_workers_full():
 
 
 def test_uncoded_twenty_workers_full():
-    """One layer, 20 workers, no redundancy, on configuration 2's data (4 GB): nobody else reads a row, so the register kernel
-    fetches every row with the non-temporal hint (only data sets of 1 GiB and more take that path)."""
+    """One layer, 20 workers, no redundancy, on configuration 2's data (4 GB): equal ranges of rows that nobody else
+    holds, read past the caches."""
     cfg = wl.config("umw20")
     data = wl.make_dataset(cfg, threads=16)
     hip = HipPath(cfg["L"], cfg["n"], cfg["s"], data["X"], data["y"], cr.CR_LINEAR, cr.CR_F32)
@@ -219,8 +219,8 @@ def test_uncoded_twenty_workers_full():
 
 @pytest.mark.parametrize("L,n,s,m,d,holders", [(1, 4, 2, 30_000, 10_000, 3), (1, 4, 1, 30_000, 10_000, 2), (1, 6, 2, 70_000, 4_096, 4)])
 def test_streamed_cells_full(L, n, s, m, d, holders):
-    """Data sets of 1.1 to 1.2 GB whose every cell belongs to one workgroup: three holders loaded straight into LDS, two and
-    three holders (one idle team) staged through registers, all fetched with the non-temporal hint."""
+    """Data sets of 1.1 to 1.2 GB whose every cell belongs to one workgroup: two, three and (in a workgroup for four) three holders, all
+    read past the caches."""
     cfg = wl.config("cfg2", L=L, n=n, s=s, m=m, d=d, lr=3e-7)
     data = wl.make_dataset(cfg, threads=16)
     hip = HipPath(L, n, s, data["X"], data["y"], cr.CR_LINEAR, cr.CR_F32)

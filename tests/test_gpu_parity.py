@@ -89,18 +89,18 @@ def test_printed_code_of_the_example():
 
 CASES = [
     # name, L, n, s, m, d, model, x_dtype, teams
-    ("cfg2-shape", 2, 4, 1, 6_007, 10_000, cr.CR_LINEAR, cr.CR_F32, None),       # 256-thread teams, 10 chunks per thread, ragged last chunk
+    ("cfg2-shape", 2, 4, 1, 6_007, 10_000, cr.CR_LINEAR, cr.CR_F32, None),       # eight wavefronts per row, five chunks per thread, the last ones partly past the row
     ("cfg2-few-teams", 2, 4, 1, 3_001, 10_000, cr.CR_LINEAR, cr.CR_F32, 37),      # pieces crossing slab boundaries
     ("cfg2-row-cells", 2, 4, 1, 3_001, 10_000, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_ROW_CELLS, 48)),  # holders of a cell run side by side
     ("cfg3-shape", 3, 4, 1, 8_400, 4_096, cr.CR_LOGISTIC, cr.CR_F32, None),
     ("cfg5-row-cells", 3, 6, 2, 25_801, 1_024, cr.CR_LINEAR, cr.CR_BF16, (cr.CR_SPLIT_ROW_CELLS, 100)),
     ("cfg5-shape", 3, 6, 2, 25_801, 1_024, cr.CR_LINEAR, cr.CR_BF16, None),       # one wavefront per row, bf16 x8 chunks
-    ("bf16-wide", 2, 3, 1, 2_000, 8_192, cr.CR_LOGISTIC, cr.CR_BF16, None),       # bf16 with 256-thread teams
+    ("bf16-wide", 2, 3, 1, 2_000, 8_192, cr.CR_LOGISTIC, cr.CR_BF16, None),       # bf16, four wavefronts per row
     ("odd-d-fp32", 2, 3, 1, 1_111, 1_003, cr.CR_LINEAR, cr.CR_F32, None),         # d % 4 != 0: the last chunk overlaps its neighbour
     ("odd-d-bf16", 2, 3, 1, 1_111, 270, cr.CR_LINEAR, cr.CR_BF16, None),
-    ("odd-d-cfg2", 2, 4, 1, 2_003, 9_999, cr.CR_LOGISTIC, cr.CR_F32, None),       # rows not 16-byte aligned, 10 chunks per thread
+    ("odd-d-cfg2", 2, 4, 1, 2_003, 9_999, cr.CR_LOGISTIC, cr.CR_F32, None),       # rows not 16-byte aligned, five chunks per thread
     ("odd-d-bf16-k3", 2, 3, 1, 1_500, 1_027, cr.CR_LINEAR, cr.CR_BF16, None),     # rows on odd 2-byte boundaries, last thread chunk mostly inert
-    ("bf16-k3-buffers", 2, 3, 1, 1_503, 1_536, cr.CR_LOGISTIC, cr.CR_BF16, None),  # buffer loads, three chunks per lane, pieces that end inside a trip of four rows
+    ("bf16-k3-buffers", 2, 3, 1, 1_503, 1_536, cr.CR_LOGISTIC, cr.CR_BF16, None),  # three chunks per lane
     ("bf16-k4-buffers", 3, 3, 2, 2_001, 2_042, cr.CR_LINEAR, cr.CR_BF16, (cr.CR_SPLIT_ROW_CELLS, 7)),   # rows on 4-byte (not 16-byte) boundaries, last chunk moved back, cells of 7 rows
     ("bf16-k1-buffers", 1, 6, 3, 999, 72, cr.CR_LOGISTIC, cr.CR_BF16, (cr.CR_SPLIT_EQUAL_RANGES, 13)),    # one chunk per lane, most lanes idle, pieces across slab boundaries
     ("d-5", 2, 3, 1, 600, 5, cr.CR_LINEAR, cr.CR_F32, None),                      # two chunks sharing three columns
@@ -110,7 +110,7 @@ CASES = [
     ("tiny-d", 1, 5, 2, 333, 4, cr.CR_LINEAR, cr.CR_F32, None),                   # one layer: master-worker gradient coding
     ("s0-plain-tree", 2, 4, 0, 4_000, 256, cr.CR_LINEAR, cr.CR_F32, None),
     ("deep", 4, 2, 1, 3_000, 520, cr.CR_LOGISTIC, cr.CR_F32, None),
-    ("big-team", 2, 3, 1, 700, 16_384, cr.CR_LINEAR, cr.CR_F32, None),            # 1024-thread teams
+    ("big-team", 2, 3, 1, 700, 16_384, cr.CR_LINEAR, cr.CR_F32, None),            # eight wavefronts per row, eight chunks per thread
     ("m-equals-N", 2, 3, 1, 12, 64, cr.CR_LINEAR, cr.CR_F32, None),               # one row per worker
     ("gc-master-worker", 1, 10, 4, 10_000, 512, cr.CR_LINEAR, cr.CR_F32, None),   # one layer, 10 workers, 4 stragglers (fractional repetition)
     ("uncoded-master-worker", 1, 10, 0, 10_000, 512, cr.CR_LINEAR, cr.CR_F32, None),
@@ -120,27 +120,28 @@ CASES = [
     ("cr-12x2-s3", 2, 12, 3, 31_200, 320, cr.CR_LOGISTIC, cr.CR_F32, None),       # the paper's (12,2) tree, 156 workers, 3 stragglers per group
     ("cr-12x2-s2", 2, 12, 2, 15_611, 1_000, cr.CR_LINEAR, cr.CR_F32, None),       # ... 2 per group
     ("cr-12x2-s5", 2, 12, 5, 49_920, 432, cr.CR_LOGISTIC, cr.CR_F32, None),       # ... 5 per group (resiliency 5/12, 49 920 points as in the network experiment): 36 holders per row
-    # rows staged through LDS and shared by the holders in one workgroup
-    ("direct-4-holders", 2, 4, 1, 3_001, 10_000, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 37)),      # rows loaded straight into LDS, weights in LDS too, 10 chunks per thread, cells of 2 and 4 holders
-    ("direct-4-holders-k8", 2, 3, 1, 2_501, 8_192, cr.CR_LOGISTIC, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 3)),    # 2048 chunks: no partial wavefront in the fetch; cells shorter than the ring
-    ("direct-4-holders-8", 3, 4, 1, 2_400, 6_500, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 20)),      # 8, 4 and 2 holders: cells of two workgroups (kept in the L2) and of one (streamed)
-    ("direct-3-holders", 1, 4, 2, 3_001, 10_000, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 37)),      # three holders per row and workgroup, weights in registers; every row streamed
-    ("direct-6-holders-5", 1, 10, 4, 2_000, 9_000, cr.CR_LOGISTIC, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 11)),   # five holders in one workgroup: three teams that work for two holders each, one of them for one
-    ("direct-6-holders-6", 1, 12, 5, 1_800, 7_000, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 5)),      # six holders, seven chunks per thread, cells shorter than the ring
-    ("direct-3-holders-k9", 1, 6, 2, 2_000, 8_196, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 1)),      # single-row cells: the ring runs across items; last fetch wavefronts idle
-    ("direct-widest", 2, 4, 1, 1_500, 10_232, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 16)),          # 2558 chunks: the ring and the weights fill LDS to the last byte
-    ("direct-default", 2, 4, 1, 70_000, 6_400, cr.CR_LINEAR, cr.CR_F32, None),                                  # large enough for the default split to pick it
-    ("staged-2-holders", 1, 4, 1, 3_001, 10_000, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 37)),      # two holders per row: register-staged kernel, 10 chunks per thread
+    # shared cells: a workgroup forms a cell once for all the holders it serves ("direct" are the rows of 1537 to 2558 chunks and three
+    # or more holders, "staged" the other widths)
+    ("direct-4-holders", 2, 4, 1, 3_001, 10_000, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 37)),      # ten chunks per thread, one run per cell for the two or four holders it has
+    ("direct-4-holders-k8", 2, 3, 1, 2_501, 8_192, cr.CR_LOGISTIC, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 3)),      # 2048 chunks: no partial wavefront; cells of three rows
+    ("direct-4-holders-8", 3, 4, 1, 2_400, 6_500, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 20)),      # 8, 4 and 2 holders: cells of two workgroups, which both form them, and of one
+    ("direct-3-holders", 1, 4, 2, 3_001, 10_000, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 37)),      # three holders per row and workgroup
+    ("direct-6-holders-5", 1, 10, 4, 2_000, 9_000, cr.CR_LOGISTIC, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 11)),      # five holders of a row in one workgroup
+    ("direct-6-holders-6", 1, 12, 5, 1_800, 7_000, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 5)),      # six holders, cells of five rows
+    ("direct-3-holders-k9", 1, 6, 2, 2_000, 8_196, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 1)),      # single-row cells; the last wavefronts' chunks lie past the row
+    ("direct-widest", 2, 4, 1, 1_500, 10_232, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 16)),      # 2558 chunks: the widest cells of four holders
+    ("direct-default", 2, 4, 1, 70_000, 6_400, cr.CR_LINEAR, cr.CR_F32, None),      # large enough for the default split to be shared cells
+    ("staged-2-holders", 1, 4, 1, 3_001, 10_000, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 37)),      # two holders per row
     ("staged-2-holders-odd-d", 2, 4, 1, 2_003, 9_999, cr.CR_LOGISTIC, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 64)),
-    ("staged-4-holders", 2, 4, 1, 5_003, 2_052, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 50)),       # four 256-thread teams, two rows per step
+    ("staged-4-holders", 2, 4, 1, 5_003, 2_052, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 50)),      # four wavefronts per row, one third of whose chunks lie past it
     ("staged-4-holders-k6", 2, 3, 1, 2_000, 5_640, cr.CR_LOGISTIC, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 90)),
-    ("staged-8-holders", 3, 4, 1, 8_400, 4_096, cr.CR_LOGISTIC, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 33)),     # eight one-wavefront teams, 16 chunks per thread
-    ("staged-8-holders-1-row", 3, 3, 1, 2_500, 3_001, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 1)),  # cells of a single row
-    ("staged-3-holders", 1, 5, 2, 4_001, 3_001, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 100)),      # one idle team per workgroup of four
-    ("staged-k12", 2, 3, 1, 900, 12_288, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 1000)),            # the widest staged rows
-    ("staged-default", 2, 4, 1, 140_000, 1_100, cr.CR_LINEAR, cr.CR_F32, None),                               # large enough for the staged default
+    ("staged-8-holders", 3, 4, 1, 8_400, 4_096, cr.CR_LOGISTIC, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 33)),      # eight holders of a row in one workgroup
+    ("staged-8-holders-1-row", 3, 3, 1, 2_500, 3_001, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 1)),      # cells of a single row
+    ("staged-3-holders", 1, 5, 2, 4_001, 3_001, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 100)),      # three holders in a workgroup for four
+    ("staged-k12", 2, 3, 1, 900, 12_288, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 1000)),      # the widest shared cells
+    ("staged-default", 2, 4, 1, 140_000, 1_100, cr.CR_LINEAR, cr.CR_F32, None),      # 616 MB: rows once, read past the caches
     ("staged-queue-gaps", 3, 2, 1, 3_000, 7_000, cr.CR_LINEAR, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 40)),      # cells of 1, 2 and 4 workgroups in gangs of 4
-    ("staged-wide-gang", 4, 3, 2, 2_400, 6_200, cr.CR_LOGISTIC, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 25)),     # 81 holders: more workgroups per cell than one L2 domain has slots
+    ("staged-wide-gang", 4, 3, 2, 2_400, 6_200, cr.CR_LOGISTIC, cr.CR_F32, (cr.CR_SPLIT_SHARED_CELLS, 25)),      # 81 holders: more workgroups per cell than one L2 domain has slots
 ]
 
 
@@ -586,8 +587,7 @@ def test_random_small_problems():
 
 
 def test_random_sweep_of_staged_kernels():
-    """Seeded sweep over the staged stage-1 kernels: every chunk count of the one-wavefront family and of both four-wavefront
-    families, odd widths, trees with 2 to 27 holders per row, random cell heights, fewer than s stragglers in some groups."""
+    """Seeded sweep over shared cells: chunk counts of every family of holders per workgroup, odd widths, trees with 2 to 27 holders per row, random cell heights, fewer than s stragglers in some groups."""
     rng = np.random.default_rng(4242)
     chunk_counts = list(range(257, 1025, 64)) + [1024, 1100, 1536, 1700, 2304, 2900, 3072]      # 16-byte chunks per row
     for trial, nq in enumerate(chunk_counts):

@@ -1,5 +1,6 @@
 """Stage 1 with every row formed once for all slabs that hold it (CR_SPLIT_ROWS_ONCE), at the widths where its kernels change: lanes per
-row, chunks per lane, threads per row; the shortest and the widest rows; sums of one step, of several steps and of whole ranges."""
+row, chunks per lane, threads per row; the shortest and the widest rows; runs of one row, of a step and whole ones (parts are short here:
+test_run_borders.py has runs of several steps)."""
 import numpy as np
 import pytest
 
@@ -52,8 +53,8 @@ def test_rows_once_tables(value):
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,bf16", WIDTHS)
 def test_rows_once_matches_the_oracle(d, bf16):
-    """Slabs against the fp64 oracle under the default split and with fp32 sums of the fewest rows there can be and of 13.  Every sum has at most a few
-    hundred terms, so fp32 accumulation stays inside the parity tests' regression gate (1e-5)."""
+    """Slabs against the fp64 oracle under the default split and with runs of one row and of up to 13.  What is in fp32 are the dot products and
+    sums of at most four rows: inside the parity tests' regression gate (1e-5)."""
     logistic = d % 2 == 0
     m = 12 * 25 + 1 if d > 1024 else 1_801
     cfg = wl.config("cfg3" if logistic else "cfg2", L=2, n=3, s=1, m=m, d=d, model=int(logistic), x_dtype=bf16,
@@ -78,7 +79,7 @@ def test_rows_once_matches_the_oracle(d, bf16):
 @pytest.mark.gpu
 def test_rows_once_streamed_past_the_caches():
     """256 MiB and more: the same kernels with the non-temporal hint.  Rows of 64 to 3000 columns, against the literal row cells (the
-    same sums in another order: rounding of runs of up to 512 rows, well under the gate)."""
+    row cells add runs of up to 256 rows in fp32, well under the gate)."""
     import torch
 
     for d, bf16 in ((64, 0), (1_000, 0), (3_000, 0), (10_000, 0), (1_027, 1), (5_000, 1), (10_000, 1)):
@@ -107,9 +108,8 @@ WIDE = [(24_577, 0, 13), (24_580, 1, 14), (30_003, 0, 897), (32_768, 1, 451), (2
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,bf16,m", WIDE)
 def test_wide_rows_once(d, bf16, m):
-    """Two passes, every row once, against the row cells of every holder separately: the same sums over runs of up to 512 rows in
-    another order, so both lie within fp32 rounding of each other, well under the gate (1e-5); `value` 1 and 70 for sums of one row and
-    of one fold and a remainder."""
+    """Two passes, every row once, against the row cells of every holder separately, which add runs of up to 64 rows in fp32, well under the
+    gate (1e-5); `value` 1 and 70 for runs of one row and for parts cut into runs and a remainder."""
     import torch
 
     for logistic in (0, 1):
