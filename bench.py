@@ -6,19 +6,20 @@ host-drawn straggler mask -> cr_partial_grads -> cr_encode_tree -> cr_decode_roo
 (issued through cr_gd_run -- cr_aggregate_run for the aggregation-only workloads -- which enqueues these steps for every mask,
 the encode programs of 16 steps per host-to-device copy; the gradient step rides in the decode launch).
 
-Prints ONE JSON line.  Its top level is the headline workload (configuration 5: the largest, end-to-end iterations/s);
-"configs" holds the same record for every benchmark configuration and for the comparison workloads of the paper's
-computation-load discussion, all measured in this run: iterations/s, the roofline of the dominant kernel (timed live
-with HIP events on the library's stream over the timed steps: average, minimum, median, maximum), the CPU oracle
-timed on a bounded sample of the same workload, and the parity of one GPU iteration with that oracle.
+Prints ONE JSON line, short enough to be kept whole.  Its top level is the headline workload (configuration 5: the largest,
+end-to-end iterations/s); "configs" holds for every benchmark configuration and for the comparison workloads of the paper's
+computation-load discussion, all measured in this run: iterations/s, the median time of the dominant kernel (HIP events on the
+library's stream over the timed steps), the fraction of its roofline, the CPU oracle timed on a bounded sample of the same workload,
+and the parity of one GPU iteration with that oracle.  --detail FILE writes the whole records (every kernel with average, minimum,
+median and maximum, the work split, the samples) there as JSON.
 
-    python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME]
+    python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME] [--detail FILE]
 
 roofline.frac is the fraction of the resource that binds: for the memory-bound kernels the bytes HBM really moved per
 launch (rocprofv3 FETCH_SIZE + WRITE_SIZE of the same kernel and work split, profiles/hbm_traffic.json) over the
-kernel's time, against 8 TB/s; the algorithmic bytes (every holder's read of a row charged) are reported beside it as
-algorithmic_GBps / algorithmic_ratio and exceed the peak where holders share a row's fetch and its sums.  What stage 1 takes when
-every holder does its own arithmetic is in config.stage1_every_holder_ms.
+kernel's time, against 8 TB/s; needed_GBps counts the bytes that the kernel's arithmetic cannot do without (the data once where the
+holders' common sums are formed once, once per holder where every holder does its own).  What stage 1 takes when every holder does
+its own arithmetic is stage1_every_holder_ms.
 """
 from __future__ import annotations
 
@@ -289,9 +290,15 @@ def run_workload(name: str, steps: int, warmup: int, cpu_budget: float, args) ->
            "frac_of_stream_read": traffic_gbps / stream_gbps if traffic and stream_gbps else None,
            "traffic_frac_whole_step": traffic / (elapsed / steps) / 1e9 / HBM_PEAK_GBPS if traffic else None,
            "stream_read_GBps": stream_gbps}
-    common = {"kernel": dominant, "kernel_ms": dk["ms"], "algorithmic_bytes_per_launch": dk["algorithmic_bytes_per_launch"],
-              "algorithmic_GBps": dk["algorithmic_GBps"], "algorithmic_ratio": dk["algorithmic_GBps"] / HBM_PEAK_GBPS}
-    if not aggregate and cfg["x_dtype"] == wl.BF16 and info.split_kind in (cr.CR_SPLIT_EQUAL_RANGES, cr.CR_SPLIT_ROW_CELLS) and s > 0:
+    every_holder = not aggregate and s > 0 and info.split_kind in (cr.CR_SPLIT_EQUAL_RANGES, cr.CR_SPLIT_ROW_CELLS)
+    if aggregate or every_holder:
+        needed = dk["algorithmic_bytes_per_launch"]
+    else:
+        needed = m * d * (2 if cfg["x_dtype"] == wl.BF16 else 4) + 4 * m + 4 * d * (info.num_slabs + 1)
+        dk.pop("algorithmic_bytes_per_launch")           # these charge every holder's read of a row
+        dk.pop("algorithmic_GBps")
+    common = {"kernel": dominant, "kernel_ms": dk["ms"], "needed_bytes_per_launch": needed, "needed_GBps": needed / avg_s / 1e9}
+    if every_holder and cfg["x_dtype"] == wl.BF16:
         # bf16 rows, every holder's arithmetic done separately (--teams, --cell-rows): stage 1 is bound by vector-ALU issue (a widening operation and two multiply-adds per element), not by memory:
         # 4 flop per element of X visited, against the vector peak of the instructions this build issues
         flops = 4.0 * info.row_visits * d
@@ -344,7 +351,7 @@ def run_workload(name: str, steps: int, warmup: int, cpu_budget: float, args) ->
         "clock_ramp_steps": ramp_steps + 4,
         "ms_per_step": elapsed / steps * 1e3,
         "us_per_iteration": elapsed / steps * 1e6,
-        "dtype": "f32",          # the arithmetic type: bf16 rows are widened and every product and sum is fp32
+        "dtype": "f32",          # the arithmetic type: bf16 rows are widened; products are fp32, sums over rows fp32 or fp64
         "config": {"workload": f"{name}: {DESCRIPTIONS[name]}", "L": L, "n": n, "s": s, "m": m, "d": d,
                    "x_storage": "bf16" if cfg["x_dtype"] == wl.BF16 else "f32",
                    "workers": info.num_workers, "slabs": info.num_slabs, "row_visits": info.row_visits,
@@ -352,8 +359,8 @@ def run_workload(name: str, steps: int, warmup: int, cpu_budget: float, args) ->
                    "stage1_teams": info.num_teams, "stage1_pieces": info.num_pieces, "code_gamma": info.gamma,
                    "stage1_split": SPLITS[info.split_kind] if info.split_kind >= 0 else None,
                    "stage1_split_value": info.split_value,
-                   "stage1_arithmetic": None if aggregate else "every holder" if s > 0 and info.split_kind in (cr.CR_SPLIT_EQUAL_RANGES, cr.CR_SPLIT_ROW_CELLS)
-                   else "every row once, for all its holders",
+                   "stage1_arithmetic": None if aggregate else "every holder" if every_holder
+                   else "every slab range once" if info.split_value == cr.CR_ROWS_WHOLE_RANGES else "every row once, for all its holders",
                    "stage1_every_holder_ms": holder_ms, "stage1_team_size": info.stage1_team_size,
                    "stage1_holders_per_workgroup": info.stage1_teams_per_group if info.stage1_staged else 1,
                    "l2_domains": info.l2_domains, "l2_sharing_checked": info.l2_sharing, "split_signature": signature},
@@ -372,6 +379,13 @@ def run_workload(name: str, steps: int, warmup: int, cpu_budget: float, args) ->
     return out
 
 
+def rounded(v):
+    """The record with its measured numbers to six digits."""
+    if isinstance(v, dict):
+        return {k: rounded(x) for k, x in v.items()}
+    return float(f"{v:.6g}") if isinstance(v, float) else v
+
+
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -384,7 +398,8 @@ def main() -> int:
                     help="untimed load before the warm-up steps, in milliseconds of device time, to bring the clocks up (0 = none)")
     ap.add_argument("--teams", type=int, default=0, help="stage-1 split: this many equal contiguous ranges")
     ap.add_argument("--cell-rows", type=int, default=0, help="stage-1 split: row cells of this many rows")
-    ap.add_argument("--shared-rows", type=int, default=0, help="stage-1 split: cells of at most this many rows shared through LDS")
+    ap.add_argument("--shared-rows", type=int, default=0, help="stage-1 split: shared cells of at most this many rows")
+    ap.add_argument("--detail", default=None, help="write the whole records to this file")
     ap.add_argument("--calibrate", action="store_true",
                     help="run only a plain 1 GiB elementwise copy kernel a few times (reference for rocprofv3 byte counters)")
     args = ap.parse_args()
@@ -413,7 +428,11 @@ def main() -> int:
     for name in names:
         records[name] = run_workload(name, args.steps, args.warmup, args.cpu_budget, args)
         log(f"{name}: {records[name]['value']:.1f} it/s, dominant kernel {records[name]['roofline']['kernel_ms']}")
+    if args.detail:
+        with open(args.detail, "w") as f:
+            json.dump(records, f, indent=1)
     head = records[names[0]]
+    roof, cpu = head["roofline"], head["cpu_baseline"]
     out = {
         "metric": "CR gradient iterations/sec",
         "value": head["value"],
@@ -427,21 +446,21 @@ def main() -> int:
         "vs_baseline": None,
         "dtype": head["dtype"],
         "data": "synthetic",
-        "config": head["config"],
-        "roofline": head["roofline"],
-        "kernels": head["kernels"],
-        "cpu_baseline": head["cpu_baseline"],
+        "config": {k: head["config"][k] for k in ("workload", "x_storage", "workers", "stage1_split", "stage1_arithmetic", "stage1_every_holder_ms")},
+        "roofline": {"kernel": roof["kernel"], "kernel_ms": roof["kernel_ms"]["median"],
+                     **{k: roof.get(k) for k in ("bound", "achieved", "peak", "unit", "frac", "traffic", "needed_GBps", "stream_read_GBps")}},
+        "cpu_baseline": cpu and {k: cpu[k] for k in ("value", "unit", "cores", "kind", "sample")},
         "parity_rel_l2_vs_oracle": head["parity_rel_l2_vs_oracle"],
     }
     if len(names) > 1:
-        out["configs"] = {k: v for k, v in records.items()}
-        # Section III-C's comparison of computation loads on configuration 2's data (20 workers, one straggler in four tolerated)
+        out["configs"] = {k: {"value": v["value"], "kernel_ms": v["roofline"]["kernel_ms"]["median"], "frac": v["roofline"]["frac"],
+                              "cpu": v["cpu_baseline"] and v["cpu_baseline"]["value"], "parity": v["parity_rel_l2_vs_oracle"]} for k, v in records.items()}
+        # Section III-C's comparison of computation loads on configuration 2's data (20 workers, one straggler in four tolerated):
+        # uncoded master-worker (r = 1/N), CodedReduce on the (4,2) tree (r_CR), gradient coding ((S+1)/N)
         out["computation_load_comparison"] = {
-            k: {"scheme": label, "load_r": records[k]["config"]["computation_load"], "iterations_per_s": records[k]["value"],
-                "stage1_ms": records[k]["roofline"]["kernel_ms"]["avg"], "stage1_every_holder_ms": records[k]["config"]["stage1_every_holder_ms"], "algorithmic_bytes_per_launch": records[k]["roofline"]["algorithmic_bytes_per_launch"],
-                "traffic_frac_of_peak": records[k]["roofline"].get("traffic_frac_of_peak")}
-            for k, label in (("umw20", "uncoded master-worker, r = 1/N"), ("cfg2", "CodedReduce (4,2) tree, r = r_CR"), ("gc20", "gradient coding, r = (S+1)/N"))
-            if k in records}
+            k: {"load_r": records[k]["config"]["computation_load"], "stage1_ms": records[k]["roofline"]["kernel_ms"]["median"],
+                "every_holder_ms": records[k]["config"]["stage1_every_holder_ms"]} for k in ("umw20", "cfg2", "gc20") if k in records}
+    out = rounded(out)
     print(json.dumps(out), flush=True)
     return 0
 
