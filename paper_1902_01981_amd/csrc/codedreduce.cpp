@@ -97,7 +97,9 @@ struct cr_plan_s {
     int32_t *d_dst = nullptr;
     int num_sums = 0;
     uint32_t *d_placement = nullptr;               // kPlacementSlots words: where the workgroups of a probe launch ran
-    char *d_program = nullptr;                     // kProgramSlots encode programs (each with its root decode terms)
+    char *d_program = nullptr;                     // kProgramSlots encode programs
+    int32_t *d_node_begin = nullptr;               // slabs of every node, their coefficients: what the tree kernels read
+    double *d_slab_coef = nullptr;
     size_t program_bytes = 0;                      // size of one
     float *d_G = nullptr, *d_M = nullptr, *d_residuals = nullptr;   // d_G: the output table, slabs then partial rows; residuals: wide-row path only
     const float *G_src = nullptr;                  // slabs the encode reads: d_G or the caller's buffer
@@ -105,14 +107,13 @@ struct cr_plan_s {
     hipEvent_t staging_done[kStagingHalves] = {};
     bool staging_used[kStagingHalves] = {};
     int staging_next = 0;
-    int dec_slot = 0;                              // program slot whose decode terms cr_decode_root uses
+    cr::DecTerms dec = {};                         // what cr_decode_root does: of the last mask encoded
     // layout of the program block (offsets in bytes, fixed per plan)
     // layout of the workspace (offsets in bytes)
     size_t at_pieces = 0, at_team_piece_begin = 0, at_parts = 0, at_runs = 0, at_sums = 0, at_dst = 0, at_placement = 0, at_program = 0,
-           at_G = 0, at_residuals = 0, at_M = 0;
-    size_t off_slab = 0, off_level = 0, off_row = 0, off_coef = 0, off_acoef = 0, off_sub = 0, off_dec = 0;
+           at_node_begin = 0, at_slab_coef = 0, at_G = 0, at_residuals = 0, at_M = 0;
+    size_t off_slab = 0, off_level = 0, off_row = 0, off_coef = 0, off_acoef = 0, off_sub = 0;
     size_t max_terms = 0;
-    int num_dec_terms = 0;
 
     bool have_grads = false, have_messages = false;
     std::vector<char> static_program;              // host copy of the encode program of cr_aggregate_static (ordinary memory)
@@ -355,7 +356,6 @@ void compute_layout(cr_plan_t *p, size_t *total)
     p->off_coef = off;  off = align_up(off + p->max_terms * sizeof(double), 256);
     p->off_acoef = off; off = align_up(off + p->max_terms * sizeof(double), 256);
     p->off_sub = off;   off = align_up(off + 2 * static_cast<size_t>(p->n) * sizeof(int32_t), 256);   // begin and end of every sub-program
-    p->off_dec = off;   off = align_up(off + p->n * sizeof(cr::DecTerm), 256);
     p->program_bytes = off;
 
     size_t w = 0;
@@ -368,6 +368,8 @@ void compute_layout(cr_plan_t *p, size_t *total)
     p->at_dst = take(p->model == CR_AGGREGATE_ONLY ? 0 : dst * sizeof(int32_t));
     p->at_placement = take(kPlacementSlots * sizeof(uint32_t));
     p->at_program = take(kProgramSlots * p->program_bytes);
+    p->at_node_begin = take((N + 1) * sizeof(int32_t));
+    p->at_slab_coef = take(S * sizeof(double));
     const size_t row = static_cast<size_t>(p->d) * sizeof(float);
     if (p->model != CR_AGGREGATE_ONLY) {
         p->at_G = take((S + (p->rows_once ? p->work.partials : P)) * row);
@@ -666,6 +668,8 @@ try {
     p->d_dst = reinterpret_cast<int32_t *>(p->ws + p->at_dst);
     p->d_placement = reinterpret_cast<uint32_t *>(p->ws + p->at_placement);
     p->d_program = p->ws + p->at_program;
+    p->d_node_begin = reinterpret_cast<int32_t *>(p->ws + p->at_node_begin);
+    p->d_slab_coef = reinterpret_cast<double *>(p->ws + p->at_slab_coef);
     const bool stage1 = p->model != CR_AGGREGATE_ONLY;
     p->d_G = stage1 ? reinterpret_cast<float *>(p->ws + p->at_G) : nullptr;
     p->d_residuals = stage1 ? reinterpret_cast<float *>(p->ws + p->at_residuals) : nullptr;
@@ -712,6 +716,10 @@ try {
     p->num_sums = static_cast<int>(sums.size());
     if (!sums.empty()) CR_HIP(hipMemcpy(p->d_sums, sums.data(), sums.size() * sizeof(cr::DevSum), hipMemcpyHostToDevice));
     if (!dst.empty()) CR_HIP(hipMemcpy(p->d_dst, dst.data(), dst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    std::vector<double> coef(S);
+    for (int32_t q = 0; q < S; ++q) coef[q] = p->slabs[q].coef;
+    CR_HIP(hipMemcpy(p->d_node_begin, p->node_slab_begin.data(), p->node_slab_begin.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    CR_HIP(hipMemcpy(p->d_slab_coef, coef.data(), coef.size() * sizeof(double), hipMemcpyHostToDevice));
     p->l2_sharing = -1;
     if (P > 0 && (p->split_kind_used == CR_SPLIT_ROW_CELLS || p->split_kind_used == CR_SPLIT_SHARED_CELLS)) {
         int rc = check_l2_sharing(p);
@@ -781,11 +789,21 @@ int cr_load_partial_grads(cr_plan_t *p, const float *G)
 
 namespace {
 
-struct ProgramCounts { int64_t active_slabs = 0, active_msgs = 0; int terms = 0, dec_terms = 0; };
+struct ProgramCounts { int64_t active_slabs = 0, active_msgs = 0; int terms = 0; cr::DecTerms dec; };
+
+void decode_terms(int n, const uint8_t *mask, const double *row, cr::DecTerms *dec)
+{
+    dec->count = dec->pad = 0;
+    for (int j = 0; j < n; ++j)
+        if (!mask[j] && row[j] != 0.0) {
+            dec->row[dec->count] = j;
+            dec->coef[dec->count++] = row[j];
+        }
+}
 
 // Turns a straggler mask into the encode program of one iteration, written into the host block h (program_bytes long, laid out
-// by compute_layout): the post-order term list of every level-1 sub-tree and the master's decode terms.  Any group beyond
-// tolerance fails the call before anything is written (CR_E_UNDECODABLE).
+// by compute_layout): the post-order term list of every level-1 sub-tree; the master's decode terms go into *counts.  Any group
+// beyond tolerance fails the call before anything is written (CR_E_UNDECODABLE).
 int build_program(cr_plan_t *p, const uint8_t *mask, char *h, ProgramCounts *counts)
 {
     const int n = p->n, L = p->L;
@@ -804,7 +822,6 @@ int build_program(cr_plan_t *p, const uint8_t *mask, char *h, ProgramCounts *cou
     double *t_acoef = reinterpret_cast<double *>(h + p->off_acoef);
     auto put = [&](size_t t, int32_t slab, double coef) { t_slab[t] = slab; t_level[t] = 0; t_row[t] = 0; t_coef[t] = coef; t_acoef[t] = 0.0; };
     int32_t *sub = reinterpret_cast<int32_t *>(h + p->off_sub);
-    cr::DecTerm *dec = reinterpret_cast<cr::DecTerm *>(h + p->off_dec);
 
     // post-order program of every level-1 sub-tree
     size_t nt = 0;
@@ -847,11 +864,31 @@ int build_program(cr_plan_t *p, const uint8_t *mask, char *h, ProgramCounts *cou
         }
         sub[n + i] = sub[i] + static_cast<int32_t>(real_terms);
     }
-    int ndec = 0;
-    for (int j = 0; j < n; ++j)
-        if (!mask[j] && rows[0][j] != 0.0) dec[ndec++] = {j, 0, rows[0][j]};
+    decode_terms(n, mask, rows[0], &counts->dec);
     counts->terms = static_cast<int>(nt);                // padding included
-    counts->dec_terms = ndec;
+    return CR_OK;
+}
+
+// The same for the tree kernels: a coefficient per node.
+int build_coefs(cr_plan_t *p, const uint8_t *mask, cr::NodeCoefs *coefs, ProgramCounts *counts)
+{
+    const int n = p->n;
+    double straggler;
+    std::memcpy(&straggler, &cr::kStraggler, sizeof straggler);
+    for (int32_t g = 0; g < p->tree.N / n; ++g) {
+        const double *row = nullptr;
+        int rc = group_decode_row(p, mask + static_cast<size_t>(g) * n, &row);
+        if (rc == CR_E_UNDECODABLE) return fail(rc, "sibling group " + std::to_string(g) + " has more than s stragglers");
+        if (rc != CR_OK) return rc;
+        if (g == 0) decode_terms(n, mask, row, &counts->dec);
+        for (int j = 0; j < n; ++j) {
+            const int32_t node = g * n + j;
+            coefs->a[node] = mask[node] ? straggler : row[j];
+            if (mask[node]) continue;
+            counts->active_slabs += p->node_slab_begin[node + 1] - p->node_slab_begin[node];
+            counts->active_msgs += 1;
+        }
+    }
     return CR_OK;
 }
 
@@ -859,8 +896,7 @@ int build_program(cr_plan_t *p, const uint8_t *mask, char *h, ProgramCounts *cou
 cr::ProgramTables program_tables(const cr_plan_t *p, char *block)
 {
     return {reinterpret_cast<int32_t *>(block + p->off_slab), reinterpret_cast<int32_t *>(block + p->off_level), reinterpret_cast<int32_t *>(block + p->off_row),
-            reinterpret_cast<double *>(block + p->off_coef), reinterpret_cast<double *>(block + p->off_acoef), reinterpret_cast<int32_t *>(block + p->off_sub),
-            reinterpret_cast<cr::DecTerm *>(block + p->off_dec)};
+            reinterpret_cast<double *>(block + p->off_coef), reinterpret_cast<double *>(block + p->off_acoef), reinterpret_cast<int32_t *>(block + p->off_sub)};
 }
 
 // the program's arrays as the encode kernel takes them, for a program block at device address d_program
@@ -921,8 +957,17 @@ int encode_slot(cr_plan_t *p, int slot, const ProgramCounts &counts)
     LaunchTimer t(p, CR_K_ENCODE, (counts.active_slabs + counts.active_msgs) * p->d * 4);
     CR_HIP(cr::launch_encode(p->G_src, p->d_M, program_view(p, p->d_program + static_cast<size_t>(slot) * p->program_bytes), p->n, p->L, p->d, p->stream));
     t.done();
-    p->num_dec_terms = counts.dec_terms;
-    p->dec_slot = slot;
+    p->dec = counts.dec;
+    p->have_messages = true;
+    return CR_OK;
+}
+
+int encode_tree(cr_plan_t *p, const cr::NodeCoefs &coefs, const ProgramCounts &counts)
+{
+    LaunchTimer t(p, CR_K_ENCODE, (counts.active_slabs + counts.active_msgs) * p->d * 4);
+    CR_HIP(cr::launch_tree_encode(p->G_src, p->d_M, p->d_node_begin, p->d_slab_coef, p->n, p->L, coefs, p->d, p->stream));
+    t.done();
+    p->dec = counts.dec;
     p->have_messages = true;
     return CR_OK;
 }
@@ -933,9 +978,8 @@ int decode_root(cr_plan_t *p, float *g, float *w, float lr)
     if (!p || !g) return fail(CR_E_INVAL, "NULL argument");
     if (!p->bound) return fail(CR_E_INVAL, "no workspace bound");
     if (!p->have_messages) return fail(CR_E_STATE, "no messages yet: call cr_encode_tree first");
-    LaunchTimer t(p, CR_K_DECODE, static_cast<int64_t>(p->num_dec_terms + 1 + (w ? 2 : 0)) * p->d * 4);
-    const char *prog = p->d_program + static_cast<size_t>(p->dec_slot) * p->program_bytes;
-    CR_HIP(cr::launch_decode(p->d_M, g, reinterpret_cast<const cr::DecTerm *>(prog + p->off_dec), p->num_dec_terms, p->d, w, lr, p->stream));
+    LaunchTimer t(p, CR_K_DECODE, static_cast<int64_t>(p->dec.count + 1 + (w ? 2 : 0)) * p->d * 4);
+    CR_HIP(cr::launch_decode(p->d_M, g, p->dec, p->d, w, lr, p->stream));
     t.done();
     return CR_OK;
 }
@@ -947,9 +991,15 @@ int cr_encode_tree(cr_plan_t *p, const uint8_t *mask)
     if (!p || !mask) return fail(CR_E_INVAL, "NULL argument");
     if (!p->bound) return fail(CR_E_INVAL, "no workspace bound");
     if (!p->have_grads) return fail(CR_E_STATE, "no partial gradients yet");
+    ProgramCounts counts;
+    if (cr::tree_side_by_side(p->n, p->L, p->tree.N, p->d)) {
+        cr::NodeCoefs coefs;
+        int rc = build_coefs(p, mask, &coefs, &counts);
+        if (rc != CR_OK) return rc;
+        return encode_tree(p, coefs, counts);
+    }
     int rc = check_masks(p, mask, 1);
     if (rc != CR_OK) return rc;
-    ProgramCounts counts;
     rc = upload_programs(p, mask, 1, &counts);
     if (rc != CR_OK) return rc;
     return encode_slot(p, 0, counts);
@@ -1047,9 +1097,9 @@ int cr_aggregate_static(cr_plan_t *p, const float *G, const uint8_t *mask, float
     CR_HIP(cr::static_scratch(&base));                  // this device's copy of the array; never the array's name
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     float *M = reinterpret_cast<float *>(base + cr::kStaticProgramBytes);
-    CR_HIP(cr::launch_program(program_tables(p, base), program_tables(p, p->static_program.data()), counts.terms, 2 * p->n, counts.dec_terms, stream));
+    CR_HIP(cr::launch_program(program_tables(p, base), program_tables(p, p->static_program.data()), counts.terms, 2 * p->n, stream));
     CR_HIP(cr::launch_encode(G, M, program_view(p, base), p->n, p->L, p->d, stream));
-    CR_HIP(cr::launch_decode(M, g, reinterpret_cast<const cr::DecTerm *>(base + p->off_dec), counts.dec_terms, p->d, nullptr, 0.f, stream));
+    CR_HIP(cr::launch_decode(M, g, counts.dec, p->d, nullptr, 0.f, stream));
     return CR_OK;
 }
 

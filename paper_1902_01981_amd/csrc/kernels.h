@@ -42,11 +42,26 @@ struct EncProgram {
     const int32_t *sub_end;      // one past its last real term; no-op terms pad it up to the next multiple of kEncodeUnroll
 };
 
-struct DecTerm {             // g += coef * M[row]
-    int32_t row;
-    int32_t pad;
-    double coef;
+struct DecTerms {            // the master's decode: g = sum of coef[j] * M[row[j]]; a kernel argument
+    int32_t count, pad;
+    int32_t row[64];         // a group has at most 64 members
+    double coef[64];
 };
+
+// The encode of short vectors takes what the mask decides as a kernel argument: a[node] = the coefficient with which the node's parent
+// folds its message in (level 1: the master), or kStraggler: the node sends none.
+constexpr int64_t kStraggler = -1;                       // bits of a NaN that no coefficient is
+struct NodeCoefs {
+    static constexpr int kNodes = 448;                   // kernel arguments take at most 4 KB
+    double a[kNodes];
+};
+// The nodes that a workgroup of the tree kernels has, leaves first, then level by level up: the nodes of level l have the places from
+// first[l - 1] on, and place t is node t + shift[l - 1] + sub * width[l - 1] in level-1 sub-tree `sub`.
+struct TreeLevels {
+    int32_t n, L, total, leaves;
+    int32_t first[8], shift[8], width[8];
+};
+TreeLevels sub_tree_levels(int n, int L);
 
 constexpr int kEncodeUnroll = 8;   // encode sub-programs are padded to a multiple of this many terms
 constexpr int kMaxLevels = 8;
@@ -99,8 +114,15 @@ hipError_t launch_wide_once(int x_dtype, const void *X, const float *y, const fl
                             hipStream_t stream);
 hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, const int32_t *dst, int64_t d, hipStream_t stream);
 hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int num_sub, int L, int64_t d, hipStream_t stream);
+// The same for trees of at most NodeCoefs::kNodes nodes and vectors of at most kTreeColumns columns (tree_side_by_side): a workgroup
+// per level-1 sub-tree and 16 chunks of columns, 64 from kTreeNarrowColumns on.  node_begin (one entry per node and one more) and
+// slab_coef: the slabs of every node and their coefficients.
+constexpr int64_t kTreeColumns = 81920, kTreeNarrowColumns = 32768;
+bool tree_side_by_side(int n, int L, int nodes, int64_t d);
+hipError_t launch_tree_encode(const float *G, float *M, const int32_t *node_begin, const double *slab_coef, int n, int L, const NodeCoefs &coefs, int64_t d,
+                              hipStream_t stream);
 // w != nullptr: also steps w <- w - lr g (g as stored, rounded to fp32) in the same launch
-hipError_t launch_decode(const float *M, float *g, const DecTerm *terms, int nterms, int64_t d, float *w, float lr, hipStream_t stream);
+hipError_t launch_decode(const float *M, float *g, const DecTerms &terms, int64_t d, float *w, float lr, hipStream_t stream);
 hipError_t launch_update(float *w, const float *g, float lr, int64_t d, hipStream_t stream);
 // plain streaming read of n16 16-byte words; every workgroup writes its sum to sink[workgroup] (kStreamGroups workgroups)
 constexpr int kStreamGroups = 256 * 8;
@@ -112,15 +134,14 @@ constexpr size_t kStaticProgramBytes = size_t(64) << 10;                 // head
 constexpr size_t kStaticScratchBytes = size_t(96) << 20;                 // the whole array; messages follow the program
 hipError_t static_scratch(char **ptr);
 // An encode program's tables, in device or in host memory; launch_program sends `terms` terms (at most 4096, of slabs and rows below
-// 4096), `subs` (an even number) sub-program words and `decs` decode terms of the host's through kernel arguments: launches only, no
-// staging buffer, no memcpy node; the host tables are consumed before the call returns
+// 4096) and `subs` (an even number) sub-program words of the host's through kernel arguments: launches only, no staging buffer, no
+// memcpy node; the host tables are consumed before the call returns
 struct ProgramTables {
     int32_t *slab, *level, *row;
     double *coef, *acoef;
     int32_t *sub;
-    DecTerm *dec;
 };
-hipError_t launch_program(const ProgramTables &out, const ProgramTables &host, int terms, int subs, int decs, hipStream_t stream);
+hipError_t launch_program(const ProgramTables &out, const ProgramTables &host, int terms, int subs, hipStream_t stream);
 
 // one wavefront per workgroup; out[workgroup id] = (die the workgroup ran on) << 16 | (shader engine and compute unit inside the die)
 hipError_t launch_placement_probe(uint32_t *out, int groups, hipStream_t stream);

@@ -7,7 +7,8 @@
 //   wide_residuals_kernel, wide_xt_kernel   rows too wide for a workgroup's registers, every row once, in two passes
 //   residuals_kernel, xt_residuals_kernel   the same for every holder separately
 //   sum_rows_kernel        sums of partial rows (fixed order, so results are reproducible bit for bit)
-//   encode_kernel          CR.Execute steps 2-5: every node's message, children folded into parents in registers
+//   tree_kernel            CR.Execute steps 2-5: every node's message, the nodes of a sub-tree side by side, children folded in LDS
+//   encode_kernel          the same for long vectors and large trees: one thread walks a sub-tree, children folded in registers
 //   decode_kernel          the master's decode  g = sum_j a_j m_(1,j), optionally followed by w <- w - lr g in the same launch
 //   update_kernel, update_metrics_kernel    w <- w - lr g, optionally with the convergence measures of eq. (6) and (8)
 //
@@ -1004,24 +1005,164 @@ encode_kernel(const float *__restrict__ G, float *__restrict__ M, EncProgram pro
     }
 }
 
+// ---- encode, the nodes of a tree side by side ---------------------------------------------------------------------------
+// The encode of short vectors takes as long as its chain of dependent fetches, not its bytes: a thread that walks a whole sub-tree
+// fetches eight terms at a time, one group after the other.  Here B lanes own B chunks of columns and the workgroup's T / B teams
+// share out the nodes: all form their own sums at once (one fetch of a node's entries, one of its slabs), the messages meet in LDS
+// and the levels above the leaves fold their children from there, one barrier per level.  Sums are fp64, formed in the order in which
+// encode_kernel forms them, and messages are rounded where it rounds them: the same bits.
+// The tree's tables stay on the device for the plan's life; what the mask decides, a coefficient per node, travels as kernel
+// arguments, so there is no copy to wait for.
+// Kernel time in us, a thread per sub-tree / nodes side by side: (2,12) tree, s = 2, 10 columns 7.5 / 4.2; s = 3, 5 001 columns
+// 12.5 / 5.9; (3,6) tree, s = 2, 1 024 columns 25.9 / 6.7; (3,4) tree, 6 500 columns 8.5 / 5.7.
+__device__ __forceinline__ bool sends(double a) { return __double_as_longlong(a) != kStraggler; }
+
+// The places of a workgroup's nodes, leaves first, then level by level up; sub: which level-1 sub-tree (0 where it has them all).
+struct TreePlaces {
+    const TreeLevels &tree;
+    int sub;
+    __device__ __forceinline__ int node(int t) const
+    {
+        int id = t + tree.shift[tree.L - 1] + sub * tree.width[tree.L - 1];
+        for (int l = tree.L - 1; l >= 1; --l)
+            if (t >= tree.first[l - 1]) id = t + tree.shift[l - 1] + sub * tree.width[l - 1];
+        return id;
+    }
+};
+
+// LDS of a workgroup that has `total` nodes, `total - leaves` of them above the leaves
+template <int VEC, int B> struct TreeLds {
+    static __host__ __device__ size_t bytes(int total, int leaves) { return static_cast<size_t>(total) * (B * VEC * 4 + 8) + static_cast<size_t>(total - leaves) * B * VEC * 8; }
+    double *coef;                                        // [total]: with which the node's message is folded in
+    double *own;                                         // [total - leaves][VEC][B]: own sums of the nodes above the leaves
+    float *msg;                                          // [total][VEC][B]: messages
+    __device__ __forceinline__ TreeLds(char *at, int total, int leaves)
+        : coef(reinterpret_cast<double *>(at)), own(coef + total), msg(reinterpret_cast<float *>(own + (total - leaves) * VEC * B)) {}
+    __device__ __forceinline__ void put_message(int t, int tl, const float (&m)[VEC]) const
+    {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) msg[(t * VEC + v) * B + tl] = m[v];
+    }
+    // acc += coef * message, the nodes [t0, t0 + n) in turn; SKIP: those with coefficient zero are left out
+    template <bool SKIP> __device__ __forceinline__ void fold(int t0, int n, int tl, double (&acc)[VEC]) const
+    {
+        for (int c = 0; c < n; ++c) {
+            const double a = coef[t0 + c];
+            if (!sends(a) || (SKIP && a == 0.0)) continue;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[v] = fma(a, static_cast<double>(msg[((t0 + c) * VEC + v) * B + tl]), acc[v]);
+        }
+    }
+};
+
+// own sum of a node: its slabs in turn, U of them in flight
+template <int VEC, typename COEF> __device__ __forceinline__ void sum_slabs(const float *G, int64_t d, int64_t col, int begin, int end, COEF coef, double (&acc)[VEC])
+{
+    constexpr int U = 8;
+    for (int s0 = begin; s0 < end; s0 += U) {
+        float x[U][VEC];
+        double c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (s0 + u < end) {
+                load_row<VEC>(G + static_cast<int64_t>(s0 + u) * d + col, x[u]);
+                c[u] = coef(s0 + u);
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (s0 + u < end) {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[v] = fma(c[u], static_cast<double>(x[u][v]), acc[v]);
+            }
+    }
+}
+
+// The messages of a workgroup's nodes, stored and left in LDS.  coef_of(node): the node's coefficient; own_sum(node, acc): its own sum
+// for the lane's columns.
+template <int VEC, int B, int T, typename COEF, typename OWN>
+__device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, const TreeLds<VEC, B> &lds, COEF coef_of, OWN own_sum, float *M, int64_t d, int64_t col, bool live)
+{
+    constexpr int TEAMS = T / B;
+    const int team = threadIdx.x / B, tl = threadIdx.x % B;
+    const TreePlaces places{tree, sub};
+    for (int t = team; t < tree.total; t += TEAMS) {
+        const int node = places.node(t);
+        const double a = coef_of(node);
+        if (tl == 0) lds.coef[t] = a;
+        if (!sends(a)) continue;
+        double acc[VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
+        own_sum(node, acc);
+        if (t < tree.leaves) {
+            float out[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) out[v] = static_cast<float>(acc[v]);
+            if (live) store_row<VEC>(M + static_cast<int64_t>(node) * d + col, out);
+            lds.put_message(t, tl, out);
+        } else {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) lds.own[((t - tree.leaves) * VEC + v) * B + tl] = acc[v];
+        }
+    }
+    for (int l = tree.L - 1; l >= 1; --l) {
+        __syncthreads();
+        const int first = tree.first[l - 1], end = l > 1 ? tree.first[l - 2] : tree.total;
+        for (int t = first + team; t < end; t += TEAMS) {
+            if (!sends(lds.coef[t])) continue;
+            double pend[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) pend[v] = 0.0;
+            lds.template fold<false>(tree.first[l] + (t - first) * tree.n, tree.n, tl, pend);
+            float out[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) out[v] = static_cast<float>(lds.own[((t - tree.leaves) * VEC + v) * B + tl] + pend[v]);
+            if (live) store_row<VEC>(M + static_cast<int64_t>(places.node(t)) * d + col, out);
+            lds.put_message(t, tl, out);
+        }
+    }
+}
+
+// one level-1 sub-tree (grid.y) per workgroup
+template <int VEC, int B, int T>
+__global__ void __launch_bounds__(T)
+tree_kernel(const float *__restrict__ G, float *__restrict__ M, const int32_t *__restrict__ node_begin, const double *__restrict__ slab_coef,
+            TreeLevels tree, NodeCoefs coefs, int64_t d, int nq)
+{
+    extern __shared__ __align__(16) char tree_lds[];
+    const TreeLds<VEC, B> lds(tree_lds, tree.total, tree.leaves);
+    const int q = blockIdx.x * B + threadIdx.x % B;
+    const int64_t col = chunk_offset<VEC>(q, nq, static_cast<int>(d));       // lanes past the row repeat its last chunk and do not store
+    tree_messages<VEC, B, T>(
+        tree, blockIdx.y, lds, [&](int node) { return coefs.a[node]; },
+        [&](int node, double (&acc)[VEC]) { sum_slabs<VEC>(G, d, col, node_begin[node], node_begin[node + 1], [&](int s) { return slab_coef[s]; }, acc); },
+        M, d, col, q < nq);
+}
+
 // ---- decode ---------------------------------------------------------------------------------------------------------
+// The terms come as kernel arguments; U rows are in flight.
 template <int VEC>
 __global__ void __launch_bounds__(256)
-decode_kernel(const float *__restrict__ M, float *__restrict__ g, const DecTerm *__restrict__ terms, int nterms, int64_t d, int nq,
-              float *__restrict__ w, float lr)
+decode_kernel(const float *__restrict__ M, float *__restrict__ g, DecTerms terms, int64_t d, int nq, float *__restrict__ w, float lr)
 {
+    constexpr int U = 8;
     const int q = blockIdx.x * 256 + threadIdx.x;
     if (q >= nq) return;
     const int64_t col = chunk_offset<VEC>(q, nq, static_cast<int>(d));
     double acc[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
-    for (int j = 0; j < nterms; ++j) {
-        const DecTerm tm = terms[j];
-        float xv[VEC];
-        load_row<VEC>(M + static_cast<int64_t>(tm.row) * d + col, xv);
+    for (int j0 = 0; j0 < terms.count; j0 += U) {
+        float xv[U][VEC];
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[v] = fma(tm.coef, static_cast<double>(xv[v]), acc[v]);
+        for (int u = 0; u < U; ++u)
+            if (j0 + u < terms.count) load_row<VEC>(M + static_cast<int64_t>(terms.row[j0 + u]) * d + col, xv[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (j0 + u < terms.count) {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[v] = fma(terms.coef[j0 + u], static_cast<double>(xv[u][v]), acc[v]);
+            }
     }
     float out[VEC];
 #pragma unroll
@@ -1322,14 +1463,61 @@ hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int n
     return launch_encode_shape<1, 1, 256, 8, double>(G, M, prog, num_sub, L, d, stream);
 }
 
-hipError_t launch_decode(const float *M, float *g, const DecTerm *terms, int nterms, int64_t d, float *w, float lr, hipStream_t stream)
+namespace {
+template <int VEC, int B, int T>
+hipError_t launch_tree(const float *G, float *M, const int32_t *node_begin, const double *slab_coef, const TreeLevels &tree, const NodeCoefs &coefs, int64_t d,
+                       hipStream_t stream)
+{
+    const int nq = static_cast<int>((d + VEC - 1) / VEC);
+    tree_kernel<VEC, B, T><<<dim3((nq + B - 1) / B, tree.n), T, TreeLds<VEC, B>::bytes(tree.total, tree.leaves), stream>>>(G, M, node_begin, slab_coef, tree, coefs, d, nq);
+    return hipGetLastError();
+}
+}  // namespace
+
+TreeLevels sub_tree_levels(int n, int L)
+{
+    TreeLevels t = {};
+    t.n = n;
+    t.L = L;
+    int offset = 0, width = 1;
+    for (int l = 1; l <= L; ++l) {
+        t.width[l - 1] = width;
+        t.shift[l - 1] = offset;
+        width *= n;
+        offset += width;                                 // a level has n times as many nodes as one sub-tree has of it
+    }
+    for (int l = L; l >= 1; --l) {
+        t.first[l - 1] = t.total;
+        t.shift[l - 1] -= t.total;
+        t.total += t.width[l - 1];
+    }
+    t.leaves = t.width[L - 1];
+    return t;
+}
+
+bool tree_side_by_side(int n, int L, int nodes, int64_t d)
+{
+    return nodes <= NodeCoefs::kNodes && d <= kTreeColumns && TreeLds<4, 16>::bytes(sub_tree_levels(n, L).total, sub_tree_levels(n, L).leaves) <= (size_t(64) << 10);
+}
+
+hipError_t launch_tree_encode(const float *G, float *M, const int32_t *node_begin, const double *slab_coef, int n, int L, const NodeCoefs &coefs, int64_t d,
+                              hipStream_t stream)
+{
+    const TreeLevels tree = sub_tree_levels(n, L);
+    if (d < 4) return launch_tree<1, 16, 256>(G, M, node_begin, slab_coef, tree, coefs, d, stream);
+    if (d > kTreeNarrowColumns && TreeLds<4, 64>::bytes(tree.total, tree.leaves) <= (size_t(64) << 10))
+        return launch_tree<4, 64, 256>(G, M, node_begin, slab_coef, tree, coefs, d, stream);
+    return launch_tree<4, 16, 256>(G, M, node_begin, slab_coef, tree, coefs, d, stream);
+}
+
+hipError_t launch_decode(const float *M, float *g, const DecTerms &terms, int64_t d, float *w, float lr, hipStream_t stream)
 {
     if (d >= 4) {
         const int nq = static_cast<int>((d + 3) / 4);
-        decode_kernel<4><<<(nq + 255) / 256, 256, 0, stream>>>(M, g, terms, nterms, d, nq, w, lr);
+        decode_kernel<4><<<(nq + 255) / 256, 256, 0, stream>>>(M, g, terms, d, nq, w, lr);
     } else {
         const int nq = static_cast<int>(d);
-        decode_kernel<1><<<(nq + 255) / 256, 256, 0, stream>>>(M, g, terms, nterms, d, nq, w, lr);
+        decode_kernel<1><<<(nq + 255) / 256, 256, 0, stream>>>(M, g, terms, d, nq, w, lr);
     }
     return hipGetLastError();
 }
@@ -1405,7 +1593,7 @@ hipError_t static_scratch(char **ptr)
 // 340 us with the program's bytes as they are (six launches per vector), 155 us in this form (one).
 struct ProgramBlock {
     static constexpr int kWords = 480;                   // 8-byte words: the coefficients, then the terms
-    int32_t first, terms, coefs, subs, decs, pad;        // subs / decs: words of the sub-program and decode tables, behind the terms
+    int32_t first, terms, coefs, subs;                   // subs: words of the sub-program table, behind the terms
     uint64_t word[kWords];
 };
 static_assert(sizeof(ProgramBlock) <= 4000, "kernel arguments");
@@ -1422,19 +1610,18 @@ __global__ void __launch_bounds__(256) program_kernel(ProgramTables out, Program
     }
     const int at = block.coefs + block.terms;
     for (int i = threadIdx.x; i < block.subs; i += 256) reinterpret_cast<uint64_t *>(out.sub)[i] = block.word[at + i];
-    for (int i = threadIdx.x; i < block.decs; i += 256) reinterpret_cast<uint64_t *>(out.dec)[i] = block.word[at + block.subs + i];
 }
 
-hipError_t launch_program(const ProgramTables &out, const ProgramTables &host, int terms, int subs, int decs, hipStream_t stream)
+hipError_t launch_program(const ProgramTables &out, const ProgramTables &host, int terms, int subs, hipStream_t stream)
 {
     constexpr int kSlots = 2048;                         // of the hash table; a block has fewer than 480 distinct coefficients
-    constexpr int kTailWords = 64 + 2 * 64;              // groups have at most 64 members: their tables leave room for terms
+    constexpr int kTailWords = 64;                       // groups have at most 64 members: their table leaves room for terms
     uint16_t slot[kSlots];
     ProgramBlock block;
-    const int subs8 = subs / 2, decs8 = decs * 2;
-    static_assert(sizeof(DecTerm) == 16 && kTailWords < ProgramBlock::kWords, "tables in 8-byte words");
-    if (terms > 4096 || subs % 2 != 0 || subs8 + decs8 > kTailWords) return hipErrorInvalidValue;
-    bool tail = false;                                   // the sub-program and decode tables are on their way
+    const int subs8 = subs / 2;
+    static_assert(kTailWords < ProgramBlock::kWords, "the table fits a block");
+    if (terms > 4096 || subs % 2 != 0 || subs8 > kTailWords) return hipErrorInvalidValue;
+    bool tail = false;                                   // the sub-program table is on its way
     for (int first = 0; first < terms || !tail;) {
         std::memset(slot, 0xff, sizeof slot);
         int coefs = 0, count = 0;
@@ -1461,14 +1648,12 @@ hipError_t launch_program(const ProgramTables &out, const ProgramTables &host, i
         block.first = first;
         block.terms = count;
         block.coefs = coefs;
-        block.subs = block.decs = block.pad = 0;
+        block.subs = 0;
         first += count;
         const int used = coefs + count;
-        if (first == terms && used + subs8 + decs8 <= ProgramBlock::kWords) {
+        if (first == terms && used + subs8 <= ProgramBlock::kWords) {
             block.subs = subs8;
-            block.decs = decs8;
             std::memcpy(block.word + used, host.sub, static_cast<size_t>(subs8) * 8);
-            std::memcpy(block.word + used + subs8, host.dec, static_cast<size_t>(decs8) * 8);
             tail = true;
         }
         program_kernel<<<1, 256, 0, stream>>>(out, block);
