@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 # groups of 64; one level; eight levels
 CASES = [(2, 3, 1, d) for d in (1, 3, 4, 5, 63, 64, 65, 67, 1_023, 1_028)]
 CASES += [(1, 2, 0, 100), (1, 64, 1, 130), (1, 10, 4, 1_027), (2, 20, 1, 77), (2, 21, 1, 77), (3, 7, 2, 70), (3, 6, 2, 1_024), (6, 2, 1, 66), (7, 2, 1, 66), (8, 2, 1, 66)]
-CASES += [(2, 12, 3, 5_001), (3, 3, 1, 32_768), (3, 3, 1, 32_769), (2, 4, 1, 81_920), (2, 4, 1, 81_921), (2, 8, 2, 81_919)]
+CASES += [(2, 12, 3, 5_001), (3, 3, 1, 32_768), (3, 3, 1, 32_769), (2, 4, 1, 81_920), (2, 4, 1, 81_921), (2, 8, 2, 81_919), (1, 3, 1, 1_048_575), (1, 3, 1, 1_048_579)]
 
 
 def _mask(rng, groups, n, s, fewer):
@@ -99,4 +99,29 @@ def test_a_bad_mask_enqueues_nothing():
     cr.cr_decode_root(plan, g)                           # still of the good mask
     cr.cr_synchronize(plan)
     assert torch.equal(ws.messages(), before) and bool((g != 0).any())
+    cr.cr_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("d", [1_048_573, 1_049_603])
+def test_gradient_step_in_the_decode_of_long_vectors(d):
+    """The gradient step that rides in the decode launch, on both sides of the decode's rule and with columns that two chunks share,
+    against the update call."""
+    import torch
+
+    m = 6
+    plan = cr.cr_plan_ex(1, 2, 0, m, d)
+    ws = cr.Workspace(plan)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    X, y, w = (torch.randn(shape, generator=gen, device="cuda") for shape in ((m, d), (m,), (d,)))
+    g, w_ref = torch.empty(d, device="cuda"), w.clone()
+    mask = np.zeros((1, 2), dtype=np.uint8)
+    cr.cr_partial_grads(plan, X, y, w_ref)
+    cr.cr_encode_tree(plan, mask[0])
+    cr.cr_decode_root(plan, g)
+    cr.cr_gd_update(plan, w_ref, g, 1e-7)
+    g_run = torch.empty_like(g)
+    cr.cr_gd_run(plan, X, y, w, g_run, mask, 1e-7)
+    torch.cuda.synchronize()
+    assert torch.equal(g, g_run) and torch.equal(w, w_ref)
+    del ws
     cr.cr_plan_destroy(plan)
