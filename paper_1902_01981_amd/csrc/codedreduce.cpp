@@ -62,6 +62,7 @@ struct cr_plan_s {
     std::vector<cr::WeightedSet> own;
     std::vector<cr::Slab> slabs;
     std::vector<int32_t> node_slab_begin;          // N+1
+    std::vector<double> slab_coef;
     int64_t row_visits = 0, min_rows = 0, max_rows = 0;
     int64_t max_holders = 1;                       // most workers that hold a row: (s+1)^L, capped at 64
     mutable std::unordered_map<uint64_t, std::vector<double>> row_cache;   // padded straggler bitmask -> decode row
@@ -100,6 +101,8 @@ struct cr_plan_s {
     char *d_program = nullptr;                     // kProgramSlots encode programs
     int32_t *d_node_begin = nullptr;               // slabs of every node, their coefficients: what the tree kernels read
     double *d_slab_coef = nullptr;
+    double *d_measures = nullptr;                  // kProgramSlots steps' sums for the convergence measures
+    size_t measures_stride = 0;                    // doubles per step
     size_t program_bytes = 0;                      // size of one
     float *d_G = nullptr, *d_M = nullptr, *d_residuals = nullptr;   // d_G: the output table, slabs then partial rows; residuals: wide-row path only
     const float *G_src = nullptr;                  // slabs the encode reads: d_G or the caller's buffer
@@ -111,7 +114,7 @@ struct cr_plan_s {
     // layout of the program block (offsets in bytes, fixed per plan)
     // layout of the workspace (offsets in bytes)
     size_t at_pieces = 0, at_team_piece_begin = 0, at_parts = 0, at_runs = 0, at_sums = 0, at_dst = 0, at_placement = 0, at_program = 0,
-           at_node_begin = 0, at_slab_coef = 0, at_G = 0, at_residuals = 0, at_M = 0;
+           at_node_begin = 0, at_slab_coef = 0, at_measures = 0, at_G = 0, at_residuals = 0, at_M = 0;
     size_t off_slab = 0, off_level = 0, off_row = 0, off_coef = 0, off_acoef = 0, off_sub = 0;
     size_t max_terms = 0;
 
@@ -370,6 +373,8 @@ void compute_layout(cr_plan_t *p, size_t *total)
     p->at_program = take(kProgramSlots * p->program_bytes);
     p->at_node_begin = take((N + 1) * sizeof(int32_t));
     p->at_slab_coef = take(S * sizeof(double));
+    p->measures_stride = p->model == CR_AGGREGATE_ONLY ? 0 : 4 * static_cast<size_t>(std::max(cr::decode_groups(p->d), cr::tree_and_decode_together(p->n, p->L, p->tree.N, p->d) ? cr::tree_decode_groups(p->n, p->L, p->d) : 0));
+    p->at_measures = take(kProgramSlots * p->measures_stride * sizeof(double));
     const size_t row = static_cast<size_t>(p->d) * sizeof(float);
     if (p->model != CR_AGGREGATE_ONLY) {
         p->at_G = take((S + (p->rows_once ? p->work.partials : P)) * row);
@@ -488,6 +493,7 @@ int cr_plan_ex(int L, int n, int s, int64_t m, int64_t d, int model, int x_dtype
         p->node_slab_begin.assign(p->tree.N + 1, 0);
         for (const cr::Slab &sl : p->slabs) p->node_slab_begin[sl.node + 1] += 1;
         for (int32_t i = 0; i < p->tree.N; ++i) p->node_slab_begin[i + 1] += p->node_slab_begin[i];
+        for (const cr::Slab &sl : p->slabs) p->slab_coef.push_back(sl.coef);
         p->min_rows = INT64_MAX;
         for (int32_t node = 0; node < p->tree.N; ++node) {
             int64_t rows = 0;
@@ -670,6 +676,7 @@ try {
     p->d_program = p->ws + p->at_program;
     p->d_node_begin = reinterpret_cast<int32_t *>(p->ws + p->at_node_begin);
     p->d_slab_coef = reinterpret_cast<double *>(p->ws + p->at_slab_coef);
+    p->d_measures = reinterpret_cast<double *>(p->ws + p->at_measures);
     const bool stage1 = p->model != CR_AGGREGATE_ONLY;
     p->d_G = stage1 ? reinterpret_cast<float *>(p->ws + p->at_G) : nullptr;
     p->d_residuals = stage1 ? reinterpret_cast<float *>(p->ws + p->at_residuals) : nullptr;
@@ -716,10 +723,8 @@ try {
     p->num_sums = static_cast<int>(sums.size());
     if (!sums.empty()) CR_HIP(hipMemcpy(p->d_sums, sums.data(), sums.size() * sizeof(cr::DevSum), hipMemcpyHostToDevice));
     if (!dst.empty()) CR_HIP(hipMemcpy(p->d_dst, dst.data(), dst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    std::vector<double> coef(S);
-    for (int32_t q = 0; q < S; ++q) coef[q] = p->slabs[q].coef;
     CR_HIP(hipMemcpy(p->d_node_begin, p->node_slab_begin.data(), p->node_slab_begin.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    CR_HIP(hipMemcpy(p->d_slab_coef, coef.data(), coef.size() * sizeof(double), hipMemcpyHostToDevice));
+    CR_HIP(hipMemcpy(p->d_slab_coef, p->slab_coef.data(), p->slab_coef.size() * sizeof(double), hipMemcpyHostToDevice));
     p->l2_sharing = -1;
     if (P > 0 && (p->split_kind_used == CR_SPLIT_ROW_CELLS || p->split_kind_used == CR_SPLIT_SHARED_CELLS)) {
         int rc = check_l2_sharing(p);
@@ -962,6 +967,9 @@ int encode_slot(cr_plan_t *p, int slot, const ProgramCounts &counts)
     return CR_OK;
 }
 
+// vectors that a gradient step reads and writes besides g
+int64_t step_rows(const cr::GradientStep &step) { return (step.w ? 2 : 0) + (step.measures && step.w_star ? 1 : 0); }
+
 int encode_tree(cr_plan_t *p, const cr::NodeCoefs &coefs, const ProgramCounts &counts)
 {
     LaunchTimer t(p, CR_K_ENCODE, (counts.active_slabs + counts.active_msgs) * p->d * 4);
@@ -972,15 +980,26 @@ int encode_tree(cr_plan_t *p, const cr::NodeCoefs &coefs, const ProgramCounts &c
     return CR_OK;
 }
 
-// the master's decode; with w != nullptr the gradient step w <- w - lr g rides in the same launch
-int decode_root(cr_plan_t *p, float *g, float *w, float lr)
+// the master's decode; with step.w the gradient step w <- w - lr g rides in the same launch
+int decode_root(cr_plan_t *p, float *g, const cr::GradientStep &step)
 {
     if (!p || !g) return fail(CR_E_INVAL, "NULL argument");
     if (!p->bound) return fail(CR_E_INVAL, "no workspace bound");
     if (!p->have_messages) return fail(CR_E_STATE, "no messages yet: call cr_encode_tree first");
-    LaunchTimer t(p, CR_K_DECODE, static_cast<int64_t>(p->dec.count + 1 + (w ? 2 : 0)) * p->d * 4);
-    CR_HIP(cr::launch_decode(p->d_M, g, p->dec, p->d, w, lr, p->stream));
+    LaunchTimer t(p, CR_K_DECODE, (p->dec.count + 1 + step_rows(step)) * p->d * 4);
+    CR_HIP(cr::launch_decode(p->d_M, g, p->dec, step, p->d, p->stream));
     t.done();
+    return CR_OK;
+}
+
+// encode, decode and gradient step in one launch, which counts as the encode's
+int encode_decode(cr_plan_t *p, const cr::NodeCoefs &coefs, const ProgramCounts &counts, float *g, const cr::GradientStep &step)
+{
+    LaunchTimer t(p, CR_K_ENCODE, (counts.active_slabs + counts.active_msgs + 1 + step_rows(step)) * p->d * 4);
+    CR_HIP(cr::launch_tree_encode_decode(p->G_src, p->d_M, p->d_node_begin, p->d_slab_coef, p->n, p->L, coefs, g, step, p->d, p->stream));
+    t.done();
+    p->dec = counts.dec;
+    p->have_messages = true;
     return CR_OK;
 }
 
@@ -1005,7 +1024,7 @@ int cr_encode_tree(cr_plan_t *p, const uint8_t *mask)
     return encode_slot(p, 0, counts);
 }
 
-int cr_decode_root(cr_plan_t *p, float *g) { return decode_root(p, g, nullptr, 0.f); }
+int cr_decode_root(cr_plan_t *p, float *g) { return decode_root(p, g, cr::GradientStep()); }
 
 int cr_gd_update(cr_plan_t *p, float *w, const float *g, float lr)
 {
@@ -1027,23 +1046,41 @@ int cr_gd_run(cr_plan_t *p, const void *X, const float *y, float *w, float *g, c
     int rc = check_masks(p, masks, steps);              // every mask is checked before anything is enqueued
     if (rc != CR_OK) return rc;
     const int32_t N = p->tree.N;
+    const bool side_by_side = cr::tree_side_by_side(p->n, p->L, N, p->d), together = cr::tree_and_decode_together(p->n, p->L, N, p->d);
     ProgramCounts counts[kProgramSlots];
+    cr::NodeCoefs coefs;
     for (int t0 = 0; t0 < steps; t0 += kProgramSlots) {
-        // the programs of the next kProgramSlots steps travel in one copy; the steps themselves are kernel launches only
         const int count = std::min(kProgramSlots, steps - t0);
-        rc = upload_programs(p, masks + static_cast<size_t>(t0) * N, count, counts);
-        if (rc != CR_OK) return rc;
-        for (int i = 0; i < count; ++i) {
-            rc = cr_partial_grads(p, X, y, w);
-            if (rc == CR_OK) rc = encode_slot(p, i, counts[i]);
-            // without the convergence measures the gradient step rides in the decode launch (same arithmetic as cr_gd_update)
-            if (rc == CR_OK) rc = decode_root(p, g, metrics ? nullptr : w, lr);
+        // where the tree's kernels take programs, those of the next kProgramSlots steps travel in one copy
+        if (!side_by_side) {
+            rc = upload_programs(p, masks + static_cast<size_t>(t0) * N, count, counts);
             if (rc != CR_OK) return rc;
-            if (metrics) {
-                LaunchTimer tm(p, CR_K_UPDATE, 3 * p->d * 4 + (w_star ? p->d * 4 : 0));
-                CR_HIP(cr::launch_update_metrics(w, g, lr, w_star, metrics + 2 * static_cast<size_t>(t0 + i), p->d, p->stream));
-                tm.done();
+        }
+        for (int i = 0; i < count; ++i) {
+            cr::GradientStep step;
+            step.w = w;
+            step.lr = lr;
+            step.w_star = w_star;
+            step.measures = metrics ? p->d_measures + i * p->measures_stride : nullptr;
+            if (side_by_side) {
+                counts[i] = ProgramCounts();
+                rc = build_coefs(p, masks + static_cast<size_t>(t0 + i) * N, &coefs, &counts[i]);
             }
+            if (rc == CR_OK) rc = cr_partial_grads(p, X, y, w);
+            if (together) {
+                if (rc == CR_OK) rc = encode_decode(p, coefs, counts[i], g, step);
+            } else {
+                if (rc == CR_OK) rc = side_by_side ? encode_tree(p, coefs, counts[i]) : encode_slot(p, i, counts[i]);
+                if (rc == CR_OK) rc = decode_root(p, g, step);
+            }
+            if (rc != CR_OK) return rc;
+        }
+        if (metrics) {
+            const int groups = together ? cr::tree_decode_groups(p->n, p->L, p->d) : cr::decode_groups(p->d);
+            LaunchTimer tm(p, CR_K_UPDATE, static_cast<int64_t>(count) * groups * 32);
+            CR_HIP(cr::launch_measures(p->d_measures, static_cast<int64_t>(p->measures_stride), groups, count, w_star != nullptr,
+                                       metrics + 2 * static_cast<size_t>(t0), p->stream));
+            tm.done();
         }
     }
     return CR_OK;
@@ -1067,7 +1104,7 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
             p->G_src = G + static_cast<int64_t>(t0 + i) * G_step_stride;
             p->have_grads = true;
             rc = encode_slot(p, i, counts[i]);
-            if (rc == CR_OK) rc = decode_root(p, g + static_cast<int64_t>(t0 + i) * g_step_stride, nullptr, 0.f);
+            if (rc == CR_OK) rc = decode_root(p, g + static_cast<int64_t>(t0 + i) * g_step_stride, cr::GradientStep());
             if (rc != CR_OK) return rc;
         }
     }
@@ -1089,17 +1126,28 @@ int cr_aggregate_static(cr_plan_t *p, const float *G, const uint8_t *mask, float
     if (msg_bytes > cr::kStaticScratchBytes - cr::kStaticProgramBytes)
         return fail(CR_E_INVAL, "cr_aggregate_static: N * d * 4 = " + std::to_string(msg_bytes) + " bytes of messages exceed the library's device array (" +
                                     std::to_string(cr::kStaticScratchBytes - cr::kStaticProgramBytes) + " bytes)");
-    if (p->static_program.size() != p->program_bytes) p->static_program.assign(p->program_bytes, 0);
     ProgramCounts counts;
+    char *base = nullptr;
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    if (cr::tree_side_by_side(p->n, p->L, p->tree.N, p->d)) {
+        cr::NodeCoefs coefs;
+        int rc = build_coefs(p, mask, &coefs, &counts);
+        if (rc != CR_OK) return rc;
+        CR_HIP(cr::static_scratch(&base));              // this device's copy of the array; never the array's name
+        const cr::ProgramSource src{p->tree.N, static_cast<int>(p->slabs.size()), p->node_slab_begin.data(), p->slab_coef.data(), &coefs};
+        bool done = false;
+        CR_HIP(cr::launch_aggregate(G, reinterpret_cast<float *>(base + cr::kStaticProgramBytes), src, p->n, p->L, counts.dec, g, p->d, stream, &done));
+        if (done) return CR_OK;
+        counts = ProgramCounts();
+    }
+    if (p->static_program.size() != p->program_bytes) p->static_program.assign(p->program_bytes, 0);
     int rc = build_program(p, mask, p->static_program.data(), &counts);
     if (rc != CR_OK) return rc;
-    char *base = nullptr;
-    CR_HIP(cr::static_scratch(&base));                  // this device's copy of the array; never the array's name
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    CR_HIP(cr::static_scratch(&base));
     float *M = reinterpret_cast<float *>(base + cr::kStaticProgramBytes);
     CR_HIP(cr::launch_program(program_tables(p, base), program_tables(p, p->static_program.data()), counts.terms, 2 * p->n, stream));
     CR_HIP(cr::launch_encode(G, M, program_view(p, base), p->n, p->L, p->d, stream));
-    CR_HIP(cr::launch_decode(M, g, counts.dec, p->d, nullptr, 0.f, stream));
+    CR_HIP(cr::launch_decode(M, g, counts.dec, cr::GradientStep(), p->d, stream));
     return CR_OK;
 }
 

@@ -61,7 +61,13 @@ struct TreeLevels {
     int32_t n, L, total, leaves;
     int32_t first[8], shift[8], width[8];
 };
-TreeLevels sub_tree_levels(int n, int L);
+// The gradient step that rides in the launch of a decode.
+struct GradientStep {
+    float *w = nullptr;              // w <- w - lr g, g as stored (rounded to fp32); nullptr: no step
+    const float *w_star = nullptr;
+    double *measures = nullptr;      // per workgroup |w_new - w|^2, |w|^2, |w_new - w*|^2, |w*|^2 over its columns; nullptr: not wanted
+    float lr = 0.f;
+};
 
 constexpr int kEncodeUnroll = 8;   // encode sub-programs are padded to a multiple of this many terms
 constexpr int kMaxLevels = 8;
@@ -121,8 +127,27 @@ constexpr int64_t kTreeColumns = 81920, kTreeNarrowColumns = 32768;
 bool tree_side_by_side(int n, int L, int nodes, int64_t d);
 hipError_t launch_tree_encode(const float *G, float *M, const int32_t *node_begin, const double *slab_coef, int n, int L, const NodeCoefs &coefs, int64_t d,
                               hipStream_t stream);
-// w != nullptr: also steps w <- w - lr g (g as stored, rounded to fp32) in the same launch
-hipError_t launch_decode(const float *M, float *g, const DecTerms &terms, int64_t d, float *w, float lr, hipStream_t stream);
+// the master's decode and, with step.w, the gradient step; decode_groups: workgroups of the launch
+hipError_t launch_decode(const float *M, float *g, const DecTerms &terms, const GradientStep &step, int64_t d, hipStream_t stream);
+int decode_groups(int64_t d);
+// Encode, decode and gradient step in one launch, where tree_and_decode_together says so: vectors of at most kTogetherColumns columns
+// (8 chunks of columns per workgroup, 16 from kTogetherNarrowColumns on).
+constexpr int64_t kTogetherColumns = 32768, kTogetherNarrowColumns = 8192;
+bool tree_and_decode_together(int n, int L, int nodes, int64_t d);
+hipError_t launch_tree_encode_decode(const float *G, float *M, const int32_t *node_begin, const double *slab_coef, int n, int L, const NodeCoefs &coefs, float *g,
+                                     const GradientStep &step, int64_t d, hipStream_t stream);
+int tree_decode_groups(int n, int L, int64_t d);
+// metrics[2t], metrics[2t + 1] of `steps` steps from the measures their launches of `groups` workgroups left at sums + t * step_stride
+hipError_t launch_measures(const double *sums, int64_t step_stride, int groups, int steps, bool with_star, float *metrics, hipStream_t stream);
+// Encode and decode with all tables as kernel arguments (host pointers; consumed before the call returns).  *done = false and nothing
+// enqueued where the tree, the vector or the tables are too large for that.
+struct ProgramSource {
+    int nodes, slabs;
+    const int32_t *node_begin;
+    const double *slab_coef;
+    const NodeCoefs *coefs;
+};
+hipError_t launch_aggregate(const float *G, float *M, const ProgramSource &src, int n, int L, const DecTerms &dec, float *g, int64_t d, hipStream_t stream, bool *done);
 hipError_t launch_update(float *w, const float *g, float lr, int64_t d, hipStream_t stream);
 // plain streaming read of n16 16-byte words; every workgroup writes its sum to sink[workgroup] (kStreamGroups workgroups)
 constexpr int kStreamGroups = 256 * 8;
@@ -145,6 +170,5 @@ hipError_t launch_program(const ProgramTables &out, const ProgramTables &host, i
 
 // one wavefront per workgroup; out[workgroup id] = (die the workgroup ran on) << 16 | (shader engine and compute unit inside the die)
 hipError_t launch_placement_probe(uint32_t *out, int groups, hipStream_t stream);
-hipError_t launch_update_metrics(float *w, const float *g, float lr, const float *w_star, float *metrics, int64_t d, hipStream_t stream);
 
 }  // namespace cr

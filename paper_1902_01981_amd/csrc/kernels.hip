@@ -10,7 +10,9 @@
 //   tree_kernel            CR.Execute steps 2-5: every node's message, the nodes of a sub-tree side by side, children folded in LDS
 //   encode_kernel          the same for long vectors and large trees: one thread walks a sub-tree, children folded in registers
 //   decode_kernel          the master's decode  g = sum_j a_j m_(1,j), optionally followed by w <- w - lr g in the same launch
-//   update_kernel, update_metrics_kernel    w <- w - lr g, optionally with the convergence measures of eq. (6) and (8)
+//   tree_decode_kernel     tree_kernel and decode_kernel in one launch, for short vectors
+//   update_kernel          w <- w - lr g
+//   measures_kernel        the convergence measures of eq. (6) and (8), from the sums that the launches with the gradient step leave
 //
 // Rows of d elements start on a 4-byte (fp32) or 2-byte (bf16) boundary whatever d is, so the 16-byte row accesses are declared
 // with that alignment; the hardware runs in unaligned-access mode and the compiler emits the same dwordx4 instructions.
@@ -1017,6 +1019,44 @@ encode_kernel(const float *__restrict__ G, float *__restrict__ M, EncProgram pro
 // 12.5 / 5.9; (3,6) tree, s = 2, 1 024 columns 25.9 / 6.7; (3,4) tree, 6 500 columns 8.5 / 5.7.
 __device__ __forceinline__ bool sends(double a) { return __double_as_longlong(a) != kStraggler; }
 
+// The tree's tables as a kernel argument: on the device for the plan's life, with the mask's coefficients beside them ...
+struct DeviceTables {
+    static constexpr size_t kLdsBytes = 0;
+    const int32_t *node_begin;
+    const double *slab_coef;
+    NodeCoefs coefs;
+    struct View {
+        const DeviceTables &t;
+        __device__ __forceinline__ double coef_of(int node) const { return t.coefs.a[node]; }
+        __device__ __forceinline__ int begin(int node) const { return t.node_begin[node]; }
+        __device__ __forceinline__ double slab_coef_of(int s) const { return t.slab_coef[s]; }
+    };
+    template <int T> __device__ __forceinline__ View view(char *) const { return {*this}; }
+};
+// ... or all of it in the argument: the distinct coefficients, then 16-bit tables of first slabs and of places among the coefficients.
+// The workgroup copies it to LDS first, since a coefficient is two dependent fetches away.
+struct ArgumentTables {
+    static constexpr int kWords = 470;
+    static constexpr size_t kLdsBytes = kWords * 8;
+    int32_t at_begin, at_coef, at_slab, used;            // in 16-bit units; 64-bit words in use
+    uint64_t word[kWords];
+    struct View {
+        const double *value;
+        const uint16_t *first, *coef, *slab;
+        __device__ __forceinline__ double coef_of(int node) const { return value[coef[node]]; }
+        __device__ __forceinline__ int begin(int node) const { return first[node]; }
+        __device__ __forceinline__ double slab_coef_of(int s) const { return value[slab[s]]; }
+    };
+    template <int T> __device__ __forceinline__ View view(char *lds) const
+    {
+        uint64_t *copy = reinterpret_cast<uint64_t *>(lds);
+        for (int i = threadIdx.x; i < used; i += T) copy[i] = word[i];
+        __syncthreads();
+        const uint16_t *half = reinterpret_cast<const uint16_t *>(lds);
+        return {reinterpret_cast<const double *>(lds), half + at_begin, half + at_coef, half + at_slab};
+    }
+};
+
 // The places of a workgroup's nodes, leaves first, then level by level up; sub: which level-1 sub-tree (0 where it has them all).
 struct TreePlaces {
     const TreeLevels &tree;
@@ -1043,14 +1083,26 @@ template <int VEC, int B> struct TreeLds {
 #pragma unroll
         for (int v = 0; v < VEC; ++v) msg[(t * VEC + v) * B + tl] = m[v];
     }
-    // acc += coef * message, the nodes [t0, t0 + n) in turn; SKIP: those with coefficient zero are left out
+    // acc += coef * message, the nodes [t0, t0 + n) in turn, four read at a time; SKIP: those with coefficient zero are left out
     template <bool SKIP> __device__ __forceinline__ void fold(int t0, int n, int tl, double (&acc)[VEC]) const
     {
-        for (int c = 0; c < n; ++c) {
-            const double a = coef[t0 + c];
-            if (!sends(a) || (SKIP && a == 0.0)) continue;
+        constexpr int U = 4;
+        for (int c0 = 0; c0 < n; c0 += U) {
+            double a[U];
+            float m[U][VEC];
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[v] = fma(a, static_cast<double>(msg[((t0 + c) * VEC + v) * B + tl]), acc[v]);
+            for (int u = 0; u < U; ++u) {
+                const int t = t0 + min(c0 + u, n - 1);
+                a[u] = coef[t];
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) m[u][v] = msg[(t * VEC + v) * B + tl];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (c0 + u < n && sends(a[u]) && !(SKIP && a[u] == 0.0)) {
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) acc[v] = fma(a[u], static_cast<double>(m[u][v]), acc[v]);
+                }
         }
     }
 };
@@ -1124,19 +1176,87 @@ __device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, c
 }
 
 // one level-1 sub-tree (grid.y) per workgroup
-template <int VEC, int B, int T>
+template <int VEC, int B, int T, typename TABLES>
 __global__ void __launch_bounds__(T)
-tree_kernel(const float *__restrict__ G, float *__restrict__ M, const int32_t *__restrict__ node_begin, const double *__restrict__ slab_coef,
-            TreeLevels tree, NodeCoefs coefs, int64_t d, int nq)
+tree_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, TreeLevels tree, int64_t d, int nq)
 {
     extern __shared__ __align__(16) char tree_lds[];
-    const TreeLds<VEC, B> lds(tree_lds, tree.total, tree.leaves);
+    const auto view = tables.template view<T>(tree_lds);
+    const TreeLds<VEC, B> lds(tree_lds + TABLES::kLdsBytes, tree.total, tree.leaves);
     const int q = blockIdx.x * B + threadIdx.x % B;
     const int64_t col = chunk_offset<VEC>(q, nq, static_cast<int>(d));       // lanes past the row repeat its last chunk and do not store
     tree_messages<VEC, B, T>(
-        tree, blockIdx.y, lds, [&](int node) { return coefs.a[node]; },
-        [&](int node, double (&acc)[VEC]) { sum_slabs<VEC>(G, d, col, node_begin[node], node_begin[node + 1], [&](int s) { return slab_coef[s]; }, acc); },
+        tree, blockIdx.y, lds, [&](int node) { return view.coef_of(node); },
+        [&](int node, double (&acc)[VEC]) { sum_slabs<VEC>(G, d, col, view.begin(node), view.begin(node + 1), [&](int s) { return view.slab_coef_of(s); }, acc); },
         M, d, col, q < nq);
+}
+
+// What one column contributes to the convergence measures of a gradient step: |w_new - w|^2, |w|^2, |w_new - w*|^2, |w*|^2.
+__device__ __forceinline__ void measure(double (&sum)[4], float w_old, float w_new, const float *w_star, int64_t col)
+{
+    const double dw = static_cast<double>(w_new) - static_cast<double>(w_old);
+    sum[0] += dw * dw;
+    sum[1] += static_cast<double>(w_old) * w_old;
+    if (w_star) {
+        const double ws = w_star[col], e = static_cast<double>(w_new) - ws;
+        sum[2] += e * e;
+        sum[3] += ws * ws;
+    }
+}
+
+// The decoded chunk q goes to g; step.w: w <- w - lr g with g as stored, a column shared with the neighbouring chunk by the chunk that
+// owns it only; step.measures: the columns' part of the measures is added to sum.
+template <int VEC, bool NT> __device__ __forceinline__ void put_gradient(const double (&acc)[VEC], float *g, int64_t col, int q, int nq, int64_t d, const GradientStep &step, double (&sum)[4])
+{
+    float out[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) out[v] = static_cast<float>(acc[v]);
+    if constexpr (NT) store_row_nt<VEC>(g + col, out);
+    else store_row<VEC>(g + col, out);
+    if (!step.w) return;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v)
+        if (chunk_owns<VEC>(q, v, nq, static_cast<int>(d))) {
+            const float w_old = step.w[col + v], w_new = fmaf(-step.lr, out[v], w_old);
+            step.w[col + v] = w_new;
+            if (step.measures) measure(sum, w_old, w_new, step.w_star, col + v);
+        }
+}
+
+// The whole tree per workgroup, the master's decode and the gradient step after it: one launch where there were two or three.  For
+// vectors of so few columns that a launch lasts no longer than its chain of fetches; longer ones have more to gain from a workgroup per
+// sub-tree and a decode of their own.  us, encode and decode apart / together: (2,12) tree, s = 2, 10 columns 4.2 + 2.0 / 6.1;
+// (3,4) tree, 6 500 columns 5.7 + 2.6 / 5.7; (2,12), s = 2, 24 576 columns 13.4 + 3.9 / 14.6, 73 728 columns 29.9 + 4.7 / 35.4.
+template <int VEC, int B, int T, typename TABLES>
+__global__ void __launch_bounds__(T)
+tree_decode_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, TreeLevels tree, float *__restrict__ g, GradientStep step, int64_t d, int nq)
+{
+    extern __shared__ __align__(16) char tree_lds[];
+    const auto view = tables.template view<T>(tree_lds);
+    const TreeLds<VEC, B> lds(tree_lds + TABLES::kLdsBytes, tree.total, tree.leaves);
+    const int tl = threadIdx.x % B, q = blockIdx.x * B + tl;
+    const int64_t col = chunk_offset<VEC>(q, nq, static_cast<int>(d));
+    tree_messages<VEC, B, T>(
+        tree, 0, lds, [&](int node) { return view.coef_of(node); },
+        [&](int node, double (&acc)[VEC]) { sum_slabs<VEC>(G, d, col, view.begin(node), view.begin(node + 1), [&](int s) { return view.slab_coef_of(s); }, acc); },
+        M, d, col, q < nq);
+    __syncthreads();
+    if (threadIdx.x >= B) return;
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    if (q < nq) {
+        double acc[VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
+        lds.template fold<true>(tree.first[0], tree.n, tl, acc);
+        put_gradient<VEC, false>(acc, g, col, q, nq, d, step, sum);
+    }
+    if (!step.measures) return;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+        for (int o = B / 2; o > 0; o >>= 1) sum[k] += __shfl_xor(sum[k], o, 64);
+        if (tl == 0) step.measures[4 * blockIdx.x + k] = sum[k];
+    }
 }
 
 // ---- decode ---------------------------------------------------------------------------------------------------------
@@ -1147,10 +1267,9 @@ tree_kernel(const float *__restrict__ G, float *__restrict__ M, const int32_t *_
 constexpr int64_t kDecodeLongColumns = int64_t(1) << 20;
 template <int VEC, int U, int C, bool NT>
 __global__ void __launch_bounds__(256)
-decode_kernel(const float *__restrict__ M, float *__restrict__ g, DecTerms terms, int64_t d, int nq, float *__restrict__ w, float lr)
+decode_kernel(const float *__restrict__ M, float *__restrict__ g, DecTerms terms, GradientStep step, int64_t d, int nq)
 {
     const int q0 = blockIdx.x * (256 * C) + threadIdx.x;
-    if (q0 >= nq) return;
     int64_t col[C];                                      // chunks past the row repeat its last one and are not stored
     double acc[C][VEC];
 #pragma unroll
@@ -1180,23 +1299,20 @@ decode_kernel(const float *__restrict__ M, float *__restrict__ g, DecTerms terms
                     for (int v = 0; v < VEC; ++v) acc[c][v] = fma(terms.coef[j0 + u], static_cast<double>(xv[u][c][v]), acc[c][v]);
             }
     }
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-        const int q = q0 + c * 256;
-        if (q >= nq) break;
-        float out[VEC];
+    for (int c = 0; c < C; ++c)
+        if (q0 + c * 256 < nq) put_gradient<VEC, NT>(acc[c], g, col[c], q0 + c * 256, nq, d, step, sum);
+    if (!step.measures) return;
+    __shared__ double part[4][4];
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) out[v] = static_cast<float>(acc[c][v]);
-        if constexpr (NT) store_row_nt<VEC>(g + col[c], out);
-        else store_row<VEC>(g + col[c], out);
-        if (w) {
-            // the gradient step of the same columns, from the rounded g that was just stored; a column shared with the neighbouring
-            // chunk is stepped by the chunk that owns it only
+    for (int k = 0; k < 4; ++k) {
 #pragma unroll
-            for (int v = 0; v < VEC; ++v)
-                if (chunk_owns<VEC>(q, v, nq, static_cast<int>(d))) w[col[c] + v] = fmaf(-lr, out[v], w[col[c] + v]);
-        }
+        for (int o = 32; o > 0; o >>= 1) sum[k] += __shfl_xor(sum[k], o, 64);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][k] = sum[k];
     }
+    __syncthreads();
+    if (threadIdx.x < 4) step.measures[4 * blockIdx.x + threadIdx.x] = part[0][threadIdx.x] + part[1][threadIdx.x] + part[2][threadIdx.x] + part[3][threadIdx.x];
 }
 
 __global__ void __launch_bounds__(256) update_kernel(float *__restrict__ w, const float *__restrict__ g, float lr, int64_t d)
@@ -1205,43 +1321,31 @@ __global__ void __launch_bounds__(256) update_kernel(float *__restrict__ w, cons
     if (i < d) w[i] = fmaf(-lr, g[i], w[i]);
 }
 
-// Gradient step fused with the two convergence measures of the paper's experiments: metrics[0] = ||w_new - w||^2 / ||w||^2
-// (relative error rate, eq. (6)), metrics[1] = ||w_new - w*||^2 / ||w*||^2 (normalised error rate, eq. (8)), or -1 without w*.
-// One workgroup, fixed summation order: the model has at most a few 10^4 entries on this path.
-__global__ void __launch_bounds__(1024)
-update_metrics_kernel(float *__restrict__ w, const float *__restrict__ g, float lr, const float *__restrict__ w_star,
-                      float *__restrict__ metrics, int64_t d)
+// The two convergence measures of the paper's experiments, one workgroup per step, from what the launches that made the steps left, four
+// sums per workgroup: metrics[0] = ||w_new - w||^2 / ||w||^2 (relative error rate, eq. (6)), metrics[1] = ||w_new - w*||^2 / ||w*||^2
+// (normalised error rate, eq. (8)), or -1 without w*.  Fixed summation order.
+__global__ void __launch_bounds__(256)
+measures_kernel(const double *__restrict__ sums, int64_t step_stride, int groups, bool with_star, float *__restrict__ metrics)
 {
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};   // |dw|^2, |w|^2, |w_new - w*|^2, |w*|^2
-    for (int64_t i = threadIdx.x; i < d; i += 1024) {
-        const float wo = w[i];
-        const float wn = fmaf(-lr, g[i], wo);
-        w[i] = wn;
-        const double dw = static_cast<double>(wn) - static_cast<double>(wo);
-        acc[0] += dw * dw;
-        acc[1] += static_cast<double>(wo) * wo;
-        if (w_star) {
-            const double ws = w_star[i], e = static_cast<double>(wn) - ws;
-            acc[2] += e * e;
-            acc[3] += ws * ws;
-        }
-    }
-    __shared__ double part[16][4];
+    const double *s = sums + blockIdx.x * step_stride;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i = threadIdx.x; i < groups; i += 256)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] += s[4 * static_cast<int64_t>(i) + k];
+    __shared__ double part[4][4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) acc[k] += __shfl_xor(acc[k], o, 64);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][k] = acc[k];
     }
-    if ((threadIdx.x & 63) == 0)
-        for (int k = 0; k < 4; ++k) part[threadIdx.x / 64][k] = acc[k];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double tot[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int wv = 0; wv < 16; ++wv)
-            for (int k = 0; k < 4; ++k) tot[k] += part[wv][k];
-        metrics[0] = static_cast<float>(tot[0] / tot[1]);
-        metrics[1] = w_star ? static_cast<float>(tot[2] / tot[3]) : -1.f;
-    }
+    if (threadIdx.x != 0) return;
+    double tot[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) tot[k] = part[0][k] + part[1][k] + part[2][k] + part[3][k];
+    metrics[2 * blockIdx.x] = static_cast<float>(tot[0] / tot[1]);
+    metrics[2 * blockIdx.x + 1] = with_star ? static_cast<float>(tot[2] / tot[3]) : -1.f;
 }
 
 // ---- variant table for stage 1 --------------------------------------------------------------------------------------
@@ -1486,59 +1590,107 @@ hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int n
 }
 
 namespace {
-template <int VEC, int B, int T>
-hipError_t launch_tree(const float *G, float *M, const int32_t *node_begin, const double *slab_coef, const TreeLevels &tree, const NodeCoefs &coefs, int64_t d,
-                       hipStream_t stream)
-{
-    const int nq = static_cast<int>((d + VEC - 1) / VEC);
-    tree_kernel<VEC, B, T><<<dim3((nq + B - 1) / B, tree.n), T, TreeLds<VEC, B>::bytes(tree.total, tree.leaves), stream>>>(G, M, node_begin, slab_coef, tree, coefs, d, nq);
-    return hipGetLastError();
-}
-}  // namespace
+constexpr size_t kTreeLdsBytes = size_t(60) << 10;          // 64 KB with ArgumentTables' copy
+static_assert(sizeof(ArgumentTables) <= 3776 && sizeof(DeviceTables) <= 3776 && sizeof(TreeLevels) + sizeof(GradientStep) + 64 <= 256, "4 KB of kernel arguments");
 
-TreeLevels sub_tree_levels(int n, int L)
+// the nodes of one level-1 sub-tree, or of all of them
+TreeLevels tree_levels(int n, int L, bool whole)
 {
     TreeLevels t = {};
     t.n = n;
     t.L = L;
-    int offset = 0, width = 1;
+    int offset = 0, width = 1, count[kMaxLevels];
     for (int l = 1; l <= L; ++l) {
         t.width[l - 1] = width;
         t.shift[l - 1] = offset;
+        count[l - 1] = whole ? width * n : width;
         width *= n;
         offset += width;                                 // a level has n times as many nodes as one sub-tree has of it
     }
     for (int l = L; l >= 1; --l) {
         t.first[l - 1] = t.total;
         t.shift[l - 1] -= t.total;
-        t.total += t.width[l - 1];
+        t.total += count[l - 1];
     }
-    t.leaves = t.width[L - 1];
+    t.leaves = count[L - 1];
     return t;
 }
 
-bool tree_side_by_side(int n, int L, int nodes, int64_t d)
+template <int VEC, int B> bool tree_fits(const TreeLevels &tree) { return TreeLds<VEC, B>::bytes(tree.total, tree.leaves) <= kTreeLdsBytes; }
+
+template <int VEC, int B, int T, typename TABLES>
+hipError_t launch_tree_shape(const float *G, float *M, const TABLES &tables, const TreeLevels &tree, int64_t d, hipStream_t stream)
 {
-    return nodes <= NodeCoefs::kNodes && d <= kTreeColumns && TreeLds<4, 16>::bytes(sub_tree_levels(n, L).total, sub_tree_levels(n, L).leaves) <= (size_t(64) << 10);
+    const int nq = static_cast<int>((d + VEC - 1) / VEC);
+    tree_kernel<VEC, B, T><<<dim3((nq + B - 1) / B, tree.n), T, TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves), stream>>>(G, M, tables, tree, d, nq);
+    return hipGetLastError();
+}
+
+template <typename TABLES>
+hipError_t launch_tree(const float *G, float *M, const TABLES &tables, int n, int L, int64_t d, hipStream_t stream)
+{
+    const TreeLevels tree = tree_levels(n, L, false);
+    if (d < 4) return launch_tree_shape<1, 16, 256>(G, M, tables, tree, d, stream);
+    if (d > kTreeNarrowColumns && tree_fits<4, 64>(tree)) return launch_tree_shape<4, 64, 256>(G, M, tables, tree, d, stream);
+    return launch_tree_shape<4, 16, 256>(G, M, tables, tree, d, stream);
+}
+
+template <int VEC, int B, int T, typename TABLES>
+hipError_t launch_tree_decode_shape(const float *G, float *M, const TABLES &tables, const TreeLevels &tree, float *g, const GradientStep &step, int64_t d, hipStream_t stream)
+{
+    const int nq = static_cast<int>((d + VEC - 1) / VEC);
+    tree_decode_kernel<VEC, B, T><<<(nq + B - 1) / B, T, TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves), stream>>>(G, M, tables, tree, g, step, d, nq);
+    return hipGetLastError();
+}
+
+template <typename TABLES>
+hipError_t launch_tree_decode(const float *G, float *M, const TABLES &tables, int n, int L, float *g, const GradientStep &step, int64_t d, hipStream_t stream)
+{
+    const TreeLevels tree = tree_levels(n, L, true);
+    if (d < 4) return launch_tree_decode_shape<1, 8, 1024>(G, M, tables, tree, g, step, d, stream);
+    if (d > kTogetherNarrowColumns && tree_fits<4, 16>(tree)) return launch_tree_decode_shape<4, 16, 512>(G, M, tables, tree, g, step, d, stream);
+    return launch_tree_decode_shape<4, 8, 1024>(G, M, tables, tree, g, step, d, stream);
+}
+}  // namespace
+
+bool tree_side_by_side(int n, int L, int nodes, int64_t d) { return nodes <= NodeCoefs::kNodes && d <= kTreeColumns && tree_fits<4, 16>(tree_levels(n, L, false)); }
+
+bool tree_and_decode_together(int n, int L, int nodes, int64_t d)
+{
+    return tree_side_by_side(n, L, nodes, d) && d <= kTogetherColumns && tree_fits<4, 8>(tree_levels(n, L, true));
+}
+
+int tree_decode_groups(int n, int L, int64_t d)
+{
+    const int64_t chunks = d < 4 ? d : (d + 3) / 4;
+    const int per = d > kTogetherNarrowColumns && tree_fits<4, 16>(tree_levels(n, L, true)) ? 16 : 8;
+    return static_cast<int>((chunks + per - 1) / per);
 }
 
 hipError_t launch_tree_encode(const float *G, float *M, const int32_t *node_begin, const double *slab_coef, int n, int L, const NodeCoefs &coefs, int64_t d,
                               hipStream_t stream)
 {
-    const TreeLevels tree = sub_tree_levels(n, L);
-    if (d < 4) return launch_tree<1, 16, 256>(G, M, node_begin, slab_coef, tree, coefs, d, stream);
-    if (d > kTreeNarrowColumns && TreeLds<4, 64>::bytes(tree.total, tree.leaves) <= (size_t(64) << 10))
-        return launch_tree<4, 64, 256>(G, M, node_begin, slab_coef, tree, coefs, d, stream);
-    return launch_tree<4, 16, 256>(G, M, node_begin, slab_coef, tree, coefs, d, stream);
+    return launch_tree(G, M, DeviceTables{node_begin, slab_coef, coefs}, n, L, d, stream);
 }
 
-hipError_t launch_decode(const float *M, float *g, const DecTerms &terms, int64_t d, float *w, float lr, hipStream_t stream)
+hipError_t launch_tree_encode_decode(const float *G, float *M, const int32_t *node_begin, const double *slab_coef, int n, int L, const NodeCoefs &coefs, float *g,
+                                     const GradientStep &step, int64_t d, hipStream_t stream)
 {
-    const int nq = static_cast<int>(d >= 4 ? (d + 3) / 4 : d);
-    const auto groups = [&](int chunks) { return static_cast<unsigned>((nq + 256 * chunks - 1) / (256 * chunks)); };
-    if (d < 4) decode_kernel<1, 8, 1, false><<<groups(1), 256, 0, stream>>>(M, g, terms, d, nq, w, lr);
-    else if (d < kDecodeLongColumns) decode_kernel<4, 8, 1, false><<<groups(1), 256, 0, stream>>>(M, g, terms, d, nq, w, lr);
-    else decode_kernel<4, 1, 4, true><<<groups(4), 256, 0, stream>>>(M, g, terms, d, nq, w, lr);
+    return launch_tree_decode(G, M, DeviceTables{node_begin, slab_coef, coefs}, n, L, g, step, d, stream);
+}
+
+int decode_groups(int64_t d)
+{
+    const int64_t chunks = d < 4 ? d : (d + 3) / 4, per = d < kDecodeLongColumns ? 256 : 1024;
+    return static_cast<int>((chunks + per - 1) / per);
+}
+
+hipError_t launch_decode(const float *M, float *g, const DecTerms &terms, const GradientStep &step, int64_t d, hipStream_t stream)
+{
+    const int nq = static_cast<int>(d >= 4 ? (d + 3) / 4 : d), groups = decode_groups(d);
+    if (d < 4) decode_kernel<1, 8, 1, false><<<groups, 256, 0, stream>>>(M, g, terms, step, d, nq);
+    else if (d < kDecodeLongColumns) decode_kernel<4, 8, 1, false><<<groups, 256, 0, stream>>>(M, g, terms, step, d, nq);
+    else decode_kernel<4, 1, 4, true><<<groups, 256, 0, stream>>>(M, g, terms, step, d, nq);
     return hipGetLastError();
 }
 
@@ -1683,6 +1835,61 @@ hipError_t launch_program(const ProgramTables &out, const ProgramTables &host, i
     return hipSuccess;
 }
 
+// The tables of a tree and a mask as one kernel argument, where they fit.
+bool argument_tables(const ProgramSource &src, ArgumentTables *out)
+{
+    constexpr int kSlots = 1024;                         // of the hash table; there is room for fewer than 470 distinct coefficients
+    uint16_t slot[kSlots];
+    std::memset(slot, 0xff, sizeof slot);
+    const int halves = (src.nodes + 1) + src.nodes + src.slabs;
+    if (src.slabs > 0xffff || halves > 4 * ArgumentTables::kWords) return false;
+    const int room = ArgumentTables::kWords - (halves + 3) / 4;
+    uint16_t half[4 * ArgumentTables::kWords];
+    int values = 0, at = 0;
+    auto place = [&](double c) {                         // the coefficient's place among the distinct ones, or -1: no room
+        uint64_t bits;
+        std::memcpy(&bits, &c, 8);
+        unsigned h = static_cast<unsigned>((bits * 0x9E3779B97F4A7C15ull) >> 54);
+        while (slot[h] != 0xffff && out->word[slot[h]] != bits) h = (h + 1) % kSlots;
+        if (slot[h] == 0xffff) {
+            if (values == room) return -1;
+            slot[h] = static_cast<uint16_t>(values);
+            out->word[values++] = bits;
+        }
+        return static_cast<int>(slot[h]);
+    };
+    out->at_begin = at;
+    for (int i = 0; i <= src.nodes; ++i) half[at++] = static_cast<uint16_t>(src.node_begin[i]);
+    out->at_coef = at;
+    for (int i = 0; i < src.nodes; ++i) {
+        const int k = place(src.coefs->a[i]);
+        if (k < 0) return false;
+        half[at++] = static_cast<uint16_t>(k);
+    }
+    out->at_slab = at;
+    for (int i = 0; i < src.slabs; ++i) {
+        const int k = place(src.slab_coef[i]);
+        if (k < 0) return false;
+        half[at++] = static_cast<uint16_t>(k);
+    }
+    std::memcpy(out->word + values, half, static_cast<size_t>(at) * 2);
+    out->at_begin += 4 * values;
+    out->at_coef += 4 * values;
+    out->at_slab += 4 * values;
+    out->used = values + (at + 3) / 4;
+    return true;
+}
+
+hipError_t launch_aggregate(const float *G, float *M, const ProgramSource &src, int n, int L, const DecTerms &dec, float *g, int64_t d, hipStream_t stream, bool *done)
+{
+    ArgumentTables tables;
+    *done = tree_side_by_side(n, L, src.nodes, d) && argument_tables(src, &tables);
+    if (!*done) return hipSuccess;
+    if (tree_and_decode_together(n, L, src.nodes, d)) return launch_tree_decode(G, M, tables, n, L, g, GradientStep(), d, stream);
+    const hipError_t e = launch_tree(G, M, tables, n, L, d, stream);
+    return e != hipSuccess ? e : launch_decode(M, g, dec, GradientStep(), d, stream);
+}
+
 // ---- where do workgroups run? -----------------------------------------------------------------------------------------
 // __smid() packs the hardware ids of the wave: die (XCC) above 6 bits of shader engine and compute unit.
 __global__ void __launch_bounds__(64) placement_probe_kernel(uint32_t *__restrict__ out)
@@ -1703,9 +1910,9 @@ hipError_t launch_update(float *w, const float *g, float lr, int64_t d, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_update_metrics(float *w, const float *g, float lr, const float *w_star, float *metrics, int64_t d, hipStream_t stream)
+hipError_t launch_measures(const double *sums, int64_t step_stride, int groups, int steps, bool with_star, float *metrics, hipStream_t stream)
 {
-    update_metrics_kernel<<<1, 1024, 0, stream>>>(w, g, lr, w_star, metrics, d);
+    measures_kernel<<<steps, 256, 0, stream>>>(sums, step_stride, groups, with_star, metrics);
     return hipGetLastError();
 }
 

@@ -1,0 +1,78 @@
+"""Encode, decode and gradient step in one launch, and apart where vectors are longer: cr_gd_run and cr_aggregate_static on both sides
+of every rule against the separate calls (the same bits), the convergence measures against 64 bits."""
+import numpy as np
+import pytest
+
+import paper_1902_01981_amd as cr
+
+pytestmark = pytest.mark.gpu
+
+WIDTHS = [1, 3, 4, 31, 33, 1_030, 8_192, 8_195, 32_768, 32_771, 40_001, 81_925]
+
+
+def _masks(rng, steps, groups, n, s):
+    masks = np.zeros((steps, groups * n), dtype=np.uint8)
+    for t in range(steps):
+        for g in range(groups):
+            masks[t, g * n + rng.choice(n, size=int(rng.integers(0, s + 1)), replace=False)] = 1
+    return masks
+
+
+@pytest.mark.parametrize("d", WIDTHS)
+@pytest.mark.parametrize("L,n,s", [(2, 3, 1), (2, 21, 0)])       # 462 workers: more than kernel arguments hold
+def test_steps_of_a_run(L, n, s, d):
+    import torch
+
+    N = sum(n ** l for l in range(1, L + 1))
+    m = 4 * N
+    if m * d > 1 << 26:
+        m = N
+    plan = cr.cr_plan_ex(L, n, s, m, d)
+    ws = cr.Workspace(plan)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    X, y, w0, w_star = (torch.randn(shape, generator=gen, device="cuda") for shape in ((m, d), (m,), (d,), (d,)))
+    steps, lr = 18, 0.1 / (m + d)                        # more steps than go into one batch of measures
+    masks = _masks(np.random.default_rng(d), steps, ws.info.num_groups, n, s)
+    w, g = w0.clone(), torch.empty(d, device="cuda")
+    want = []
+    for t in range(steps):
+        before = w.double()
+        cr.cr_partial_grads(plan, X, y, w)
+        cr.cr_encode_tree(plan, masks[t])
+        cr.cr_decode_root(plan, g)
+        cr.cr_gd_update(plan, w, g, lr)
+        want.append([float((w.double() - before).pow(2).sum() / before.pow(2).sum()), float((w.double() - w_star.double()).pow(2).sum() / w_star.double().pow(2).sum())])
+    messages = ws.messages().clone()
+    for measured in (False, True):
+        w_run, g_run = w0.clone(), torch.full((d + 4,), 7.0, device="cuda")
+        metrics = torch.full((steps + 1, 2), 7.0, device="cuda") if measured else None
+        cr.cr_gd_run(plan, X, y, w_run, g_run, masks, lr, w_star if measured else None, metrics)
+        cr.cr_synchronize(plan)
+        assert torch.equal(w, w_run) and torch.equal(g, g_run[:d]) and bool((g_run[d:] == 7.0).all())
+        assert torch.equal(ws.messages(), messages)
+    # sums and quotient in 64 bits, rounded to fp32
+    np.testing.assert_allclose(metrics[:steps].cpu().numpy(), np.array(want), rtol=2.0 ** -22)
+    assert bool((metrics[steps] == 7.0).all())
+    del ws
+    cr.cr_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("d", WIDTHS)
+@pytest.mark.parametrize("L,n,s", [(2, 12, 2), (3, 6, 2), (3, 4, 1), (2, 8, 2)])     # two and many distinct coefficients; (3, 6): more than fit
+def test_static_aggregation(L, n, s, d):
+    import torch
+
+    plan = cr.cr_plan_ex(L, n, s, 40 * n ** L, d, model=cr.CR_AGGREGATE_ONLY)
+    info = cr.cr_plan_info(plan)
+    ws = cr.Workspace(plan)
+    G = torch.randn(info.num_slabs, d, device="cuda")
+    want, got = torch.empty(d, device="cuda"), torch.full((d + 4,), 7.0, device="cuda")
+    for mask in _masks(np.random.default_rng(d), 2, info.num_groups, n, s):
+        cr.cr_load_partial_grads(plan, G)
+        cr.cr_encode_tree(plan, mask)
+        cr.cr_decode_root(plan, want)
+        cr.cr_aggregate_static(plan, G, mask, got, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(got[:d], want) and bool((got[d:] == 7.0).all())
+    del ws
+    cr.cr_plan_destroy(plan)
