@@ -115,7 +115,7 @@ struct cr_plan_s {
     // layout of the workspace (offsets in bytes)
     size_t at_pieces = 0, at_team_piece_begin = 0, at_parts = 0, at_runs = 0, at_sums = 0, at_dst = 0, at_placement = 0, at_program = 0,
            at_node_begin = 0, at_slab_coef = 0, at_measures = 0, at_G = 0, at_residuals = 0, at_M = 0;
-    size_t off_slab = 0, off_level = 0, off_row = 0, off_coef = 0, off_acoef = 0, off_sub = 0;
+    size_t off_slab = 0, off_level = 0, off_row = 0, off_coef = 0, off_acoef = 0, off_sub = 0, off_dec = 0;
     size_t max_terms = 0;
 
     bool have_grads = false, have_messages = false;
@@ -359,6 +359,7 @@ void compute_layout(cr_plan_t *p, size_t *total)
     p->off_coef = off;  off = align_up(off + p->max_terms * sizeof(double), 256);
     p->off_acoef = off; off = align_up(off + p->max_terms * sizeof(double), 256);
     p->off_sub = off;   off = align_up(off + 2 * static_cast<size_t>(p->n) * sizeof(int32_t), 256);   // begin and end of every sub-program
+    p->off_dec = off;   off = align_up(off + p->n * sizeof(double), 256);
     p->program_bytes = off;
 
     size_t w = 0;
@@ -870,6 +871,8 @@ int build_program(cr_plan_t *p, const uint8_t *mask, char *h, ProgramCounts *cou
         sub[n + i] = sub[i] + static_cast<int32_t>(real_terms);
     }
     decode_terms(n, mask, rows[0], &counts->dec);
+    double *dec = reinterpret_cast<double *>(h + p->off_dec);
+    for (int j = 0; j < n; ++j) dec[j] = mask[j] ? 0.0 : rows[0][j];
     counts->terms = static_cast<int>(nt);                // padding included
     return CR_OK;
 }
@@ -915,6 +918,7 @@ cr::EncProgram program_view(const cr_plan_t *p, const char *d_program)
     prog.acoef = reinterpret_cast<const double *>(d_program + p->off_acoef);
     prog.sub_begin = reinterpret_cast<const int32_t *>(d_program + p->off_sub);
     prog.sub_end = prog.sub_begin + p->n;
+    prog.dec = reinterpret_cast<const double *>(d_program + p->off_dec);
     return prog;
 }
 
@@ -1095,11 +1099,37 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
     int rc = check_masks(p, masks, steps);
     if (rc != CR_OK) return rc;
     const int32_t N = p->tree.N;
+    if (cr::tree_and_decode_together(p->n, p->L, N, p->d)) {
+        cr::NodeCoefs coefs;
+        for (int t = 0; t < steps; ++t) {
+            ProgramCounts counts;
+            rc = build_coefs(p, masks + static_cast<size_t>(t) * N, &coefs, &counts);
+            if (rc != CR_OK) return rc;
+            p->G_src = G + static_cast<int64_t>(t) * G_step_stride;
+            p->have_grads = true;
+            rc = encode_decode(p, coefs, counts, g + static_cast<int64_t>(t) * g_step_stride, cr::GradientStep());
+            if (rc != CR_OK) return rc;
+        }
+        return CR_OK;
+    }
     ProgramCounts counts[kProgramSlots];
     for (int t0 = 0; t0 < steps; t0 += kProgramSlots) {
         const int count = std::min(kProgramSlots, steps - t0);
         rc = upload_programs(p, masks + static_cast<size_t>(t0) * N, count, counts);
         if (rc != CR_OK) return rc;
+        if (cr::encode_in_steps(p->n, p->L, p->d, count)) {
+            int64_t rows = 0;
+            for (int i = 0; i < count; ++i) rows += counts[i].active_slabs + counts[i].active_msgs + 1;
+            p->G_src = G + static_cast<int64_t>(t0 + count - 1) * G_step_stride;
+            p->have_grads = true;
+            LaunchTimer t(p, CR_K_ENCODE, rows * p->d * 4);
+            CR_HIP(cr::launch_encode_steps(G + static_cast<int64_t>(t0) * G_step_stride, G_step_stride, p->d_M, program_view(p, p->d_program), static_cast<int64_t>(p->program_bytes), count,
+                                           p->n, p->L, g + static_cast<int64_t>(t0) * g_step_stride, g_step_stride, p->d, p->stream));
+            t.done();
+            p->dec = counts[count - 1].dec;
+            p->have_messages = true;
+            continue;
+        }
         for (int i = 0; i < count; ++i) {
             p->G_src = G + static_cast<int64_t>(t0 + i) * G_step_stride;
             p->have_grads = true;

@@ -40,6 +40,15 @@ struct EncProgram {
     const double *acoef;
     const int32_t *sub_begin;    // first term of each sub-program, a multiple of kEncodeUnroll
     const int32_t *sub_end;      // one past its last real term; no-op terms pad it up to the next multiple of kEncodeUnroll
+    const double *dec;           // per level-1 node, what the master's decode takes of its message (0: nothing)
+#ifdef __HIPCC__
+    // the program that lies `bytes` further on
+    __device__ __forceinline__ EncProgram at(int64_t bytes) const
+    {
+        auto move = [&](auto *p) { return reinterpret_cast<decltype(p)>(reinterpret_cast<const char *>(p) + bytes); };
+        return {move(slab), move(level), move(row), move(coef), move(acoef), move(sub_begin), move(sub_end), move(dec)};
+    }
+#endif
 };
 
 struct DecTerms {            // the master's decode: g = sum of coef[j] * M[row[j]]; a kernel argument
@@ -120,6 +129,11 @@ hipError_t launch_wide_once(int x_dtype, const void *X, const float *y, const fl
                             hipStream_t stream);
 hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, const int32_t *dst, int64_t d, hipStream_t stream);
 hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int num_sub, int L, int64_t d, hipStream_t stream);
+// Encode and decode of `steps` masks, one after the other, in one launch (where encode_in_steps says so); the programs lie prog_stride
+// bytes apart.
+bool encode_in_steps(int n, int L, int64_t d, int steps);
+hipError_t launch_encode_steps(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L, float *g, int64_t g_stride, int64_t d,
+                               hipStream_t stream);
 // The same for trees of at most NodeCoefs::kNodes nodes and vectors of at most kTreeColumns columns (tree_side_by_side): a workgroup
 // per level-1 sub-tree and 16 chunks of columns, 64 from kTreeNarrowColumns on.  node_begin (one entry per node and one more) and
 // slab_coef: the slabs of every node and their coefficients.

@@ -147,6 +147,11 @@ template <> struct Chunk<1, 1> {
     static __device__ __forceinline__ void widen(const raw_t &r, float (&v)[1]) { v[0] = __uint_as_float(static_cast<uint32_t>(r) << 16); }
 };
 
+template <typename T> __device__ __forceinline__ T *at_byte(T *p, unsigned bytes)
+{
+    return reinterpret_cast<T *>(reinterpret_cast<std::conditional_t<std::is_const_v<T>, const char, char> *>(p) + bytes);
+}
+
 // VEC consecutive floats of an fp32 row (slab gradients, piece partials, messages)
 template <int VEC> __device__ __forceinline__ void load_row(const float *src, float (&v)[VEC])
 {
@@ -921,34 +926,22 @@ sum_rows_kernel(float *__restrict__ rows, const DevSum *__restrict__ sums, const
 // as a transmitted message would be) and folded into pending[level-1] with the parent's decode coefficient.  Child messages
 // therefore never come back from HBM; every active slab is read once and every message written once.  The program is the same for
 // every thread, so it is read with wide scalar loads, U terms at a time; the slab loads of those terms are all issued before the
-// first is used.  Slabs and messages are touched once: loads and stores are non-temporal.
+// first is used.  Slabs are touched once: non-temporal loads.  Messages of short vectors are written the ordinary way, since the decode
+// reads some of them and the next mask's replace them; those of long ones are non-temporal too (3 000 000 columns: 509 against 557 us).
 // A workgroup of BS threads covers BS*C*VEC contiguous columns of every row it touches.  Two shapes are used:
 //   narrow  C=1, U=8, fp64 accumulators: for short vectors, where the launch has few threads and latency decides;
 //   wide    C=32, U=1, fp32 accumulators: for long vectors.  A workgroup then streams 128 KB-aligned, 128 KB-long pieces of one
 //           slab at a time, which is what HBM likes best (the same 31-stream pattern read 4 KB at a time reaches 4.9 TB/s, this
 //           6.1 TB/s); the 32 chunks in flight fill the register file, hence fp32 accumulation: two or three extra roundings
 //           of the size of the message's own fp32 rounding.
-template <int VEC, int LT, int C, int BS, int U, typename acc_t>
-__global__ void __launch_bounds__(BS)
-encode_kernel(const float *__restrict__ G, float *__restrict__ M, EncProgram prog, int64_t d, int nq)
+// walk_sub_tree: terms [tb, te) of a program for a thread's C chunks, off bytes into a row; live: is the chunk in the row; top(c, out): the
+// finished message of the level-1 node.
+template <int VEC, int LT, int C, int U, bool NTS, typename acc_t, typename TOP>
+__device__ __forceinline__ void walk_sub_tree(const float *G, float *M, const EncProgram &prog, int tb, int te, int64_t d, const unsigned (&off)[C], const bool (&live)[C], TOP top)
 {
     static_assert(kEncodeUnroll % U == 0, "sub-programs are padded to kEncodeUnroll terms");
     typedef int iuv __attribute__((ext_vector_type(U)));
     typedef double duv __attribute__((ext_vector_type(U)));
-    const int q0 = blockIdx.x * (BS * C) + threadIdx.x;
-    if (q0 >= nq) return;
-    // whole groups of U terms: the padding terms are only fetched when U does not divide the real length
-    const int tb = prog.sub_begin[blockIdx.y], te = tb + (prog.sub_end[blockIdx.y] - tb + U - 1) / U * U;
-    // chunk c of this thread; a chunk past the end of the row is redirected to the row's last chunk and not stored
-    int64_t col[C];
-    bool live[C];
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-        const int q = q0 + c * BS;
-        live[c] = q < nq;
-        col[c] = chunk_offset<VEC>(q, nq, static_cast<int>(d));
-    }
-
     acc_t pend[LT + 1][C][VEC];
     acc_t own[C][VEC];
 #pragma unroll
@@ -961,17 +954,17 @@ encode_kernel(const float *__restrict__ G, float *__restrict__ M, EncProgram pro
         }
 
     for (int t = tb; t < te; t += U) {
-        const iuv slab = *reinterpret_cast<const iuv *>(prog.slab + t);
-        const iuv level = *reinterpret_cast<const iuv *>(prog.level + t);
-        const iuv row = *reinterpret_cast<const iuv *>(prog.row + t);
-        const duv coef = *reinterpret_cast<const duv *>(prog.coef + t);
-        const duv acoef = *reinterpret_cast<const duv *>(prog.acoef + t);
+        const iuv slab = *table(reinterpret_cast<const iuv *>(prog.slab + t));
+        const iuv level = *table(reinterpret_cast<const iuv *>(prog.level + t));
+        const iuv row = *table(reinterpret_cast<const iuv *>(prog.row + t));
+        const duv coef = *table(reinterpret_cast<const duv *>(prog.coef + t));
+        const duv acoef = *table(reinterpret_cast<const duv *>(prog.acoef + t));
         float xv[U][C][VEC];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const float *src = G + static_cast<int64_t>(slab[u]) * d;
+            const float *src = G + static_cast<int64_t>(slab[u]) * d;      // the same for all lanes: a scalar base and the lane's 32-bit offset
 #pragma unroll
-            for (int c = 0; c < C; ++c) load_row_nt<VEC>(src + col[c], xv[u][c]);
+            for (int c = 0; c < C; ++c) load_row_nt<VEC>(at_byte(src, off[c]), xv[u][c]);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -994,7 +987,11 @@ encode_kernel(const float *__restrict__ G, float *__restrict__ M, EncProgram pro
                         out[v] = static_cast<float>(msg);
                         own[c][v] = 0;
                     }
-                    if (live[c]) store_row_nt<VEC>(dst + col[c], out);
+                    if (live[c]) {
+                        if constexpr (NTS) store_row_nt<VEC>(at_byte(dst, off[c]), out);
+                        else store_row<VEC>(at_byte(dst, off[c]), out);
+                    }
+                    if (lvl == 1) top(c, out);
 #pragma unroll
                     for (int l = 1; l < LT; ++l)
                         if (l == lvl - 1) {
@@ -1004,6 +1001,77 @@ encode_kernel(const float *__restrict__ G, float *__restrict__ M, EncProgram pro
                 }
             }
         }
+    }
+}
+
+template <int VEC, int LT, int C, int BS, int U, bool NTS, typename acc_t>
+__global__ void __launch_bounds__(BS)
+encode_kernel(const float *__restrict__ G, float *__restrict__ M, EncProgram prog, int64_t d, int nq)
+{
+    const int q0 = blockIdx.x * (BS * C) + threadIdx.x;
+    if (q0 >= nq) return;
+    // whole groups of U terms: the padding terms are only fetched when U does not divide the real length
+    const int tb = prog.sub_begin[blockIdx.y], te = tb + (prog.sub_end[blockIdx.y] - tb + U - 1) / U * U;
+    // chunk c of this thread; a chunk past the end of the row is redirected to the row's last chunk and not stored
+    unsigned off[C];
+    bool live[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const int q = q0 + c * BS;
+        live[c] = q < nq;
+        off[c] = 4u * chunk_offset<VEC>(q, nq, static_cast<int>(d));
+    }
+    walk_sub_tree<VEC, LT, C, U, NTS, acc_t>(G, M, prog, tb, te, d, off, live, [](int, const float (&)[VEC]) {});
+}
+
+// Encode and decode of several masks, one after the other, in one launch: a workgroup owns 64 chunks of columns for all of them, its
+// wavefronts share out the level-1 sub-trees, whose messages meet in LDS for the decode (two sets in turn: one barrier per mask, after
+// which one wavefront decodes while the others go on).  No launches, ramps and last waves between the masks, and the master's messages
+// are not read back.  us a mask, a launch each for encode and decode / this: (2,4) tree, 2 000 000 columns, four masks 62.2 / 54.6;
+// (3,4), 60 001 columns, eight masks 17.3 / 12.1; (2,12), s = 5, 117 706 columns, eight masks 61.8 / 60.7 (rows on 8-byte boundaries;
+// 117 760 columns 56).  A single mask gains less, and groups of more than four nothing once their rows fill the chip many times over
+// ((2,8), 1 000 000 columns 174.8 / 177.6; (2,4), 2 000 000 65.5 / 60.5; (2,12), 60 000 44.5 / 42.0).
+// Slabs are read past the caches and messages are not written past them: the next mask's messages often replace them there (encode
+// alone, 117 706 columns: 59.6 against 61.8).
+template <int VEC, int LT>
+__global__ void __launch_bounds__(1024)
+encode_steps_kernel(const float *__restrict__ G, int64_t G_stride, float *__restrict__ M, EncProgram prog, int64_t prog_stride, int steps, int n, float *__restrict__ g, int64_t g_stride,
+                    int64_t d, int nq)
+{
+    extern __shared__ __align__(16) char step_lds[];
+    float *top = reinterpret_cast<float *>(step_lds);    // [2][n][VEC][64]
+    const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // workgroups are dealt to the eight dies in turn: neighbouring columns on one die, whose L2 joins the lines they share
+    const int block = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3), q = block * 64 + lane;
+    if (block * 64 >= nq) return;
+    const bool live[1] = {q < nq};
+    const unsigned off[1] = {4u * chunk_offset<VEC>(q, nq, static_cast<int>(d))};
+    for (int t = 0; t < steps; ++t) {
+        float *set = top + (t & 1) * n * VEC * 64;
+        EncProgram p = prog.at(t * prog_stride);
+        for (int i = wave; i < n; i += waves) {
+            const int tb = table(p.sub_begin)[i], te = tb + (table(p.sub_end)[i] - tb + kEncodeUnroll - 1) / kEncodeUnroll * kEncodeUnroll;
+            walk_sub_tree<VEC, LT, 1, kEncodeUnroll, false, double>(G + t * G_stride, M, p, tb, te, d, off, live, [&](int, const float (&out)[VEC]) {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) set[(i * VEC + v) * 64 + lane] = out[v];
+            });
+        }
+        __syncthreads();
+        if (wave != t % waves) continue;
+        double acc[VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
+        for (int j = 0; j < n; ++j) {
+            const double a = table(p.dec)[j];                   // zero: not used
+            if (a == 0.0) continue;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[v] = fma(a, static_cast<double>(set[(j * VEC + v) * 64 + lane]), acc[v]);
+        }
+        float out[VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) out[v] = static_cast<float>(acc[v]);
+        if (live[0]) store_row<VEC>(at_byte(g + t * g_stride, off[0]), out);
     }
 }
 
@@ -1563,30 +1631,57 @@ hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, const 
     return hipGetLastError();
 }
 
-template <int VEC, int C, int BS, int U, typename acc_t>
+template <int VEC, int C, int BS, int U, bool NTS, typename acc_t>
 static hipError_t launch_encode_shape(const float *G, float *M, const EncProgram &prog, int num_sub, int L, int64_t d, hipStream_t stream)
 {
     const int nq = static_cast<int>((d + VEC - 1) / VEC);
     const dim3 grid((nq + BS * C - 1) / (BS * C), num_sub), block(BS);
-    if (L <= 1) encode_kernel<VEC, 1, C, BS, U, acc_t><<<grid, block, 0, stream>>>(G, M, prog, d, nq);
-    else if (L == 2) encode_kernel<VEC, 2, C, BS, U, acc_t><<<grid, block, 0, stream>>>(G, M, prog, d, nq);
-    else if (L == 3) encode_kernel<VEC, 3, C, BS, U, acc_t><<<grid, block, 0, stream>>>(G, M, prog, d, nq);
+    if (L <= 1) encode_kernel<VEC, 1, C, BS, U, NTS, acc_t><<<grid, block, 0, stream>>>(G, M, prog, d, nq);
+    else if (L == 2) encode_kernel<VEC, 2, C, BS, U, NTS, acc_t><<<grid, block, 0, stream>>>(G, M, prog, d, nq);
+    else if (L == 3) encode_kernel<VEC, 3, C, BS, U, NTS, acc_t><<<grid, block, 0, stream>>>(G, M, prog, d, nq);
     else if constexpr (C == 1) {                         // deeper trees only in the narrow shape (the wide one would spill)
-        if (L == 4) encode_kernel<VEC, 4, C, BS, U, acc_t><<<grid, block, 0, stream>>>(G, M, prog, d, nq);
-        else encode_kernel<VEC, kMaxLevels, C, BS, U, acc_t><<<grid, block, 0, stream>>>(G, M, prog, d, nq);
+        if (L == 4) encode_kernel<VEC, 4, C, BS, U, NTS, acc_t><<<grid, block, 0, stream>>>(G, M, prog, d, nq);
+        else encode_kernel<VEC, kMaxLevels, C, BS, U, NTS, acc_t><<<grid, block, 0, stream>>>(G, M, prog, d, nq);
     } else return hipErrorInvalidValue;
     return hipGetLastError();
+}
+
+// wide shape once its 8192-chunk workgroups are enough to fill the chip, and only up to 3 levels (registers)
+static bool encode_is_wide(int n, int L, int64_t d) { return d >= 4 && ((d + 3) / 4 + 8191) / 8192 * n >= 256 && L <= 3; }
+
+template <int VEC>
+static hipError_t launch_encode_steps_shape(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L, float *g, int64_t g_stride,
+                                            int64_t d, hipStream_t stream)
+{
+    const int nq = static_cast<int>((d + VEC - 1) / VEC);
+    const unsigned groups = ((nq + 63) / 64 + 7) / 8 * 8, block = 64 * (n < 16 ? n : 16);
+    const size_t lds = static_cast<size_t>(2) * n * VEC * 64 * sizeof(float);
+    if (L <= 1) encode_steps_kernel<VEC, 1><<<groups, block, lds, stream>>>(G, G_stride, M, prog, prog_stride, steps, n, g, g_stride, d, nq);
+    else if (L == 2) encode_steps_kernel<VEC, 2><<<groups, block, lds, stream>>>(G, G_stride, M, prog, prog_stride, steps, n, g, g_stride, d, nq);
+    else if (L == 3) encode_steps_kernel<VEC, 3><<<groups, block, lds, stream>>>(G, G_stride, M, prog, prog_stride, steps, n, g, g_stride, d, nq);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+bool encode_in_steps(int n, int L, int64_t d, int steps)
+{
+    return n <= 32 && L <= 3 && !encode_is_wide(n, L, d) && (steps > 1 || n <= 4 || n * d <= (int64_t(1) << 22));
+}
+
+hipError_t launch_encode_steps(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L, float *g, int64_t g_stride, int64_t d,
+                               hipStream_t stream)
+{
+    return d >= 4 ? launch_encode_steps_shape<4>(G, G_stride, M, prog, prog_stride, steps, n, L, g, g_stride, d, stream)
+                  : launch_encode_steps_shape<1>(G, G_stride, M, prog, prog_stride, steps, n, L, g, g_stride, d, stream);
 }
 
 hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int num_sub, int L, int64_t d, hipStream_t stream)
 {
     if (d >= 4) {
-        // wide shape once its 8192-chunk workgroups are enough to fill the chip, and only up to 3 levels (registers)
-        const int64_t wide_groups = ((d + 3) / 4 + 8191) / 8192 * num_sub;
-        if (wide_groups >= 256 && L <= 3) return launch_encode_shape<4, 32, 256, 1, float>(G, M, prog, num_sub, L, d, stream);
-        return launch_encode_shape<4, 1, 256, 8, double>(G, M, prog, num_sub, L, d, stream);
+        if (encode_is_wide(num_sub, L, d)) return launch_encode_shape<4, 32, 256, 1, true, float>(G, M, prog, num_sub, L, d, stream);
+        return launch_encode_shape<4, 1, 256, 8, false, double>(G, M, prog, num_sub, L, d, stream);
     }
-    return launch_encode_shape<1, 1, 256, 8, double>(G, M, prog, num_sub, L, d, stream);
+    return launch_encode_shape<1, 1, 256, 8, false, double>(G, M, prog, num_sub, L, d, stream);
 }
 
 namespace {

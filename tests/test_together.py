@@ -76,3 +76,36 @@ def test_static_aggregation(L, n, s, d):
         assert torch.equal(got[:d], want) and bool((got[d:] == 7.0).all())
     del ws
     cr.cr_plan_destroy(plan)
+
+
+@pytest.mark.parametrize("L,n,s,d,steps", [(2, 3, 1, 3, 5), (2, 12, 5, 1_003, 19), (2, 3, 1, 32_769, 17), (1, 33, 1, 33_000, 2), (1, 32, 1, 33_001, 3), (3, 4, 1, 40_003, 2),
+                                            (4, 2, 1, 40_003, 2), (2, 8, 1, 81_921, 1), (2, 5, 1, 838_861, 1), (2, 4, 1, 1_048_580, 1), (2, 2, 0, 4_194_305, 2)])
+def test_runs_of_masks(L, n, s, d, steps):
+    """Both sides of the rules for one launch per mask, one for all of them, and two per mask: three calls per mask give the same bits.
+    The masks' vectors lie apart, with gaps that stay as they were."""
+    import torch
+
+    plan = cr.cr_plan_ex(L, n, s, 40 * n ** L, d, model=cr.CR_AGGREGATE_ONLY)
+    ws = cr.Workspace(plan)
+    S = ws.info.num_slabs
+    stride, apart = (S * d + 3) // 4 * 4 + 8, d + 5
+    G = torch.randn(steps * stride, device="cuda")
+    g = torch.full((steps, apart), 7.0, device="cuda")
+    masks = _masks(np.random.default_rng(d), steps, ws.info.num_groups, n, s)
+    want, M = torch.empty(d, device="cuda"), ws.messages()
+    M.zero_()
+    cr.cr_aggregate_run(plan, G, masks, g, G_step_stride=stride, g_step_stride=apart)
+    after = M.clone()
+    M.zero_()
+    for t in range(steps):
+        cr.cr_load_partial_grads(plan, G[t * stride:t * stride + S * d])
+        cr.cr_encode_tree(plan, masks[t])
+        cr.cr_decode_root(plan, want)
+        assert torch.equal(want, g[t, :d]) and bool((g[t, d:] == 7.0).all()), t
+    assert torch.equal(M, after)
+    again = torch.empty(d, device="cuda")                # the plan is left as the last mask's calls leave it
+    cr.cr_aggregate_run(plan, G, masks, g, G_step_stride=stride, g_step_stride=apart)
+    cr.cr_decode_root(plan, again)
+    assert torch.equal(again, want)
+    del ws
+    cr.cr_plan_destroy(plan)
