@@ -114,7 +114,7 @@ struct cr_plan_s {
     // layout of the program block (offsets in bytes, fixed per plan)
     // layout of the workspace (offsets in bytes)
     size_t at_pieces = 0, at_team_piece_begin = 0, at_parts = 0, at_runs = 0, at_sums = 0, at_dst = 0, at_placement = 0, at_program = 0,
-           at_node_begin = 0, at_slab_coef = 0, at_measures = 0, at_G = 0, at_residuals = 0, at_M = 0;
+           at_node_begin = 0, at_slab_coef = 0, tables_bytes = 0, at_measures = 0, at_G = 0, at_residuals = 0, at_M = 0;
     size_t off_slab = 0, off_level = 0, off_row = 0, off_coef = 0, off_acoef = 0, off_sub = 0, off_dec = 0;
     size_t max_terms = 0;
 
@@ -370,10 +370,11 @@ void compute_layout(cr_plan_t *p, size_t *total)
     p->at_runs = take(runs * sizeof(cr::DevRun));
     p->at_sums = take(p->model == CR_AGGREGATE_ONLY ? 0 : sums * sizeof(cr::DevSum));
     p->at_dst = take(p->model == CR_AGGREGATE_ONLY ? 0 : dst * sizeof(int32_t));
-    p->at_placement = take(kPlacementSlots * sizeof(uint32_t));
-    p->at_program = take(kProgramSlots * p->program_bytes);
     p->at_node_begin = take((N + 1) * sizeof(int32_t));
     p->at_slab_coef = take(S * sizeof(double));
+    p->tables_bytes = w;                                 // what the plan fills in at binding, in one copy
+    p->at_placement = take(kPlacementSlots * sizeof(uint32_t));
+    p->at_program = take(kProgramSlots * p->program_bytes);
     p->measures_stride = p->model == CR_AGGREGATE_ONLY ? 0 : 4 * static_cast<size_t>(std::max(cr::decode_groups(p->d), cr::tree_and_decode_together(p->n, p->L, p->tree.N, p->d) ? cr::tree_decode_groups(p->n, p->L, p->d) : 0));
     p->at_measures = take(kProgramSlots * p->measures_stride * sizeof(double));
     const size_t row = static_cast<size_t>(p->d) * sizeof(float);
@@ -684,6 +685,8 @@ try {
     p->d_M = reinterpret_cast<float *>(p->ws + p->at_M);
     p->G_src = p->d_G;
 
+    std::vector<char> tables(p->tables_bytes);
+    auto put = [&](size_t at, const auto &table) { if (!table.empty()) std::memcpy(tables.data() + at, table.data(), table.size() * sizeof table[0]); };
     std::vector<cr::DevSum> sums;
     std::vector<int32_t> dst;
     if (p->rows_once) {
@@ -697,8 +700,8 @@ try {
         }
         for (const cr::RowSum &sum : p->work.sums) sums.push_back({sum.row_begin, sum.row_end, sum.dst_begin, sum.dst_end});
         dst = p->work.dst;
-        CR_HIP(hipMemcpy(p->d_parts, parts.data(), parts.size() * sizeof(cr::DevRun), hipMemcpyHostToDevice));
-        CR_HIP(hipMemcpy(p->d_runs, runs.data(), runs.size() * sizeof(cr::DevRun), hipMemcpyHostToDevice));
+        put(p->at_parts, parts);
+        put(p->at_runs, runs);
     } else if (stage1) {
         // every piece's partial row lies where its slab's sum reads it: slab by slab, in row order
         std::vector<int32_t> out_row(P);
@@ -718,14 +721,15 @@ try {
             sums.push_back({S + p->split.slab_piece_begin[q], S + p->split.slab_piece_begin[q + 1], q, q + 1});
             dst.push_back(q);
         }
-        CR_HIP(hipMemcpy(p->d_pieces, hp.data(), P * sizeof(cr::DevPiece), hipMemcpyHostToDevice));
-        CR_HIP(hipMemcpy(p->d_team_piece_begin, p->split.team_piece_begin.data(), (p->split.teams + 1) * sizeof(int32_t), hipMemcpyHostToDevice));
+        put(p->at_pieces, hp);
+        put(p->at_team_piece_begin, p->split.team_piece_begin);
     }
     p->num_sums = static_cast<int>(sums.size());
-    if (!sums.empty()) CR_HIP(hipMemcpy(p->d_sums, sums.data(), sums.size() * sizeof(cr::DevSum), hipMemcpyHostToDevice));
-    if (!dst.empty()) CR_HIP(hipMemcpy(p->d_dst, dst.data(), dst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    CR_HIP(hipMemcpy(p->d_node_begin, p->node_slab_begin.data(), p->node_slab_begin.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    CR_HIP(hipMemcpy(p->d_slab_coef, p->slab_coef.data(), p->slab_coef.size() * sizeof(double), hipMemcpyHostToDevice));
+    put(p->at_sums, sums);
+    put(p->at_dst, dst);
+    put(p->at_node_begin, p->node_slab_begin);
+    put(p->at_slab_coef, p->slab_coef);
+    CR_HIP(hipMemcpy(p->ws, tables.data(), tables.size(), hipMemcpyHostToDevice));
     p->l2_sharing = -1;
     if (P > 0 && (p->split_kind_used == CR_SPLIT_ROW_CELLS || p->split_kind_used == CR_SPLIT_SHARED_CELLS)) {
         int rc = check_l2_sharing(p);
