@@ -370,6 +370,7 @@ class Workspace:
         self.info = cr_plan_info(plan)
         nbytes = cr_workspace_bytes(plan)
         self.buffer = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
+        self._floats = self.buffer.view(torch.float32)
         base = self.buffer.data_ptr()
         self.base = (base + 255) // 256 * 256
         self.nbytes = nbytes
@@ -378,12 +379,10 @@ class Workspace:
         self.info = cr_plan_info(plan)
 
     def _view(self, addr: int, rows: int):
-        import torch
-
         d = self.info.d
         off = addr - self.buffer.data_ptr()
         assert 0 <= off and off + rows * d * 4 <= self.buffer.numel()
-        return self.buffer[off:off + rows * d * 4].view(torch.float32).view(rows, d)
+        return self._floats.as_strided((rows, d), (d, 1), off // 4)
 
     def messages(self):
         """M[N][d] as a torch view of the workspace (rows of stragglers hold stale data)."""
