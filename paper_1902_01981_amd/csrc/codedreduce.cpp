@@ -75,6 +75,7 @@ struct cr_plan_s {
     const cr::Stage1Variant *variant_regs = nullptr;
     int cell_holders = 0;            // holders a workgroup of the shared-cells split serves; 0: no such split for this type and width
     cr::OnceWork work;               // `rows_once`: the runs and sums behind the split
+    const cr::OnceVariant *wide_variant = nullptr;     // wide rows in one pass; null: two passes
     int units = 0;                   // compute units the wide-row launches are sized for
     bool streams = false;            // rows_once: X is read past the caches
     bool rows_as_buffers = false;    // every row starts on a 4-byte boundary and every piece has fewer than 2^31 bytes
@@ -238,10 +239,19 @@ void make_rows_once(cr_plan_t *p, int64_t rows_per_run)
     cr::once_equal_parts(p->slabs, p->m, parts, rows_per_run, p->work);
 }
 
-// The same for wide rows: the parts of the second pass, each of which has one workgroup per block of columns.  Four workgroups per
-// compute unit, no fewer rows per part than a workgroup has in flight.
+// Rows of more than 24 576 columns whose weights fit LDS take one pass from this size of X on.  Below it the partial rows of a part per
+// compute unit cost more than the second pass (us with sums, one pass / two: 300 x 30 000 bf16 22.8 / 18.2, 600 x 30 000 bf16 24.9 / 24.2,
+// 1 200 x 26 000 bf16, 62 MB, 28.3 / 31.7, 700 x 32 000 fp32, 90 MB on a (12,2) tree, 41.8 / 46.5, 3 000 x 30 001 fp32 78 / 118,
+// 6 000 x 32 768 fp32 141 / 249).
+constexpr int64_t kWideOnePassBytes = int64_t(48) << 20;
+
+// The same for wide rows.  Where they take one pass: a part per compute unit, at least four rows.  Where they take two: the parts of the
+// second pass, each of which has one workgroup per block of columns; four workgroups per compute unit, no fewer rows per part than a
+// workgroup has in flight.
 void make_wide_once(cr_plan_t *p, int64_t rows_per_run)
 {
+    p->wide_variant = p->m * p->d * elem_size(p) >= kWideOnePassBytes ? cr::select_once_wide(p->x_dtype, p->d) : nullptr;
+    if (p->wide_variant) return cr::once_equal_parts(p->slabs, p->m, std::max<int64_t>(1, std::min<int64_t>(query_units(), p->m / 4)), rows_per_run, p->work);
     const int64_t vec = p->x_dtype == CR_BF16 ? 8 : 4, blocks = ((p->d + vec - 1) / vec + cr::kWideColumnChunks - 1) / cr::kWideColumnChunks;
     p->units = query_units();
     const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(4 * static_cast<int64_t>(p->units) / blocks, p->m / 16));
@@ -254,6 +264,7 @@ int make_split(cr_plan_t *p)
     int64_t value = p->split_value;
     p->variant = nullptr;
     p->once = nullptr;
+    p->wide_variant = nullptr;
     p->rows_once = false;
     p->work = cr::OnceWork();
     const int domains = query_l2_domains();
@@ -380,7 +391,7 @@ void compute_layout(cr_plan_t *p, size_t *total)
     const size_t row = static_cast<size_t>(p->d) * sizeof(float);
     if (p->model != CR_AGGREGATE_ONLY) {
         p->at_G = take((S + (p->rows_once ? p->work.partials : P)) * row);
-        p->at_residuals = take(p->once || p->variant ? 0 : static_cast<size_t>(p->rows_once ? p->m : p->row_visits) * sizeof(float));
+        p->at_residuals = take(p->once || p->wide_variant || p->variant ? 0 : static_cast<size_t>(p->rows_once ? p->m : p->row_visits) * sizeof(float));
     }
     p->at_M = take(N * row);
     *total = w;
@@ -759,8 +770,9 @@ int cr_partial_grads(cr_plan_t *p, const void *X, const float *y, const float *w
         // what the method must move: every holder reads its rows and targets once, each slab gradient is written once
         const int64_t bytes = p->row_visits * p->d * elem_size(p) + p->row_visits * 4 + S * p->d * 4 + p->d * 4;
         LaunchTimer t(p, CR_K_PARTIAL_GRADS, bytes);
-        if (p->once) {
-            CR_HIP(cr::launch_rows_once(*p->once, X, y, w, p->d_parts, static_cast<int>(p->work.part_run_begin.size()) - 1, p->d_runs, p->d_dst,
+        const cr::OnceVariant *once = p->once ? p->once : p->wide_variant;
+        if (once) {
+            CR_HIP(cr::launch_rows_once(*once, X, y, w, p->d_parts, static_cast<int>(p->work.part_run_begin.size()) - 1, p->d_runs, p->d_dst,
                                         p->d_G, p->d, logistic, p->streams, p->stream));
         } else if (p->rows_once) {
             const int64_t cached_from = std::max<int64_t>(0, p->m - kKeptBytes / (p->d * elem_size(p)));

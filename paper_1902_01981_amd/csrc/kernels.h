@@ -102,6 +102,8 @@ struct OnceVariant {
 };
 // For (x_dtype, d), or nullptr if the row is too wide for the registers of a workgroup.
 const OnceVariant *select_once(int x_dtype, int64_t d);
+// The same for rows one and a half times as wide as those of select_once, or nullptr: their weights are in LDS.
+const OnceVariant *select_once_wide(int x_dtype, int64_t d);
 // The same with as many wavefronts per workgroup as there are for rows this narrow, for launches of a few workgroups.
 const OnceVariant *select_once_whole(int x_dtype, int64_t d);
 // Workgroup b runs parts[b], then runs[parts[b].more_begin .. more_end).  rows: the output table.

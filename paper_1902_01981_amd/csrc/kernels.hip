@@ -561,7 +561,11 @@ rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const 
 // per step exchanges the wavefronts' parts of the dot products (double buffered in LDS).  PF: the next step's rows are loaded before
 // the current step is computed; beyond 9 chunks per thread the second register set costs more than it hides (a row is then long
 // enough: 12 chunks, 24576 columns, 3.2 GB: 497 us without, 604 with it).
-template <int XD, int VEC, int TS, int K, int R, bool PF, bool NT>
+// WL: the weights are in LDS, every thread's in slots of its own, which leaves the registers for rows half as wide again, 34 816 fp32 or
+// 36 864 bf16 columns, that took two passes (stage 1 in us, two passes / this: 6 000 x 32 768 fp32 245 / 133, 3 000 x 30 001 fp32 115 / 70,
+// 10 000 x 36 864 bf16 225 / 141, 4 000 x 25 000 bf16 68 / 38).  Up to 12 fp32 chunks per thread it gains nothing, not with the next
+// row's loads ahead either (3 000 x 24 000: 56.9 without, 58.7 with both).
+template <int XD, int VEC, int TS, int K, int R, bool PF, bool WL, bool NT>
 __global__ void __launch_bounds__(TS)
 rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w, const DevRun *__restrict__ parts,
                       const DevRun *__restrict__ runs, const int32_t *__restrict__ dst, float *__restrict__ rows, int d, int nq, int logistic)
@@ -576,15 +580,21 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
     int next = part->more_begin;
     Run run = read_run(part);
 
-    unsigned off[K];
-    float wv[K][VEC];
+    // only a thread's last chunk can be the row's last one or past it: the others lie k * TS chunks after the first
+    constexpr unsigned kElem = XD == 1 ? 2 : 4;
+    const unsigned off = tl * VEC, off_last = chunk_offset<VEC>(tl + (K - 1) * TS, nq, d);
+    float wv[WL ? 1 : K][VEC];
+    __shared__ f4a wl[WL ? K : 1][WL ? VEC / 4 : 1][WL ? TS : 1];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int q = tl + k * TS;
-        off[k] = chunk_offset<VEC>(q, nq, d);
-        load_row<VEC>(w + off[k], wv[k]);
+        float (&t)[VEC] = wv[WL ? 0 : k];
+        load_row<VEC>(w + (k < K - 1 ? k * TS * VEC + off : off_last), t);
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) wv[k][v] = chunk_owns<VEC>(q, v, nq, d) ? wv[k][v] : 0.f;
+        for (int v = 0; v < VEC; ++v) t[v] = chunk_owns<VEC>(q, v, nq, d) ? t[v] : 0.f;
+        if constexpr (WL)
+#pragma unroll
+            for (int i = 0; i < VEC / 4; ++i) wl[k][i][tl] = f4a{t[4 * i], t[4 * i + 1], t[4 * i + 2], t[4 * i + 3]};
     }
 
     struct Step {
@@ -608,7 +618,11 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
                 const void *row = row_ptr<XD>(base, at, d);
                 s.yy[r] = yb[at];
 #pragma unroll
-                for (int k = 0; k < K; ++k) s.x[r][k] = NT ? C::load_once(row, off[k]) : C::load(row, off[k]);
+                for (int k = 0; k < K; ++k) {
+                    const void *from = static_cast<const char *>(row) + (k < K - 1 ? k * TS * VEC * kElem : 0u);
+                    const unsigned e = k < K - 1 ? off : off_last;
+                    s.x[r][k] = NT ? C::load_once(from, e) : C::load(from, e);
+                }
             }
         };
         auto compute = [&](const Step &s, int r0) {
@@ -619,8 +633,19 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
                 for (int k = 0; k < K; ++k) {
                     float xv[VEC];
                     C::widen(s.x[r][k], xv);
+                    if constexpr (WL) {
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) t[k & 1] = fmaf(xv[v], wv[k][v], t[k & 1]);
+                        for (int i = 0; i < VEC / 4; ++i) {
+                            const f4a wt = wl[k][i][tl];
+                            t[k & 1] = fmaf(xv[4 * i], wt.x, t[k & 1]);
+                            t[k & 1] = fmaf(xv[4 * i + 1], wt.y, t[k & 1]);
+                            t[k & 1] = fmaf(xv[4 * i + 2], wt.z, t[k & 1]);
+                            t[k & 1] = fmaf(xv[4 * i + 3], wt.w, t[k & 1]);
+                        }
+                    } else {
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) t[k & 1] = fmaf(xv[v], wv[k][v], t[k & 1]);
+                    }
                 }
                 const float dot = group_sum<64>(t[0] + t[1]);
                 if ((tl & 63) == 0) red[buf][r][wave] = dot;
@@ -663,7 +688,7 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
                 float sum[VEC];
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) sum[v] = static_cast<float>(acc[k][v]);
-                if (tl + k * TS < nq) store_row<VEC>(out + off[k], sum);
+                if (tl + k * TS < nq) store_row<VEC>(out + (k < K - 1 ? k * TS * VEC + off : off_last), sum);
             }
         }
         if (next >= more) break;
@@ -672,7 +697,8 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
 }
 
 // ---- stage 1 for wide rows, every row once ---------------------------------------------------------------------------
-// A row whose accumulators do not fit the registers of a workgroup is read twice: first the residuals phi(x.w) - y of every row
+// A row whose accumulators do not fit the registers of a workgroup, even with the weights in LDS, is read twice (and wide rows of small
+// matrices are, whose partial rows would cost more): first the residuals phi(x.w) - y of every row
 // (R rows per workgroup, so that the weights, twice the size of a bf16 row, come out of the L2 once for R rows), then X^T r by
 // blocks of columns and parts of rows.  Both passes are bound by the read of X.  The rows from cached_from on are read with plain
 // loads and stay in the last-level cache for the second pass, which takes the parts from the end; the rest streams past (NT).
@@ -1453,8 +1479,12 @@ const Stage1Variant kVariants[] = {
       reinterpret_cast<const void *>(&rows_once_kernel<XD, VEC, LPR, K, R, WAVES, true>)}}
 #define CR_OT(XD, VEC, TS, K, R, PF)                                                                    \
     {XD, VEC, TS, K, R, TS, XD == 1 && TS == 128 ? 2 : 1,                                               \
-     {reinterpret_cast<const void *>(&rows_once_team_kernel<XD, VEC, TS, K, R, PF, false>),             \
-      reinterpret_cast<const void *>(&rows_once_team_kernel<XD, VEC, TS, K, R, PF, true>)}}
+     {reinterpret_cast<const void *>(&rows_once_team_kernel<XD, VEC, TS, K, R, PF, false, false>),      \
+      reinterpret_cast<const void *>(&rows_once_team_kernel<XD, VEC, TS, K, R, PF, false, true>)}}
+#define CR_OW(XD, VEC, K, PF)                                                                           \
+    {XD, VEC, 512, K, 1, 512, 1,                                                                        \
+     {reinterpret_cast<const void *>(&rows_once_team_kernel<XD, VEC, 512, K, 1, PF, true, false>),      \
+      reinterpret_cast<const void *>(&rows_once_team_kernel<XD, VEC, 512, K, 1, PF, true, true>)}}
 const OnceVariant kOnceVariants[] = {
     // fp32: up to 256 chunks (1024 columns) a wavefront or a part of one per row ...
     CR_O(0, 4, 2, 1, 4, 4), CR_O(0, 4, 4, 1, 4, 4), CR_O(0, 4, 8, 1, 4, 4), CR_O(0, 4, 16, 1, 4, 4), CR_O(0, 4, 32, 1, 4, 4),
@@ -1478,6 +1508,11 @@ const OnceVariant kOnceVariants[] = {
     CR_OT(1, 8, 512, 6, 1, true),
     // rows shorter than one wide chunk: one column per lane
     CR_O(0, 1, 4, 1, 4, 4), CR_O(1, 1, 8, 1, 4, 4),
+};
+// wide rows whose weights fit LDS
+const OnceVariant kOnceVariantsWide[] = {
+    CR_OW(0, 4, 13, false), CR_OW(0, 4, 14, false), CR_OW(0, 4, 15, false), CR_OW(0, 4, 16, false), CR_OW(0, 4, 17, false),
+    CR_OW(1, 8, 7, true), CR_OW(1, 8, 8, false), CR_OW(1, 8, 9, false),
 };
 // one row per wavefront or less, sixteen wavefronts: for launches of a few workgroups that each have a whole slab range to do
 const OnceVariant kOnceVariants16[] = {
@@ -1524,6 +1559,7 @@ const OnceVariant *find_once(const OnceVariant *begin, const OnceVariant *end, i
 }  // namespace
 
 const OnceVariant *select_once(int x_dtype, int64_t d) { return find_once(std::begin(kOnceVariants), std::end(kOnceVariants), x_dtype, d); }
+const OnceVariant *select_once_wide(int x_dtype, int64_t d) { return find_once(std::begin(kOnceVariantsWide), std::end(kOnceVariantsWide), x_dtype, d); }
 const OnceVariant *select_once_whole(int x_dtype, int64_t d)
 {
     const OnceVariant *v = find_once(std::begin(kOnceVariants16), std::end(kOnceVariants16), x_dtype, d);
