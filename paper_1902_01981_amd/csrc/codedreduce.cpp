@@ -210,8 +210,9 @@ int shared_cell_holders(int x_dtype, int64_t d, int64_t max_holders)
     return max_holders >= 3 && nq <= 1536 ? 4 : 2;
 }
 
-// Bytes of X that the first pass over wide rows leaves in the 256 MB last-level cache for the second.
-constexpr int64_t kKeptBytes = int64_t(160) << 20;
+// Bytes of X that the first pass over wide rows leaves in the 256 MB last-level cache for the second (both passes over 400 MB, 4 000 x 50 008
+// bf16, with 0, 64, 160 and 220 MB: 142.6, 136.8, 132.9 and 129.8 us; 200 and 240 MB take the same as 220).
+constexpr int64_t kKeptBytes = int64_t(200) << 20;
 
 int64_t longest_range(const cr_plan_t *p)
 {
@@ -246,15 +247,16 @@ void make_rows_once(cr_plan_t *p, int64_t rows_per_run)
 constexpr int64_t kWideOnePassBytes = int64_t(48) << 20;
 
 // The same for wide rows.  Where they take one pass: a part per compute unit, at least four rows.  Where they take two: the parts of the
-// second pass, each of which has one workgroup per block of columns; four workgroups per compute unit, no fewer rows per part than a
-// workgroup has in flight.
+// second pass, each of which has one workgroup per block of columns; two workgroups per compute unit, no fewer rows per part than a
+// workgroup has in flight (4 000 x 50 008 bf16 with one, two, four and eight: 123, 124, 130 and 138 us, 4 000 x 60 000 fp32 290, 281, 287 and
+// more; fewer partial rows to add up as well).
 void make_wide_once(cr_plan_t *p, int64_t rows_per_run)
 {
     p->wide_variant = p->m * p->d * elem_size(p) >= kWideOnePassBytes ? cr::select_once_wide(p->x_dtype, p->d) : nullptr;
     if (p->wide_variant) return cr::once_equal_parts(p->slabs, p->m, std::max<int64_t>(1, std::min<int64_t>(query_units(), p->m / 4)), rows_per_run, p->work);
     const int64_t vec = p->x_dtype == CR_BF16 ? 8 : 4, blocks = ((p->d + vec - 1) / vec + cr::kWideColumnChunks - 1) / cr::kWideColumnChunks;
     p->units = query_units();
-    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(4 * static_cast<int64_t>(p->units) / blocks, p->m / 16));
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(2 * static_cast<int64_t>(p->units) / blocks, p->m / 16));
     cr::once_equal_parts(p->slabs, p->m, parts, rows_per_run, p->work);
 }
 

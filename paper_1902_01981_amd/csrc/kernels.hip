@@ -702,7 +702,7 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
 // (R rows per workgroup, so that the weights, twice the size of a bf16 row, come out of the L2 once for R rows), then X^T r by
 // blocks of columns and parts of rows.  Both passes are bound by the read of X.  The rows from cached_from on are read with plain
 // loads and stay in the last-level cache for the second pass, which takes the parts from the end; the rest streams past (NT).
-// 4000 x 50008 bf16 (400 MB) on a (2,4) tree with s = 1: 63 and 67 us, the whole iteration 160 us; every holder's rows read for itself,
+// 4000 x 50008 bf16 (400 MB) on a (2,4) tree with s = 1: both 124 us, the whole iteration 154 us; every holder's rows read for itself,
 // in cells of 16 rows, took 1683 us.
 template <int XD, int VEC, int R>
 __global__ void __launch_bounds__(512)
