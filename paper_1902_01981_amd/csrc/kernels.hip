@@ -1357,8 +1357,9 @@ tree_decode_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES ta
 // The terms come as kernel arguments.  A thread owns C chunks of columns, 256 chunks apart, and has U rows of them in flight: eight rows
 // of one chunk where latency decides, one row of four chunks, past the caches, for long vectors, where HBM prefers long pieces of one
 // row (six rows of 16 777 216 columns: 92 us with eight rows of one chunk, 83 one by one, 79 in this shape; 4 000 000: 23.4, 23.2, 22.3;
-// 1 000 000: 8.7, 8.6, 8.5).
-constexpr int64_t kDecodeLongColumns = int64_t(1) << 20;
+// 1 000 000: 8.7, 8.6, 8.5; two rows of 2 500 000: 8.8 one by one, 8.4 in this shape, of 1 634 474, where its 400 workgroups fill the chip one
+// and a half times: 7.4, 8.1).
+constexpr int64_t kDecodeLongColumns = int64_t(1) << 21;
 template <int VEC, int U, int C, bool NT>
 __global__ void __launch_bounds__(256)
 decode_kernel(const float *__restrict__ M, float *__restrict__ g, DecTerms terms, GradientStep step, int64_t d, int nq)
