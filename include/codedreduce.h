@@ -69,7 +69,7 @@ typedef struct cr_plan_info {
     int32_t num_teams;       /* stage-1 work split (0 until known, see cr_plan_set_split) */
     int32_t num_pieces;      /* entries of cr_plan_get_pieces (0 until the split is known) */
     int32_t split_kind;      /* enum cr_split of the split in force; -1 until it is known */
-    int32_t stage1_team_size;       /* threads that share one row in the stage-1 kernel in force; 0: two-pass path for very wide rows */
+    int32_t stage1_team_size;       /* threads that share one row in the stage-1 kernel in force; 0: rows of more than 24576 columns */
     int32_t stage1_teams_per_group; /* teams per workgroup; shared cells: holders of a cell that a workgroup serves */
     int32_t stage1_staged;   /* 1 under shared cells: rows are fetched once per workgroup for all the holders it serves */
     int64_t m, d;
@@ -130,15 +130,17 @@ int cr_plan_decode_row(const cr_plan_t *plan, const uint8_t *flags /* host, n */
  *                          3072 16-byte chunks with s > 0 only, else CR_E_INVAL.
  *   CR_SPLIT_ROWS_ONCE     value = most rows per run: X is cut into one or two contiguous parts per compute unit, a part into runs at
  *                          slab boundaries and after `value` rows; a workgroup forms every row of its part once, for all slabs that
- *                          hold it, and adds a run up in fp64 (all but the up to four rows it has in hand at a time).  Rows too wide
- *                          for the registers of a workgroup (d > 24576) take two passes over X, the second cut into parts of rows
- *                          and blocks of columns.  CR_ROWS_WHOLE_RANGES as value (d <= 24576): a workgroup per distinct slab range,
+ *                          hold it, and adds a run up in fp64 (all but the up to four rows it has in hand at a time).  Rows of more
+ *                          than 24576 columns take one pass where their weights fit LDS (34816 columns fp32, 36864 bf16), X has
+ *                          48 MB and more and `value` is at most a compute unit's share of the rows; else two passes, the second cut
+ *                          into parts of rows and blocks of columns.  CR_ROWS_WHOLE_RANGES as value (d <= 24576): a workgroup per distinct slab range,
  *                          which it adds up whole; rows of ranges that overlap are then formed once per range.
  * With the first two every holder of a row does its own arithmetic on it, as separate workers would: they are there to measure what
  * the redundancy of a scheme costs (with s = 0 no row has a second holder, and equal ranges run the kernels of rows once, a
  * workgroup per team).  With the other two the holders' identical sums are formed once (per workgroup) and handed to
  * every slab they belong to.  The slab gradients agree to rounding under every split.
- * Default (when this is never called): rows once, for the smallest problems by whole ranges.  With X of 1 GiB and more: equal ranges of the rows when s = 0 (no row is held twice), shared cells where one workgroup serves all holders of a
+ * Default (when this is never called): rows once, for the smallest problems by whole ranges, else without a limit on runs (wide rows that
+ * can take one pass: a compute unit's share of the rows).  With X of 1 GiB and more: equal ranges of the rows when s = 0 (no row is held twice), shared cells where one workgroup serves all holders of a
  * row, with the cell height (16 to 1024 rows) that gives the shortest longest queue. */
 enum cr_split { CR_SPLIT_EQUAL_RANGES = 0, CR_SPLIT_ROW_CELLS = 1, CR_SPLIT_SHARED_CELLS = 2, CR_SPLIT_ROWS_ONCE = 3 };
 #define CR_ROWS_WHOLE_RANGES ((int64_t)1 << 62)
@@ -160,9 +162,9 @@ int cr_simulate_iteration(const cr_plan_t *plan, double a, double mu, double t_c
                           uint8_t *mask, double *ready, double *total);
 
 /* ---- device binding --------------------------------------------------------------------------------------------
- * The workspace holds the device tables, 16 encode programs, the stage-1 partial rows, the slab gradients
+ * The workspace holds the device tables, 16 encode programs (for trees and vectors whose encode takes programs), the stage-1 partial rows, the slab gradients
  * G[S][d] (not for CR_AGGREGATE_ONLY) and the messages M[N][d], all fp32 rows of d floats.  dev_ptr must be 256-byte aligned and stay valid while the plan
- * is used; hip_stream is a hipStream_t (NULL = the default stream).  cr_bind_workspace copies the tables synchronously. */
+ * is used; hip_stream is a hipStream_t (NULL = the default stream).  cr_bind_workspace copies the tables synchronously, in one copy. */
 int cr_workspace_bytes(cr_plan_t *plan, size_t *bytes);
 int cr_bind_workspace(cr_plan_t *plan, void *dev_ptr, size_t bytes, void *hip_stream);
 
@@ -170,7 +172,7 @@ int cr_bind_workspace(cr_plan_t *plan, void *dev_ptr, size_t bytes, void *hip_st
  * cr_partial_grads (CR.Execute step 1): for every slab p,  G[p] = X[b:e]^T (phi(X[b:e] w) - y[b:e]),  phi = identity or sigmoid.
  *   X_dev  m x d row-major, contiguous, fp32 or bf16 per the plan, 16-byte aligned;  y_dev m floats;  w_dev d floats.
  *   One pass over X as long as a row fits the registers of a workgroup (d <= 24576, whether or not d is a multiple of the 16-byte
- *   chunk); wider rows take two passes.  Every slab of every worker is written; what the workers that hold a row have in common is
+ *   chunk) or its weights LDS beside them (34816 fp32, 36864 bf16, from 48 MB of X on); other rows take two passes.  Every slab of every worker is written; what the workers that hold a row have in common is
  *   formed once for all of them unless the split says otherwise (see cr_plan_set_split).
  * cr_load_partial_grads: use caller-supplied slab gradients G_dev[S][d] (fp32, 16-byte aligned) in place of stage 1;
  *   the buffer is read in place by cr_encode_tree and must stay valid until then.
@@ -178,6 +180,8 @@ int cr_bind_workspace(cr_plan_t *plan, void *dev_ptr, size_t bytes, void *hip_st
  *   m_(l,i) = sum_p coef_p G[p] over its slabs  +  sum_j a_j m_(l+1, n i + j)  with a = the decode row of its children group.
  *   Stragglers write no message (their row of M keeps stale data); all other nodes do, also below a straggler.
  *   CR_E_UNDECODABLE, before anything is enqueued and with no state change, if any group has more than s stragglers.
+ *   On trees of at most 448 workers with vectors of at most 81920 columns all it enqueues is one kernel launch, with what the mask
+ *   decides as kernel arguments; else the mask's encode program travels in a copy from pinned memory first.
  * cr_decode_root (the last step of CR.Execute, Algorithm 2: the master recovers g from any n-s of its children):
  *   g_dev[d] = sum_j a_j m_(1,j) with the decode row of group 0 from the last cr_encode_tree; by eq. (3) this is the full gradient.
  * cr_gd_update: w <- w - lr * g (plain gradient step used by the benchmark loop).
@@ -189,20 +193,23 @@ int cr_decode_root(cr_plan_t *plan, float *g_dev);
 int cr_gd_update(cr_plan_t *plan, float *w_dev, const float *g_dev, float lr);
 
 /* Gradient descent loop kept on the device (eq. (2) with a plain step): `steps` times  g = CodedReduce(w);  w <- w - lr g,  enqueued
- * back to back.  The encode programs of 16 steps at a time travel to the device in one copy, so a step is kernel launches only; the
- * host waits only when it runs more than 32 steps ahead of the copies (two pinned staging batches).
+ * back to back, kernel launches only where cr_encode_tree is one: stage 1, its sums, and one launch for encode, decode and the gradient
+ * step (two for d > 32768).  Elsewhere the encode programs of 16 steps at a time travel to the device in one copy, and the host waits
+ * only when it runs more than 32 steps ahead of the copies (two pinned staging batches).
  *   masks_host      steps x N bytes, one straggler mask per step; all are checked first: CR_E_UNDECODABLE before anything is enqueued
  *   w_dev, g_dev    d floats each; w is updated in place, g holds the last decoded gradient
  *   w_star_or_null  d floats (device): the reference model of the normalised error rate, or NULL
  *   metrics_or_null device, steps x 2 floats: [2t] = ||w_t+1 - w_t||^2 / ||w_t||^2 (relative error rate, eq. (6)),
- *                   [2t+1] = ||w_t+1 - w*||^2 / ||w*||^2 (normalised error rate, eq. (8); -1 without w*); NULL = plain update,
- *                   which then rides in the decode launch (the same arithmetic as cr_gd_update, one launch fewer per step) */
+ *                   [2t+1] = ||w_t+1 - w*||^2 / ||w*||^2 (normalised error rate, eq. (8); -1 without w*); NULL = not wanted.  The sums
+ *                   behind them are formed by the launch that makes the step, the quotients by one launch per 16 steps */
 int cr_gd_run(cr_plan_t *plan, const void *X_dev, const float *y_dev, float *w_dev, float *g_dev, const uint8_t *masks_host,
               int steps, float lr, const float *w_star_or_null, float *metrics_or_null);
 
 /* Aggregation alone, many masks in one call (CR.Execute steps 2 to the end, Algorithm 2, once per mask): step t encodes the slab
  * gradients at G_dev + t * G_step_stride under masks_host[t] and decodes into g_dev + t * g_step_stride; like cr_load_partial_grads,
- * cr_encode_tree and cr_decode_root called in turn (the same bits), but with the programs of 16 steps per host-to-device copy.
+ * cr_encode_tree and cr_decode_root called in turn (the same bits).  Short vectors (d <= 32768) take one launch per mask; longer ones on
+ * trees of up to three levels and 32 children per parent one launch for up to 16 masks, behind one copy of their programs; very long
+ * ones two launches per mask.
  *   G_dev          device, S x d floats per step, 16-byte aligned; G_step_stride in floats (a multiple of 4): 0 = the same slabs every step
  *   masks_host     steps x N bytes; all are checked first: CR_E_UNDECODABLE before anything is enqueued
  *   g_dev          device, d floats per step; g_step_stride in floats: 0 = every step overwrites the same vector
@@ -215,8 +222,9 @@ int cr_aggregate_run(cr_plan_t *plan, const float *G_dev, int64_t G_step_stride,
  * hipMalloc.  cr_aggregate_static is cr_load_partial_grads + cr_encode_tree + cr_decode_root in one call, with everything those
  * keep in a workspace -- the per-call encode program and the messages M[N][d] -- held in a device array that is part of the library
  * itself (CR_STATIC_SCRATCH_BYTES; each GPU the library runs on holds one until the process ends).  The plan needs no workspace.
- * The call allocates and frees nothing on the device or in pinned memory and records no copy: the program reaches the device as
- * kernel arguments, so all it enqueues on hip_stream is kernel launches (a handful of small ones, encode, decode).
+ * The call allocates and frees nothing on the device or in pinned memory and records no copy: what the kernels need reaches the device
+ * as kernel arguments, so all it enqueues on hip_stream is kernel launches: one for encode and decode where the tree's tables fit the
+ * arguments and d <= 32768, two up to 81920 columns, else a few small ones that write the program out, encode and decode.
  *   plan        any plan; its model is not consulted (no stage 1 runs)
  *   G_dev       device, S x d floats, 16-byte aligned: the slab gradients, read in place
  *   mask_host   host, N bytes, non-zero = straggler; read before the call returns
@@ -239,7 +247,9 @@ int cr_get_messages(const cr_plan_t *plan, const float **M_dev);   /* N x d, row
  * bound stream from now on (CR_PROFILE_ALL: all of them, 0: none); a non-zero call also clears the totals.  Each bracket costs
  * a few microseconds of device time, which shows on small problems.  cr_profile_read waits for the stream, then returns for one
  * kernel id the summed duration, the number of launches and the algorithmic bytes of those launches (bytes the method must
- * move: rows read once per holder, each result written once) since the last non-zero cr_profile_enable; any may be NULL.
+ * move: rows read once per holder, each result written once) since the last non-zero cr_profile_enable; any may be NULL.  A launch that does the
+ * work of several counts once, with all its bytes: encode, decode and gradient step in one as CR_K_ENCODE, decode and step as CR_K_DECODE;
+ * CR_K_UPDATE is cr_gd_update and the convergence measures.
  * Totals read after cr_profile_enable(plan, 0) are those gathered until then. */
 #define CR_PROFILE_ALL ((1 << CR_K_COUNT) - 1)
 int cr_profile_enable(cr_plan_t *plan, int kernels);

@@ -246,14 +246,25 @@ void make_rows_once(cr_plan_t *p, int64_t rows_per_run)
 // 6 000 x 32 768 fp32 141 / 249).
 constexpr int64_t kWideOnePassBytes = int64_t(48) << 20;
 
-// The same for wide rows.  Where they take one pass: a part per compute unit, at least four rows.  Where they take two: the parts of the
+// One pass over wide rows: a part per compute unit, at least four rows; the most rows that a part has, or 0: two passes.
+int64_t wide_one_pass_rows(const cr_plan_t *p)
+{
+    if (p->m * p->d * elem_size(p) < kWideOnePassBytes || !cr::select_once_wide(p->x_dtype, p->d)) return 0;
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(query_units(), p->m / 4));
+    return (p->m + parts - 1) / parts;
+}
+
+// The same for wide rows.  One pass where that is possible and runs of no more rows are asked for than its parts have, which the default
+// split does; longer runs take two passes, where parts are long.  One pass: parts as above.  Two passes: the parts of the
 // second pass, each of which has one workgroup per block of columns; two workgroups per compute unit, no fewer rows per part than a
 // workgroup has in flight (4 000 x 50 008 bf16 with one, two, four and eight: 123, 124, 130 and 138 us, 4 000 x 60 000 fp32 290, 281, 287 and
 // more; fewer partial rows to add up as well).
 void make_wide_once(cr_plan_t *p, int64_t rows_per_run)
 {
-    p->wide_variant = p->m * p->d * elem_size(p) >= kWideOnePassBytes ? cr::select_once_wide(p->x_dtype, p->d) : nullptr;
-    if (p->wide_variant) return cr::once_equal_parts(p->slabs, p->m, std::max<int64_t>(1, std::min<int64_t>(query_units(), p->m / 4)), rows_per_run, p->work);
+    if (rows_per_run <= wide_one_pass_rows(p)) {
+        p->wide_variant = cr::select_once_wide(p->x_dtype, p->d);
+        return cr::once_equal_parts(p->slabs, p->m, std::max<int64_t>(1, std::min<int64_t>(query_units(), p->m / 4)), rows_per_run, p->work);
+    }
     const int64_t vec = p->x_dtype == CR_BF16 ? 8 : 4, blocks = ((p->d + vec - 1) / vec + cr::kWideColumnChunks - 1) / cr::kWideColumnChunks;
     p->units = query_units();
     const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(2 * static_cast<int64_t>(p->units) / blocks, p->m / 16));
@@ -298,7 +309,8 @@ int make_split(cr_plan_t *p)
     }
     if (kind < 0) {
         kind = CR_SPLIT_ROWS_ONCE;
-        value = whole_ranges_pay(p) ? CR_ROWS_WHOLE_RANGES : p->m;
+        const int64_t wide = p->once_variant ? 0 : wide_one_pass_rows(p);
+        value = whole_ranges_pay(p) ? CR_ROWS_WHOLE_RANGES : wide ? wide : p->m;
     }
     p->split_kind_used = kind;
     p->split_value_used = value;

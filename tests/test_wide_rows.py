@@ -4,8 +4,6 @@ import pytest
 
 import paper_1902_01981_amd as cr
 
-pytestmark = pytest.mark.gpu
-
 # one pass (48 MB of X and more): the fewest and most chunks per thread of each type and one column on, rows that end in a whole chunk, an
 # overlapping one, a chunk of one column; two passes: the same sizes with too few rows, wider rows with 1, 2, 4 and 8 rows per workgroup
 CASES = [(24_577, 0, 600), (26_624, 0, 500), (26_625, 0, 480), (30_003, 0, 700), (32_768, 0, 400), (32_769, 0, 400), (34_816, 0, 367), (34_817, 0, 450),
@@ -13,6 +11,20 @@ CASES = [(24_577, 0, 600), (26_624, 0, 500), (26_625, 0, 480), (30_003, 0, 700),
          (24_577, 0, 300), (36_861, 1, 200), (40_000, 0, 13), (40_003, 1, 451), (40_001, 0, 897), (37_002, 1, 1_801), (36_866, 1, 3_601)]
 
 
+@pytest.mark.parametrize("d,bf16,m,one_pass", [(30_001, 0, 3_000, True), (36_864, 1, 700, True), (30_001, 0, 300, False), (36_865, 1, 900, False)])
+def test_what_a_plan_reports_is_the_same_work_when_set(d, bf16, m, one_pass):
+    p, q, r = (cr.cr_plan_ex(2, 4, 1, m, d, x_dtype=bf16) for _ in range(3))
+    size, info = cr.cr_workspace_bytes(p), cr.cr_plan_info(p)
+    cr.cr_plan_set_split(q, info.split_kind, info.split_value)
+    assert cr.cr_workspace_bytes(q) == size and all(np.array_equal(a, b) for a, b in zip(cr.cr_plan_get_pieces(p), cr.cr_plan_get_pieces(q)))
+    assert (info.split_kind, info.stage1_team_size) == (cr.CR_SPLIT_ROWS_ONCE, 0) and (info.split_value < m) == one_pass
+    cr.cr_plan_set_split(r, cr.CR_SPLIT_ROWS_ONCE, m)    # no limit: two passes, long parts
+    assert (cr.cr_plan_info(r).num_teams < info.num_teams) == one_pass
+    for plan in (p, q, r):
+        cr.cr_plan_destroy(plan)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("d,bf16,m", CASES)
 def test_slabs_against_64_bits(d, bf16, m):
     """The dot product and the residual are fp32 (some 1e-7 of the sum of magnitudes, which is about one here), everything across rows
@@ -23,7 +35,7 @@ def test_slabs_against_64_bits(d, bf16, m):
     X = torch.empty(m, d, device="cuda", dtype=torch.bfloat16 if bf16 else torch.float32).normal_(generator=gen)
     w = torch.randn(d, generator=gen, device="cuda") / d ** 0.5
     y = torch.randn(m, generator=gen, device="cuda") + 4.0           # residuals away from zero
-    for logistic, rows_per_run in ((0, None), (1, None), (0, 7)):
+    for logistic, rows_per_run in ((0, None), (1, None), (0, 1), (0, m)):         # m: two passes for all sizes
         plan = cr.cr_plan_ex(1, 3, 1, m, d, model=logistic, x_dtype=bf16)
         if rows_per_run:
             cr.cr_plan_set_split(plan, cr.CR_SPLIT_ROWS_ONCE, rows_per_run)
