@@ -1890,11 +1890,11 @@ hipError_t static_scratch(char **ptr)
     return hipSuccess;
 }
 
-// An encode program travels as kernel arguments (copied when the launch is enqueued) and one workgroup writes it out with vector
-// stores.  What bounds it is the number of launches, 4 KB of arguments at most each, so a term of 28 bytes travels as 8: slab, row,
+// Where the tree's tables do not fit the arguments of the launch that encodes (launch_aggregate), the encode program travels as kernel
+// arguments of launches of its own (copied when the launch is enqueued) and one workgroup writes it out with vector stores.  What bounds it is the number of launches, 4 KB of arguments at most each, so a term of 28 bytes travels as 8: slab, row,
 // level and the places of its two coefficients in a table of the block's distinct ones.  Every block is complete in itself, and only
 // the terms that the mask leaves travel.  Ten vectors of 10 to 73728 entries on a tree of two levels of twelve with s = 2: 305 to
-// 340 us with the program's bytes as they are (six launches per vector), 155 us in this form (one).
+// 340 us with the program's bytes as they are (six launches per vector), 155 us in this form (one), 119 us with the tables as arguments.
 struct ProgramBlock {
     static constexpr int kWords = 480;                   // 8-byte words: the coefficients, then the terms
     int32_t first, terms, coefs, subs;                   // subs: words of the sub-program table, behind the terms
