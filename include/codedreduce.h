@@ -164,7 +164,9 @@ int cr_simulate_iteration(const cr_plan_t *plan, double a, double mu, double t_c
 /* ---- device binding --------------------------------------------------------------------------------------------
  * The workspace holds the device tables, 16 encode programs (for trees and vectors whose encode takes programs), the stage-1 partial rows, the slab gradients
  * G[S][d] (not for CR_AGGREGATE_ONLY) and the messages M[N][d], all fp32 rows of d floats.  dev_ptr must be 256-byte aligned and stay valid while the plan
- * is used; hip_stream is a hipStream_t (NULL = the default stream).  cr_bind_workspace copies the tables synchronously, in one copy. */
+ * is used; hip_stream is a hipStream_t (NULL = the default stream).  cr_bind_workspace copies the tables synchronously, in one copy.
+ * The tables of stage 1 must stay as bound.  A call on slab gradients of the caller's (cr_load_partial_grads, cr_aggregate_run) relies on
+ * nothing that the workspace held before it, so aggregation-only plans may take turns in one block. */
 int cr_workspace_bytes(cr_plan_t *plan, size_t *bytes);
 int cr_bind_workspace(cr_plan_t *plan, void *dev_ptr, size_t bytes, void *hip_stream);
 
@@ -181,7 +183,9 @@ int cr_bind_workspace(cr_plan_t *plan, void *dev_ptr, size_t bytes, void *hip_st
  *   Stragglers write no message (their row of M keeps stale data); all other nodes do, also below a straggler.
  *   CR_E_UNDECODABLE, before anything is enqueued and with no state change, if any group has more than s stragglers.
  *   On trees of at most 448 workers with vectors of at most 81920 columns all it enqueues is one kernel launch, with what the mask
- *   decides as kernel arguments; else the mask's encode program travels in a copy from pinned memory first.
+ *   decides as kernel arguments; else the mask's encode program travels in a copy from pinned memory first.  (The tree's tables are read
+ *   from the workspace with stage 1's slabs, from 1 MB that the library keeps for bound plans with the caller's; while that is all in
+ *   use they travel with the call, in a copy where they do not fit the arguments.)
  * cr_decode_root (the last step of CR.Execute, Algorithm 2: the master recovers g from any n-s of its children):
  *   g_dev[d] = sum_j a_j m_(1,j) with the decode row of group 0 from the last cr_encode_tree; by eq. (3) this is the full gradient.
  * cr_gd_update: w <- w - lr * g (plain gradient step used by the benchmark loop).

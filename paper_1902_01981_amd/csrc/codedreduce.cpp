@@ -8,6 +8,8 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
+#include <mutex>
 #include <new>
 #include <string>
 #include <unordered_map>
@@ -46,6 +48,35 @@ constexpr size_t kMaxSamples = size_t(1) << 16;
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// The pages of the library's table pool that plans hold, per device.  A plan takes a run of them when it is first bound and gives it
+// back when it is destroyed, after the last launch that reads it.
+class TablePages {
+    static constexpr int kPages = cr::kTablePoolBytes / cr::kTablePageBytes;
+    std::mutex mutex_;
+    bool held_[cr::kMaxDevices][kPages] = {};
+
+public:
+    int take(int device, int pages)                      // the first page of the run, or -1: none is free
+    {
+        const std::lock_guard<std::mutex> lock(mutex_);
+        if (device < 0 || device >= cr::kMaxDevices) return -1;
+        for (int run = 0, at = 0; at < kPages; ++at) {
+            run = held_[device][at] ? 0 : run + 1;
+            if (run < pages) continue;
+            const int first = at - pages + 1;
+            std::fill(&held_[device][first], &held_[device][first] + pages, true);
+            return first;
+        }
+        return -1;
+    }
+    void give(int device, int first, int pages)
+    {
+        const std::lock_guard<std::mutex> lock(mutex_);
+        std::fill(&held_[device][first], &held_[device][first] + pages, false);
+    }
+};
+TablePages g_table_pages;
+
 struct TimedLaunch {
     int kernel;
     hipEvent_t start, stop;
@@ -63,6 +94,7 @@ struct cr_plan_s {
     std::vector<cr::Slab> slabs;
     std::vector<int32_t> node_slab_begin;          // N+1
     std::vector<double> slab_coef;
+    std::unique_ptr<cr::TreeArguments> tree_arguments;                     // trees that the tree kernels take
     int64_t row_visits = 0, min_rows = 0, max_rows = 0;
     int64_t max_holders = 1;                       // most workers that hold a row: (s+1)^L, capped at 64
     mutable std::unordered_map<uint64_t, std::vector<double>> row_cache;   // padded straggler bitmask -> decode row
@@ -102,12 +134,14 @@ struct cr_plan_s {
     char *d_program = nullptr;                     // kProgramSlots encode programs
     int32_t *d_node_begin = nullptr;               // slabs of every node, their coefficients: what the tree kernels read
     double *d_slab_coef = nullptr;
+    bool slabs_here = false;                       // the slabs are those that stage 1 left in the workspace, beside the tables
+    int pool_device = -1, pool_first = -1, pool_pages = 0;      // pages of the table pool where d_node_begin and d_slab_coef lie instead
     double *d_measures = nullptr;                  // kProgramSlots steps' sums for the convergence measures
     size_t measures_stride = 0;                    // doubles per step
     size_t program_bytes = 0;                      // size of one
     float *d_G = nullptr, *d_M = nullptr, *d_residuals = nullptr;   // d_G: the output table, slabs then partial rows; residuals: wide-row path only
     const float *G_src = nullptr;                  // slabs the encode reads: d_G or the caller's buffer
-    char *h_staging = nullptr;                     // pinned, kStagingHalves * kProgramSlots * program_bytes
+    char *h_staging = nullptr;                     // pinned, kStagingHalves * kProgramSlots * program_bytes, then a copy of the tree's tables
     hipEvent_t staging_done[kStagingHalves] = {};
     bool staging_used[kStagingHalves] = {};
     int staging_next = 0;
@@ -484,6 +518,33 @@ int check_l2_sharing(cr_plan_t *p)
     return CR_OK;
 }
 
+// An aggregation-only plan keeps nothing in the workspace between calls, which may serve other plans in the meantime: its tree's tables
+// go to pages of the library's, as long as there are free ones (else they go with every call, see mask_tables).
+hipError_t keep_tables(cr_plan_t *p, const char *tables)
+{
+    const size_t bytes = p->tables_bytes - p->at_node_begin;
+    int device = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e != hipSuccess) return e;
+    if (p->pool_first >= 0 && p->pool_device != device) {
+        g_table_pages.give(p->pool_device, p->pool_first, p->pool_pages);
+        p->pool_first = -1;
+    }
+    if (p->pool_first < 0) {
+        p->pool_device = device;
+        p->pool_pages = static_cast<int>((bytes + cr::kTablePageBytes - 1) / cr::kTablePageBytes);
+        p->pool_first = g_table_pages.take(device, p->pool_pages);
+    }
+    if (p->pool_first < 0) return hipSuccess;
+    char *pool = nullptr;
+    e = cr::table_pool(&pool);
+    if (e != hipSuccess) return e;
+    char *at = pool + static_cast<size_t>(p->pool_first) * cr::kTablePageBytes;
+    p->d_node_begin = reinterpret_cast<int32_t *>(at);
+    p->d_slab_coef = reinterpret_cast<double *>(at + (p->at_slab_coef - p->at_node_begin));
+    return hipMemcpy(at, tables, bytes, hipMemcpyHostToDevice);
+}
+
 }  // namespace
 
 extern "C" {
@@ -521,6 +582,10 @@ int cr_plan_ex(int L, int n, int s, int64_t m, int64_t d, int model, int x_dtype
         for (const cr::Slab &sl : p->slabs) p->node_slab_begin[sl.node + 1] += 1;
         for (int32_t i = 0; i < p->tree.N; ++i) p->node_slab_begin[i + 1] += p->node_slab_begin[i];
         for (const cr::Slab &sl : p->slabs) p->slab_coef.push_back(sl.coef);
+        if (cr::tree_side_by_side(n, L, p->tree.N, d)) {
+            p->tree_arguments = std::make_unique<cr::TreeArguments>();
+            cr::lay_out_tree(p->tree.N, static_cast<int>(p->slabs.size()), p->node_slab_begin.data(), p->slab_coef.data(), p->tree_arguments.get());
+        }
         p->min_rows = INT64_MAX;
         for (int32_t node = 0; node < p->tree.N; ++node) {
             int64_t rows = 0;
@@ -547,7 +612,8 @@ int cr_plan_ex(int L, int n, int s, int64_t m, int64_t d, int model, int x_dtype
 void cr_plan_destroy(cr_plan_t *p)
 {
     if (!p) return;
-    if (p->bound) (void)hipStreamSynchronize(p->stream);
+    const bool idle = !p->bound || hipStreamSynchronize(p->stream) == hipSuccess;
+    if (p->pool_first >= 0 && idle) g_table_pages.give(p->pool_device, p->pool_first, p->pool_pages);
     for (const TimedLaunch &t : p->timed) { (void)hipEventDestroy(t.start); (void)hipEventDestroy(t.stop); }
     for (hipEvent_t e : p->event_pool) (void)hipEventDestroy(e);
     for (hipEvent_t e : p->staging_done)
@@ -754,17 +820,21 @@ try {
     put(p->at_dst, dst);
     put(p->at_node_begin, p->node_slab_begin);
     put(p->at_slab_coef, p->slab_coef);
-    CR_HIP(hipMemcpy(p->ws, tables.data(), tables.size(), hipMemcpyHostToDevice));
+    if (stage1) CR_HIP(hipMemcpy(p->ws, tables.data(), tables.size(), hipMemcpyHostToDevice));
+    else if (p->tree_arguments) CR_HIP(keep_tables(p, tables.data() + p->at_node_begin));
     p->l2_sharing = -1;
     if (P > 0 && (p->split_kind_used == CR_SPLIT_ROW_CELLS || p->split_kind_used == CR_SPLIT_SHARED_CELLS)) {
         int rc = check_l2_sharing(p);
         if (rc != CR_OK) return rc;
     }
     if (!p->h_staging) {
-        CR_HIP(hipHostMalloc(reinterpret_cast<void **>(&p->h_staging), p->program_bytes * kProgramSlots * kStagingHalves, hipHostMallocDefault));
+        const size_t programs = p->program_bytes * kProgramSlots * kStagingHalves, tree_tables = p->tree_arguments ? p->tables_bytes - p->at_node_begin : 0;
+        CR_HIP(hipHostMalloc(reinterpret_cast<void **>(&p->h_staging), programs + tree_tables, hipHostMallocDefault));
+        std::memcpy(p->h_staging + programs, tables.data() + p->at_node_begin, tree_tables);
         for (int i = 0; i < kStagingHalves; ++i) CR_HIP(hipEventCreateWithFlags(&p->staging_done[i], hipEventDisableTiming));
     }
     p->bound = true;
+    p->slabs_here = false;
     p->have_grads = false;
     p->have_messages = false;
     return CR_OK;
@@ -807,6 +877,7 @@ int cr_partial_grads(cr_plan_t *p, const void *X, const float *y, const float *w
         t.done();
     }
     p->G_src = p->d_G;
+    p->slabs_here = true;
     p->have_grads = true;
     p->have_messages = false;
     return CR_OK;
@@ -818,6 +889,7 @@ int cr_load_partial_grads(cr_plan_t *p, const float *G)
     if (!p->bound) return fail(CR_E_INVAL, "no workspace bound");
     if (reinterpret_cast<uintptr_t>(G) % 16 != 0) return fail(CR_E_INVAL, "G must be 16-byte aligned");
     p->G_src = G;
+    p->slabs_here = false;
     p->have_grads = true;
     p->have_messages = false;
     return CR_OK;
@@ -1004,10 +1076,37 @@ int encode_slot(cr_plan_t *p, int slot, const ProgramCounts &counts)
 // vectors that a gradient step reads and writes besides g
 int64_t step_rows(const cr::GradientStep &step) { return (step.w ? 2 : 0) + (step.measures && step.w_star ? 1 : 0); }
 
-int encode_tree(cr_plan_t *p, const cr::NodeCoefs &coefs, const ProgramCounts &counts)
+// What the tree kernels take of the tree and a mask.
+struct MaskTables {
+    bool as_arguments = false;
+    cr::DeviceTables device;                             // the coefficients of the mask in any case
+    cr::ArgumentTables arguments;
+};
+
+// The tables in the workspace are those that were written there with stage 1's, and stand as long as its slabs do.  With slabs of the
+// caller's nothing in the workspace is relied on: the tables are in the plan's pages, or travel as kernel arguments, or, where they do not fit, in a
+// copy from pinned memory, once per call (*sent).
+int mask_tables(cr_plan_t *p, const uint8_t *mask, bool slabs_here, MaskTables *t, ProgramCounts *counts, bool *sent)
+{
+    *counts = ProgramCounts();
+    int rc = build_coefs(p, mask, &t->device.coefs, counts);
+    if (rc != CR_OK) return rc;
+    t->device.node_begin = p->d_node_begin;
+    t->device.slab_coef = p->d_slab_coef;
+    const bool there = slabs_here || p->pool_first >= 0;
+    t->as_arguments = !there && cr::argument_tables(*p->tree_arguments, t->device.coefs, &t->arguments);
+    if (there || t->as_arguments || *sent) return CR_OK;
+    CR_HIP(hipMemcpyAsync(p->ws + p->at_node_begin, p->h_staging + p->program_bytes * kProgramSlots * kStagingHalves, p->tables_bytes - p->at_node_begin,
+                          hipMemcpyHostToDevice, p->stream));
+    *sent = true;
+    return CR_OK;
+}
+
+int encode_tree(cr_plan_t *p, const MaskTables &tables, const ProgramCounts &counts)
 {
     LaunchTimer t(p, CR_K_ENCODE, (counts.active_slabs + counts.active_msgs) * p->d * 4);
-    CR_HIP(cr::launch_tree_encode(p->G_src, p->d_M, p->d_node_begin, p->d_slab_coef, p->n, p->L, coefs, p->d, p->stream));
+    CR_HIP(tables.as_arguments ? cr::launch_tree_encode(p->G_src, p->d_M, tables.arguments, p->n, p->L, p->d, p->stream)
+                               : cr::launch_tree_encode(p->G_src, p->d_M, tables.device, p->n, p->L, p->d, p->stream));
     t.done();
     p->dec = counts.dec;
     p->have_messages = true;
@@ -1027,10 +1126,11 @@ int decode_root(cr_plan_t *p, float *g, const cr::GradientStep &step)
 }
 
 // encode, decode and gradient step in one launch, which counts as the encode's
-int encode_decode(cr_plan_t *p, const cr::NodeCoefs &coefs, const ProgramCounts &counts, float *g, const cr::GradientStep &step)
+int encode_decode(cr_plan_t *p, const MaskTables &tables, const ProgramCounts &counts, float *g, const cr::GradientStep &step)
 {
     LaunchTimer t(p, CR_K_ENCODE, (counts.active_slabs + counts.active_msgs + 1 + step_rows(step)) * p->d * 4);
-    CR_HIP(cr::launch_tree_encode_decode(p->G_src, p->d_M, p->d_node_begin, p->d_slab_coef, p->n, p->L, coefs, g, step, p->d, p->stream));
+    CR_HIP(tables.as_arguments ? cr::launch_tree_encode_decode(p->G_src, p->d_M, tables.arguments, p->n, p->L, g, step, p->d, p->stream)
+                               : cr::launch_tree_encode_decode(p->G_src, p->d_M, tables.device, p->n, p->L, g, step, p->d, p->stream));
     t.done();
     p->dec = counts.dec;
     p->have_messages = true;
@@ -1046,10 +1146,11 @@ int cr_encode_tree(cr_plan_t *p, const uint8_t *mask)
     if (!p->have_grads) return fail(CR_E_STATE, "no partial gradients yet");
     ProgramCounts counts;
     if (cr::tree_side_by_side(p->n, p->L, p->tree.N, p->d)) {
-        cr::NodeCoefs coefs;
-        int rc = build_coefs(p, mask, &coefs, &counts);
+        MaskTables tables;
+        bool sent = false;
+        int rc = mask_tables(p, mask, p->slabs_here, &tables, &counts, &sent);
         if (rc != CR_OK) return rc;
-        return encode_tree(p, coefs, counts);
+        return encode_tree(p, tables, counts);
     }
     int rc = check_masks(p, mask, 1);
     if (rc != CR_OK) return rc;
@@ -1082,7 +1183,8 @@ int cr_gd_run(cr_plan_t *p, const void *X, const float *y, float *w, float *g, c
     const int32_t N = p->tree.N;
     const bool side_by_side = cr::tree_side_by_side(p->n, p->L, N, p->d), together = cr::tree_and_decode_together(p->n, p->L, N, p->d);
     ProgramCounts counts[kProgramSlots];
-    cr::NodeCoefs coefs;
+    MaskTables tables;
+    bool sent = false;
     for (int t0 = 0; t0 < steps; t0 += kProgramSlots) {
         const int count = std::min(kProgramSlots, steps - t0);
         // where the tree's kernels take programs, those of the next kProgramSlots steps travel in one copy
@@ -1096,15 +1198,12 @@ int cr_gd_run(cr_plan_t *p, const void *X, const float *y, float *w, float *g, c
             step.lr = lr;
             step.w_star = w_star;
             step.measures = metrics ? p->d_measures + i * p->measures_stride : nullptr;
-            if (side_by_side) {
-                counts[i] = ProgramCounts();
-                rc = build_coefs(p, masks + static_cast<size_t>(t0 + i) * N, &coefs, &counts[i]);
-            }
+            if (side_by_side) rc = mask_tables(p, masks + static_cast<size_t>(t0 + i) * N, true, &tables, &counts[i], &sent);
             if (rc == CR_OK) rc = cr_partial_grads(p, X, y, w);
             if (together) {
-                if (rc == CR_OK) rc = encode_decode(p, coefs, counts[i], g, step);
+                if (rc == CR_OK) rc = encode_decode(p, tables, counts[i], g, step);
             } else {
-                if (rc == CR_OK) rc = side_by_side ? encode_tree(p, coefs, counts[i]) : encode_slot(p, i, counts[i]);
+                if (rc == CR_OK) rc = side_by_side ? encode_tree(p, tables, counts[i]) : encode_slot(p, i, counts[i]);
                 if (rc == CR_OK) rc = decode_root(p, g, step);
             }
             if (rc != CR_OK) return rc;
@@ -1129,15 +1228,17 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
     int rc = check_masks(p, masks, steps);
     if (rc != CR_OK) return rc;
     const int32_t N = p->tree.N;
+    if (steps > 0) p->slabs_here = false;
     if (cr::tree_and_decode_together(p->n, p->L, N, p->d)) {
-        cr::NodeCoefs coefs;
+        MaskTables tables;
+        bool sent = false;
         for (int t = 0; t < steps; ++t) {
             ProgramCounts counts;
-            rc = build_coefs(p, masks + static_cast<size_t>(t) * N, &coefs, &counts);
+            rc = mask_tables(p, masks + static_cast<size_t>(t) * N, false, &tables, &counts, &sent);
             if (rc != CR_OK) return rc;
             p->G_src = G + static_cast<int64_t>(t) * G_step_stride;
             p->have_grads = true;
-            rc = encode_decode(p, coefs, counts, g + static_cast<int64_t>(t) * g_step_stride, cr::GradientStep());
+            rc = encode_decode(p, tables, counts, g + static_cast<int64_t>(t) * g_step_stride, cr::GradientStep());
             if (rc != CR_OK) return rc;
         }
         return CR_OK;
@@ -1189,15 +1290,22 @@ int cr_aggregate_static(cr_plan_t *p, const float *G, const uint8_t *mask, float
     ProgramCounts counts;
     char *base = nullptr;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (cr::tree_side_by_side(p->n, p->L, p->tree.N, p->d)) {
+    if (cr::tree_side_by_side(p->n, p->L, p->tree.N, p->d) && p->tree_arguments->fits) {
         cr::NodeCoefs coefs;
+        cr::ArgumentTables tables;
         int rc = build_coefs(p, mask, &coefs, &counts);
         if (rc != CR_OK) return rc;
-        CR_HIP(cr::static_scratch(&base));              // this device's copy of the array; never the array's name
-        const cr::ProgramSource src{p->tree.N, static_cast<int>(p->slabs.size()), p->node_slab_begin.data(), p->slab_coef.data(), &coefs};
-        bool done = false;
-        CR_HIP(cr::launch_aggregate(G, reinterpret_cast<float *>(base + cr::kStaticProgramBytes), src, p->n, p->L, counts.dec, g, p->d, stream, &done));
-        if (done) return CR_OK;
+        if (cr::argument_tables(*p->tree_arguments, coefs, &tables)) {
+            CR_HIP(cr::static_scratch(&base));          // this device's copy of the array; never the array's name
+            float *M = reinterpret_cast<float *>(base + cr::kStaticProgramBytes);
+            if (cr::tree_and_decode_together(p->n, p->L, p->tree.N, p->d)) {
+                CR_HIP(cr::launch_tree_encode_decode(G, M, tables, p->n, p->L, g, cr::GradientStep(), p->d, stream));
+            } else {
+                CR_HIP(cr::launch_tree_encode(G, M, tables, p->n, p->L, p->d, stream));
+                CR_HIP(cr::launch_decode(M, g, counts.dec, cr::GradientStep(), p->d, stream));
+            }
+            return CR_OK;
+        }
         counts = ProgramCounts();
     }
     if (p->static_program.size() != p->program_bytes) p->static_program.assign(p->program_bytes, 0);

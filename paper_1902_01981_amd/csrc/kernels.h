@@ -64,6 +64,33 @@ struct NodeCoefs {
     static constexpr int kNodes = 448;                   // kernel arguments take at most 4 KB
     double a[kNodes];
 };
+// The tree's tables as a kernel argument.  On the device, with the mask's coefficients beside them: the slabs of every node
+// (node_begin: one entry per node and one more) and their coefficients.
+struct DeviceTables {
+    static constexpr size_t kLdsBytes = 0;
+    const int32_t *node_begin;
+    const double *slab_coef;
+    NodeCoefs coefs;
+};
+// Or all of it in the argument: the distinct coefficients, then 16-bit tables of first slabs and of places among the coefficients.
+struct ArgumentTables {
+    static constexpr int kWords = 470;
+    static constexpr size_t kLdsBytes = kWords * 8;
+    int32_t at_begin, at_coef, at_slab, used;            // in 16-bit units; 64-bit words in use
+    uint64_t word[kWords];
+};
+// What the tree itself puts into ArgumentTables, laid out once per plan; argument_tables completes it for a mask, or says that there
+// is no room for the mask's coefficients.
+struct TreeArguments {
+    static constexpr int kSlots = 1024;                  // of the hash table; there is room for fewer than 470 distinct coefficients
+    bool fits = false;                                   // the tree's own part does
+    int nodes = 0, values = 0, halves = 0;
+    uint16_t slot[kSlots];                               // place of a coefficient among the values by its hash, 0xffff: none
+    uint64_t value[ArgumentTables::kWords];
+    uint16_t half[4 * ArgumentTables::kWords];           // first slab of every node and one more, place of every node's coefficient, of every slab's
+};
+void lay_out_tree(int nodes, int slabs, const int32_t *node_begin, const double *slab_coef, TreeArguments *out);
+bool argument_tables(const TreeArguments &tree, const NodeCoefs &coefs, ArgumentTables *out);
 // The nodes that a workgroup of the tree kernels has, leaves first, then level by level up: the nodes of level l have the places from
 // first[l - 1] on, and place t is node t + shift[l - 1] + sub * width[l - 1] in level-1 sub-tree `sub`.
 struct TreeLevels {
@@ -136,13 +163,12 @@ hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int n
 bool encode_in_steps(int n, int L, int64_t d, int steps);
 hipError_t launch_encode_steps(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L, float *g, int64_t g_stride, int64_t d,
                                hipStream_t stream);
-// The same for trees of at most NodeCoefs::kNodes nodes and vectors of at most kTreeColumns columns (tree_side_by_side): a workgroup
-// per level-1 sub-tree and 16 chunks of columns, 64 from kTreeNarrowColumns on.  node_begin (one entry per node and one more) and
-// slab_coef: the slabs of every node and their coefficients.
+// The encode of trees of at most NodeCoefs::kNodes nodes and vectors of at most kTreeColumns columns (tree_side_by_side): a workgroup
+// per level-1 sub-tree and 16 chunks of columns, 64 from kTreeNarrowColumns on.  The tables travel with the launch or are on the device.
 constexpr int64_t kTreeColumns = 81920, kTreeNarrowColumns = 32768;
 bool tree_side_by_side(int n, int L, int nodes, int64_t d);
-hipError_t launch_tree_encode(const float *G, float *M, const int32_t *node_begin, const double *slab_coef, int n, int L, const NodeCoefs &coefs, int64_t d,
-                              hipStream_t stream);
+hipError_t launch_tree_encode(const float *G, float *M, const DeviceTables &tables, int n, int L, int64_t d, hipStream_t stream);
+hipError_t launch_tree_encode(const float *G, float *M, const ArgumentTables &tables, int n, int L, int64_t d, hipStream_t stream);
 // the master's decode and, with step.w, the gradient step; decode_groups: workgroups of the launch
 hipError_t launch_decode(const float *M, float *g, const DecTerms &terms, const GradientStep &step, int64_t d, hipStream_t stream);
 int decode_groups(int64_t d);
@@ -150,20 +176,11 @@ int decode_groups(int64_t d);
 // (8 chunks of columns per workgroup, 16 from kTogetherNarrowColumns on).
 constexpr int64_t kTogetherColumns = 32768, kTogetherNarrowColumns = 8192;
 bool tree_and_decode_together(int n, int L, int nodes, int64_t d);
-hipError_t launch_tree_encode_decode(const float *G, float *M, const int32_t *node_begin, const double *slab_coef, int n, int L, const NodeCoefs &coefs, float *g,
-                                     const GradientStep &step, int64_t d, hipStream_t stream);
+hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, int n, int L, float *g, const GradientStep &step, int64_t d, hipStream_t stream);
+hipError_t launch_tree_encode_decode(const float *G, float *M, const ArgumentTables &tables, int n, int L, float *g, const GradientStep &step, int64_t d, hipStream_t stream);
 int tree_decode_groups(int n, int L, int64_t d);
 // metrics[2t], metrics[2t + 1] of `steps` steps from the measures their launches of `groups` workgroups left at sums + t * step_stride
 hipError_t launch_measures(const double *sums, int64_t step_stride, int groups, int steps, bool with_star, float *metrics, hipStream_t stream);
-// Encode and decode with all tables as kernel arguments (host pointers; consumed before the call returns).  *done = false and nothing
-// enqueued where the tree, the vector or the tables are too large for that.
-struct ProgramSource {
-    int nodes, slabs;
-    const int32_t *node_begin;
-    const double *slab_coef;
-    const NodeCoefs *coefs;
-};
-hipError_t launch_aggregate(const float *G, float *M, const ProgramSource &src, int n, int L, const DecTerms &dec, float *g, int64_t d, hipStream_t stream, bool *done);
 hipError_t launch_update(float *w, const float *g, float lr, int64_t d, hipStream_t stream);
 // plain streaming read of n16 16-byte words; every workgroup writes its sum to sink[workgroup] (kStreamGroups workgroups)
 constexpr int kStreamGroups = 256 * 8;
@@ -171,9 +188,13 @@ hipError_t launch_stream_read(const void *src, size_t n16, float *sink, hipStrea
 // ---- the library's own device memory, for callers that cannot allocate -------------------------------------------------------
 // A file-scope device array of kStaticScratchBytes (every GPU the library runs on holds its own copy until the process ends).
 // static_scratch returns its address on the CURRENT device (looked up once per device, no allocation) in *ptr.
+constexpr int kMaxDevices = 64;
 constexpr size_t kStaticProgramBytes = size_t(64) << 10;                 // head of the array: one encode program
 constexpr size_t kStaticScratchBytes = size_t(96) << 20;                 // the whole array; messages follow the program
 hipError_t static_scratch(char **ptr);
+// Another one, whose pages hold the trees' tables of bound plans that are given their slabs.
+constexpr size_t kTablePoolBytes = size_t(1) << 20, kTablePageBytes = size_t(4) << 10;
+hipError_t table_pool(char **ptr);
 // An encode program's tables, in device or in host memory; launch_program sends `terms` terms (at most 4096, of slabs and rows below
 // 4096) and `subs` (an even number) sub-program words of the host's through kernel arguments: launches only, no staging buffer, no
 // memcpy node; the host tables are consumed before the call returns

@@ -1107,49 +1107,36 @@ encode_steps_kernel(const float *__restrict__ G, int64_t G_stride, float *__rest
 // share out the nodes: all form their own sums at once (one fetch of a node's entries, one of its slabs), the messages meet in LDS
 // and the levels above the leaves fold their children from there, one barrier per level.  Sums are fp64, formed in the order in which
 // encode_kernel forms them, and messages are rounded where it rounds them: the same bits.
-// The tree's tables stay on the device for the plan's life; what the mask decides, a coefficient per node, travels as kernel
-// arguments, so there is no copy to wait for.
+// What the mask decides, a coefficient per node, travels as kernel arguments, so there is no copy to wait for; the tree's tables are on
+// the device beside the slabs that stage 1 leaves there, or travel as arguments too.
 // Kernel time in us, a thread per sub-tree / nodes side by side: (2,12) tree, s = 2, 10 columns 7.5 / 4.2; s = 3, 5 001 columns
 // 12.5 / 5.9; (3,6) tree, s = 2, 1 024 columns 25.9 / 6.7; (3,4) tree, 6 500 columns 8.5 / 5.7.
 __device__ __forceinline__ bool sends(double a) { return __double_as_longlong(a) != kStraggler; }
 
-// The tree's tables as a kernel argument: on the device for the plan's life, with the mask's coefficients beside them ...
-struct DeviceTables {
-    static constexpr size_t kLdsBytes = 0;
-    const int32_t *node_begin;
-    const double *slab_coef;
-    NodeCoefs coefs;
-    struct View {
-        const DeviceTables &t;
-        __device__ __forceinline__ double coef_of(int node) const { return t.coefs.a[node]; }
-        __device__ __forceinline__ int begin(int node) const { return t.node_begin[node]; }
-        __device__ __forceinline__ double slab_coef_of(int s) const { return t.slab_coef[s]; }
-    };
-    template <int T> __device__ __forceinline__ View view(char *) const { return {*this}; }
+// A workgroup's view of the tables: read in place where they are on the device ...
+struct DeviceView {
+    const DeviceTables &t;
+    __device__ __forceinline__ double coef_of(int node) const { return t.coefs.a[node]; }
+    __device__ __forceinline__ int begin(int node) const { return t.node_begin[node]; }
+    __device__ __forceinline__ double slab_coef_of(int s) const { return t.slab_coef[s]; }
 };
-// ... or all of it in the argument: the distinct coefficients, then 16-bit tables of first slabs and of places among the coefficients.
-// The workgroup copies it to LDS first, since a coefficient is two dependent fetches away.
-struct ArgumentTables {
-    static constexpr int kWords = 470;
-    static constexpr size_t kLdsBytes = kWords * 8;
-    int32_t at_begin, at_coef, at_slab, used;            // in 16-bit units; 64-bit words in use
-    uint64_t word[kWords];
-    struct View {
-        const double *value;
-        const uint16_t *first, *coef, *slab;
-        __device__ __forceinline__ double coef_of(int node) const { return value[coef[node]]; }
-        __device__ __forceinline__ int begin(int node) const { return first[node]; }
-        __device__ __forceinline__ double slab_coef_of(int s) const { return value[slab[s]]; }
-    };
-    template <int T> __device__ __forceinline__ View view(char *lds) const
-    {
-        uint64_t *copy = reinterpret_cast<uint64_t *>(lds);
-        for (int i = threadIdx.x; i < used; i += T) copy[i] = word[i];
-        __syncthreads();
-        const uint16_t *half = reinterpret_cast<const uint16_t *>(lds);
-        return {reinterpret_cast<const double *>(lds), half + at_begin, half + at_coef, half + at_slab};
-    }
+template <int T> __device__ __forceinline__ DeviceView view_tables(const DeviceTables &t, char *) { return {t}; }
+// ... and copied to LDS first where they are arguments, since a coefficient is two dependent fetches away.
+struct ArgumentView {
+    const double *value;
+    const uint16_t *first, *coef, *slab;
+    __device__ __forceinline__ double coef_of(int node) const { return value[coef[node]]; }
+    __device__ __forceinline__ int begin(int node) const { return first[node]; }
+    __device__ __forceinline__ double slab_coef_of(int s) const { return value[slab[s]]; }
 };
+template <int T> __device__ __forceinline__ ArgumentView view_tables(const ArgumentTables &t, char *lds)
+{
+    uint64_t *copy = reinterpret_cast<uint64_t *>(lds);
+    for (int i = threadIdx.x; i < t.used; i += T) copy[i] = t.word[i];
+    __syncthreads();
+    const uint16_t *half = reinterpret_cast<const uint16_t *>(lds);
+    return {reinterpret_cast<const double *>(lds), half + t.at_begin, half + t.at_coef, half + t.at_slab};
+}
 
 // The places of a workgroup's nodes, leaves first, then level by level up; sub: which level-1 sub-tree (0 where it has them all).
 struct TreePlaces {
@@ -1275,7 +1262,7 @@ __global__ void __launch_bounds__(T)
 tree_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, TreeLevels tree, int64_t d, int nq)
 {
     extern __shared__ __align__(16) char tree_lds[];
-    const auto view = tables.template view<T>(tree_lds);
+    const auto view = view_tables<T>(tables, tree_lds);
     const TreeLds<VEC, B> lds(tree_lds + TABLES::kLdsBytes, tree.total, tree.leaves);
     const int q = blockIdx.x * B + threadIdx.x % B;
     const int64_t col = chunk_offset<VEC>(q, nq, static_cast<int>(d));       // lanes past the row repeat its last chunk and do not store
@@ -1326,7 +1313,7 @@ __global__ void __launch_bounds__(T)
 tree_decode_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, TreeLevels tree, float *__restrict__ g, GradientStep step, int64_t d, int nq)
 {
     extern __shared__ __align__(16) char tree_lds[];
-    const auto view = tables.template view<T>(tree_lds);
+    const auto view = view_tables<T>(tables, tree_lds);
     const TreeLds<VEC, B> lds(tree_lds + TABLES::kLdsBytes, tree.total, tree.leaves);
     const int tl = threadIdx.x % B, q = blockIdx.x * B + tl;
     const int64_t col = chunk_offset<VEC>(q, nq, static_cast<int>(d));
@@ -1799,16 +1786,17 @@ int tree_decode_groups(int n, int L, int64_t d)
     return static_cast<int>((chunks + per - 1) / per);
 }
 
-hipError_t launch_tree_encode(const float *G, float *M, const int32_t *node_begin, const double *slab_coef, int n, int L, const NodeCoefs &coefs, int64_t d,
-                              hipStream_t stream)
+hipError_t launch_tree_encode(const float *G, float *M, const DeviceTables &tables, int n, int L, int64_t d, hipStream_t stream) { return launch_tree(G, M, tables, n, L, d, stream); }
+hipError_t launch_tree_encode(const float *G, float *M, const ArgumentTables &tables, int n, int L, int64_t d, hipStream_t stream) { return launch_tree(G, M, tables, n, L, d, stream); }
+
+hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, int n, int L, float *g, const GradientStep &step, int64_t d, hipStream_t stream)
 {
-    return launch_tree(G, M, DeviceTables{node_begin, slab_coef, coefs}, n, L, d, stream);
+    return launch_tree_decode(G, M, tables, n, L, g, step, d, stream);
 }
 
-hipError_t launch_tree_encode_decode(const float *G, float *M, const int32_t *node_begin, const double *slab_coef, int n, int L, const NodeCoefs &coefs, float *g,
-                                     const GradientStep &step, int64_t d, hipStream_t stream)
+hipError_t launch_tree_encode_decode(const float *G, float *M, const ArgumentTables &tables, int n, int L, float *g, const GradientStep &step, int64_t d, hipStream_t stream)
 {
-    return launch_tree_decode(G, M, DeviceTables{node_begin, slab_coef, coefs}, n, L, g, step, d, stream);
+    return launch_tree_decode(G, M, tables, n, L, g, step, d, stream);
 }
 
 int decode_groups(int64_t d)
@@ -1865,32 +1853,35 @@ hipError_t launch_stream_read(const void *src, size_t n16, float *sink, hipStrea
 // and outputs -- one encode program and the message rows M[N][d] -- lives in this array.  In host code the array's name is only a
 // stand-in; its device address is asked for once per device, with that device current, and kept.
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char tables_of_trees[kTablePoolBytes];
 
 namespace {
-constexpr int kMaxDevices = 64;
-std::atomic<char *> g_scratch_ptr[kMaxDevices];           // per device: where that device's copy of `scratch` lives
-}  // namespace
+std::atomic<char *> g_scratch_ptr[kMaxDevices], g_tables_ptr[kMaxDevices];      // per device: where that device's copy of the array lives
 
-hipError_t static_scratch(char **ptr)
+hipError_t array_address(const void *name, std::atomic<char *> (&known)[kMaxDevices], char **ptr)
 {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-    char *p = g_scratch_ptr[dev].load(std::memory_order_acquire);
+    char *p = known[dev].load(std::memory_order_acquire);
     if (!p) {
         void *sym = nullptr;
-        e = hipGetSymbolAddress(&sym, HIP_SYMBOL(scratch));
+        e = hipGetSymbolAddress(&sym, name);
         if (e != hipSuccess) return e;
         if (!sym) return hipErrorInvalidSymbol;
         p = static_cast<char *>(sym);
-        g_scratch_ptr[dev].store(p, std::memory_order_release);    // two threads racing here store the same address
+        known[dev].store(p, std::memory_order_release);            // two threads racing here store the same address
     }
     *ptr = p;
     return hipSuccess;
 }
+}  // namespace
 
-// Where the tree's tables do not fit the arguments of the launch that encodes (launch_aggregate), the encode program travels as kernel
+hipError_t static_scratch(char **ptr) { return array_address(HIP_SYMBOL(scratch), g_scratch_ptr, ptr); }
+hipError_t table_pool(char **ptr) { return array_address(HIP_SYMBOL(tables_of_trees), g_tables_ptr, ptr); }
+
+// Where the tree's tables do not fit the arguments of the launch that encodes (argument_tables), the encode program travels as kernel
 // arguments of launches of its own (copied when the launch is enqueued) and one workgroup writes it out with vector stores.  What bounds it is the number of launches, 4 KB of arguments at most each, so a term of 28 bytes travels as 8: slab, row,
 // level and the places of its two coefficients in a table of the block's distinct ones.  Every block is complete in itself, and only
 // the terms that the mask leaves travel.  Ten vectors of 10 to 73728 entries on a tree of two levels of twelve with s = 2: 305 to
@@ -1967,59 +1958,67 @@ hipError_t launch_program(const ProgramTables &out, const ProgramTables &host, i
     return hipSuccess;
 }
 
-// The tables of a tree and a mask as one kernel argument, where they fit.
-bool argument_tables(const ProgramSource &src, ArgumentTables *out)
+// ---- the tables of a tree and a mask as one kernel argument --------------------------------------------------------------
+namespace {
+// the coefficient's place among the distinct ones, or -1: no room
+int place_coefficient(double c, uint16_t *slot, uint64_t *value, int &values, int room)
 {
-    constexpr int kSlots = 1024;                         // of the hash table; there is room for fewer than 470 distinct coefficients
-    uint16_t slot[kSlots];
-    std::memset(slot, 0xff, sizeof slot);
-    const int halves = (src.nodes + 1) + src.nodes + src.slabs;
-    if (src.slabs > 0xffff || halves > 4 * ArgumentTables::kWords) return false;
-    const int room = ArgumentTables::kWords - (halves + 3) / 4;
-    uint16_t half[4 * ArgumentTables::kWords];
-    int values = 0, at = 0;
-    auto place = [&](double c) {                         // the coefficient's place among the distinct ones, or -1: no room
-        uint64_t bits;
-        std::memcpy(&bits, &c, 8);
-        unsigned h = static_cast<unsigned>((bits * 0x9E3779B97F4A7C15ull) >> 54);
-        while (slot[h] != 0xffff && out->word[slot[h]] != bits) h = (h + 1) % kSlots;
-        if (slot[h] == 0xffff) {
-            if (values == room) return -1;
-            slot[h] = static_cast<uint16_t>(values);
-            out->word[values++] = bits;
-        }
-        return static_cast<int>(slot[h]);
-    };
-    out->at_begin = at;
-    for (int i = 0; i <= src.nodes; ++i) half[at++] = static_cast<uint16_t>(src.node_begin[i]);
-    out->at_coef = at;
-    for (int i = 0; i < src.nodes; ++i) {
-        const int k = place(src.coefs->a[i]);
-        if (k < 0) return false;
-        half[at++] = static_cast<uint16_t>(k);
+    uint64_t bits;
+    std::memcpy(&bits, &c, 8);
+    unsigned h = static_cast<unsigned>((bits * 0x9E3779B97F4A7C15ull) >> 54);
+    static_assert(TreeArguments::kSlots == 1 << 10 && TreeArguments::kSlots > 2 * ArgumentTables::kWords, "ten bits of hash, a table half empty");
+    while (slot[h] != 0xffff && value[slot[h]] != bits) h = (h + 1) % TreeArguments::kSlots;
+    if (slot[h] == 0xffff) {
+        if (values == room) return -1;
+        slot[h] = static_cast<uint16_t>(values);
+        value[values++] = bits;
     }
-    out->at_slab = at;
-    for (int i = 0; i < src.slabs; ++i) {
-        const int k = place(src.slab_coef[i]);
-        if (k < 0) return false;
-        half[at++] = static_cast<uint16_t>(k);
-    }
-    std::memcpy(out->word + values, half, static_cast<size_t>(at) * 2);
-    out->at_begin += 4 * values;
-    out->at_coef += 4 * values;
-    out->at_slab += 4 * values;
-    out->used = values + (at + 3) / 4;
-    return true;
+    return slot[h];
 }
 
-hipError_t launch_aggregate(const float *G, float *M, const ProgramSource &src, int n, int L, const DecTerms &dec, float *g, int64_t d, hipStream_t stream, bool *done)
+int room_for_values(int halves) { return ArgumentTables::kWords - (halves + 3) / 4; }
+}  // namespace
+
+void lay_out_tree(int nodes, int slabs, const int32_t *node_begin, const double *slab_coef, TreeArguments *out)
 {
-    ArgumentTables tables;
-    *done = tree_side_by_side(n, L, src.nodes, d) && argument_tables(src, &tables);
-    if (!*done) return hipSuccess;
-    if (tree_and_decode_together(n, L, src.nodes, d)) return launch_tree_decode(G, M, tables, n, L, g, GradientStep(), d, stream);
-    const hipError_t e = launch_tree(G, M, tables, n, L, d, stream);
-    return e != hipSuccess ? e : launch_decode(M, g, dec, GradientStep(), d, stream);
+    out->fits = false;
+    out->nodes = nodes;
+    out->values = 0;
+    if (nodes > NodeCoefs::kNodes || slabs > 4 * ArgumentTables::kWords) return;
+    out->halves = (nodes + 1) + nodes + slabs;
+    const int room = room_for_values(out->halves);
+    if (room <= 0) return;
+    std::memset(out->slot, 0xff, sizeof out->slot);
+    for (int i = 0; i <= nodes; ++i) out->half[i] = static_cast<uint16_t>(node_begin[i]);
+    for (int i = 0; i < slabs; ++i) {
+        const int k = place_coefficient(slab_coef[i], out->slot, out->value, out->values, room);
+        if (k < 0) return;
+        out->half[2 * nodes + 1 + i] = static_cast<uint16_t>(k);
+    }
+    out->fits = true;
+}
+
+bool argument_tables(const TreeArguments &tree, const NodeCoefs &coefs, ArgumentTables *out)
+{
+    if (!tree.fits) return false;
+    const int room = room_for_values(tree.halves);
+    uint16_t slot[TreeArguments::kSlots], places[NodeCoefs::kNodes];
+    std::memcpy(slot, tree.slot, sizeof slot);
+    std::memcpy(out->word, tree.value, static_cast<size_t>(tree.values) * 8);
+    int values = tree.values;
+    for (int i = 0; i < tree.nodes; ++i) {
+        const int k = place_coefficient(coefs.a[i], slot, out->word, values, room);
+        if (k < 0) return false;
+        places[i] = static_cast<uint16_t>(k);
+    }
+    char *halves = reinterpret_cast<char *>(out->word + values);
+    std::memcpy(halves, tree.half, static_cast<size_t>(tree.halves) * 2);
+    std::memcpy(halves + (tree.nodes + 1) * 2, places, static_cast<size_t>(tree.nodes) * 2);
+    out->at_begin = 4 * values;
+    out->at_coef = out->at_begin + tree.nodes + 1;
+    out->at_slab = out->at_coef + tree.nodes;
+    out->used = values + (tree.halves + 3) / 4;
+    return true;
 }
 
 // ---- where do workgroups run? -----------------------------------------------------------------------------------------
