@@ -216,7 +216,8 @@ int cr_gd_run(cr_plan_t *plan, const void *X_dev, const float *y_dev, float *w_d
  * ones two launches per mask.
  *   G_dev          device, S x d floats per step, 16-byte aligned; G_step_stride in floats (a multiple of 4): 0 = the same slabs every step
  *   masks_host     steps x N bytes; all are checked first: CR_E_UNDECODABLE before anything is enqueued
- *   g_dev          device, d floats per step; g_step_stride in floats: 0 = every step overwrites the same vector
+ *   g_dev          device, d floats per step; g_step_stride in floats: 0 = every step overwrites the same vector.  The vectors may lie
+ *                  among the slabs or overlap in part: the steps then take launches of their own, in order
  * Afterwards the plan is in the state the last step's three calls would have left (messages of the last mask). */
 int cr_aggregate_run(cr_plan_t *plan, const float *G_dev, int64_t G_step_stride, const uint8_t *masks_host, int steps, float *g_dev,
                      int64_t g_step_stride);
@@ -232,7 +233,8 @@ int cr_aggregate_run(cr_plan_t *plan, const float *G_dev, int64_t G_step_stride,
  *   plan        any plan; its model is not consulted (no stage 1 runs)
  *   G_dev       device, S x d floats, 16-byte aligned: the slab gradients, read in place
  *   mask_host   host, N bytes, non-zero = straggler; read before the call returns
- *   g_dev       device, d floats: receives the decoded gradient (the same bits cr_decode_root gives for the same G and mask)
+ *   g_dev       device, d floats: receives the decoded gradient (the same bits cr_decode_root gives for the same G and mask); may lie
+ *               among the slabs (two launches then)
  *   hip_stream  a hipStream_t (NULL = the default stream)
  * Limits: the messages must fit, N * d * 4 <= CR_STATIC_SCRATCH_BYTES - 64 KiB (the paper's network, 156 workers x 117 706
  * parameters, does), and the encode program (28 bytes per slab and per worker) must fit 64 KiB: CR_E_INVAL otherwise, before

@@ -1125,6 +1125,14 @@ int decode_root(cr_plan_t *p, float *g, const cr::GradientStep &step)
     return CR_OK;
 }
 
+// Does the decoded vector lie among the slabs?  Encode and decode are then launches of their own: in one, a workgroup would decode over
+// slabs that another has yet to read.
+bool overlap(const float *a, int64_t a_floats, const float *b, int64_t b_floats)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + static_cast<uintptr_t>(b_floats) * sizeof(float) && y < x + static_cast<uintptr_t>(a_floats) * sizeof(float);
+}
+
 // encode, decode and gradient step in one launch, which counts as the encode's
 int encode_decode(cr_plan_t *p, const MaskTables &tables, const ProgramCounts &counts, float *g, const cr::GradientStep &step)
 {
@@ -1181,7 +1189,8 @@ int cr_gd_run(cr_plan_t *p, const void *X, const float *y, float *w, float *g, c
     int rc = check_masks(p, masks, steps);              // every mask is checked before anything is enqueued
     if (rc != CR_OK) return rc;
     const int32_t N = p->tree.N;
-    const bool side_by_side = cr::tree_side_by_side(p->n, p->L, N, p->d), together = cr::tree_and_decode_together(p->n, p->L, N, p->d);
+    const bool side_by_side = cr::tree_side_by_side(p->n, p->L, N, p->d);
+    const bool together = cr::tree_and_decode_together(p->n, p->L, N, p->d) && !overlap(g, p->d, p->d_G, static_cast<int64_t>(p->slabs.size()) * p->d);
     ProgramCounts counts[kProgramSlots];
     MaskTables tables;
     bool sent = false;
@@ -1229,7 +1238,11 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
     if (rc != CR_OK) return rc;
     const int32_t N = p->tree.N;
     if (steps > 0) p->slabs_here = false;
-    if (cr::tree_and_decode_together(p->n, p->L, N, p->d)) {
+    const int64_t more = std::max(0, steps - 1);
+    const bool in_place = overlap(g, p->d + more * g_step_stride, G, static_cast<int64_t>(p->slabs.size()) * p->d + more * G_step_stride);
+    // one launch for several masks leaves the order in which workgroups decode open: vectors that overlap in part need it
+    const bool in_order = in_place || (g_step_stride > 0 && g_step_stride < p->d);
+    if (cr::tree_and_decode_together(p->n, p->L, N, p->d) && !in_place) {
         MaskTables tables;
         bool sent = false;
         for (int t = 0; t < steps; ++t) {
@@ -1248,7 +1261,7 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
         const int count = std::min(kProgramSlots, steps - t0);
         rc = upload_programs(p, masks + static_cast<size_t>(t0) * N, count, counts);
         if (rc != CR_OK) return rc;
-        if (cr::encode_in_steps(p->n, p->L, p->d, count)) {
+        if (!in_order && cr::encode_in_steps(p->n, p->L, p->d, count)) {
             int64_t rows = 0;
             for (int i = 0; i < count; ++i) rows += counts[i].active_slabs + counts[i].active_msgs + 1;
             p->G_src = G + static_cast<int64_t>(t0 + count - 1) * G_step_stride;
@@ -1298,7 +1311,7 @@ int cr_aggregate_static(cr_plan_t *p, const float *G, const uint8_t *mask, float
         if (cr::argument_tables(*p->tree_arguments, coefs, &tables)) {
             CR_HIP(cr::static_scratch(&base));          // this device's copy of the array; never the array's name
             float *M = reinterpret_cast<float *>(base + cr::kStaticProgramBytes);
-            if (cr::tree_and_decode_together(p->n, p->L, p->tree.N, p->d)) {
+            if (cr::tree_and_decode_together(p->n, p->L, p->tree.N, p->d) && !overlap(g, p->d, G, static_cast<int64_t>(p->slabs.size()) * p->d)) {
                 CR_HIP(cr::launch_tree_encode_decode(G, M, tables, p->n, p->L, g, cr::GradientStep(), p->d, stream));
             } else {
                 CR_HIP(cr::launch_tree_encode(G, M, tables, p->n, p->L, p->d, stream));
