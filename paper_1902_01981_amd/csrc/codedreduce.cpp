@@ -931,20 +931,23 @@ int build_program(cr_plan_t *p, const uint8_t *mask, char *h, ProgramCounts *cou
     auto put = [&](size_t t, int32_t slab, double coef) { t_slab[t] = slab; t_level[t] = 0; t_row[t] = 0; t_coef[t] = coef; t_acoef[t] = 0.0; };
     int32_t *sub = reinterpret_cast<int32_t *>(h + p->off_sub);
 
-    // post-order program of every level-1 sub-tree
+    // Post-order program of every level-1 sub-tree.  The messages of a straggler's children are used by nobody, but the kernel folds
+    // them into the sum of the straggler's level, times zero, which is not nothing where they are not finite.  What hangs below
+    // stragglers therefore comes after all else, below stragglers of the first levels first: a level's sum is then used no more once
+    // it has taken such a message.
     size_t nt = 0;
     struct Frame { int32_t node; int level; int next_child; };
     std::vector<Frame> stack;
-    for (int i = 0; i < n; ++i) {
-        sub[i] = static_cast<int32_t>(nt);
-        size_t real_terms = 0;
-        stack.push_back({static_cast<int32_t>(i), 1, 0});
+    std::vector<int32_t> below[cr::kMaxLevels + 1];       // children of stragglers, by their own level
+    auto walk = [&](int32_t root, int root_level) {
+        stack.push_back({root, root_level, 0});
         while (!stack.empty()) {
             Frame &f = stack.back();
             if (f.level < L && f.next_child < n) {
                 const int32_t child = p->tree.level_offset[f.level + 1] + (f.node - p->tree.level_offset[f.level]) * n + f.next_child;
                 ++f.next_child;
-                stack.push_back({child, f.level + 1, 0});
+                if (mask[f.node]) below[f.level + 1].push_back(child);
+                else stack.push_back({child, f.level + 1, 0});
                 continue;
             }
             const int32_t node = f.node;
@@ -965,7 +968,15 @@ int build_program(cr_plan_t *p, const uint8_t *mask, char *h, ProgramCounts *cou
             counts->active_slabs += se - sb;
             counts->active_msgs += 1;
         }
-        real_terms = nt - static_cast<size_t>(sub[i]);
+    };
+    for (int i = 0; i < n; ++i) {
+        sub[i] = static_cast<int32_t>(nt);
+        below[1].assign(1, i);
+        for (int level = 1; level <= L; ++level) {
+            for (size_t k = 0; k < below[level].size(); ++k) walk(below[level][k], level);
+            below[level].clear();
+        }
+        const size_t real_terms = nt - static_cast<size_t>(sub[i]);
         while (nt % cr::kEncodeUnroll != 0) {             // pad with no-op terms on an already fetched slab
             put(nt, nt > 0 ? t_slab[nt - 1] : 0, 0.0);
             ++nt;
