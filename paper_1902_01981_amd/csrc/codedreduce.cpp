@@ -94,6 +94,7 @@ struct cr_plan_s {
     std::vector<cr::Slab> slabs;
     std::vector<int32_t> node_slab_begin;          // N+1
     std::vector<double> slab_coef;
+    cr::TreeShape shape = {};
     std::unique_ptr<cr::TreeArguments> tree_arguments;                     // trees that the tree kernels take
     int64_t row_visits = 0, min_rows = 0, max_rows = 0;
     int64_t max_holders = 1;                       // most workers that hold a row: (s+1)^L, capped at 64
@@ -434,7 +435,7 @@ void compute_layout(cr_plan_t *p, size_t *total)
     p->tables_bytes = w;                                 // what the plan fills in at binding, in one copy
     p->at_placement = take(kPlacementSlots * sizeof(uint32_t));
     p->at_program = take(kProgramSlots * p->program_bytes);
-    p->measures_stride = p->model == CR_AGGREGATE_ONLY ? 0 : 4 * static_cast<size_t>(std::max(cr::decode_groups(p->d), cr::tree_and_decode_together(p->n, p->L, p->tree.N, p->d) ? cr::tree_decode_groups(p->n, p->L, p->d) : 0));
+    p->measures_stride = p->model == CR_AGGREGATE_ONLY ? 0 : 4 * static_cast<size_t>(std::max(cr::decode_groups(p->d), cr::tree_and_decode_together(p->shape, p->d) ? cr::tree_decode_groups(p->n, p->L, p->d) : 0));
     p->at_measures = take(kProgramSlots * p->measures_stride * sizeof(double));
     const size_t row = static_cast<size_t>(p->d) * sizeof(float);
     if (p->model != CR_AGGREGATE_ONLY) {
@@ -582,7 +583,9 @@ int cr_plan_ex(int L, int n, int s, int64_t m, int64_t d, int model, int x_dtype
         for (const cr::Slab &sl : p->slabs) p->node_slab_begin[sl.node + 1] += 1;
         for (int32_t i = 0; i < p->tree.N; ++i) p->node_slab_begin[i + 1] += p->node_slab_begin[i];
         for (const cr::Slab &sl : p->slabs) p->slab_coef.push_back(sl.coef);
-        if (cr::tree_side_by_side(n, L, p->tree.N, d)) {
+        p->shape = {n, L, s, p->tree.N, static_cast<int64_t>(p->slabs.size())};
+        if (cr::tree_side_by_side(p->shape, d, cr::Otherwise::kCopy) || cr::tree_side_by_side(p->shape, d, cr::Otherwise::kLaunches) ||
+            cr::tree_side_by_side(p->shape, d, cr::Otherwise::kBatch)) {
             p->tree_arguments = std::make_unique<cr::TreeArguments>();
             cr::lay_out_tree(p->tree.N, static_cast<int>(p->slabs.size()), p->node_slab_begin.data(), p->slab_coef.data(), p->tree_arguments.get());
         }
@@ -1164,7 +1167,7 @@ int cr_encode_tree(cr_plan_t *p, const uint8_t *mask)
     if (!p->bound) return fail(CR_E_INVAL, "no workspace bound");
     if (!p->have_grads) return fail(CR_E_STATE, "no partial gradients yet");
     ProgramCounts counts;
-    if (cr::tree_side_by_side(p->n, p->L, p->tree.N, p->d)) {
+    if (cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kCopy)) {
         MaskTables tables;
         bool sent = false;
         int rc = mask_tables(p, mask, p->slabs_here, &tables, &counts, &sent);
@@ -1200,8 +1203,8 @@ int cr_gd_run(cr_plan_t *p, const void *X, const float *y, float *w, float *g, c
     int rc = check_masks(p, masks, steps);              // every mask is checked before anything is enqueued
     if (rc != CR_OK) return rc;
     const int32_t N = p->tree.N;
-    const bool side_by_side = cr::tree_side_by_side(p->n, p->L, N, p->d);
-    const bool together = cr::tree_and_decode_together(p->n, p->L, N, p->d) && !overlap(g, p->d, p->d_G, static_cast<int64_t>(p->slabs.size()) * p->d);
+    const bool side_by_side = cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kBatch);
+    const bool together = cr::tree_and_decode_together(p->shape, p->d) && !overlap(g, p->d, p->d_G, static_cast<int64_t>(p->slabs.size()) * p->d);
     ProgramCounts counts[kProgramSlots];
     MaskTables tables;
     bool sent = false;
@@ -1253,7 +1256,7 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
     const bool in_place = overlap(g, p->d + more * g_step_stride, G, static_cast<int64_t>(p->slabs.size()) * p->d + more * G_step_stride);
     // one launch for several masks leaves the order in which workgroups decode open: vectors that overlap in part need it
     const bool in_order = in_place || (g_step_stride > 0 && g_step_stride < p->d);
-    if (cr::tree_and_decode_together(p->n, p->L, N, p->d) && !in_place) {
+    if (cr::tree_and_decode_together(p->shape, p->d) && !in_place) {
         MaskTables tables;
         bool sent = false;
         for (int t = 0; t < steps; ++t) {
@@ -1314,7 +1317,7 @@ int cr_aggregate_static(cr_plan_t *p, const float *G, const uint8_t *mask, float
     ProgramCounts counts;
     char *base = nullptr;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    if (cr::tree_side_by_side(p->n, p->L, p->tree.N, p->d) && p->tree_arguments->fits) {
+    if (cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kLaunches) && p->tree_arguments->fits) {
         cr::NodeCoefs coefs;
         cr::ArgumentTables tables;
         int rc = build_coefs(p, mask, &coefs, &counts);
@@ -1322,7 +1325,7 @@ int cr_aggregate_static(cr_plan_t *p, const float *G, const uint8_t *mask, float
         if (cr::argument_tables(*p->tree_arguments, coefs, &tables)) {
             CR_HIP(cr::static_scratch(&base));          // this device's copy of the array; never the array's name
             float *M = reinterpret_cast<float *>(base + cr::kStaticProgramBytes);
-            if (cr::tree_and_decode_together(p->n, p->L, p->tree.N, p->d) && !overlap(g, p->d, G, static_cast<int64_t>(p->slabs.size()) * p->d)) {
+            if (cr::tree_and_decode_together(p->shape, p->d) && !overlap(g, p->d, G, static_cast<int64_t>(p->slabs.size()) * p->d)) {
                 CR_HIP(cr::launch_tree_encode_decode(G, M, tables, p->n, p->L, g, cr::GradientStep(), p->d, stream));
             } else {
                 CR_HIP(cr::launch_tree_encode(G, M, tables, p->n, p->L, p->d, stream));

@@ -91,6 +91,10 @@ struct TreeArguments {
 };
 void lay_out_tree(int nodes, int slabs, const int32_t *node_begin, const double *slab_coef, TreeArguments *out);
 bool argument_tables(const TreeArguments &tree, const NodeCoefs &coefs, ArgumentTables *out);
+struct TreeShape {           // what the rules of the encode go by
+    int n, L, s, nodes;
+    int64_t slabs;
+};
 // The nodes that a workgroup of the tree kernels has, leaves first, then level by level up: the nodes of level l have the places from
 // first[l - 1] on, and place t is node t + shift[l - 1] + sub * width[l - 1] in level-1 sub-tree `sub`.
 struct TreeLevels {
@@ -164,9 +168,11 @@ bool encode_in_steps(int n, int L, int64_t d, int steps);
 hipError_t launch_encode_steps(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L, float *g, int64_t g_stride, int64_t d,
                                hipStream_t stream);
 // The encode of trees of at most NodeCoefs::kNodes nodes and vectors of at most kTreeColumns columns (tree_side_by_side): a workgroup
-// per level-1 sub-tree and 16 chunks of columns, 64 from kTreeNarrowColumns on.  The tables travel with the launch or are on the device.
+// per level-1 sub-tree and 16 or 64 chunks of columns.  The tables travel with the launch or are on the device.
 constexpr int64_t kTreeColumns = 81920, kTreeNarrowColumns = 32768;
-bool tree_side_by_side(int n, int L, int nodes, int64_t d);
+// What the encode would take instead: a copy of one program, a program written out by launches, a program of which 16 share a copy.
+enum class Otherwise { kCopy, kLaunches, kBatch };
+bool tree_side_by_side(const TreeShape &tree, int64_t d, Otherwise otherwise);
 hipError_t launch_tree_encode(const float *G, float *M, const DeviceTables &tables, int n, int L, int64_t d, hipStream_t stream);
 hipError_t launch_tree_encode(const float *G, float *M, const ArgumentTables &tables, int n, int L, int64_t d, hipStream_t stream);
 // the master's decode and, with step.w, the gradient step; decode_groups: workgroups of the launch
@@ -175,7 +181,7 @@ int decode_groups(int64_t d);
 // Encode, decode and gradient step in one launch, where tree_and_decode_together says so: vectors of at most kTogetherColumns columns
 // (8 chunks of columns per workgroup, 16 from kTogetherNarrowColumns on).
 constexpr int64_t kTogetherColumns = 32768, kTogetherNarrowColumns = 8192;
-bool tree_and_decode_together(int n, int L, int nodes, int64_t d);
+bool tree_and_decode_together(const TreeShape &tree, int64_t d);
 hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, int n, int L, float *g, const GradientStep &step, int64_t d, hipStream_t stream);
 hipError_t launch_tree_encode_decode(const float *G, float *M, const ArgumentTables &tables, int n, int L, float *g, const GradientStep &step, int64_t d, hipStream_t stream);
 int tree_decode_groups(int n, int L, int64_t d);

@@ -1750,7 +1750,9 @@ hipError_t launch_tree(const float *G, float *M, const TABLES &tables, int n, in
 {
     const TreeLevels tree = tree_levels(n, L, false);
     if (d < 4) return launch_tree_shape<1, 16, 256>(G, M, tables, tree, d, stream);
-    if (d > kTreeNarrowColumns && tree_fits<4, 64>(tree)) return launch_tree_shape<4, 64, 256>(G, M, tables, tree, d, stream);
+    // 64 chunks: longer pieces of a slab.  Sub-trees of two levels have the workgroups for it from half as many columns on (us, 16 chunks / 64:
+    // (2,20), 16 385 columns 27.9 / 22.1, 32 768 45.0 / 35.2; (2,4) 16 385 7.7 / 7.8, 24 576 8.8 / 7.9; (3,4) 24 576 13.0 / 12.1, (3,6) 22.6 / 32.9)
+    if (d > (L == 2 ? kTreeNarrowColumns / 2 : kTreeNarrowColumns) && tree_fits<4, 64>(tree)) return launch_tree_shape<4, 64, 256>(G, M, tables, tree, d, stream);
     return launch_tree_shape<4, 16, 256>(G, M, tables, tree, d, stream);
 }
 
@@ -1772,11 +1774,38 @@ hipError_t launch_tree_decode(const float *G, float *M, const TABLES &tables, in
 }
 }  // namespace
 
-bool tree_side_by_side(int n, int L, int nodes, int64_t d) { return nodes <= NodeCoefs::kNodes && d <= kTreeColumns && tree_fits<4, 16>(tree_levels(n, L, false)); }
-
-bool tree_and_decode_together(int n, int L, int nodes, int64_t d)
+// Up to 32 768 columns the nodes side by side are ahead of a walk on every tree.  Beyond, it depends on what the walk's program costs, on
+// the wavefronts that the LDS of 64 chunks leaves in flight (32 KB: five workgroups per compute unit), and on whether slabs and
+// messages in use leave room in the last-level cache, past which the walk reads.  us of a whole iteration on few rows, walk / side by side:
+//   a copy each      32 KB        (2,12), s = 2, 40 001 columns 75.4 / 53.9, 81 920 (164 MB in use) 111 / 104; (2,17) 40 001 (141 MB) 169 / 159,
+//                                 57 344 (202 MB) 222 / 238; (2,12), s = 5, 65 536 (160 MB) 125 / 123, 73 728 (180 MB) 142 / 145
+//                    60 KB        (3,6), s = 2, 40 001 117 / 104, 49 152 128 / 139; (3,5), s = 1, 40 001 (64 MB) 82.4 / 84.7, 57 344 (92 MB)
+//                                 96 / 102; s = 4, 49 152 (37 MB) 77.9 / 67.1, 65 536 (49 MB) 103 / 95
+//                    more         (4,3) 45 001 69.0 / 65.3, 57 344 71.0 / 75.2; (6,2) 40 001 55.7 / 55.6, 65 536 70.5 / 73.4; (3,7) 36 001
+//                                 (146 MB) 190 / 204
+//   16 in a copy     one level    (1,64), 40 001 columns 46.5 / 42.8, 81 920 64.2 / 59.1; (1,10) 28.7 / 28.4, 32.8 / 33.7
+//                    8 to 16      (2,8), s = 2, 40 001 54.8 / 52.0, 49 152 55.9 / 57.3; (2,12), s = 5, 70.3 / 64.8, 79.6 / 80.5
+//                    else         (2,4) 40 001 27.9 / 29.3; (4,2) 26.8 / 29.7; (2,17) 152 / 159; (3,4) 41.2 / 41.3; (3,6) 100 / 105
+//   launches         32 KB        (2,12), s = 2, 40 001 22.7 / 22.3, (1,10) 14.5 / 9.6; beside the arguments' copy (3,4), 31 KB, 65 536 16.9 / 15.7,
+//                                 81 920 19.7 / 22.3, (4,2), 29 KB, 14.8 / 13.1
+//                    more         40 001 (3,5), s = 4, 16.0 / 19.4, (5,2) 18.1 / 19.5
+bool tree_side_by_side(const TreeShape &tree, int64_t d, Otherwise otherwise)
 {
-    return tree_side_by_side(n, L, nodes, d) && d <= kTogetherColumns && tree_fits<4, 8>(tree_levels(n, L, true));
+    const TreeLevels sub = tree.nodes <= NodeCoefs::kNodes ? tree_levels(tree.n, tree.L, false) : TreeLevels();
+    if (tree.nodes > NodeCoefs::kNodes || d > kTreeColumns || !tree_fits<4, 16>(sub)) return false;
+    if (d <= kTreeNarrowColumns) return true;
+    if (otherwise == Otherwise::kBatch) return tree.L == 1 || (tree.L == 2 && tree.n >= 8 && tree.n <= 16 && d <= 45056);
+    const size_t lds = TreeLds<4, 64>::bytes(sub.total, sub.leaves);
+    if (otherwise == Otherwise::kLaunches) return lds <= size_t(d <= 65536 ? 32 : 30) << 10;
+    const int64_t in_use = (tree.slabs + tree.nodes) * d * 4 / tree.n * (tree.n - tree.s);
+    if (lds <= size_t(32) << 10) return in_use <= int64_t(164) << 20;
+    if (in_use > int64_t(140) << 20) return false;
+    return tree_fits<4, 64>(sub) ? d <= 40960 || in_use <= int64_t(64) << 20 : d <= 49152;
+}
+
+bool tree_and_decode_together(const TreeShape &tree, int64_t d)
+{
+    return d <= kTogetherColumns && tree_side_by_side(tree, d, Otherwise::kCopy) && tree_fits<4, 8>(tree_levels(tree.n, tree.L, true));
 }
 
 int tree_decode_groups(int n, int L, int64_t d)

@@ -19,7 +19,8 @@ def _masks(rng, steps, groups, n, s):
 
 
 @pytest.mark.parametrize("d", WIDTHS)
-@pytest.mark.parametrize("L,n,s", [(2, 3, 1), (2, 21, 0)])       # 462 workers: more than kernel arguments hold
+# 155 workers whose sub-trees leave a compute unit less LDS than five workgroups need; 462: more than kernel arguments hold
+@pytest.mark.parametrize("L,n,s", [(2, 3, 1), (3, 5, 1), (2, 21, 0)])
 def test_steps_of_a_run(L, n, s, d):
     import torch
 
@@ -57,8 +58,12 @@ def test_steps_of_a_run(L, n, s, d):
     cr.cr_plan_destroy(plan)
 
 
-@pytest.mark.parametrize("d", WIDTHS)
-@pytest.mark.parametrize("L,n,s", [(2, 12, 2), (3, 6, 2), (3, 4, 1), (2, 8, 2)])     # two and many distinct coefficients; (3, 6): more than fit
+# two and many distinct coefficients; (3, 6): more than fit; widths at which only some of the calls have the nodes side by side
+STATIC = [(*tree, d) for tree in [(2, 12, 2), (3, 6, 2), (3, 4, 1), (2, 8, 2)] for d in WIDTHS]
+STATIC += [(2, 12, 5, 81_920), (3, 4, 1, 65_536), (3, 4, 1, 65_537), (4, 2, 1, 81_920), (4, 3, 1, 32_769), (1, 10, 4, 81_920)]
+
+
+@pytest.mark.parametrize("L,n,s,d", STATIC)
 def test_static_aggregation(L, n, s, d):
     import torch
 

@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 # groups of 64; one level; eight levels
 CASES = [(2, 3, 1, d) for d in (1, 3, 4, 5, 63, 64, 65, 67, 1_023, 1_028)]
 CASES += [(1, 2, 0, 100), (1, 64, 1, 130), (1, 10, 4, 1_027), (2, 20, 1, 77), (2, 21, 1, 77), (3, 7, 2, 70), (3, 6, 2, 1_024), (6, 2, 1, 66), (7, 2, 1, 66), (8, 2, 1, 66)]
+CASES += [(2, 20, 1, 16_384), (2, 20, 1, 16_385), (3, 5, 4, 65_537), (3, 4, 1, 81_920), (4, 3, 1, 49_152), (4, 3, 1, 49_153), (2, 17, 1, 49_153)]
 CASES += [(2, 12, 3, 5_001), (3, 3, 1, 32_768), (3, 3, 1, 32_769), (2, 4, 1, 81_920), (2, 4, 1, 81_921), (2, 8, 2, 81_919), (1, 3, 1, 2_097_151), (1, 3, 1, 2_097_155)]
 
 
