@@ -212,9 +212,9 @@ int cr_gd_run(cr_plan_t *plan, const void *X_dev, const float *y_dev, float *w_d
 
 /* Aggregation alone, many masks in one call (CR.Execute steps 2 to the end, Algorithm 2, once per mask): step t encodes the slab
  * gradients at G_dev + t * G_step_stride under masks_host[t] and decodes into g_dev + t * g_step_stride; like cr_load_partial_grads,
- * cr_encode_tree and cr_decode_root called in turn (the same bits).  Short vectors (d <= 32768) take one launch per mask; longer ones on
- * trees of up to three levels and 32 children per parent one launch for up to 16 masks, behind one copy of their programs; very long
- * ones two launches per mask.
+ * cr_encode_tree and cr_decode_root called in turn (the same bits).  Short vectors (d <= 32768) take one launch per mask, two on
+ * trees of more than some 400 workers; longer ones on trees of up to three levels and 32 children per parent mostly one launch for up to 16
+ * masks, behind one copy of their programs; else two launches per mask.
  *   G_dev          device, S x d floats per step, 16-byte aligned; G_step_stride in floats (a multiple of 4): 0 = the same slabs every step
  *   masks_host     steps x N bytes; all are checked first: CR_E_UNDECODABLE before anything is enqueued
  *   g_dev          device, d floats per step; g_step_stride in floats: 0 = every step overwrites the same vector.  The vectors may lie

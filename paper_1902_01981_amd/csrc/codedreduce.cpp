@@ -1256,26 +1256,21 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
     const bool in_place = overlap(g, p->d + more * g_step_stride, G, static_cast<int64_t>(p->slabs.size()) * p->d + more * G_step_stride);
     // one launch for several masks leaves the order in which workgroups decode open: vectors that overlap in part need it
     const bool in_order = in_place || (g_step_stride > 0 && g_step_stride < p->d);
-    if (cr::tree_and_decode_together(p->shape, p->d) && !in_place) {
-        MaskTables tables;
-        bool sent = false;
-        for (int t = 0; t < steps; ++t) {
-            ProgramCounts counts;
-            rc = mask_tables(p, masks + static_cast<size_t>(t) * N, false, &tables, &counts, &sent);
-            if (rc != CR_OK) return rc;
-            p->G_src = G + static_cast<int64_t>(t) * G_step_stride;
-            p->have_grads = true;
-            rc = encode_decode(p, tables, counts, g + static_cast<int64_t>(t) * g_step_stride, cr::GradientStep());
-            if (rc != CR_OK) return rc;
-        }
-        return CR_OK;
-    }
+    const bool together = cr::tree_and_decode_together(p->shape, p->d) && !in_place;
     ProgramCounts counts[kProgramSlots];
+    MaskTables tables;
+    bool sent = false;
     for (int t0 = 0; t0 < steps; t0 += kProgramSlots) {
         const int count = std::min(kProgramSlots, steps - t0);
-        rc = upload_programs(p, masks + static_cast<size_t>(t0) * N, count, counts);
-        if (rc != CR_OK) return rc;
-        if (!in_order && cr::encode_in_steps(p->n, p->L, p->d, count)) {
+        // one mask: the nodes side by side need no copy of a program
+        const bool alone = cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kCopy) && count == 1;
+        const bool in_steps = !in_order && !alone && cr::encode_in_steps(p->shape, p->d, count);
+        const bool side_by_side = alone || cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kBatch);
+        if (in_steps || !side_by_side) {
+            rc = upload_programs(p, masks + static_cast<size_t>(t0) * N, count, counts);
+            if (rc != CR_OK) return rc;
+        }
+        if (in_steps) {
             int64_t rows = 0;
             for (int i = 0; i < count; ++i) rows += counts[i].active_slabs + counts[i].active_msgs + 1;
             p->G_src = G + static_cast<int64_t>(t0 + count - 1) * G_step_stride;
@@ -1289,10 +1284,16 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
             continue;
         }
         for (int i = 0; i < count; ++i) {
+            float *out = g + static_cast<int64_t>(t0 + i) * g_step_stride;
+            if (side_by_side) rc = mask_tables(p, masks + static_cast<size_t>(t0 + i) * N, false, &tables, &counts[i], &sent);
+            if (rc != CR_OK) return rc;
             p->G_src = G + static_cast<int64_t>(t0 + i) * G_step_stride;
             p->have_grads = true;
-            rc = encode_slot(p, i, counts[i]);
-            if (rc == CR_OK) rc = decode_root(p, g + static_cast<int64_t>(t0 + i) * g_step_stride, cr::GradientStep());
+            if (together) rc = encode_decode(p, tables, counts[i], out, cr::GradientStep());
+            else {
+                rc = side_by_side ? encode_tree(p, tables, counts[i]) : encode_slot(p, i, counts[i]);
+                if (rc == CR_OK) rc = decode_root(p, out, cr::GradientStep());
+            }
             if (rc != CR_OK) return rc;
         }
     }

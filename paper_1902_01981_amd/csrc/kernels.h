@@ -164,7 +164,7 @@ hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, const 
 hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int num_sub, int L, int64_t d, hipStream_t stream);
 // Encode and decode of `steps` masks, one after the other, in one launch (where encode_in_steps says so); the programs lie prog_stride
 // bytes apart.
-bool encode_in_steps(int n, int L, int64_t d, int steps);
+bool encode_in_steps(const TreeShape &tree, int64_t d, int steps);
 hipError_t launch_encode_steps(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L, float *g, int64_t g_stride, int64_t d,
                                hipStream_t stream);
 // The encode of trees of at most NodeCoefs::kNodes nodes and vectors of at most kTreeColumns columns (tree_side_by_side): a workgroup

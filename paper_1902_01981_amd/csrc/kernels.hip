@@ -1055,15 +1055,15 @@ encode_kernel(const float *__restrict__ G, float *__restrict__ M, EncProgram pro
 // which one wavefront decodes while the others go on).  No launches, ramps and last waves between the masks, and the master's messages
 // are not read back.  us a mask, a launch each for encode and decode / this: (2,4) tree, 2 000 000 columns, four masks 62.2 / 54.6;
 // (3,4), 60 001 columns, eight masks 17.3 / 12.1; (2,12), s = 5, 117 706 columns, eight masks 61.8 / 60.7 (rows on 8-byte boundaries;
-// 117 760 columns 56).  A single mask gains less, and groups of more than four nothing once their rows fill the chip many times over
-// ((2,8), 1 000 000 columns 174.8 / 177.6; (2,4), 2 000 000 65.5 / 60.5; (2,12), 60 000 44.5 / 42.0).
+// 117 760 columns 56).  Where it loses: see encode_in_steps.
 // Slabs are read past the caches and messages are not written past them: the next mask's messages often replace them there (encode
 // alone, 117 706 columns: 59.6 against 61.8).
-template <int VEC, int LT>
+template <int LT>
 __global__ void __launch_bounds__(1024)
 encode_steps_kernel(const float *__restrict__ G, int64_t G_stride, float *__restrict__ M, EncProgram prog, int64_t prog_stride, int steps, int n, float *__restrict__ g, int64_t g_stride,
                     int64_t d, int nq)
 {
+    constexpr int VEC = 4;
     extern __shared__ __align__(16) char step_lds[];
     float *top = reinterpret_cast<float *>(step_lds);    // [2][n][VEC][64]
     const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
@@ -1673,30 +1673,43 @@ static hipError_t launch_encode_shape(const float *G, float *M, const EncProgram
 // wide shape once its 8192-chunk workgroups are enough to fill the chip, and only up to 3 levels (registers)
 static bool encode_is_wide(int n, int L, int64_t d) { return d >= 4 && ((d + 3) / 4 + 8191) / 8192 * n >= 256 && L <= 3; }
 
-template <int VEC>
-static hipError_t launch_encode_steps_shape(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L, float *g, int64_t g_stride,
-                                            int64_t d, hipStream_t stream)
+// The rule for one launch of all masks.  A workgroup keeps its 64 chunks of columns for all of them, so that a round of a workgroup per
+// compute unit that is less than half full costs as much as a full one, and every next one the more the more slabs there are.  What the
+// launch saves is the launches and ramps of each mask and, where the messages of a mask do not fit the last-level cache, writing them
+// more than once.  us a mask, eight masks with gradients of their own, a launch of each kind per mask / one launch:
+//   one round    (2,12), s = 2, 65 536 columns 29.4 / 24.7; (3,6), s = 2, 40.9 / 34.6; (2,24), s = 1, 81.6 / 74.9
+//   two          73 728 columns: (2,8), s = 2 (248 slabs) 21.0 / 17.9; (2,12), s = 1 (300) 29.4 / 28.3; s = 2 (444) 33.3 / 34.4; s = 5 (888)
+//                41.3 / 44.2; (2,17) (629) 53.2 / 60.2; 117 706: s = 5 62.0 / 60.7; (2,17) 80.6 / 77.6; (3,8), s = 2 (2104) 186.6 / 187.7
+//   three, four  160 001: (2,8) 35.1 / 32.5; (3,5) (345) 56.1 / 50.8; (2,12), s = 5 81.9 / 83.7; 200 003: s = 2 77.6 / 83.8, s = 5 100 / 110
+//   more         400 001: s = 2 147 / 157, s = 5 190 / 208; (3,4) (148) 58.5 / 54.3
+//   messages of 256 MB and more   (2,12), s = 1, 600 001 224 / 183; (3,6) 400 001 258 / 229; (2,24) 160 001 249 / 206
+// Up to 32 768 columns a launch per mask is ahead on every tree: (2,24), s = 1, 1 000 columns 17.5 / 30.1, 32 768 46.8 / 49.4.  A single
+// mask has less to save (and the nodes side by side where tree_side_by_side says so): (2,12), s = 2, 117 706 66.2 / 64.9, 200 003
+// 94.3 / 101; s = 5, 81 920 59.8 / 64.4; (2,32), s = 1, 40 001 117 / 125.
+bool encode_in_steps(const TreeShape &tree, int64_t d, int steps)
 {
-    const int nq = static_cast<int>((d + VEC - 1) / VEC);
+    if (tree.n > 32 || tree.L > 3 || d <= kTogetherColumns || encode_is_wide(tree.n, tree.L, d)) return false;
+    if (tree.n <= 4 || (tree.L == 1 && tree.n * d <= int64_t(1) << 22)) return true;
+    constexpr int64_t kUnits = 256;
+    const int64_t groups = (d + 255) / 256, messages = static_cast<int64_t>(tree.nodes) * d * 4 / tree.n * (tree.n - tree.s);
+    const bool half_empty = groups > kUnits && 2 * groups < 3 * kUnits;
+    const int64_t load = tree.slabs * groups;
+    if (steps == 1) return groups <= 2 * kUnits && load <= (half_empty ? 160000 : 300000);
+    if (groups <= 2 * kUnits && !half_empty) return true;
+    return messages >= int64_t(256) << 20 || load <= (4 * groups < 5 * kUnits ? 100000 : 300000);
+}
+
+hipError_t launch_encode_steps(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L, float *g, int64_t g_stride,
+                               int64_t d, hipStream_t stream)
+{
+    const int nq = static_cast<int>((d + 3) / 4);
     const unsigned groups = ((nq + 63) / 64 + 7) / 8 * 8, block = 64 * (n < 16 ? n : 16);
-    const size_t lds = static_cast<size_t>(2) * n * VEC * 64 * sizeof(float);
-    if (L <= 1) encode_steps_kernel<VEC, 1><<<groups, block, lds, stream>>>(G, G_stride, M, prog, prog_stride, steps, n, g, g_stride, d, nq);
-    else if (L == 2) encode_steps_kernel<VEC, 2><<<groups, block, lds, stream>>>(G, G_stride, M, prog, prog_stride, steps, n, g, g_stride, d, nq);
-    else if (L == 3) encode_steps_kernel<VEC, 3><<<groups, block, lds, stream>>>(G, G_stride, M, prog, prog_stride, steps, n, g, g_stride, d, nq);
+    const size_t lds = static_cast<size_t>(2) * n * 4 * 64 * sizeof(float);
+    if (L <= 1) encode_steps_kernel<1><<<groups, block, lds, stream>>>(G, G_stride, M, prog, prog_stride, steps, n, g, g_stride, d, nq);
+    else if (L == 2) encode_steps_kernel<2><<<groups, block, lds, stream>>>(G, G_stride, M, prog, prog_stride, steps, n, g, g_stride, d, nq);
+    else if (L == 3) encode_steps_kernel<3><<<groups, block, lds, stream>>>(G, G_stride, M, prog, prog_stride, steps, n, g, g_stride, d, nq);
     else return hipErrorInvalidValue;
     return hipGetLastError();
-}
-
-bool encode_in_steps(int n, int L, int64_t d, int steps)
-{
-    return n <= 32 && L <= 3 && !encode_is_wide(n, L, d) && (steps > 1 || n <= 4 || n * d <= (int64_t(1) << 22));
-}
-
-hipError_t launch_encode_steps(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L, float *g, int64_t g_stride, int64_t d,
-                               hipStream_t stream)
-{
-    return d >= 4 ? launch_encode_steps_shape<4>(G, G_stride, M, prog, prog_stride, steps, n, L, g, g_stride, d, stream)
-                  : launch_encode_steps_shape<1>(G, G_stride, M, prog, prog_stride, steps, n, L, g, g_stride, d, stream);
 }
 
 hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int num_sub, int L, int64_t d, hipStream_t stream)

@@ -114,3 +114,37 @@ def test_runs_of_masks(L, n, s, d, steps):
     assert torch.equal(again, want)
     del ws
     cr.cr_plan_destroy(plan)
+
+
+# one launch per mask; the nodes side by side and a decode; programs and a decode; all masks in one launch
+LAUNCHES = [(2, 12, 5, 32_768, 3, 3, 0), (2, 20, 1, 1_003, 3, 3, 3), (2, 24, 1, 1_003, 3, 3, 3), (3, 8, 2, 32_768, 2, 2, 2), (2, 24, 1, 32_769, 3, 1, 0),
+            (2, 12, 5, 65_536, 2, 1, 0), (2, 12, 5, 65_537, 2, 2, 2), (2, 8, 2, 65_537, 2, 1, 0), (2, 12, 5, 98_305, 2, 1, 0), (2, 12, 5, 131_073, 2, 2, 2),
+            (3, 5, 1, 131_073, 2, 1, 0), (3, 4, 1, 400_001, 2, 1, 0), (2, 17, 1, 235_000, 2, 1, 0), (2, 12, 1, 40_001, 1, 1, 1), (2, 12, 1, 90_001, 1, 1, 0), (2, 12, 5, 81_920, 1, 1, 1),
+            (2, 12, 1, 40_001, 17, 2, 1), (4, 2, 1, 40_001, 3, 3, 3), (1, 33, 1, 40_001, 3, 3, 3)]
+
+
+@pytest.mark.parametrize("L,n,s,d,steps,encodes,decodes", LAUNCHES)
+def test_launches_of_a_run(L, n, s, d, steps, encodes, decodes):
+    """Which launches a call over several masks takes on both sides of its rules (a launch that does the work of several counts as the
+    encode's), with the same bits as three calls per mask: all masks on the same slabs, into the same vector."""
+    import torch
+
+    plan = cr.cr_plan_ex(L, n, s, 40 * n ** L, d, model=cr.CR_AGGREGATE_ONLY)
+    ws = cr.Workspace(plan)
+    G, g, want = torch.randn(ws.info.num_slabs, d, device="cuda"), torch.empty(d, device="cuda"), torch.empty(d, device="cuda")
+    masks, M = _masks(np.random.default_rng(d), steps, ws.info.num_groups, n, s), ws.messages()
+    M.zero_()
+    cr.cr_profile_enable(plan, True)
+    cr.cr_aggregate_run(plan, G, masks, g)
+    assert (cr.cr_profile_read(plan, cr.CR_K_ENCODE)[1], cr.cr_profile_read(plan, cr.CR_K_DECODE)[1]) == (encodes, decodes)
+    cr.cr_profile_enable(plan, False)
+    after = M.clone()
+    M.zero_()
+    for mask in masks:
+        cr.cr_load_partial_grads(plan, G)
+        cr.cr_encode_tree(plan, mask)
+        cr.cr_decode_root(plan, want)
+    cr.cr_synchronize(plan)
+    assert torch.equal(g, want) and torch.equal(M, after)
+    del ws
+    cr.cr_plan_destroy(plan)
