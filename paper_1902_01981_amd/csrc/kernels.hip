@@ -1816,9 +1816,15 @@ bool tree_side_by_side(const TreeShape &tree, int64_t d, Otherwise otherwise)
     return tree_fits<4, 64>(sub) ? d <= 40960 || in_use <= int64_t(64) << 20 : d <= 49152;
 }
 
+// From 8 192 columns on, where the whole tree's messages do not fit LDS for 16 chunks, the launch has twice the workgroups, of eight chunks,
+// each with the whole chain of a deep tree; on two levels that still pays.  us of encode and decode apart / together: (6,2) 12 288 columns
+// 16.2 / 19.4, 32 768 18.4 / 38.0; (3,6), s = 2, 8 195 13.4 / 17.5, 16 384 19.4 / 18.4, 32 768 28.8 / 33.5; (2,17), s = 1, 16 384 18.8 / 18.8,
+// 24 576 25.4 / 26.4, 12 288 20.3 / 17.3; (2,19) 16 384 20.8 / 21.7.
 bool tree_and_decode_together(const TreeShape &tree, int64_t d)
 {
-    return d <= kTogetherColumns && tree_side_by_side(tree, d, Otherwise::kCopy) && tree_fits<4, 8>(tree_levels(tree.n, tree.L, true));
+    const TreeLevels whole = tree.nodes <= NodeCoefs::kNodes ? tree_levels(tree.n, tree.L, true) : TreeLevels();
+    if (d > kTogetherColumns || !tree_side_by_side(tree, d, Otherwise::kCopy) || !tree_fits<4, 8>(whole)) return false;
+    return d <= kTogetherNarrowColumns || tree.L <= 2 || tree_fits<4, 16>(whole);
 }
 
 int tree_decode_groups(int n, int L, int64_t d)

@@ -117,7 +117,7 @@ def test_runs_of_masks(L, n, s, d, steps):
 
 
 # one launch per mask; the nodes side by side and a decode; programs and a decode; all masks in one launch
-LAUNCHES = [(2, 12, 5, 32_768, 3, 3, 0), (2, 20, 1, 1_003, 3, 3, 3), (2, 24, 1, 1_003, 3, 3, 3), (3, 8, 2, 32_768, 2, 2, 2), (2, 24, 1, 32_769, 3, 1, 0),
+LAUNCHES = [(2, 12, 5, 32_768, 3, 3, 0), (3, 6, 2, 8_192, 3, 3, 0), (3, 6, 2, 8_193, 3, 3, 3), (6, 2, 1, 32_768, 3, 3, 3), (2, 17, 1, 32_768, 3, 3, 0), (2, 20, 1, 1_003, 3, 3, 3), (2, 24, 1, 1_003, 3, 3, 3), (3, 8, 2, 32_768, 2, 2, 2), (2, 24, 1, 32_769, 3, 1, 0),
             (2, 12, 5, 65_536, 2, 1, 0), (2, 12, 5, 65_537, 2, 2, 2), (2, 8, 2, 65_537, 2, 1, 0), (2, 12, 5, 98_305, 2, 1, 0), (2, 12, 5, 131_073, 2, 2, 2),
             (3, 5, 1, 131_073, 2, 1, 0), (3, 4, 1, 400_001, 2, 1, 0), (2, 17, 1, 235_000, 2, 1, 0), (2, 12, 1, 40_001, 1, 1, 1), (2, 12, 1, 90_001, 1, 1, 0), (2, 12, 5, 81_920, 1, 1, 1),
             (2, 12, 1, 40_001, 17, 2, 1), (4, 2, 1, 40_001, 3, 3, 3), (1, 33, 1, 40_001, 3, 3, 3)]
