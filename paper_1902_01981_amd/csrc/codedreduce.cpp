@@ -275,35 +275,60 @@ void make_rows_once(cr_plan_t *p, int64_t rows_per_run)
     cr::once_equal_parts(p->slabs, p->m, parts, rows_per_run, p->work);
 }
 
-// Rows of more than 24 576 columns whose weights fit LDS take one pass from this size of X on.  Below it the partial rows of a part per
-// compute unit cost more than the second pass (us with sums, one pass / two: 300 x 30 000 bf16 22.8 / 18.2, 600 x 30 000 bf16 24.9 / 24.2,
-// 1 200 x 26 000 bf16, 62 MB, 28.3 / 31.7, 700 x 32 000 fp32, 90 MB on a (12,2) tree, 41.8 / 46.5, 3 000 x 30 001 fp32 78 / 118,
-// 6 000 x 32 768 fp32 141 / 249).
+int64_t wide_one_pass_parts(const cr_plan_t *p) { return std::max<int64_t>(1, std::min<int64_t>(query_units(), p->m / 4)); }
+
+// The parts of the second of two passes, each of which has one workgroup per block of columns; two workgroups per compute unit, no fewer
+// rows per part than a workgroup has in flight (4 000 x 50 008 bf16 with one, two, four and eight: 123, 124, 130 and 138 us, 4 000 x 60 000
+// fp32 290, 281, 287 and more; fewer partial rows to add up as well).
+int64_t wide_two_pass_parts(const cr_plan_t *p)
+{
+    const int64_t vec = p->x_dtype == CR_BF16 ? 8 : 4, blocks = ((p->d + vec - 1) / vec + cr::kWideColumnChunks - 1) / cr::kWideColumnChunks;
+    return std::max<int64_t>(1, std::min<int64_t>(2 * static_cast<int64_t>(query_units()) / blocks, p->m / 16));
+}
+
+// Rows of more than 24 576 columns whose weights fit LDS take one pass where X has more bytes than nine tenths of the rows that the part
+// per compute unit puts away and adds up beyond those of two passes, and from 48 MB of X on (us with sums, one pass / two:
+// 300 x 30 000 bf16 22.8 / 18.2, 600 x 30 000 bf16, 36 MB, 24.9 / 24.2, 1 200 x 26 000 bf16 28.3 / 31.7, 3 000 x 30 001 fp32 78 / 118,
+// 6 000 x 32 768 fp32 141 / 249; (2,12), s = 1, 300 slabs: 712 x 36 864 bf16 62.2 / 46.1, 2 134 x 28 672 56 / 60; (3,6), s = 2, 774 slabs:
+// 1 423 x 36 864 bf16 79.0 / 69.5, 4 369 x 30 001 fp32 125 / 209).  On 1 089 trees and sizes the rule is 0.4 % behind the faster of the two, and 16 % at
+// worst.
 constexpr int64_t kWideOnePassBytes = int64_t(48) << 20;
+
+bool one_pass_pays(const cr_plan_t *p)
+{
+    const int64_t bytes = p->m * p->d * elem_size(p);
+    if (bytes < kWideOnePassBytes || !cr::select_once_wide(p->x_dtype, p->d)) return false;
+    auto rows_put_away = [&](int64_t parts) {
+        cr::OnceWork work;
+        cr::once_equal_parts(p->slabs, p->m, parts, p->m, work);
+        int64_t rows = static_cast<int64_t>(work.runs.size());
+        for (const cr::RowSum &sum : work.sums) rows += sum.row_end - sum.row_begin;
+        return rows;
+    };
+    return bytes / 9 * 10 > (rows_put_away(wide_one_pass_parts(p)) - rows_put_away(wide_two_pass_parts(p))) * p->d * 4;
+}
 
 // One pass over wide rows: a part per compute unit, at least four rows; the most rows that a part has, or 0: two passes.
 int64_t wide_one_pass_rows(const cr_plan_t *p)
 {
-    if (p->m * p->d * elem_size(p) < kWideOnePassBytes || !cr::select_once_wide(p->x_dtype, p->d)) return 0;
-    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(query_units(), p->m / 4));
-    return (p->m + parts - 1) / parts;
+    const int64_t parts = wide_one_pass_parts(p);
+    return one_pass_pays(p) ? (p->m + parts - 1) / parts : 0;
 }
 
-// The same for wide rows.  One pass where that is possible and runs of no more rows are asked for than its parts have, which the default
-// split does; longer runs take two passes, where parts are long.  One pass: parts as above.  Two passes: the parts of the
-// second pass, each of which has one workgroup per block of columns; two workgroups per compute unit, no fewer rows per part than a
-// workgroup has in flight (4 000 x 50 008 bf16 with one, two, four and eight: 123, 124, 130 and 138 us, 4 000 x 60 000 fp32 290, 281, 287 and
-// more; fewer partial rows to add up as well).
+// Slabs that a workgroup of the one pass writes a run's whole row to; a row of 100 to 147 KB takes it a microsecond each, one after the
+// other.  To more of them the sums' launch hands it, a workgroup per 64 chunks.
+constexpr size_t kWideCopies = 2;
+
+// The same for wide rows.  One pass where that pays and runs of no more rows are asked for than its parts have, which the default
+// split does; longer runs take two passes, where parts are long.
 void make_wide_once(cr_plan_t *p, int64_t rows_per_run)
 {
     if (rows_per_run <= wide_one_pass_rows(p)) {
         p->wide_variant = cr::select_once_wide(p->x_dtype, p->d);
-        return cr::once_equal_parts(p->slabs, p->m, std::max<int64_t>(1, std::min<int64_t>(query_units(), p->m / 4)), rows_per_run, p->work);
+        return cr::once_equal_parts(p->slabs, p->m, wide_one_pass_parts(p), rows_per_run, p->work, kWideCopies);
     }
-    const int64_t vec = p->x_dtype == CR_BF16 ? 8 : 4, blocks = ((p->d + vec - 1) / vec + cr::kWideColumnChunks - 1) / cr::kWideColumnChunks;
     p->units = query_units();
-    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>(2 * static_cast<int64_t>(p->units) / blocks, p->m / 16));
-    cr::once_equal_parts(p->slabs, p->m, parts, rows_per_run, p->work);
+    cr::once_equal_parts(p->slabs, p->m, wide_two_pass_parts(p), rows_per_run, p->work);
 }
 
 int make_split(cr_plan_t *p)

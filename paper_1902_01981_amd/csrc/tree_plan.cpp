@@ -273,8 +273,9 @@ void split_shared_queues(const std::vector<Slab> &slabs, int64_t cell_rows, int 
 }
 
 namespace {
-// Given the runs of `out` (part-major, disjoint, covering every slab in whole runs): who receives what.
-void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
+// Given the runs of `out` (part-major, disjoint, covering every slab in whole runs): who receives what.  A run that makes up more than
+// `most_copies` slabs by itself goes to them by way of a sum, as runs that only together make up slabs do.
+void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out, size_t most_copies = SIZE_MAX)
 {
     const int32_t S = static_cast<int32_t>(slabs.size());
     std::vector<int32_t> by_row(out.runs.size());
@@ -288,7 +289,7 @@ void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
     std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
         return slabs[a].row_begin != slabs[b].row_begin ? slabs[a].row_begin < slabs[b].row_begin : slabs[a].row_end < slabs[b].row_end;
     });
-    struct Range { size_t ob, oe, rb, re; };             // slabs order[ob .. oe), runs by_row[rb .. re)
+    struct Range { size_t ob, oe, rb, re; bool summed; };            // slabs order[ob .. oe), runs by_row[rb .. re)
     std::vector<Range> ranges;
     std::vector<char> partial(by_row.size(), 0);
     for (size_t i = 0; i < order.size();) {
@@ -297,8 +298,9 @@ void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
         while (k < order.size() && slabs[order[k]].row_begin == sl.row_begin && slabs[order[k]].row_end == sl.row_end) ++k;
         const size_t rb = static_cast<size_t>(std::lower_bound(begins.begin(), begins.end(), sl.row_begin) - begins.begin());
         const size_t re = static_cast<size_t>(std::lower_bound(begins.begin(), begins.end(), sl.row_end) - begins.begin());
-        ranges.push_back({i, k, rb, re});
-        if (re - rb > 1) std::fill(partial.begin() + rb, partial.begin() + re, 1);
+        const bool summed = re - rb > 1 || k - i > most_copies;
+        ranges.push_back({i, k, rb, re, summed});
+        if (summed) std::fill(partial.begin() + rb, partial.begin() + re, 1);
         i = k;
     }
     std::vector<int32_t> partial_row(by_row.size() + 1);             // partial row of a run that has one
@@ -310,7 +312,7 @@ void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
     }
     partial_row[by_row.size()] = S + out.partials;
     for (const Range &r : ranges)
-        if (r.re - r.rb == 1) to[r.rb].insert(to[r.rb].end(), order.begin() + r.ob, order.begin() + r.oe);
+        if (!r.summed) to[r.rb].insert(to[r.rb].end(), order.begin() + r.ob, order.begin() + r.oe);
     for (size_t i = 0; i < by_row.size(); ++i) {
         RowRun &run = out.runs[by_row[i]];
         run.dst_begin = static_cast<int32_t>(out.dst.size());
@@ -318,7 +320,7 @@ void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
         run.dst_end = static_cast<int32_t>(out.dst.size());
     }
     for (const Range &r : ranges)
-        if (r.re - r.rb > 1) {
+        if (r.summed) {
             const int32_t begin = static_cast<int32_t>(out.dst.size());
             out.dst.insert(out.dst.end(), order.begin() + r.ob, order.begin() + r.oe);
             out.sums.push_back({partial_row[r.rb], partial_row[r.re], begin, static_cast<int32_t>(out.dst.size())});
@@ -326,7 +328,7 @@ void assign_outputs(const std::vector<Slab> &slabs, OnceWork &out)
 }
 }  // namespace
 
-void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, int64_t rows_per_run, OnceWork &out)
+void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, int64_t rows_per_run, OnceWork &out, size_t most_copies)
 {
     rows_per_run = std::min(rows_per_run, kMaxRunRows);
     out = OnceWork();
@@ -342,7 +344,7 @@ void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, 
         }
         out.part_run_begin.push_back(static_cast<int32_t>(out.runs.size()));
     }
-    assign_outputs(slabs, out);
+    assign_outputs(slabs, out, most_copies);
 }
 
 void once_whole_ranges(const std::vector<Slab> &slabs, OnceWork &out)

@@ -1,5 +1,6 @@
 // (n,L)-regular tree, CompAlloc (Algorithm 1) and CR.Allocate (Algorithm 2): which rows of X every worker holds, with which scalar.
 #pragma once
+#include <cstddef>
 #include <cstdint>
 #include <vector>
 
@@ -84,8 +85,9 @@ struct OnceWork {
     std::vector<int32_t> dst;
     int32_t partials = 0;
 };
-// `parts` contiguous, near-equal parts of the rows [0, m), cut at slab boundaries and after every `rows_per_run` rows.
-void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, int64_t rows_per_run, OnceWork &out);
+// `parts` contiguous, near-equal parts of the rows [0, m), cut at slab boundaries and after every `rows_per_run` rows.  Runs that make up
+// more than `most_copies` slabs by themselves are handed to them by a sum.
+void once_equal_parts(const std::vector<Slab> &slabs, int64_t m, int64_t parts, int64_t rows_per_run, OnceWork &out, size_t most_copies = SIZE_MAX);
 // One part per distinct slab range, whole (ranges that overlap are then formed separately, none of more than kMaxRunRows rows): no
 // sums, no partial rows.
 void once_whole_ranges(const std::vector<Slab> &slabs, OnceWork &out);

@@ -24,6 +24,47 @@ def test_what_a_plan_reports_is_the_same_work_when_set(d, bf16, m, one_pass):
         cr.cr_plan_destroy(plan)
 
 
+@pytest.mark.parametrize("L,n,s,m,one_pass", [(3, 3, 2, 874, True), (2, 12, 1, 712, False), (2, 12, 1, 2_845, True), (3, 6, 2, 1_423, False), (3, 6, 2, 8_000, True)])
+def test_one_pass_where_the_partial_rows_allow_it(L, n, s, m, one_pass):
+    """Many slabs cut the parts of one pass into many runs; below some size of X the second pass costs less."""
+    p, q = (cr.cr_plan_ex(L, n, s, m, 36_864, x_dtype=1) for _ in range(2))
+    cr.cr_workspace_bytes(p)
+    info = cr.cr_plan_info(p)
+    assert (info.split_value < m) == one_pass
+    cr.cr_plan_set_split(q, info.split_kind, info.split_value)
+    assert cr.cr_workspace_bytes(q) == cr.cr_workspace_bytes(p) and all(np.array_equal(a, b) for a, b in zip(cr.cr_plan_get_pieces(p), cr.cr_plan_get_pieces(q)))
+    for plan in (p, q):
+        cr.cr_plan_destroy(plan)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,n,s,d,bf16,m", [(3, 3, 2, 30_001, 1, 874), (2, 12, 5, 34_816, 0, 452), (2, 12, 3, 36_864, 1, 1_400)])
+def test_runs_that_many_slabs_take(L, n, s, d, bf16, m):
+    """Up to 36 workers hold the same rows: their slabs of one pass against those of two, bit for bit where a run makes up the slab, and
+    every one of them written."""
+    import torch
+
+    gen = torch.Generator(device="cuda").manual_seed(d + m)
+    X = torch.empty(m, d, device="cuda", dtype=torch.bfloat16 if bf16 else torch.float32).normal_(generator=gen)
+    w = torch.randn(d, generator=gen, device="cuda") / d ** 0.5
+    y = torch.randn(m, generator=gen, device="cuda") + 4.0
+    slabs = []
+    for rows in (None, m):
+        plan = cr.cr_plan_ex(L, n, s, m, d, x_dtype=bf16)
+        if rows:
+            cr.cr_plan_set_split(plan, cr.CR_SPLIT_ROWS_ONCE, rows)
+        ws = cr.Workspace(plan)
+        assert (ws.info.split_value < m) == (rows is None)
+        ws.slab_grads().fill_(float("nan"))
+        cr.cr_partial_grads(plan, X, y, w)
+        cr.cr_synchronize(plan)
+        slabs.append(ws.slab_grads().double())
+        del ws
+        cr.cr_plan_destroy(plan)
+    one, two = slabs
+    assert float(((one - two).abs().amax(1) / two.pow(2).mean(1).sqrt()).max()) <= 6e-6       # each within 3e-6 of 64 bits
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,bf16,m", CASES)
 def test_slabs_against_64_bits(d, bf16, m):

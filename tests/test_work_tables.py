@@ -22,6 +22,7 @@ extern "C" void set_slabs(int n, const int64_t *rb, const int64_t *re, const int
     for (int i = 0; i < n; ++i) { cr::Slab s{}; s.node = node[i]; s.row_begin = rb[i]; s.row_end = re[i]; s.coef = 1.0; slabs.push_back(s); }
 }
 extern "C" void equal_parts(int64_t m, int64_t parts, int64_t limit) { cr::once_equal_parts(slabs, m, parts, limit, work); }
+extern "C" void equal_parts_copies(int64_t m, int64_t parts, int64_t limit, int64_t most) { cr::once_equal_parts(slabs, m, parts, limit, work, most); }
 extern "C" void whole_ranges() { cr::once_whole_ranges(slabs, work); }
 extern "C" void equal_ranges(int teams) { cr::split_equal_ranges(slabs, teams, split); cr::once_of_pieces(slabs, split, work); }
 extern "C" void queues(int64_t cell_rows, int lanes, int per_group, int slots)
@@ -138,3 +139,19 @@ def test_a_workgroup_does_the_cells_it_is_said_to_do(lib, L, n, s, m, per_group)
             mine = {(int(b), int(e)) for b, e in pieces[group == g, 1:3]}
             have = [(int(b), int(e)) for b, e in runs[begin[part]:begin[part + 1], :2]]
             assert len(have) == len(mine) and set(have) == mine
+
+
+@pytest.mark.parametrize("L,n,s,m", TREES)
+def test_runs_with_many_slabs_are_handed_on_by_a_sum(lib, L, n, s, m):
+    """No run is written to more slabs than allowed, besides its partial row; the same runs, and every slab still complete."""
+    rb, re_ = _load(lib, L, n, s, m)
+    for parts in (1, 7, min(m, 256)):
+        lib.equal_parts(ctypes.c_int64(m), ctypes.c_int64(parts), ctypes.c_int64(1 << 40))
+        lib.as_split()
+        want, _, pieces, _ = _replay(lib, rb, re_, m)
+        for most in (0, 1, 2):
+            lib.equal_parts_copies(ctypes.c_int64(m), ctypes.c_int64(parts), ctypes.c_int64(1 << 40), ctypes.c_int64(most))
+            lib.as_split()
+            runs, _, again, _ = _replay(lib, rb, re_, m)
+            assert np.array_equal(runs[:, :2], want[:, :2]) and (runs[:, 3] - runs[:, 2]).max() <= most + 1
+            assert sorted(map(tuple, again)) == sorted(map(tuple, pieces))
