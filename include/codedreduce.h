@@ -131,10 +131,11 @@ int cr_plan_decode_row(const cr_plan_t *plan, const uint8_t *flags /* host, n */
  *   CR_SPLIT_ROWS_ONCE     value = most rows per run: X is cut into one or two contiguous parts per compute unit, a part into runs at
  *                          slab boundaries and after `value` rows; a workgroup forms every row of its part once, for all slabs that
  *                          hold it, and adds a run up in fp64 (all but the up to four rows it has in hand at a time).  Rows of more
- *                          than 24576 columns take one pass where their weights fit LDS (34816 columns fp32, 36864 bf16), X has
- *                          48 MB and more and `value` is at most a compute unit's share of the rows; else two passes, the second cut
- *                          into parts of rows and blocks of columns.  CR_ROWS_WHOLE_RANGES as value (d <= 24576): a workgroup per distinct slab range,
- *                          which it adds up whole; rows of ranges that overlap are then formed once per range.
+ *                          than 24576 columns take one pass where their weights fit LDS (34816 columns fp32, 36864 bf16), X is
+ *                          large against the rows that its parts put away (48 MB at least) and `value` is at most a compute unit's
+ *                          share of the rows; else two passes, the second cut into parts of rows and blocks of columns.
+ *                          CR_ROWS_WHOLE_RANGES as value (d <= 24576): a workgroup per distinct slab range, which it adds up whole; rows
+ *                          of ranges that overlap are then formed once per range.
  * With the first two every holder of a row does its own arithmetic on it, as separate workers would: they are there to measure what
  * the redundancy of a scheme costs (with s = 0 no row has a second holder, and equal ranges run the kernels of rows once, a
  * workgroup per team).  With the other two the holders' identical sums are formed once (per workgroup) and handed to
@@ -174,7 +175,8 @@ int cr_bind_workspace(cr_plan_t *plan, void *dev_ptr, size_t bytes, void *hip_st
  * cr_partial_grads (CR.Execute step 1): for every slab p,  G[p] = X[b:e]^T (phi(X[b:e] w) - y[b:e]),  phi = identity or sigmoid.
  *   X_dev  m x d row-major, contiguous, fp32 or bf16 per the plan, 16-byte aligned;  y_dev m floats;  w_dev d floats.
  *   One pass over X as long as a row fits the registers of a workgroup (d <= 24576, whether or not d is a multiple of the 16-byte
- *   chunk) or its weights LDS beside them (34816 fp32, 36864 bf16, from 48 MB of X on); other rows take two passes.  Every slab of every worker is written; what the workers that hold a row have in common is
+ *   chunk) or its weights LDS beside them (34816 fp32, 36864 bf16, X of 48 MB or more
+ *   depending on the tree); other rows take two passes.  Every slab of every worker is written; what the workers that hold a row have in common is
  *   formed once for all of them unless the split says otherwise (see cr_plan_set_split).
  * cr_load_partial_grads: use caller-supplied slab gradients G_dev[S][d] (fp32, 16-byte aligned) in place of stage 1;
  *   the buffer is read in place by cr_encode_tree and must stay valid until then.

@@ -147,10 +147,10 @@ struct cr_plan_s {
     bool staging_used[kStagingHalves] = {};
     int staging_next = 0;
     cr::DecTerms dec = {};                         // what cr_decode_root does: of the last mask encoded
-    // layout of the program block (offsets in bytes, fixed per plan)
     // layout of the workspace (offsets in bytes)
     size_t at_pieces = 0, at_team_piece_begin = 0, at_parts = 0, at_runs = 0, at_sums = 0, at_dst = 0, at_placement = 0, at_program = 0,
            at_node_begin = 0, at_slab_coef = 0, tables_bytes = 0, at_measures = 0, at_G = 0, at_residuals = 0, at_M = 0;
+    // layout of a program block (offsets in bytes, fixed per plan)
     size_t off_slab = 0, off_level = 0, off_row = 0, off_coef = 0, off_acoef = 0, off_sub = 0, off_dec = 0;
     size_t max_terms = 0;
 
@@ -460,7 +460,8 @@ void compute_layout(cr_plan_t *p, size_t *total)
     p->tables_bytes = w;                                 // what the plan fills in at binding, in one copy
     p->at_placement = take(kPlacementSlots * sizeof(uint32_t));
     p->at_program = take(kProgramSlots * p->program_bytes);
-    p->measures_stride = p->model == CR_AGGREGATE_ONLY ? 0 : 4 * static_cast<size_t>(std::max(cr::decode_groups(p->d), cr::tree_and_decode_together(p->shape, p->d) ? cr::tree_decode_groups(p->n, p->L, p->d) : 0));
+    const int groups_together = cr::tree_and_decode_together(p->shape, p->d) ? cr::tree_decode_groups(p->n, p->L, p->d) : 0;
+    p->measures_stride = p->model == CR_AGGREGATE_ONLY ? 0 : 4 * static_cast<size_t>(std::max(cr::decode_groups(p->d), groups_together));
     p->at_measures = take(kProgramSlots * p->measures_stride * sizeof(double));
     const size_t row = static_cast<size_t>(p->d) * sizeof(float);
     if (p->model != CR_AGGREGATE_ONLY) {
@@ -1301,8 +1302,9 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
             p->G_src = G + static_cast<int64_t>(t0 + count - 1) * G_step_stride;
             p->have_grads = true;
             LaunchTimer t(p, CR_K_ENCODE, rows * p->d * 4);
-            CR_HIP(cr::launch_encode_steps(G + static_cast<int64_t>(t0) * G_step_stride, G_step_stride, p->d_M, program_view(p, p->d_program), static_cast<int64_t>(p->program_bytes), count,
-                                           p->n, p->L, g + static_cast<int64_t>(t0) * g_step_stride, g_step_stride, p->d, p->stream));
+            CR_HIP(cr::launch_encode_steps(G + static_cast<int64_t>(t0) * G_step_stride, G_step_stride, p->d_M, program_view(p, p->d_program),
+                                           static_cast<int64_t>(p->program_bytes), count, p->n, p->L, g + static_cast<int64_t>(t0) * g_step_stride,
+                                           g_step_stride, p->d, p->stream));
             t.done();
             p->dec = counts[count - 1].dec;
             p->have_messages = true;

@@ -165,8 +165,8 @@ hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int n
 // Encode and decode of `steps` masks, one after the other, in one launch (where encode_in_steps says so); the programs lie prog_stride
 // bytes apart.
 bool encode_in_steps(const TreeShape &tree, int64_t d, int steps);
-hipError_t launch_encode_steps(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L, float *g, int64_t g_stride, int64_t d,
-                               hipStream_t stream);
+hipError_t launch_encode_steps(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L,
+                               float *g, int64_t g_stride, int64_t d, hipStream_t stream);
 // The encode of trees of at most NodeCoefs::kNodes nodes and vectors of at most kTreeColumns columns (tree_side_by_side): a workgroup
 // per level-1 sub-tree and 16 or 64 chunks of columns.  The tables travel with the launch or are on the device.
 constexpr int64_t kTreeColumns = 81920, kTreeNarrowColumns = 32768;
@@ -179,11 +179,13 @@ hipError_t launch_tree_encode(const float *G, float *M, const ArgumentTables &ta
 hipError_t launch_decode(const float *M, float *g, const DecTerms &terms, const GradientStep &step, int64_t d, hipStream_t stream);
 int decode_groups(int64_t d);
 // Encode, decode and gradient step in one launch, where tree_and_decode_together says so: vectors of at most kTogetherColumns columns
-// (8 chunks of columns per workgroup, 16 from kTogetherNarrowColumns on).
+// (8 chunks of columns per workgroup; beyond kTogetherNarrowColumns 16 where the whole tree's messages fit LDS for them).
 constexpr int64_t kTogetherColumns = 32768, kTogetherNarrowColumns = 8192;
 bool tree_and_decode_together(const TreeShape &tree, int64_t d);
-hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, int n, int L, float *g, const GradientStep &step, int64_t d, hipStream_t stream);
-hipError_t launch_tree_encode_decode(const float *G, float *M, const ArgumentTables &tables, int n, int L, float *g, const GradientStep &step, int64_t d, hipStream_t stream);
+hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, int n, int L, float *g, const GradientStep &step,
+                                     int64_t d, hipStream_t stream);
+hipError_t launch_tree_encode_decode(const float *G, float *M, const ArgumentTables &tables, int n, int L, float *g, const GradientStep &step,
+                                     int64_t d, hipStream_t stream);
 int tree_decode_groups(int n, int L, int64_t d);
 // metrics[2t], metrics[2t + 1] of `steps` steps from the measures their launches of `groups` workgroups left at sums + t * step_stride
 hipError_t launch_measures(const double *sums, int64_t step_stride, int groups, int steps, bool with_star, float *metrics, hipStream_t stream);

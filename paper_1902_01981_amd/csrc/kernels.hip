@@ -564,7 +564,8 @@ rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const 
 // WL: the weights are in LDS, every thread's in slots of its own, which leaves the registers for rows half as wide again, 34 816 fp32 or
 // 36 864 bf16 columns, that took two passes (stage 1 in us, two passes / this: 6 000 x 32 768 fp32 245 / 133, 3 000 x 30 001 fp32 115 / 70,
 // 10 000 x 36 864 bf16 225 / 141, 4 000 x 25 000 bf16 68 / 38).  Up to 12 fp32 chunks per thread it gains nothing, not with the next
-// row's loads ahead either (3 000 x 24 000: 56.9 without, 58.7 with both).
+// row's loads ahead either (3 000 x 24 000: 56.9 without, 58.7 with both).  The widest of these (17 fp32 or 9 bf16 chunks) use all 256
+// registers and keep 28 bytes per lane in scratch: 10 000 x 36 864 bf16 takes 1.35 times a plain read of it.
 template <int XD, int VEC, int TS, int K, int R, bool PF, bool WL, bool NT>
 __global__ void __launch_bounds__(TS)
 rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w, const DevRun *__restrict__ parts,
@@ -963,7 +964,8 @@ sum_rows_kernel(float *__restrict__ rows, const DevSum *__restrict__ sums, const
 // walk_sub_tree: terms [tb, te) of a program for a thread's C chunks, off bytes into a row; live: is the chunk in the row; top(c, out): the
 // finished message of the level-1 node.
 template <int VEC, int LT, int C, int U, bool NTS, typename acc_t, typename TOP>
-__device__ __forceinline__ void walk_sub_tree(const float *G, float *M, const EncProgram &prog, int tb, int te, int64_t d, const unsigned (&off)[C], const bool (&live)[C], TOP top)
+__device__ __forceinline__ void walk_sub_tree(const float *G, float *M, const EncProgram &prog, int tb, int te, int64_t d, const unsigned (&off)[C],
+                                              const bool (&live)[C], TOP top)
 {
     static_assert(kEncodeUnroll % U == 0, "sub-programs are padded to kEncodeUnroll terms");
     typedef int iuv __attribute__((ext_vector_type(U)));
@@ -1060,15 +1062,16 @@ encode_kernel(const float *__restrict__ G, float *__restrict__ M, EncProgram pro
 // alone, 117 706 columns: 59.6 against 61.8).
 template <int LT>
 __global__ void __launch_bounds__(1024)
-encode_steps_kernel(const float *__restrict__ G, int64_t G_stride, float *__restrict__ M, EncProgram prog, int64_t prog_stride, int steps, int n, float *__restrict__ g, int64_t g_stride,
-                    int64_t d, int nq)
+encode_steps_kernel(const float *__restrict__ G, int64_t G_stride, float *__restrict__ M, EncProgram prog, int64_t prog_stride, int steps, int n,
+                    float *__restrict__ g, int64_t g_stride, int64_t d, int nq)
 {
     constexpr int VEC = 4;
     extern __shared__ __align__(16) char step_lds[];
     float *top = reinterpret_cast<float *>(step_lds);    // [2][n][VEC][64]
     const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // workgroups are dealt to the eight dies in turn: neighbouring columns on one die, whose L2 joins the lines they share
+    // workgroups are dealt to the eight dies in turn: neighbouring columns on one die, whose L2 joins the lines they share (with another
+    // number of dies the same columns, on others)
     const int block = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3), q = block * 64 + lane;
     if (block * 64 >= nq) return;
     const bool live[1] = {q < nq};
@@ -1189,7 +1192,8 @@ template <int VEC, int B> struct TreeLds {
 };
 
 // own sum of a node: its slabs in turn, U of them in flight
-template <int VEC, typename COEF> __device__ __forceinline__ void sum_slabs(const float *G, int64_t d, int64_t col, int begin, int end, COEF coef, double (&acc)[VEC])
+template <int VEC, typename COEF>
+__device__ __forceinline__ void sum_slabs(const float *G, int64_t d, int64_t col, int begin, int end, COEF coef, double (&acc)[VEC])
 {
     constexpr int U = 8;
     for (int s0 = begin; s0 < end; s0 += U) {
@@ -1213,7 +1217,8 @@ template <int VEC, typename COEF> __device__ __forceinline__ void sum_slabs(cons
 // The messages of a workgroup's nodes, stored and left in LDS.  coef_of(node): the node's coefficient; own_sum(node, acc): its own sum
 // for the lane's columns.
 template <int VEC, int B, int T, typename COEF, typename OWN>
-__device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, const TreeLds<VEC, B> &lds, COEF coef_of, OWN own_sum, float *M, int64_t d, int64_t col, bool live)
+__device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, const TreeLds<VEC, B> &lds, COEF coef_of, OWN own_sum, float *M,
+                                              int64_t d, int64_t col, bool live)
 {
     constexpr int TEAMS = T / B;
     const int team = threadIdx.x / B, tl = threadIdx.x % B;
@@ -1287,7 +1292,9 @@ __device__ __forceinline__ void measure(double (&sum)[4], float w_old, float w_n
 
 // The decoded chunk q goes to g; step.w: w <- w - lr g with g as stored, a column shared with the neighbouring chunk by the chunk that
 // owns it only; step.measures: the columns' part of the measures is added to sum.
-template <int VEC, bool NT> __device__ __forceinline__ void put_gradient(const double (&acc)[VEC], float *g, int64_t col, int q, int nq, int64_t d, const GradientStep &step, double (&sum)[4])
+template <int VEC, bool NT>
+__device__ __forceinline__ void put_gradient(const double (&acc)[VEC], float *g, int64_t col, int q, int nq, int64_t d, const GradientStep &step,
+                                             double (&sum)[4])
 {
     float out[VEC];
 #pragma unroll
@@ -1310,7 +1317,8 @@ template <int VEC, bool NT> __device__ __forceinline__ void put_gradient(const d
 // (3,4) tree, 6 500 columns 5.7 + 2.6 / 5.7; (2,12), s = 2, 24 576 columns 13.4 + 3.9 / 14.6, 73 728 columns 29.9 + 4.7 / 35.4.
 template <int VEC, int B, int T, typename TABLES>
 __global__ void __launch_bounds__(T)
-tree_decode_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, TreeLevels tree, float *__restrict__ g, GradientStep step, int64_t d, int nq)
+tree_decode_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, TreeLevels tree, float *__restrict__ g, GradientStep step,
+                   int64_t d, int nq)
 {
     extern __shared__ __align__(16) char tree_lds[];
     const auto view = view_tables<T>(tables, tree_lds);
@@ -1699,8 +1707,8 @@ bool encode_in_steps(const TreeShape &tree, int64_t d, int steps)
     return messages >= int64_t(256) << 20 || load <= (4 * groups < 5 * kUnits ? 100000 : 300000);
 }
 
-hipError_t launch_encode_steps(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L, float *g, int64_t g_stride,
-                               int64_t d, hipStream_t stream)
+hipError_t launch_encode_steps(const float *G, int64_t G_stride, float *M, const EncProgram &prog, int64_t prog_stride, int steps, int n, int L,
+                               float *g, int64_t g_stride, int64_t d, hipStream_t stream)
 {
     const int nq = static_cast<int>((d + 3) / 4);
     const unsigned groups = ((nq + 63) / 64 + 7) / 8 * 8, block = 64 * (n < 16 ? n : 16);
@@ -1754,7 +1762,8 @@ template <int VEC, int B, int T, typename TABLES>
 hipError_t launch_tree_shape(const float *G, float *M, const TABLES &tables, const TreeLevels &tree, int64_t d, hipStream_t stream)
 {
     const int nq = static_cast<int>((d + VEC - 1) / VEC);
-    tree_kernel<VEC, B, T><<<dim3((nq + B - 1) / B, tree.n), T, TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves), stream>>>(G, M, tables, tree, d, nq);
+    const size_t lds = TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves);
+    tree_kernel<VEC, B, T><<<dim3((nq + B - 1) / B, tree.n), T, lds, stream>>>(G, M, tables, tree, d, nq);
     return hipGetLastError();
 }
 
@@ -1770,15 +1779,18 @@ hipError_t launch_tree(const float *G, float *M, const TABLES &tables, int n, in
 }
 
 template <int VEC, int B, int T, typename TABLES>
-hipError_t launch_tree_decode_shape(const float *G, float *M, const TABLES &tables, const TreeLevels &tree, float *g, const GradientStep &step, int64_t d, hipStream_t stream)
+hipError_t launch_tree_decode_shape(const float *G, float *M, const TABLES &tables, const TreeLevels &tree, float *g, const GradientStep &step,
+                                    int64_t d, hipStream_t stream)
 {
     const int nq = static_cast<int>((d + VEC - 1) / VEC);
-    tree_decode_kernel<VEC, B, T><<<(nq + B - 1) / B, T, TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves), stream>>>(G, M, tables, tree, g, step, d, nq);
+    const size_t lds = TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves);
+    tree_decode_kernel<VEC, B, T><<<(nq + B - 1) / B, T, lds, stream>>>(G, M, tables, tree, g, step, d, nq);
     return hipGetLastError();
 }
 
 template <typename TABLES>
-hipError_t launch_tree_decode(const float *G, float *M, const TABLES &tables, int n, int L, float *g, const GradientStep &step, int64_t d, hipStream_t stream)
+hipError_t launch_tree_decode(const float *G, float *M, const TABLES &tables, int n, int L, float *g, const GradientStep &step, int64_t d,
+                              hipStream_t stream)
 {
     const TreeLevels tree = tree_levels(n, L, true);
     if (d < 4) return launch_tree_decode_shape<1, 8, 1024>(G, M, tables, tree, g, step, d, stream);
@@ -1834,15 +1846,24 @@ int tree_decode_groups(int n, int L, int64_t d)
     return static_cast<int>((chunks + per - 1) / per);
 }
 
-hipError_t launch_tree_encode(const float *G, float *M, const DeviceTables &tables, int n, int L, int64_t d, hipStream_t stream) { return launch_tree(G, M, tables, n, L, d, stream); }
-hipError_t launch_tree_encode(const float *G, float *M, const ArgumentTables &tables, int n, int L, int64_t d, hipStream_t stream) { return launch_tree(G, M, tables, n, L, d, stream); }
+hipError_t launch_tree_encode(const float *G, float *M, const DeviceTables &tables, int n, int L, int64_t d, hipStream_t stream)
+{
+    return launch_tree(G, M, tables, n, L, d, stream);
+}
 
-hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, int n, int L, float *g, const GradientStep &step, int64_t d, hipStream_t stream)
+hipError_t launch_tree_encode(const float *G, float *M, const ArgumentTables &tables, int n, int L, int64_t d, hipStream_t stream)
+{
+    return launch_tree(G, M, tables, n, L, d, stream);
+}
+
+hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, int n, int L, float *g, const GradientStep &step,
+                                     int64_t d, hipStream_t stream)
 {
     return launch_tree_decode(G, M, tables, n, L, g, step, d, stream);
 }
 
-hipError_t launch_tree_encode_decode(const float *G, float *M, const ArgumentTables &tables, int n, int L, float *g, const GradientStep &step, int64_t d, hipStream_t stream)
+hipError_t launch_tree_encode_decode(const float *G, float *M, const ArgumentTables &tables, int n, int L, float *g, const GradientStep &step,
+                                     int64_t d, hipStream_t stream)
 {
     return launch_tree_decode(G, M, tables, n, L, g, step, d, stream);
 }
@@ -1930,9 +1951,10 @@ hipError_t static_scratch(char **ptr) { return array_address(HIP_SYMBOL(scratch)
 hipError_t table_pool(char **ptr) { return array_address(HIP_SYMBOL(tables_of_trees), g_tables_ptr, ptr); }
 
 // Where the tree's tables do not fit the arguments of the launch that encodes (argument_tables), the encode program travels as kernel
-// arguments of launches of its own (copied when the launch is enqueued) and one workgroup writes it out with vector stores.  What bounds it is the number of launches, 4 KB of arguments at most each, so a term of 28 bytes travels as 8: slab, row,
-// level and the places of its two coefficients in a table of the block's distinct ones.  Every block is complete in itself, and only
-// the terms that the mask leaves travel.  Ten vectors of 10 to 73728 entries on a tree of two levels of twelve with s = 2: 305 to
+// arguments of launches of its own (copied when the launch is enqueued) and one workgroup writes it out with vector stores.  What bounds
+// it is the number of launches, 4 KB of arguments at most each, so a term of 28 bytes travels as 8: slab, row, level and the places of
+// its two coefficients in a table of the block's distinct ones.  Every block is complete in itself, and only the terms that the mask
+// leaves travel.  Ten vectors of 10 to 73728 entries on a tree of two levels of twelve with s = 2: 305 to
 // 340 us with the program's bytes as they are (six launches per vector), 155 us in this form (one), 119 us with the tables as arguments.
 struct ProgramBlock {
     static constexpr int kWords = 480;                   // 8-byte words: the coefficients, then the terms

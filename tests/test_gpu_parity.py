@@ -349,8 +349,8 @@ def test_aggregation_only_network_sized(s):
 
 
 def test_aggregate_run_matches_the_three_calls():
-    """cr_aggregate_run over 37 masks (three program uploads) against cr_load_partial_grads + cr_encode_tree + cr_decode_root per mask:
-    the same bits, with one set of slab gradients for all steps and with one per step; and a bad mask enqueues nothing."""
+    """cr_aggregate_run over 37 masks (a launch per mask at this width) against cr_load_partial_grads + cr_encode_tree + cr_decode_root per
+    mask: the same bits, with one set of slab gradients for all steps and with one per step; and a bad mask enqueues nothing."""
     torch = _torch()
     L, n, s, d, steps = 2, 12, 5, 1_003, 37
     m = 156 * 8
@@ -394,7 +394,7 @@ def test_aggregate_run_matches_the_three_calls():
 
 
 def test_gd_run_across_program_batches():
-    """40 steps in one cr_gd_run call (three uploads of encode programs) against the step-by-step calls: bit-identical models and
+    """40 steps in one cr_gd_run call (three batches of convergence measures) against the step-by-step calls: bit-identical models and
     convergence measures; then the same masks in two calls of 23 and 17."""
     torch = _torch()
     cfg = wl.config("cfg1")
