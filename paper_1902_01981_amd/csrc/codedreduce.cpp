@@ -108,7 +108,9 @@ struct cr_plan_s {
     const cr::Stage1Variant *variant_regs = nullptr;
     int cell_holders = 0;            // holders a workgroup of the shared-cells split serves; 0: no such split for this type and width
     cr::OnceWork work;               // `rows_once`: the runs and sums behind the split
-    const cr::OnceVariant *wide_variant = nullptr;     // wide rows in one pass; null: two passes
+    const cr::OnceVariant *wide_variant = nullptr;     // wide rows in one pass; null: two passes, or
+    std::unique_ptr<cr::CrewVariant> crew;             // one pass with several workgroups per row
+    int patience = cr::kCrewPatience;                  // polls for what another workgroup of a crew has to say
     int units = 0;                   // compute units the wide-row launches are sized for
     bool streams = false;            // rows_once: X is read past the caches
     bool rows_as_buffers = false;    // every row starts on a 4-byte boundary and every piece has fewer than 2^31 bytes
@@ -130,6 +132,8 @@ struct cr_plan_s {
     cr::DevRun *d_parts = nullptr, *d_runs = nullptr;
     cr::DevSum *d_sums = nullptr;
     int32_t *d_dst = nullptr;
+    uint64_t *d_crew_slots = nullptr;              // `crew`: what its kernel exchanges in
+    uint32_t *d_crew_state = nullptr;
     int num_sums = 0;
     uint32_t *d_placement = nullptr;               // kPlacementSlots words: where the workgroups of a probe launch ran
     char *d_program = nullptr;                     // kProgramSlots encode programs
@@ -148,7 +152,7 @@ struct cr_plan_s {
     int staging_next = 0;
     cr::DecTerms dec = {};                         // what cr_decode_root does: of the last mask encoded
     // layout of the workspace (offsets in bytes)
-    size_t at_pieces = 0, at_team_piece_begin = 0, at_parts = 0, at_runs = 0, at_sums = 0, at_dst = 0, at_placement = 0, at_program = 0,
+    size_t at_pieces = 0, at_team_piece_begin = 0, at_parts = 0, at_runs = 0, at_sums = 0, at_dst = 0, at_crew_slots = 0, at_crew_state = 0, at_placement = 0, at_program = 0,
            at_node_begin = 0, at_slab_coef = 0, tables_bytes = 0, at_measures = 0, at_G = 0, at_residuals = 0, at_M = 0;
     // layout of a program block (offsets in bytes, fixed per plan)
     size_t off_slab = 0, off_level = 0, off_row = 0, off_coef = 0, off_acoef = 0, off_sub = 0, off_dec = 0;
@@ -294,18 +298,21 @@ int64_t wide_two_pass_parts(const cr_plan_t *p)
 // worst.
 constexpr int64_t kWideOnePassBytes = int64_t(48) << 20;
 
+// Rows that a split into `parts` parts puts away, and adds up where slabs are sums of several.
+int64_t rows_put_away(const cr_plan_t *p, int64_t parts)
+{
+    cr::OnceWork work;
+    cr::once_equal_parts(p->slabs, p->m, parts, p->m, work);
+    int64_t rows = static_cast<int64_t>(work.runs.size());
+    for (const cr::RowSum &sum : work.sums) rows += sum.row_end - sum.row_begin;
+    return rows;
+}
+
 bool one_pass_pays(const cr_plan_t *p)
 {
     const int64_t bytes = p->m * p->d * elem_size(p);
     if (bytes < kWideOnePassBytes || !cr::select_once_wide(p->x_dtype, p->d)) return false;
-    auto rows_put_away = [&](int64_t parts) {
-        cr::OnceWork work;
-        cr::once_equal_parts(p->slabs, p->m, parts, p->m, work);
-        int64_t rows = static_cast<int64_t>(work.runs.size());
-        for (const cr::RowSum &sum : work.sums) rows += sum.row_end - sum.row_begin;
-        return rows;
-    };
-    return bytes / 9 * 10 > (rows_put_away(wide_one_pass_parts(p)) - rows_put_away(wide_two_pass_parts(p))) * p->d * 4;
+    return bytes / 9 * 10 > (rows_put_away(p, wide_one_pass_parts(p)) - rows_put_away(p, wide_two_pass_parts(p))) * p->d * 4;
 }
 
 // One pass over wide rows: a part per compute unit, at least four rows; the most rows that a part has, or 0: two passes.
@@ -319,8 +326,29 @@ int64_t wide_one_pass_rows(const cr_plan_t *p)
 // other.  To more of them the sums' launch hands it, a workgroup per 64 chunks.
 constexpr size_t kWideCopies = 2;
 
-// The same for wide rows.  One pass where that pays and runs of no more rows are asked for than its parts have, which the default
-// split does; longer runs take two passes, where parts are long.
+// Crews: as many as the dies have workgroups for, and at least four rows for each (us with sums, parts of at least 1, 2, 4, 8 and 16 rows:
+// (2,4), s = 1, 40 x 37 000 bf16 17.8, 15.1, 13.8, 16.4, 23.4; 80 x 60 000 fp32 23.1, 22.9, 22.5, 22.6, 27.2; the same from 160 rows on).
+int64_t crew_parts(const cr_plan_t *p, const cr::CrewVariant &crew)
+{
+    const int64_t units = query_units(), crews = units >= 64 ? units / 8 / crew.members * 8 : units / crew.members;
+    return std::max<int64_t>(1, std::min<int64_t>(crews, p->m / 4));
+}
+
+// Rows too wide for one workgroup, weights in LDS or not, are shared by crews in one pass, or take two.  Two passes have long parts and so
+// fewer partial rows, which pays where X is small against the rows that crews put away and add up beyond those of two passes, and there
+// are rows enough for five parts (us with sums, crews / two passes, by that share of X: (1,10), s = 4, 640 x 37 000 bf16 (0.04)
+// 22.9 / 32.2; (3,6), s = 2, 640 x 37 000 bf16 (0.20) 54.3 / 68.7; (2,12), s = 2, 320 x 36 000 fp32 (0.23) 36.8 / 36.9; (1,10), s = 4, fp32
+// 160 x 100 000 (0.24) 32.5 / 27.3, 160 x 36 000 (0.44) 19.4 / 13.7, 40 x 60 000 (0.25) 17.0 / 16.7, 20 x 60 000 (0.50) 17.0 / 22.2;
+// (2,4), s = 1, 40 x 60 000 fp32 (0.57) 17.9 / 21.4, 160 x 60 000 fp32 (0.19) 24.0 / 23.0).  Large X: 400 MB 75 to 95 / 125 to 144.
+bool crew_pays(const cr_plan_t *p, const cr::CrewVariant &crew)
+{
+    if (p->m < 80) return true;
+    const int64_t more = rows_put_away(p, crew_parts(p, crew)) - rows_put_away(p, wide_two_pass_parts(p));
+    return p->m * p->d * elem_size(p) / 17 * 4 > more * p->d * 4;
+}
+
+// The same for wide rows.  One workgroup per row where that pays and runs of no more rows are asked for than its parts have, which the default
+// split does; longer runs take two passes, where parts are long, and so do wider rows where crews do not pay.
 void make_wide_once(cr_plan_t *p, int64_t rows_per_run)
 {
     if (rows_per_run <= wide_one_pass_rows(p)) {
@@ -328,6 +356,11 @@ void make_wide_once(cr_plan_t *p, int64_t rows_per_run)
         return cr::once_equal_parts(p->slabs, p->m, wide_one_pass_parts(p), rows_per_run, p->work, kWideCopies);
     }
     p->units = query_units();
+    cr::CrewVariant crew;
+    if (!cr::select_once_wide(p->x_dtype, p->d) && cr::select_crew(p->x_dtype, p->d, p->units, &crew) && crew_pays(p, crew)) {
+        p->crew = std::make_unique<cr::CrewVariant>(crew);
+        return cr::once_equal_parts(p->slabs, p->m, crew_parts(p, crew), rows_per_run, p->work, kWideCopies);
+    }
     cr::once_equal_parts(p->slabs, p->m, wide_two_pass_parts(p), rows_per_run, p->work);
 }
 
@@ -338,6 +371,7 @@ int make_split(cr_plan_t *p)
     p->variant = nullptr;
     p->once = nullptr;
     p->wide_variant = nullptr;
+    p->crew.reset();
     p->rows_once = false;
     p->work = cr::OnceWork();
     const int domains = query_l2_domains();
@@ -455,6 +489,8 @@ void compute_layout(cr_plan_t *p, size_t *total)
     p->at_runs = take(runs * sizeof(cr::DevRun));
     p->at_sums = take(p->model == CR_AGGREGATE_ONLY ? 0 : sums * sizeof(cr::DevSum));
     p->at_dst = take(p->model == CR_AGGREGATE_ONLY ? 0 : dst * sizeof(int32_t));
+    p->at_crew_slots = take(p->crew ? parts * cr::crew_exchange_words(*p->crew) * sizeof(uint64_t) : 0);
+    p->at_crew_state = take(p->crew ? 2 * sizeof(uint32_t) : 0);
     p->at_node_begin = take((N + 1) * sizeof(int32_t));
     p->at_slab_coef = take(S * sizeof(double));
     p->tables_bytes = w;                                 // what the plan fills in at binding, in one copy
@@ -466,7 +502,7 @@ void compute_layout(cr_plan_t *p, size_t *total)
     const size_t row = static_cast<size_t>(p->d) * sizeof(float);
     if (p->model != CR_AGGREGATE_ONLY) {
         p->at_G = take((S + (p->rows_once ? p->work.partials : P)) * row);
-        p->at_residuals = take(p->once || p->wide_variant || p->variant ? 0 : static_cast<size_t>(p->rows_once ? p->m : p->row_visits) * sizeof(float));
+        p->at_residuals = take(p->once || p->wide_variant || p->crew || p->variant ? 0 : static_cast<size_t>(p->rows_once ? p->m : p->row_visits) * sizeof(float));
     }
     p->at_M = take(N * row);
     *total = w;
@@ -794,6 +830,8 @@ try {
     p->d_runs = reinterpret_cast<cr::DevRun *>(p->ws + p->at_runs);
     p->d_sums = reinterpret_cast<cr::DevSum *>(p->ws + p->at_sums);
     p->d_dst = reinterpret_cast<int32_t *>(p->ws + p->at_dst);
+    p->d_crew_slots = reinterpret_cast<uint64_t *>(p->ws + p->at_crew_slots);
+    p->d_crew_state = reinterpret_cast<uint32_t *>(p->ws + p->at_crew_state);
     p->d_placement = reinterpret_cast<uint32_t *>(p->ws + p->at_placement);
     p->d_program = p->ws + p->at_program;
     p->d_node_begin = reinterpret_cast<int32_t *>(p->ws + p->at_node_begin);
@@ -820,6 +858,7 @@ try {
         }
         for (const cr::RowSum &sum : p->work.sums) sums.push_back({sum.row_begin, sum.row_end, sum.dst_begin, sum.dst_end});
         dst = p->work.dst;
+        if (p->crew) put(p->at_crew_state, std::vector<uint32_t>{1, 0});
         put(p->at_parts, parts);
         put(p->at_runs, runs);
     } else if (stage1) {
@@ -887,6 +926,9 @@ int cr_partial_grads(cr_plan_t *p, const void *X, const float *y, const float *w
         if (once) {
             CR_HIP(cr::launch_rows_once(*once, X, y, w, p->d_parts, static_cast<int>(p->work.part_run_begin.size()) - 1, p->d_runs, p->d_dst,
                                         p->d_G, p->d, logistic, p->streams, p->stream));
+        } else if (p->crew) {
+            CR_HIP(cr::launch_rows_once_crew(*p->crew, X, y, w, p->d_parts, static_cast<int>(p->work.part_run_begin.size()) - 1, p->d_runs, p->d_dst,
+                                             p->d_G, p->d, logistic, p->streams, p->d_crew_slots, p->d_crew_state, p->patience, p->stream));
         } else if (p->rows_once) {
             const int64_t cached_from = std::max<int64_t>(0, p->m - kKeptBytes / (p->d * elem_size(p)));
             CR_HIP(cr::launch_wide_once(p->x_dtype, X, y, w, p->d_residuals, p->m, p->d_parts, static_cast<int>(p->work.part_run_begin.size()) - 1,
@@ -1471,6 +1513,14 @@ int cr_synchronize(cr_plan_t *p)
     if (!p) return fail(CR_E_INVAL, "NULL plan");
     if (!p->bound) return fail(CR_E_INVAL, "no workspace bound");
     CR_HIP(hipStreamSynchronize(p->stream));
+    return CR_OK;
+}
+
+// Not part of the interface: how often a workgroup of a crew asks for what another has not published yet.  Tests take the waiting away.
+int cr_testing_patience(cr_plan_t *p, int polls)
+{
+    if (!p || polls < 0) return CR_E_INVAL;
+    p->patience = polls;
     return CR_OK;
 }
 

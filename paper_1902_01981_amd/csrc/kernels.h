@@ -142,6 +142,23 @@ hipError_t launch_rows_once(const OnceVariant &v, const void *X, const float *y,
                             const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int logistic, bool stream_past_caches,
                             hipStream_t stream);
 
+// The same with several workgroups per row, `members` of them, for rows too wide for one (see rows_once_crew_kernel).  A part needs
+// crew_exchange_words 8-byte words to exchange in; they are zero, and the two words of state 1 and 0, before the first launch, and
+// nobody else writes to either.
+struct CrewVariant {
+    int xd, vec, k, rows_per_step;
+    int members;                     // workgroups per row
+    const void *fn[2];               // plain loads, loads with the non-temporal hint
+};
+constexpr int kCrewMembers = 16;     // at most
+constexpr int kCrewThreads = 448;    // that hold a member's slice of a row
+constexpr int kCrewPatience = 64;    // polls for the others' part of a dot product, some 0.7 us each, before it is worked out again
+bool select_crew(int x_dtype, int64_t d, int units, CrewVariant *v);       // units: compute units of the device
+int64_t crew_exchange_words(const CrewVariant &v);
+hipError_t launch_rows_once_crew(const CrewVariant &v, const void *X, const float *y, const float *w, const DevRun *parts, int num_parts,
+                                 const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int logistic, bool stream_past_caches,
+                                 uint64_t *slots, uint32_t *state, int patience, hipStream_t stream);
+
 // rows_as_buffers: every row starts on a 4-byte boundary and every piece has fewer than 2^31 bytes; variants that have a
 // buffer-load twin (bf16 rows, one wavefront per team) then run it
 hipError_t launch_partial_grads(const Stage1Variant &v, const void *X, const float *y, const float *w, const DevPiece *pieces,

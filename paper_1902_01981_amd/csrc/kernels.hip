@@ -4,7 +4,8 @@
 //   rows_once_kernel, rows_once_team_kernel   CR.Execute step 1: X[b:e]^T (phi(X[b:e] w) - y[b:e]) in ONE pass over X, every row's
 //                          contribution formed once for all workers that hold it
 //   partial_grads_kernel   the same for every holder separately (the splits that lay out every holder's own work)
-//   wide_residuals_kernel, wide_xt_kernel   rows too wide for a workgroup's registers, every row once, in two passes
+//   rows_once_crew_kernel  the same for rows too wide for one workgroup, shared by several
+//   wide_residuals_kernel, wide_xt_kernel   rows wider still, and wide rows of small matrices, every row once, in two passes
 //   residuals_kernel, xt_residuals_kernel   the same for every holder separately
 //   sum_rows_kernel        sums of partial rows (fixed order, so results are reproducible bit for bit)
 //   tree_kernel            CR.Execute steps 2-5: every node's message, the nodes of a sub-tree side by side, children folded in LDS
@@ -697,14 +698,252 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
     }
 }
 
+// ---- stage 1 for wide rows, every row once, in one pass ------------------------------------------------------------------
+// Rows too wide for a workgroup's registers are shared by the workgroups of a *crew*, a contiguous slice of columns each.  Seven
+// wavefronts of a member form its parts of the dot products and, a step later, add up the rows; the eighth publishes the member's part
+// of every dot product in a slot of its own, one 8-byte word of value and tag, collects the others' and hands out the residuals.  It
+// has no rows of its own to wait for, so the exchange (about 1 us) passes behind the loads and the arithmetic of the other seven.
+// The members of a crew are 8 workgroup ids apart: on one die where workgroups are dealt to the dies in turn, which is worth a shorter
+// exchange and nothing else.  No member depends on another one running: what has not arrived after `patience` polls a member's eighth
+// wavefront works out itself, from the rest of the row, in the same order (the same bits), and from then on it looks once per step only.
+// A tag is the launch's number and the step's, so that what a slot held before is never taken for an answer: a launch writes every slot
+// that it reads, and its number, kept in state[0], is counted up by the last workgroup to finish (state[1] counts those).
+// What bounds it is the read of X, 6.5 TB/s over long parts (20 000 x 50 008 bf16, 2 GB, 301 us), and some 10 us to fill the chip and put
+// the partial rows away: 4 000 x 50 008 bf16 (400 MB) 75 us against 138 in two passes, 4 000 x 60 000 fp32 (960 MB) 168 against 281.
+// What it took: the exchange in a wavefront of its own (loads return in order, so that polls behind a wavefront's own rows wait for
+// those: 113 us), two steps for it instead of one (100), rows per step times chunks per thread near eight (two rows instead of four 88),
+// no re-reading of the last row at the part's end (82).  Twice the wavefronts with half the chunks each: 107.
+constexpr int kCrewRing = 16;                            // steps; a member is at most two ahead of the others' answers unless they are late
+template <int XD, int VEC, int K, int R, bool NT>
+__global__ void __launch_bounds__(kCrewThreads + 64)
+rows_once_crew_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w, const DevRun *__restrict__ parts,
+                      const DevRun *__restrict__ runs, const int32_t *__restrict__ dst, float *__restrict__ rows, int d, int nq, int logistic,
+                      int num_parts, int members, uint64_t *slots, uint32_t *state, int patience)
+{
+    using C = Chunk<XD, VEC>;
+    constexpr int TS = kCrewThreads, WAVES = TS / 64, SETS = 4, LAG = 2;
+    static_assert(kCrewMembers * R <= 64, "a lane per slot of a step");
+    __shared__ float red[2][R][kCrewThreads / 64], res_of[2][R];
+    const int crew = static_cast<int>(blockIdx.x >> 3) / members * 8 + static_cast<int>(blockIdx.x & 7), member = static_cast<int>(blockIdx.x >> 3) % members;
+    if (crew >= num_parts) return;
+    const int tl = threadIdx.x, lane = tl & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const table_t<DevRun> part = table(parts) + crew;
+    const int more = part->more_end;
+    int next = part->more_begin;
+    Run run = read_run(part);
+    const int64_t part_begin = run.row_begin;
+    const Run last = next < more ? read_run(table(runs) + (more - 1)) : run;
+    const int total = static_cast<int>(last.row_begin + last.nrows - part_begin), steps = (total + R - 1) / R;      // rows past the last one re-read it and count for nothing
+    auto slice = [&](int j) { return static_cast<int>(static_cast<int64_t>(nq) * j / members); };       // the last slice is never shorter than another
+
+    if (wave == WAVES) {
+        const uint32_t launch = __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint64_t *const ring = slots + static_cast<int64_t>(crew) * kCrewRing * members * R;
+        auto targets = [&](int row) { return y[part_begin + min(row + lane, total - 1)]; };
+        float y_now = targets(0), y_ahead = targets(64); // of 64 rows each: a load per step would be waited for with the polls
+        int y_row = 0;
+        for (int i = 0; i < steps + LAG; ++i) {
+            auto tag = [&](int step) { return launch << 20 | (static_cast<uint32_t>(step) & 0xfffffu); };
+            auto slot = [&](int step) { return ring + step % kCrewRing * members * R; };
+            __syncthreads();                             // the wavefronts' parts of step i are in red
+            if (i < steps && lane < R) {
+                float p = 0.f;
+#pragma unroll
+                for (int j = 0; j < WAVES; ++j) p += red[i & 1][lane][j];
+                __hip_atomic_store(slot(i) + member * R + lane, static_cast<uint64_t>(tag(i)) << 32 | __float_as_uint(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            const int step = i - (LAG - 1);
+            if (step < 0 || step >= steps) continue;
+            const bool mine = lane < members * R;
+            uint64_t word = 0, late;
+            bool here = !mine;
+            for (int polls = 0;; ++polls) {
+                if (!here) word = __hip_atomic_load(slot(step) + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                here = here || static_cast<uint32_t>(word >> 32) == tag(step);
+                late = __ballot(!here);
+                if (!late || polls >= patience) break;
+            }
+            float part_of = __uint_as_float(static_cast<uint32_t>(word));
+            if (late) patience = 0;
+            for (; late; late &= late - 1) {
+                const int at = __builtin_ctzll(late), from_q = slice(at / R), to_q = slice(at / R + 1);
+                const void *row = row_ptr<XD>(X, part_begin + min(step * R + at % R, total - 1), d);
+                float p = 0.f;
+                for (int i = 0; i < WAVES; ++i) {
+                    float t[2] = {0.f, 0.f};
+#pragma unroll 1
+                    for (int k = 0; k < K; ++k) {
+                        const int q = from_q + i * 64 + lane + k * TS, e = chunk_offset<VEC>(min(q, to_q - 1), nq, d);
+                        float xv[VEC], wt[VEC], sum = k & 1 ? t[1] : t[0];
+                        C::widen(C::load(row, e), xv);
+                        load_row<VEC>(w + e, wt);
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) sum = fmaf(xv[v], q < to_q && chunk_owns<VEC>(q, v, nq, d) ? wt[v] : 0.f, sum);
+                        if (k & 1) t[1] = sum;
+                        else t[0] = sum;
+                    }
+                    p += group_sum<64>(t[0] + t[1]);
+                }
+                if (lane == at) part_of = p;
+            }
+            float z = 0.f;
+            for (int j = 0; j < members; ++j) z += __shfl(part_of, j * R + (lane < R ? lane : 0), 64);
+            const int at = step * R + (lane < R ? lane : 0) - y_row;
+            const float y0 = __shfl(y_now, at & 63, 64), y1 = __shfl(y_ahead, at & 63, 64);
+            if (lane < R) res_of[step & 1][lane] = residual(z, at < 64 ? y0 : y1, logistic);
+            if ((step + 1) * R - y_row >= 64) {
+                y_row += 64;
+                y_now = y_ahead;
+                y_ahead = targets(y_row + 64);
+            }
+        }
+        if (lane == 0 && __hip_atomic_fetch_add(state + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == static_cast<uint32_t>(num_parts * members - 1)) {
+            __hip_atomic_store(state + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(state, launch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        return;
+    }
+
+    // only a thread's last chunk can be the row's last one or past the slice
+    constexpr unsigned kElem = XD == 1 ? 2 : 4;
+    const int q_begin = slice(member), q_end = slice(member + 1);
+    const unsigned off = (q_begin + tl) * VEC, off_last = chunk_offset<VEC>(min(q_begin + tl + (K - 1) * TS, q_end - 1), nq, d);
+    float wv[K][VEC];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int q = q_begin + tl + k * TS;
+        load_row<VEC>(w + (k < K - 1 ? k * TS * VEC + off : off_last), wv[k]);
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) wv[k][v] = q < q_end && chunk_owns<VEC>(q, v, nq, d) ? wv[k][v] : 0.f;
+    }
+    using Set = typename C::raw_t[R][K];
+    Set s[SETS];
+    double acc[K][VEC];
+    auto clear = [&] {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) acc[k][v] = 0.0;
+    };
+    auto load = [&](Set &x, int step) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const void *row = row_ptr<XD>(X, part_begin + min(step * R + r, total - 1), d);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const void *from = static_cast<const char *>(row) + (k < K - 1 ? k * TS * VEC * kElem : 0u);
+                const unsigned e = k < K - 1 ? off : off_last;
+                x[r][k] = NT ? C::load_once(from, e) : C::load(from, e);
+            }
+        }
+    };
+    auto dots = [&](const Set &x, int step) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            float t[2] = {0.f, 0.f};
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                float xv[VEC];
+                C::widen(x[r][k], xv);
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) t[k & 1] = fmaf(xv[v], wv[k][v], t[k & 1]);
+            }
+            const float p = group_sum<64>(t[0] + t[1]);
+            if (lane == 0) red[step & 1][r][wave] = p;
+        }
+    };
+    int run_end = run.nrows;                             // rows are counted from the part's first
+    auto put_away = [&] {
+        for (int j = run.dst_begin; j < run.dst_end; ++j) {
+            float *out = rows + static_cast<int64_t>(table(dst)[j]) * d;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                float sum[VEC];
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) sum[v] = static_cast<float>(acc[k][v]);
+                if (q_begin + tl + k * TS < q_end) store_row<VEC>(out + (k < K - 1 ? k * TS * VEC + off : off_last), sum);
+            }
+        }
+        clear();
+        if (next >= more) return;
+        run = read_run(table(runs) + next++);
+        run_end += run.nrows;
+    };
+    // a chunk to be widened where it is used: the compiler would keep what the dot product widened, or widen ahead of a branch, and there
+    // are no registers for that
+    auto again = [](typename C::raw_t x) {
+        if constexpr (XD == 1) asm volatile("" : "+v"(x));
+        return x;
+    };
+    auto add = [&](const Set &x, int step) {
+        const int r0 = step * R;
+        float res[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) res[r] = res_of[step & 1][r];
+        // where a run ends inside a step of several rows: row by row, since a row must not touch another run's sums, not even times zero
+        if (R == 1 || r0 + R <= run_end) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                float xv[R][VEC];
+#pragma unroll
+                for (int r = 0; r < R; ++r) C::widen(again(x[r][k]), xv[r]);
+                add_rows<VEC, R>(acc[k], res, xv);
+            }
+            if (r0 + R == run_end) put_away();
+            return;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r0 + r >= total) break;
+            const float one[1] = {res[r]};
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                float xv[1][VEC];
+                C::widen(again(x[r][k]), xv[0]);
+                add_rows<VEC, 1>(acc[k], one, xv);
+            }
+            if (r0 + r + 1 == run_end) put_away();
+        }
+    };
+
+    clear();
+#pragma unroll
+    for (int i = 0; i < SETS; ++i) load(s[i], i);
+#pragma unroll
+    for (int i = 0; i < LAG; ++i) {
+        if (i < steps) dots(s[i], i);
+        __syncthreads();
+    }
+    // the dot products of LAG steps are with the eighth wavefront
+    int step = 0;
+    for (; step + 2 * SETS <= steps; step += SETS) {     // nothing conditional: a load that may not have been issued would be waited for at once
+#pragma unroll
+        for (int i = 0; i < SETS; ++i) {
+            dots(s[(i + LAG) % SETS], step + i + LAG);
+            __syncthreads();
+            add(s[i], step + i);
+            load(s[i], step + i + SETS);
+        }
+    }
+    while (step < steps) {
+#pragma unroll
+        for (int i = 0; i < SETS; ++i) {
+            if (step + LAG < steps) dots(s[(i + LAG) % SETS], step + LAG);
+            __syncthreads();
+            add(s[i], step);
+            if (++step == steps) break;
+            if (step + SETS - 1 < steps) load(s[i], step + SETS - 1);
+        }
+    }
+}
+
 // ---- stage 1 for wide rows, every row once ---------------------------------------------------------------------------
-// A row whose accumulators do not fit the registers of a workgroup, even with the weights in LDS, is read twice (and wide rows of small
-// matrices are, whose partial rows would cost more): first the residuals phi(x.w) - y of every row
+// Rows too wide even for a crew, and wide rows of small matrices, whose partial rows would cost more, are read twice: first the residuals phi(x.w) - y of every row
 // (R rows per workgroup, so that the weights, twice the size of a bf16 row, come out of the L2 once for R rows), then X^T r by
 // blocks of columns and parts of rows.  Both passes are bound by the read of X.  The rows from cached_from on are read with plain
 // loads and stay in the last-level cache for the second pass, which takes the parts from the end; the rest streams past (NT).
-// 4000 x 50008 bf16 (400 MB) on a (2,4) tree with s = 1: both 124 us, the whole iteration 154 us; every holder's rows read for itself,
-// in cells of 16 rows, took 1683 us.
+// 4000 x 50008 bf16 (400 MB) on a (2,4) tree with s = 1: both 124 us; every holder's rows read for itself, in cells of 16 rows, took 1683 us.
 template <int XD, int VEC, int R>
 __global__ void __launch_bounds__(512)
 wide_residuals_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w, float *__restrict__ residuals,
@@ -1510,6 +1749,14 @@ const OnceVariant kOnceVariantsWide[] = {
     CR_OW(0, 4, 13, false), CR_OW(0, 4, 14, false), CR_OW(0, 4, 15, false), CR_OW(0, 4, 16, false), CR_OW(0, 4, 17, false),
     CR_OW(1, 8, 7, true), CR_OW(1, 8, 8, false), CR_OW(1, 8, 9, false),
 };
+// several workgroups per row
+#define CR_OC(XD, VEC, K, R)                                                                            \
+    {XD, VEC, K, R, 0,                                                                                  \
+     {reinterpret_cast<const void *>(&rows_once_crew_kernel<XD, VEC, K, R, false>),                     \
+      reinterpret_cast<const void *>(&rows_once_crew_kernel<XD, VEC, K, R, true>)}}
+const CrewVariant kCrewVariants[] = {
+    CR_OC(0, 4, 2, 4), CR_OC(0, 4, 3, 2), CR_OC(0, 4, 4, 2), CR_OC(1, 8, 2, 4), CR_OC(1, 8, 3, 2),
+};
 // one row per wavefront or less, sixteen wavefronts: for launches of a few workgroups that each have a whole slab range to do
 const OnceVariant kOnceVariants16[] = {
     CR_O(0, 4, 2, 1, 4, 16), CR_O(0, 4, 4, 1, 4, 16), CR_O(0, 4, 8, 1, 4, 16), CR_O(0, 4, 16, 1, 4, 16), CR_O(0, 4, 32, 1, 4, 16),
@@ -1560,6 +1807,42 @@ const OnceVariant *select_once_whole(int x_dtype, int64_t d)
 {
     const OnceVariant *v = find_once(std::begin(kOnceVariants16), std::end(kOnceVariants16), x_dtype, d);
     return v ? v : select_once(x_dtype, d);
+}
+
+// Of the numbers of workgroups that can share the row: full dies count most, then slices that fill their threads' chunks, then few rows
+// per step against them.  400 MB, us with sums, by workgroups (share of the chunks in use), two passes: bf16 37 000 columns K = 2 x 6
+// (0.86) 79.0, K = 3 x 4 (0.86) 84.6, 131; 50 008 K = 2 x 8 (0.87) 79.0, x 7 (1.00) 80.8, K = 3 x 5 (0.93) 87.3, 131; 80 001 K = 3 x 8 (0.93)
+// 95.0, K = 2 x 12 (0.93) 108, 144; 100 000 K = 2 x 16 (0.87) 84.6, x 14 (1.00) 86.0, 134; fp32 40 001 K = 3 x 8 (0.93) 75.8, K = 2 x 12 (0.93)
+// 77.9, K = 4 x 6 (0.93) 80.3, 128; 60 000 K = 4 x 10 (0.84) 85.2, x 9 (0.93) 89.9, K = 3 x 16 (0.70) 91.8, 125.
+bool select_crew(int x_dtype, int64_t d, int units, CrewVariant *v)
+{
+    const int vec = stage1_chunk_width(x_dtype, d), on_die = units / 8 > 0 ? units / 8 : 1;
+    const int64_t nq = (d + vec - 1) / vec;
+    double best = 0.0;
+    for (int members = 2; members <= kCrewMembers && members <= on_die; ++members) {
+        const int64_t per = (nq + members - 1) / members;
+        for (const CrewVariant &c : kCrewVariants) {
+            if (c.xd != x_dtype || c.vec != vec || c.k != (per + kCrewThreads - 1) / kCrewThreads) continue;
+            const double used = static_cast<double>(on_die / members * members) / on_die;
+            const double score = used * used * static_cast<double>(per) / (c.k * kCrewThreads) * (x_dtype == 1 && c.k > 2 ? 0.85 : 1.0);
+            if (score <= best) continue;
+            best = score;
+            *v = c;
+            v->members = members;
+        }
+    }
+    return best > 0.0;
+}
+
+int64_t crew_exchange_words(const CrewVariant &v) { return static_cast<int64_t>(kCrewRing) * v.members * v.rows_per_step; }
+
+hipError_t launch_rows_once_crew(const CrewVariant &v, const void *X, const float *y, const float *w, const DevRun *parts, int num_parts,
+                                 const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int logistic, bool stream_past_caches,
+                                 uint64_t *slots, uint32_t *state, int patience, hipStream_t stream)
+{
+    int di = static_cast<int>(d), nq = static_cast<int>((d + v.vec - 1) / v.vec), members = v.members;
+    void *args[] = {&X, &y, &w, &parts, &runs, &dst, &rows, &di, &nq, &logistic, &num_parts, &members, &slots, &state, &patience};
+    return hipLaunchKernel(v.fn[stream_past_caches ? 1 : 0], dim3((num_parts + 7) / 8 * 8 * members), dim3(kCrewThreads + 64), args, 0, stream);
 }
 
 hipError_t launch_rows_once(const OnceVariant &v, const void *X, const float *y, const float *w, const DevRun *parts, int num_parts,

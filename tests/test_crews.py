@@ -1,0 +1,74 @@
+"""Rows that several workgroups share: slices of every width, runs that end inside a step, and answers that nobody waits for."""
+import ctypes
+
+import pytest
+
+import paper_1902_01981_amd as cr
+
+# the narrowest and widest rows that are shared, both sides of a chunk more per thread, slices of unequal length, odd rows
+WIDTHS = [(34_817, 0), (50_001, 0), (60_000, 0), (80_003, 0), (114_688, 0), (36_865, 1), (57_344, 1), (57_347, 1), (80_001, 1), (172_032, 1)]
+
+
+@pytest.mark.parametrize("d,bf16,m,teams", [(36_865, 1, 40, 10), (36_865, 1, 4_000, 40), (50_008, 1, 4_000, 32), (60_000, 0, 4_000, 24), (114_688, 0, 4_000, 16),
+                                            (114_689, 0, 4_000, 4), (172_033, 1, 4_000, 6)])
+def test_parts(d, bf16, m, teams):
+    """A part per crew, four rows and more; wider rows take two passes, whose parts have the chip's workgroups twice between them."""
+    p = cr.cr_plan_ex(2, 4, 1, m, d, x_dtype=bf16)
+    cr.cr_workspace_bytes(p)
+    assert cr.cr_plan_info(p).num_teams == teams
+    cr.cr_plan_destroy(p)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,bf16", WIDTHS)
+@pytest.mark.parametrize("m,rows_per_run", [(4, None), (23, None), (61, 3), (79, None), (700, 5)])
+def test_nobody_waits(d, bf16, m, rows_per_run):
+    """fp32 dot products, everything across rows fp64: 3e-6 of a slab's rms per entry, as for the other wide rows.  With no patience most
+    parts of the dot products are worked out again: the same bits."""
+    import torch
+
+    gen = torch.Generator(device="cuda").manual_seed(d + m)
+    X = torch.empty(m, d, device="cuda", dtype=torch.bfloat16 if bf16 else torch.float32).normal_(generator=gen)
+    w = torch.randn(d, generator=gen, device="cuda") / d ** 0.5
+    y = torch.randn(m, generator=gen, device="cuda") + 4.0
+    slabs = []
+    for patience in (None, 0):
+        plan = cr.cr_plan_ex(1, 3, 1, m, d, model=cr.CR_LOGISTIC if m == 23 else cr.CR_LINEAR, x_dtype=bf16)
+        if rows_per_run:
+            cr.cr_plan_set_split(plan, cr.CR_SPLIT_ROWS_ONCE, rows_per_run)
+        if patience is not None:
+            assert cr.load_library().cr_testing_patience(ctypes.c_void_p(plan), patience) == 0
+        ws = cr.Workspace(plan)
+        for _ in range(3):                               # launches one after the other: what the last one left is no answer
+            ws.slab_grads().fill_(float("nan"))
+            cr.cr_partial_grads(plan, X, y, w)
+            cr.cr_synchronize(plan)
+            slabs.append(ws.slab_grads().clone())
+        rb, re_, _, _ = cr.cr_plan_get_segments(plan)
+        del ws
+        cr.cr_plan_destroy(plan)
+    assert all(torch.equal(slabs[0], s) for s in slabs[1:])
+    for q in range(len(rb)):
+        x = X[int(rb[q]):int(re_[q])].double()
+        z = x @ w.double()
+        ref = x.T @ ((torch.sigmoid(z) if m == 23 else z) - y[int(rb[q]):int(re_[q])].double())
+        assert float((slabs[0][q].double() - ref).abs().max() / ref.pow(2).mean().sqrt()) <= 3e-6
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bf16", [0, 1])
+def test_rows_that_are_not_finite_stay_with_their_slabs(bf16):
+    import torch
+
+    m, d = 23, 60_001
+    X = torch.randn(m, d, device="cuda").to(torch.bfloat16 if bf16 else torch.float32)
+    plan = cr.cr_plan_ex(1, 3, 0, m, d, x_dtype=bf16)
+    rb, re_, _, _ = cr.cr_plan_get_segments(plan)
+    X[int(rb[1]), 7], X[int(re_[1]) - 1, d - 1] = float("inf"), float("nan")     # the first and the last row of the second slab
+    ws = cr.Workspace(plan)
+    cr.cr_partial_grads(plan, X, torch.zeros(m, device="cuda"), torch.randn(d, device="cuda"))
+    cr.cr_synchronize(plan)
+    finite = torch.isfinite(ws.slab_grads()).all(1).tolist()
+    assert finite == [True, False, True]
+    del ws
+    cr.cr_plan_destroy(plan)
