@@ -98,7 +98,7 @@ struct TreeShape {           // what the rules of the encode go by
 // The nodes that a workgroup of the tree kernels has, leaves first, then level by level up: the nodes of level l have the places from
 // first[l - 1] on, and place t is node t + shift[l - 1] + sub * width[l - 1] in level-1 sub-tree `sub`.
 struct TreeLevels {
-    int32_t n, L, total, leaves;
+    int32_t n, L, total, leaves, threads;        // threads of the workgroup, as an argument: its size is a fetch of its own
     int32_t first[8], shift[8], width[8];
 };
 // The gradient step that rides in the launch of a decode.
@@ -196,7 +196,7 @@ hipError_t launch_tree_encode(const float *G, float *M, const ArgumentTables &ta
 hipError_t launch_decode(const float *M, float *g, const DecTerms &terms, const GradientStep &step, int64_t d, hipStream_t stream);
 int decode_groups(int64_t d);
 // Encode, decode and gradient step in one launch, where tree_and_decode_together says so: vectors of at most kTogetherColumns columns
-// (8 chunks of columns per workgroup; beyond kTogetherNarrowColumns 16 where the whole tree's messages fit LDS for them).
+// (4 or 8 chunks of columns per workgroup; beyond kTogetherNarrowColumns 16 where the whole tree's messages fit LDS for them).
 constexpr int64_t kTogetherColumns = 32768, kTogetherNarrowColumns = 8192;
 bool tree_and_decode_together(const TreeShape &tree, int64_t d);
 hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, int n, int L, float *g, const GradientStep &step,

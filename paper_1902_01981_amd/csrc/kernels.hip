@@ -24,6 +24,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstring>
 #include <iterator>
@@ -1362,7 +1363,7 @@ struct DeviceView {
     __device__ __forceinline__ int begin(int node) const { return t.node_begin[node]; }
     __device__ __forceinline__ double slab_coef_of(int s) const { return t.slab_coef[s]; }
 };
-template <int T> __device__ __forceinline__ DeviceView view_tables(const DeviceTables &t, char *) { return {t}; }
+__device__ __forceinline__ DeviceView view_tables(const DeviceTables &t, int, char *) { return {t}; }
 // ... and copied to LDS first where they are arguments, since a coefficient is two dependent fetches away.
 struct ArgumentView {
     const double *value;
@@ -1371,10 +1372,10 @@ struct ArgumentView {
     __device__ __forceinline__ int begin(int node) const { return first[node]; }
     __device__ __forceinline__ double slab_coef_of(int s) const { return value[slab[s]]; }
 };
-template <int T> __device__ __forceinline__ ArgumentView view_tables(const ArgumentTables &t, char *lds)
+__device__ __forceinline__ ArgumentView view_tables(const ArgumentTables &t, int threads, char *lds)
 {
     uint64_t *copy = reinterpret_cast<uint64_t *>(lds);
-    for (int i = threadIdx.x; i < t.used; i += T) copy[i] = t.word[i];
+    for (int i = threadIdx.x; i < t.used; i += threads) copy[i] = t.word[i];
     __syncthreads();
     const uint16_t *half = reinterpret_cast<const uint16_t *>(lds);
     return {reinterpret_cast<const double *>(lds), half + t.at_begin, half + t.at_coef, half + t.at_slab};
@@ -1453,24 +1454,24 @@ __device__ __forceinline__ void sum_slabs(const float *G, int64_t d, int64_t col
     }
 }
 
-// The messages of a workgroup's nodes, stored and left in LDS.  coef_of(node): the node's coefficient; own_sum(node, acc): its own sum
-// for the lane's columns.
-template <int VEC, int B, int T, typename COEF, typename OWN>
-__device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, const TreeLds<VEC, B> &lds, COEF coef_of, OWN own_sum, float *M,
+// The messages of a workgroup's nodes, stored and left in LDS.
+template <int VEC, int B, typename VIEW>
+__device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, const TreeLds<VEC, B> &lds, const VIEW &view, const float *G, float *M,
                                               int64_t d, int64_t col, bool live)
 {
-    constexpr int TEAMS = T / B;
+    const int TEAMS = tree.threads / B;
     const int team = threadIdx.x / B, tl = threadIdx.x % B;
     const TreePlaces places{tree, sub};
     for (int t = team; t < tree.total; t += TEAMS) {
         const int node = places.node(t);
-        const double a = coef_of(node);
+        const double a = view.coef_of(node);
+        const int begin = view.begin(node), end = view.begin(node + 1);
         if (tl == 0) lds.coef[t] = a;
         if (!sends(a)) continue;
         double acc[VEC];
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
-        own_sum(node, acc);
+        sum_slabs<VEC>(G, d, col, begin, end, [&](int s) { return view.slab_coef_of(s); }, acc);
         if (t < tree.leaves) {
             float out[VEC];
 #pragma unroll
@@ -1501,39 +1502,43 @@ __device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, c
 }
 
 // one level-1 sub-tree (grid.y) per workgroup
-template <int VEC, int B, int T, typename TABLES>
-__global__ void __launch_bounds__(T)
+template <int VEC, int B, typename TABLES>
+__global__ void __launch_bounds__(1024)
 tree_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, TreeLevels tree, int64_t d, int nq)
 {
     extern __shared__ __align__(16) char tree_lds[];
-    const auto view = view_tables<T>(tables, tree_lds);
+    const auto view = view_tables(tables, tree.threads, tree_lds);
     const TreeLds<VEC, B> lds(tree_lds + TABLES::kLdsBytes, tree.total, tree.leaves);
     const int q = blockIdx.x * B + threadIdx.x % B;
     const int64_t col = chunk_offset<VEC>(q, nq, static_cast<int>(d));       // lanes past the row repeat its last chunk and do not store
-    tree_messages<VEC, B, T>(
-        tree, blockIdx.y, lds, [&](int node) { return view.coef_of(node); },
-        [&](int node, double (&acc)[VEC]) { sum_slabs<VEC>(G, d, col, view.begin(node), view.begin(node + 1), [&](int s) { return view.slab_coef_of(s); }, acc); },
-        M, d, col, q < nq);
+    tree_messages<VEC, B>(tree, blockIdx.y, lds, view, G, M, d, col, q < nq);
 }
 
 // What one column contributes to the convergence measures of a gradient step: |w_new - w|^2, |w|^2, |w_new - w*|^2, |w*|^2.
-__device__ __forceinline__ void measure(double (&sum)[4], float w_old, float w_new, const float *w_star, int64_t col)
+__device__ __forceinline__ void measure(double (&sum)[4], float w_old, float w_new, bool with_star, float w_star)
 {
     const double dw = static_cast<double>(w_new) - static_cast<double>(w_old);
     sum[0] += dw * dw;
     sum[1] += static_cast<double>(w_old) * w_old;
-    if (w_star) {
-        const double ws = w_star[col], e = static_cast<double>(w_new) - ws;
+    if (with_star) {
+        const double ws = w_star, e = static_cast<double>(w_new) - ws;
         sum[2] += e * e;
         sum[3] += ws * ws;
     }
+}
+
+// What the step reads of the chunk at column col.  The chunk that owns a column is the only one that uses and writes its entry.
+template <int VEC> __device__ __forceinline__ void load_step(const GradientStep &step, int64_t col, float (&w_old)[VEC], float (&w_star)[VEC])
+{
+    if (step.w) load_row<VEC>(step.w + col, w_old);
+    if (step.measures && step.w_star) load_row<VEC>(step.w_star + col, w_star);
 }
 
 // The decoded chunk q goes to g; step.w: w <- w - lr g with g as stored, a column shared with the neighbouring chunk by the chunk that
 // owns it only; step.measures: the columns' part of the measures is added to sum.
 template <int VEC, bool NT>
 __device__ __forceinline__ void put_gradient(const double (&acc)[VEC], float *g, int64_t col, int q, int nq, int64_t d, const GradientStep &step,
-                                             double (&sum)[4])
+                                             const float (&w_old)[VEC], const float (&w_star)[VEC], double (&sum)[4])
 {
     float out[VEC];
 #pragma unroll
@@ -1544,9 +1549,9 @@ __device__ __forceinline__ void put_gradient(const double (&acc)[VEC], float *g,
 #pragma unroll
     for (int v = 0; v < VEC; ++v)
         if (chunk_owns<VEC>(q, v, nq, static_cast<int>(d))) {
-            const float w_old = step.w[col + v], w_new = fmaf(-step.lr, out[v], w_old);
+            const float w_new = fmaf(-step.lr, out[v], w_old[v]);
             step.w[col + v] = w_new;
-            if (step.measures) measure(sum, w_old, w_new, step.w_star, col + v);
+            if (step.measures) measure(sum, w_old[v], w_new, step.w_star != nullptr, w_star[v]);
         }
 }
 
@@ -1554,20 +1559,19 @@ __device__ __forceinline__ void put_gradient(const double (&acc)[VEC], float *g,
 // vectors of so few columns that a launch lasts no longer than its chain of fetches; longer ones have more to gain from a workgroup per
 // sub-tree and a decode of their own.  us, encode and decode apart / together: (2,12) tree, s = 2, 10 columns 4.2 + 2.0 / 6.1;
 // (3,4) tree, 6 500 columns 5.7 + 2.6 / 5.7; (2,12), s = 2, 24 576 columns 13.4 + 3.9 / 14.6, 73 728 columns 29.9 + 4.7 / 35.4.
-template <int VEC, int B, int T, typename TABLES>
-__global__ void __launch_bounds__(T)
+template <int VEC, int B, typename TABLES>
+__global__ void __launch_bounds__(1024)
 tree_decode_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, TreeLevels tree, float *__restrict__ g, GradientStep step,
                    int64_t d, int nq)
 {
     extern __shared__ __align__(16) char tree_lds[];
-    const auto view = view_tables<T>(tables, tree_lds);
+    const auto view = view_tables(tables, tree.threads, tree_lds);
     const TreeLds<VEC, B> lds(tree_lds + TABLES::kLdsBytes, tree.total, tree.leaves);
     const int tl = threadIdx.x % B, q = blockIdx.x * B + tl;
     const int64_t col = chunk_offset<VEC>(q, nq, static_cast<int>(d));
-    tree_messages<VEC, B, T>(
-        tree, 0, lds, [&](int node) { return view.coef_of(node); },
-        [&](int node, double (&acc)[VEC]) { sum_slabs<VEC>(G, d, col, view.begin(node), view.begin(node + 1), [&](int s) { return view.slab_coef_of(s); }, acc); },
-        M, d, col, q < nq);
+    float w_old[VEC] = {}, w_star[VEC] = {};             // on their way from the start, not once the gradient is there
+    if (threadIdx.x < B) load_step<VEC>(step, col, w_old, w_star);
+    tree_messages<VEC, B>(tree, 0, lds, view, G, M, d, col, q < nq);
     __syncthreads();
     if (threadIdx.x >= B) return;
     double sum[4] = {0.0, 0.0, 0.0, 0.0};
@@ -1576,7 +1580,7 @@ tree_decode_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES ta
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
         lds.template fold<true>(tree.first[0], tree.n, tl, acc);
-        put_gradient<VEC, false>(acc, g, col, q, nq, d, step, sum);
+        put_gradient<VEC, false>(acc, g, col, q, nq, d, step, w_old, w_star, sum);
     }
     if (!step.measures) return;
 #pragma unroll
@@ -1630,8 +1634,11 @@ decode_kernel(const float *__restrict__ M, float *__restrict__ g, DecTerms terms
     }
     double sum[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int c = 0; c < C; ++c)
-        if (q0 + c * 256 < nq) put_gradient<VEC, NT>(acc[c], g, col[c], q0 + c * 256, nq, d, step, sum);
+    for (int c = 0; c < C; ++c) {
+        float w_old[VEC] = {}, w_star[VEC] = {};
+        load_step<VEC>(step, col[c], w_old, w_star);
+        if (q0 + c * 256 < nq) put_gradient<VEC, NT>(acc[c], g, col[c], q0 + c * 256, nq, d, step, w_old, w_star, sum);
+    }
     if (!step.measures) return;
     __shared__ double part[4][4];
 #pragma unroll
@@ -2041,12 +2048,25 @@ TreeLevels tree_levels(int n, int L, bool whole)
 
 template <int VEC, int B> bool tree_fits(const TreeLevels &tree) { return TreeLds<VEC, B>::bytes(tree.total, tree.leaves) <= kTreeLdsBytes; }
 
-template <int VEC, int B, int T, typename TABLES>
-hipError_t launch_tree_shape(const float *G, float *M, const TABLES &tables, const TreeLevels &tree, int64_t d, hipStream_t stream)
+// Threads of a workgroup that has `nodes` nodes and B lanes for each: the more nodes have a team of their own the fewer fetches follow
+// one another, as long as all workgroups are on the chip at once (us of the kernel, 256 threads / more): (3,6), s = 2, 1 024 columns
+// 8.2 / 6.5 (704), 4 096 9.5 / 8.0, 6 500 10.9 / 10.7 (512) / 12.4 (704, two rounds), 16 384 13.5 / 18.9 (512, two rounds); (3,4) 6 500 6.9 /
+// 6.1 (384), 16 384 7.8 / 9.2; encode and decode together, (2,12), s = 2, 512 / 1 024: 12 288 columns 12.0 / 10.0, 24 576 14.1 / 16.8.
+// Fewer threads where there are fewer nodes: (1,64) 16 384 columns 10.8 (256) / 7.5 (64).
+template <int B, typename TABLES> int tree_threads(int nodes, int groups, int least)
 {
-    const int nq = static_cast<int>((d + VEC - 1) / VEC);
+    constexpr int kUnits = 256, kWavefronts = std::is_same_v<TABLES, DeviceTables> ? 20 : 16;      // of a compute unit, by their registers
+    const int wanted = std::min(1024, (nodes * B + 63) / 64 * 64), fit = kWavefronts / ((groups + kUnits - 1) / kUnits) * 64;
+    return std::min(wanted, std::max(least, fit));
+}
+
+template <int VEC, int B, typename TABLES>
+hipError_t launch_tree_shape(const float *G, float *M, const TABLES &tables, TreeLevels tree, int64_t d, hipStream_t stream)
+{
+    const int nq = static_cast<int>((d + VEC - 1) / VEC), groups = (nq + B - 1) / B;
     const size_t lds = TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves);
-    tree_kernel<VEC, B, T><<<dim3((nq + B - 1) / B, tree.n), T, lds, stream>>>(G, M, tables, tree, d, nq);
+    tree.threads = tree_threads<B, TABLES>(tree.total, groups * tree.n, 256);
+    tree_kernel<VEC, B><<<dim3(groups, tree.n), tree.threads, lds, stream>>>(G, M, tables, tree, d, nq);
     return hipGetLastError();
 }
 
@@ -2054,21 +2074,31 @@ template <typename TABLES>
 hipError_t launch_tree(const float *G, float *M, const TABLES &tables, int n, int L, int64_t d, hipStream_t stream)
 {
     const TreeLevels tree = tree_levels(n, L, false);
-    if (d < 4) return launch_tree_shape<1, 16, 256>(G, M, tables, tree, d, stream);
+    if (d < 4) return launch_tree_shape<1, 16>(G, M, tables, tree, d, stream);
     // 64 chunks: longer pieces of a slab.  Sub-trees of two levels have the workgroups for it from half as many columns on (us, 16 chunks / 64:
     // (2,20), 16 385 columns 27.9 / 22.1, 32 768 45.0 / 35.2; (2,4) 16 385 7.7 / 7.8, 24 576 8.8 / 7.9; (3,4) 24 576 13.0 / 12.1, (3,6) 22.6 / 32.9)
-    if (d > (L == 2 ? kTreeNarrowColumns / 2 : kTreeNarrowColumns) && tree_fits<4, 64>(tree)) return launch_tree_shape<4, 64, 256>(G, M, tables, tree, d, stream);
-    return launch_tree_shape<4, 16, 256>(G, M, tables, tree, d, stream);
+    if (d > (L == 2 ? kTreeNarrowColumns / 2 : kTreeNarrowColumns) && tree_fits<4, 64>(tree)) return launch_tree_shape<4, 64>(G, M, tables, tree, d, stream);
+    return launch_tree_shape<4, 16>(G, M, tables, tree, d, stream);
 }
 
-template <int VEC, int B, int T, typename TABLES>
-hipError_t launch_tree_decode_shape(const float *G, float *M, const TABLES &tables, const TreeLevels &tree, float *g, const GradientStep &step,
-                                    int64_t d, hipStream_t stream)
+template <int VEC, int B, typename TABLES>
+hipError_t launch_tree_decode_shape(const float *G, float *M, const TABLES &tables, TreeLevels tree, float *g, const GradientStep &step, int64_t d,
+                                    hipStream_t stream)
 {
-    const int nq = static_cast<int>((d + VEC - 1) / VEC);
+    const int nq = static_cast<int>((d + VEC - 1) / VEC), groups = (nq + B - 1) / B;
     const size_t lds = TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves);
-    tree_decode_kernel<VEC, B, T><<<(nq + B - 1) / B, T, lds, stream>>>(G, M, tables, tree, g, step, d, nq);
+    tree.threads = tree_threads<B, TABLES>(tree.total, groups, 512);
+    tree_decode_kernel<VEC, B><<<groups, tree.threads, lds, stream>>>(G, M, tables, tree, g, step, d, nq);
     return hipGetLastError();
+}
+
+// Chunks of columns per workgroup that has the whole tree.  Four where the nodes are more than teams of eight lanes and the vector is short
+// (us, eight / four: (2,12), s = 2, 10 columns 6.3 / 5.5, 1 024 7.2 / 6.6, 2 048 7.2 / 6.8, 4 096 7.4 / 7.7; (3,5) 1 024 8.2 / 7.5, 4 096 8.5 / 7.9,
+// 6 000 9.0 / 10.0).
+int tree_decode_chunks(const TreeLevels &tree, int64_t d)
+{
+    if (d > kTogetherNarrowColumns && tree_fits<4, 16>(tree)) return 16;
+    return d >= 4 && d <= 2048 && tree.total * 8 > 1024 ? 4 : 8;
 }
 
 template <typename TABLES>
@@ -2076,9 +2106,11 @@ hipError_t launch_tree_decode(const float *G, float *M, const TABLES &tables, in
                               hipStream_t stream)
 {
     const TreeLevels tree = tree_levels(n, L, true);
-    if (d < 4) return launch_tree_decode_shape<1, 8, 1024>(G, M, tables, tree, g, step, d, stream);
-    if (d > kTogetherNarrowColumns && tree_fits<4, 16>(tree)) return launch_tree_decode_shape<4, 16, 512>(G, M, tables, tree, g, step, d, stream);
-    return launch_tree_decode_shape<4, 8, 1024>(G, M, tables, tree, g, step, d, stream);
+    if (d < 4) return launch_tree_decode_shape<1, 8>(G, M, tables, tree, g, step, d, stream);
+    const int chunks = tree_decode_chunks(tree, d);
+    if (chunks == 16) return launch_tree_decode_shape<4, 16>(G, M, tables, tree, g, step, d, stream);
+    if (chunks == 4) return launch_tree_decode_shape<4, 4>(G, M, tables, tree, g, step, d, stream);
+    return launch_tree_decode_shape<4, 8>(G, M, tables, tree, g, step, d, stream);
 }
 }  // namespace
 
@@ -2125,7 +2157,7 @@ bool tree_and_decode_together(const TreeShape &tree, int64_t d)
 int tree_decode_groups(int n, int L, int64_t d)
 {
     const int64_t chunks = d < 4 ? d : (d + 3) / 4;
-    const int per = d > kTogetherNarrowColumns && tree_fits<4, 16>(tree_levels(n, L, true)) ? 16 : 8;
+    const int per = tree_decode_chunks(tree_levels(n, L, true), d);
     return static_cast<int>((chunks + per - 1) / per);
 }
 
