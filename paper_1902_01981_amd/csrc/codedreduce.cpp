@@ -158,6 +158,7 @@ struct cr_plan_s {
     size_t off_slab = 0, off_level = 0, off_row = 0, off_coef = 0, off_acoef = 0, off_sub = 0, off_dec = 0;
     size_t max_terms = 0;
 
+    std::vector<int32_t> last_send;                // N: the last step of the call at hand in which a node sends (see Stores)
     bool have_grads = false, have_messages = false;
     std::vector<char> static_program;              // host copy of the encode program of cr_aggregate_static (ordinary memory)
 
@@ -645,6 +646,7 @@ int cr_plan_ex(int L, int n, int s, int64_t m, int64_t d, int model, int x_dtype
         for (const cr::Slab &sl : p->slabs) p->node_slab_begin[sl.node + 1] += 1;
         for (int32_t i = 0; i < p->tree.N; ++i) p->node_slab_begin[i + 1] += p->node_slab_begin[i];
         for (const cr::Slab &sl : p->slabs) p->slab_coef.push_back(sl.coef);
+        p->last_send.assign(p->tree.N, -1);
         p->shape = {n, L, s, p->tree.N, static_cast<int64_t>(p->slabs.size())};
         if (cr::tree_side_by_side(p->shape, d, cr::Otherwise::kCopy) || cr::tree_side_by_side(p->shape, d, cr::Otherwise::kLaunches) ||
             cr::tree_side_by_side(p->shape, d, cr::Otherwise::kBatch)) {
@@ -968,7 +970,28 @@ int cr_load_partial_grads(cr_plan_t *p, const float *G)
 
 namespace {
 
-struct ProgramCounts { int64_t active_slabs = 0, active_msgs = 0; int terms = 0; cr::DecTerms dec; };
+struct ProgramCounts { int64_t active_slabs = 0, stored_msgs = 0; int terms = 0; cr::DecTerms dec; };
+
+// Which messages a mask's launches write to memory.  Nobody can read the messages of one call of several masks before the call is done
+// but its own decode: a node's message is then the one of the last mask under which it sends, and the earlier ones need not leave the
+// chip.  15 to 22 % of an aggregation's bytes are messages.
+struct Stores {
+    enum { kAll = -1, kNone = -2 };
+    int step = kAll;                                     // or the step of a call of several, whose last_send is filled in
+    bool first_level = true;                             // the master's children's in any case: a launch of its own decodes
+};
+bool stored(const cr_plan_t *p, const Stores &stores, int32_t node)
+{
+    return stores.step == Stores::kAll || (stores.first_level && node < p->n) || (stores.step >= 0 && p->last_send[node] == stores.step);
+}
+
+void note_last_sends(cr_plan_t *p, const uint8_t *masks, int steps)
+{
+    const int32_t N = p->tree.N;
+    for (int t = 0; t < steps; ++t)
+        for (int32_t i = 0; i < N; ++i)
+            if (!masks[static_cast<size_t>(t) * N + i]) p->last_send[i] = t;
+}
 
 void decode_terms(int n, const uint8_t *mask, const double *row, cr::DecTerms *dec)
 {
@@ -983,7 +1006,7 @@ void decode_terms(int n, const uint8_t *mask, const double *row, cr::DecTerms *d
 // Turns a straggler mask into the encode program of one iteration, written into the host block h (program_bytes long, laid out
 // by compute_layout): the post-order term list of every level-1 sub-tree; the master's decode terms go into *counts.  Any group
 // beyond tolerance fails the call before anything is written (CR_E_UNDECODABLE).
-int build_program(cr_plan_t *p, const uint8_t *mask, char *h, ProgramCounts *counts)
+int build_program(cr_plan_t *p, const uint8_t *mask, const Stores &stores, char *h, ProgramCounts *counts)
 {
     const int n = p->n, L = p->L;
     const int32_t N = p->tree.N, groups = N / n;
@@ -1034,10 +1057,11 @@ int build_program(cr_plan_t *p, const uint8_t *mask, char *h, ProgramCounts *cou
             for (int32_t q = sb; q < se; ++q) put(nt++, q, p->slabs[q].coef);
             if (se == sb) put(nt++, 0, 0.0);              // a node without rows still sends its children's combination
             t_level[nt - 1] = level;                      // the node's last term finishes it
-            t_row[nt - 1] = node;
+            const bool put_down = stored(p, stores, node);
+            t_row[nt - 1] = put_down ? node : ~node;
             t_acoef[nt - 1] = acoef;
             counts->active_slabs += se - sb;
-            counts->active_msgs += 1;
+            counts->stored_msgs += put_down;
         }
     };
     for (int i = 0; i < n; ++i) {
@@ -1061,9 +1085,10 @@ int build_program(cr_plan_t *p, const uint8_t *mask, char *h, ProgramCounts *cou
     return CR_OK;
 }
 
-// The same for the tree kernels: a coefficient per node.
-int build_coefs(cr_plan_t *p, const uint8_t *mask, cr::NodeCoefs *coefs, ProgramCounts *counts)
+// The same for the tree kernels: a coefficient per node, and whether its message is written.
+int build_coefs(cr_plan_t *p, const uint8_t *mask, const Stores &stores, cr::NodeCoefs *coefs, cr::NodeBits *bits, ProgramCounts *counts)
 {
+    *bits = cr::NodeBits();
     const int n = p->n;
     double straggler;
     std::memcpy(&straggler, &cr::kStraggler, sizeof straggler);
@@ -1078,7 +1103,9 @@ int build_coefs(cr_plan_t *p, const uint8_t *mask, cr::NodeCoefs *coefs, Program
             coefs->a[node] = mask[node] ? straggler : row[j];
             if (mask[node]) continue;
             counts->active_slabs += p->node_slab_begin[node + 1] - p->node_slab_begin[node];
-            counts->active_msgs += 1;
+            if (!stored(p, stores, node)) continue;
+            bits->word[node / 32] |= 1u << node % 32;
+            counts->stored_msgs += 1;
         }
     }
     return CR_OK;
@@ -1128,15 +1155,16 @@ int check_masks(const cr_plan_t *p, const uint8_t *masks, int steps)
 
 // Builds the encode programs of `count` <= kProgramSlots masks in pinned staging and sends them to program slots 0 .. count-1 with
 // one copy on the plan's stream (which therefore follows every kernel that still reads the slots).  counts[i] describes program i.
-int upload_programs(cr_plan_t *p, const uint8_t *masks, int count, ProgramCounts *counts)
+int upload_programs(cr_plan_t *p, const uint8_t *masks, int count, Stores stores, ProgramCounts *counts)
 {
     const int half = p->staging_next;
     if (p->staging_used[half]) CR_HIP(hipEventSynchronize(p->staging_done[half]));     // the copy that last read this half is done
     char *h = p->h_staging + static_cast<size_t>(half) * kProgramSlots * p->program_bytes;
     for (int i = 0; i < count; ++i) {
         counts[i] = ProgramCounts();
-        int rc = build_program(p, masks + static_cast<size_t>(i) * p->tree.N, h + static_cast<size_t>(i) * p->program_bytes, &counts[i]);
+        int rc = build_program(p, masks + static_cast<size_t>(i) * p->tree.N, stores, h + static_cast<size_t>(i) * p->program_bytes, &counts[i]);
         if (rc != CR_OK) return rc;
+        if (stores.step >= 0) ++stores.step;
     }
     p->staging_next = (half + 1) % kStagingHalves;
     CR_HIP(hipMemcpyAsync(p->d_program, h, static_cast<size_t>(count) * p->program_bytes, hipMemcpyHostToDevice, p->stream));
@@ -1147,7 +1175,7 @@ int upload_programs(cr_plan_t *p, const uint8_t *masks, int count, ProgramCounts
 
 int encode_slot(cr_plan_t *p, int slot, const ProgramCounts &counts)
 {
-    LaunchTimer t(p, CR_K_ENCODE, (counts.active_slabs + counts.active_msgs) * p->d * 4);
+    LaunchTimer t(p, CR_K_ENCODE, (counts.active_slabs + counts.stored_msgs) * p->d * 4);
     CR_HIP(cr::launch_encode(p->G_src, p->d_M, program_view(p, p->d_program + static_cast<size_t>(slot) * p->program_bytes), p->n, p->L, p->d, p->stream));
     t.done();
     p->dec = counts.dec;
@@ -1163,15 +1191,16 @@ struct MaskTables {
     bool as_arguments = false;
     cr::DeviceTables device;                             // the coefficients of the mask in any case
     cr::ArgumentTables arguments;
+    cr::NodeBits stored;
 };
 
 // The tables in the workspace are those that were written there with stage 1's, and stand as long as its slabs do.  With slabs of the
 // caller's nothing in the workspace is relied on: the tables are in the plan's pages, or travel as kernel arguments, or, where they do not fit, in a
 // copy from pinned memory, once per call (*sent).
-int mask_tables(cr_plan_t *p, const uint8_t *mask, bool slabs_here, MaskTables *t, ProgramCounts *counts, bool *sent)
+int mask_tables(cr_plan_t *p, const uint8_t *mask, const Stores &stores, bool slabs_here, MaskTables *t, ProgramCounts *counts, bool *sent)
 {
     *counts = ProgramCounts();
-    int rc = build_coefs(p, mask, &t->device.coefs, counts);
+    int rc = build_coefs(p, mask, stores, &t->device.coefs, &t->stored, counts);
     if (rc != CR_OK) return rc;
     t->device.node_begin = p->d_node_begin;
     t->device.slab_coef = p->d_slab_coef;
@@ -1186,9 +1215,9 @@ int mask_tables(cr_plan_t *p, const uint8_t *mask, bool slabs_here, MaskTables *
 
 int encode_tree(cr_plan_t *p, const MaskTables &tables, const ProgramCounts &counts)
 {
-    LaunchTimer t(p, CR_K_ENCODE, (counts.active_slabs + counts.active_msgs) * p->d * 4);
-    CR_HIP(tables.as_arguments ? cr::launch_tree_encode(p->G_src, p->d_M, tables.arguments, p->n, p->L, p->d, p->stream)
-                               : cr::launch_tree_encode(p->G_src, p->d_M, tables.device, p->n, p->L, p->d, p->stream));
+    LaunchTimer t(p, CR_K_ENCODE, (counts.active_slabs + counts.stored_msgs) * p->d * 4);
+    CR_HIP(tables.as_arguments ? cr::launch_tree_encode(p->G_src, p->d_M, tables.arguments, tables.stored, p->n, p->L, p->d, p->stream)
+                               : cr::launch_tree_encode(p->G_src, p->d_M, tables.device, tables.stored, p->n, p->L, p->d, p->stream));
     t.done();
     p->dec = counts.dec;
     p->have_messages = true;
@@ -1218,9 +1247,9 @@ bool overlap(const float *a, int64_t a_floats, const float *b, int64_t b_floats)
 // encode, decode and gradient step in one launch, which counts as the encode's
 int encode_decode(cr_plan_t *p, const MaskTables &tables, const ProgramCounts &counts, float *g, const cr::GradientStep &step)
 {
-    LaunchTimer t(p, CR_K_ENCODE, (counts.active_slabs + counts.active_msgs + 1 + step_rows(step)) * p->d * 4);
-    CR_HIP(tables.as_arguments ? cr::launch_tree_encode_decode(p->G_src, p->d_M, tables.arguments, p->n, p->L, g, step, p->d, p->stream)
-                               : cr::launch_tree_encode_decode(p->G_src, p->d_M, tables.device, p->n, p->L, g, step, p->d, p->stream));
+    LaunchTimer t(p, CR_K_ENCODE, (counts.active_slabs + counts.stored_msgs + 1 + step_rows(step)) * p->d * 4);
+    CR_HIP(tables.as_arguments ? cr::launch_tree_encode_decode(p->G_src, p->d_M, tables.arguments, tables.stored, p->n, p->L, g, step, p->d, p->stream)
+                               : cr::launch_tree_encode_decode(p->G_src, p->d_M, tables.device, tables.stored, p->n, p->L, g, step, p->d, p->stream));
     t.done();
     p->dec = counts.dec;
     p->have_messages = true;
@@ -1238,13 +1267,13 @@ int cr_encode_tree(cr_plan_t *p, const uint8_t *mask)
     if (cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kCopy)) {
         MaskTables tables;
         bool sent = false;
-        int rc = mask_tables(p, mask, p->slabs_here, &tables, &counts, &sent);
+        int rc = mask_tables(p, mask, Stores(), p->slabs_here, &tables, &counts, &sent);
         if (rc != CR_OK) return rc;
         return encode_tree(p, tables, counts);
     }
     int rc = check_masks(p, mask, 1);
     if (rc != CR_OK) return rc;
-    rc = upload_programs(p, mask, 1, &counts);
+    rc = upload_programs(p, mask, 1, Stores(), &counts);
     if (rc != CR_OK) return rc;
     return encode_slot(p, 0, counts);
 }
@@ -1273,14 +1302,17 @@ int cr_gd_run(cr_plan_t *p, const void *X, const float *y, float *w, float *g, c
     const int32_t N = p->tree.N;
     const bool side_by_side = cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kBatch);
     const bool together = cr::tree_and_decode_together(p->shape, p->d) && !overlap(g, p->d, p->d_G, static_cast<int64_t>(p->slabs.size()) * p->d);
+    const bool among_messages = overlap(g, p->d, p->d_M, N * p->d) || overlap(w, p->d, p->d_M, N * p->d);
+    note_last_sends(p, masks, steps);
     ProgramCounts counts[kProgramSlots];
     MaskTables tables;
     bool sent = false;
     for (int t0 = 0; t0 < steps; t0 += kProgramSlots) {
         const int count = std::min(kProgramSlots, steps - t0);
+        auto stores = [&](int i) { return Stores{among_messages ? Stores::kAll : t0 + i, !together}; };
         // where the tree's kernels take programs, those of the next kProgramSlots steps travel in one copy
         if (!side_by_side) {
-            rc = upload_programs(p, masks + static_cast<size_t>(t0) * N, count, counts);
+            rc = upload_programs(p, masks + static_cast<size_t>(t0) * N, count, stores(0), counts);
             if (rc != CR_OK) return rc;
         }
         for (int i = 0; i < count; ++i) {
@@ -1289,7 +1321,7 @@ int cr_gd_run(cr_plan_t *p, const void *X, const float *y, float *w, float *g, c
             step.lr = lr;
             step.w_star = w_star;
             step.measures = metrics ? p->d_measures + i * p->measures_stride : nullptr;
-            if (side_by_side) rc = mask_tables(p, masks + static_cast<size_t>(t0 + i) * N, true, &tables, &counts[i], &sent);
+            if (side_by_side) rc = mask_tables(p, masks + static_cast<size_t>(t0 + i) * N, stores(i), true, &tables, &counts[i], &sent);
             if (rc == CR_OK) rc = cr_partial_grads(p, X, y, w);
             if (together) {
                 if (rc == CR_OK) rc = encode_decode(p, tables, counts[i], g, step);
@@ -1325,6 +1357,10 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
     // one launch for several masks leaves the order in which workgroups decode open: vectors that overlap in part need it
     const bool in_order = in_place || (g_step_stride > 0 && g_step_stride < p->d);
     const bool together = cr::tree_and_decode_together(p->shape, p->d) && !in_place;
+    // vectors of the caller's that lie among the messages: everything in its place, as the separate calls leave it
+    const bool among_messages = overlap(g, p->d + more * g_step_stride, p->d_M, N * p->d) ||
+                                overlap(G, static_cast<int64_t>(p->slabs.size()) * p->d + more * G_step_stride, p->d_M, N * p->d);
+    note_last_sends(p, masks, steps);
     ProgramCounts counts[kProgramSlots];
     MaskTables tables;
     bool sent = false;
@@ -1334,13 +1370,14 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
         const bool alone = cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kCopy) && count == 1;
         const bool in_steps = !in_order && !alone && cr::encode_in_steps(p->shape, p->d, count);
         const bool side_by_side = alone || cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kBatch);
+        auto stores = [&](int i) { return Stores{among_messages ? Stores::kAll : t0 + i, !in_steps && !together}; };
         if (in_steps || !side_by_side) {
-            rc = upload_programs(p, masks + static_cast<size_t>(t0) * N, count, counts);
+            rc = upload_programs(p, masks + static_cast<size_t>(t0) * N, count, stores(0), counts);
             if (rc != CR_OK) return rc;
         }
         if (in_steps) {
             int64_t rows = 0;
-            for (int i = 0; i < count; ++i) rows += counts[i].active_slabs + counts[i].active_msgs + 1;
+            for (int i = 0; i < count; ++i) rows += counts[i].active_slabs + counts[i].stored_msgs + 1;
             p->G_src = G + static_cast<int64_t>(t0 + count - 1) * G_step_stride;
             p->have_grads = true;
             LaunchTimer t(p, CR_K_ENCODE, rows * p->d * 4);
@@ -1354,7 +1391,7 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
         }
         for (int i = 0; i < count; ++i) {
             float *out = g + static_cast<int64_t>(t0 + i) * g_step_stride;
-            if (side_by_side) rc = mask_tables(p, masks + static_cast<size_t>(t0 + i) * N, false, &tables, &counts[i], &sent);
+            if (side_by_side) rc = mask_tables(p, masks + static_cast<size_t>(t0 + i) * N, stores(i), false, &tables, &counts[i], &sent);
             if (rc != CR_OK) return rc;
             p->G_src = G + static_cast<int64_t>(t0 + i) * G_step_stride;
             p->have_grads = true;
@@ -1389,16 +1426,18 @@ int cr_aggregate_static(cr_plan_t *p, const float *G, const uint8_t *mask, float
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kLaunches) && p->tree_arguments->fits) {
         cr::NodeCoefs coefs;
+        cr::NodeBits stored;
         cr::ArgumentTables tables;
-        int rc = build_coefs(p, mask, &coefs, &counts);
+        const bool together = cr::tree_and_decode_together(p->shape, p->d) && !overlap(g, p->d, G, static_cast<int64_t>(p->slabs.size()) * p->d);
+        int rc = build_coefs(p, mask, {Stores::kNone, !together}, &coefs, &stored, &counts);
         if (rc != CR_OK) return rc;
         if (cr::argument_tables(*p->tree_arguments, coefs, &tables)) {
             CR_HIP(cr::static_scratch(&base));          // this device's copy of the array; never the array's name
             float *M = reinterpret_cast<float *>(base + cr::kStaticProgramBytes);
-            if (cr::tree_and_decode_together(p->shape, p->d) && !overlap(g, p->d, G, static_cast<int64_t>(p->slabs.size()) * p->d)) {
-                CR_HIP(cr::launch_tree_encode_decode(G, M, tables, p->n, p->L, g, cr::GradientStep(), p->d, stream));
+            if (together) {
+                CR_HIP(cr::launch_tree_encode_decode(G, M, tables, stored, p->n, p->L, g, cr::GradientStep(), p->d, stream));
             } else {
-                CR_HIP(cr::launch_tree_encode(G, M, tables, p->n, p->L, p->d, stream));
+                CR_HIP(cr::launch_tree_encode(G, M, tables, stored, p->n, p->L, p->d, stream));
                 CR_HIP(cr::launch_decode(M, g, counts.dec, cr::GradientStep(), p->d, stream));
             }
             return CR_OK;
@@ -1406,7 +1445,7 @@ int cr_aggregate_static(cr_plan_t *p, const float *G, const uint8_t *mask, float
         counts = ProgramCounts();
     }
     if (p->static_program.size() != p->program_bytes) p->static_program.assign(p->program_bytes, 0);
-    int rc = build_program(p, mask, p->static_program.data(), &counts);
+    int rc = build_program(p, mask, {Stores::kNone, true}, p->static_program.data(), &counts);
     if (rc != CR_OK) return rc;
     CR_HIP(cr::static_scratch(&base));
     float *M = reinterpret_cast<float *>(base + cr::kStaticProgramBytes);

@@ -31,7 +31,8 @@ struct DevSum {              // rows dst[dst_begin .. dst_end) = sum of rows [ro
 
 // Encode program: a post-order list of terms, stored as parallel arrays so that a wavefront fetches kEncodeUnroll terms with a few
 // wide scalar loads.  Term t:  own += coef[t] * G[slab[t]];  if level[t] > 0 the term is the last of a node at that level:
-// message = own + pending[level], stored to M[row[t]] and folded into pending[level-1] with acoef[t]; own = 0.
+// message = own + pending[level], stored to M[row[t]], or not at all where row[t] is negative, and folded into pending[level-1] with
+// acoef[t]; own = 0.
 struct EncProgram {
     const int32_t *slab;
     const int32_t *level;
@@ -78,6 +79,11 @@ struct ArgumentTables {
     static constexpr size_t kLdsBytes = kWords * 8;
     int32_t at_begin, at_coef, at_slab, used;            // in 16-bit units; 64-bit words in use
     uint64_t word[kWords];
+};
+// The nodes whose messages are written to memory: a message that nobody can read before another of the same call replaces it, or that
+// lies in the library's own array, is formed and folded in but not stored.
+struct NodeBits {
+    uint32_t word[NodeCoefs::kNodes / 32] = {};
 };
 // What the tree itself puts into ArgumentTables, laid out once per plan; argument_tables completes it for a mask, or says that there
 // is no room for the mask's coefficients.
@@ -190,8 +196,8 @@ constexpr int64_t kTreeColumns = 81920, kTreeNarrowColumns = 32768;
 // What the encode would take instead: a copy of one program, a program written out by launches, a program of which 16 share a copy.
 enum class Otherwise { kCopy, kLaunches, kBatch };
 bool tree_side_by_side(const TreeShape &tree, int64_t d, Otherwise otherwise);
-hipError_t launch_tree_encode(const float *G, float *M, const DeviceTables &tables, int n, int L, int64_t d, hipStream_t stream);
-hipError_t launch_tree_encode(const float *G, float *M, const ArgumentTables &tables, int n, int L, int64_t d, hipStream_t stream);
+hipError_t launch_tree_encode(const float *G, float *M, const DeviceTables &tables, const NodeBits &stored, int n, int L, int64_t d, hipStream_t stream);
+hipError_t launch_tree_encode(const float *G, float *M, const ArgumentTables &tables, const NodeBits &stored, int n, int L, int64_t d, hipStream_t stream);
 // the master's decode and, with step.w, the gradient step; decode_groups: workgroups of the launch
 hipError_t launch_decode(const float *M, float *g, const DecTerms &terms, const GradientStep &step, int64_t d, hipStream_t stream);
 int decode_groups(int64_t d);
@@ -199,10 +205,10 @@ int decode_groups(int64_t d);
 // (4 or 8 chunks of columns per workgroup; beyond kTogetherNarrowColumns 16 where the whole tree's messages fit LDS for them).
 constexpr int64_t kTogetherColumns = 32768, kTogetherNarrowColumns = 8192;
 bool tree_and_decode_together(const TreeShape &tree, int64_t d);
-hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, int n, int L, float *g, const GradientStep &step,
-                                     int64_t d, hipStream_t stream);
-hipError_t launch_tree_encode_decode(const float *G, float *M, const ArgumentTables &tables, int n, int L, float *g, const GradientStep &step,
-                                     int64_t d, hipStream_t stream);
+hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, const NodeBits &stored, int n, int L, float *g,
+                                     const GradientStep &step, int64_t d, hipStream_t stream);
+hipError_t launch_tree_encode_decode(const float *G, float *M, const ArgumentTables &tables, const NodeBits &stored, int n, int L, float *g,
+                                     const GradientStep &step, int64_t d, hipStream_t stream);
 int tree_decode_groups(int n, int L, int64_t d);
 // metrics[2t], metrics[2t + 1] of `steps` steps from the measures their launches of `groups` workgroups left at sums + t * step_stride
 hipError_t launch_measures(const double *sums, int64_t step_stride, int groups, int steps, bool with_star, float *metrics, hipStream_t stream);

@@ -1255,7 +1255,7 @@ __device__ __forceinline__ void walk_sub_tree(const float *G, float *M, const En
                         out[v] = static_cast<float>(msg);
                         own[c][v] = 0;
                     }
-                    if (live[c]) {
+                    if (live[c] && row[u] >= 0) {
                         if constexpr (NTS) store_row_nt<VEC>(at_byte(dst, off[c]), out);
                         else store_row<VEC>(at_byte(dst, off[c]), out);
                     }
@@ -1298,8 +1298,8 @@ encode_kernel(const float *__restrict__ G, float *__restrict__ M, EncProgram pro
 // are not read back.  us a mask, a launch each for encode and decode / this: (2,4) tree, 2 000 000 columns, four masks 62.2 / 54.6;
 // (3,4), 60 001 columns, eight masks 17.3 / 12.1; (2,12), s = 5, 117 706 columns, eight masks 61.8 / 60.7 (rows on 8-byte boundaries;
 // 117 760 columns 56).  Where it loses: see encode_in_steps.
-// Slabs are read past the caches and messages are not written past them: the next mask's messages often replace them there (encode
-// alone, 117 706 columns: 59.6 against 61.8).
+// Slabs are read past the caches.  Messages that a later mask replaces are not written at all (row < 0): 117 706 columns, s = 5, eight masks
+// 411 us, 499 with every one written.
 template <int LT>
 __global__ void __launch_bounds__(1024)
 encode_steps_kernel(const float *__restrict__ G, int64_t G_stride, float *__restrict__ M, EncProgram prog, int64_t prog_stride, int steps, int n,
@@ -1456,12 +1456,13 @@ __device__ __forceinline__ void sum_slabs(const float *G, int64_t d, int64_t col
 
 // The messages of a workgroup's nodes, stored and left in LDS.
 template <int VEC, int B, typename VIEW>
-__device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, const TreeLds<VEC, B> &lds, const VIEW &view, const float *G, float *M,
-                                              int64_t d, int64_t col, bool live)
+__device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, const TreeLds<VEC, B> &lds, const VIEW &view, const NodeBits &stored,
+                                              const float *G, float *M, int64_t d, int64_t col, bool live)
 {
     const int TEAMS = tree.threads / B;
     const int team = threadIdx.x / B, tl = threadIdx.x % B;
     const TreePlaces places{tree, sub};
+    auto stores = [&](int node) { return (stored.word[node >> 5] >> (node & 31) & 1u) != 0; };
     for (int t = team; t < tree.total; t += TEAMS) {
         const int node = places.node(t);
         const double a = view.coef_of(node);
@@ -1476,7 +1477,7 @@ __device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, c
             float out[VEC];
 #pragma unroll
             for (int v = 0; v < VEC; ++v) out[v] = static_cast<float>(acc[v]);
-            if (live) store_row<VEC>(M + static_cast<int64_t>(node) * d + col, out);
+            if (live && stores(node)) store_row<VEC>(M + static_cast<int64_t>(node) * d + col, out);
             lds.put_message(t, tl, out);
         } else {
 #pragma unroll
@@ -1495,7 +1496,8 @@ __device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, c
             float out[VEC];
 #pragma unroll
             for (int v = 0; v < VEC; ++v) out[v] = static_cast<float>(lds.own[((t - tree.leaves) * VEC + v) * B + tl] + pend[v]);
-            if (live) store_row<VEC>(M + static_cast<int64_t>(places.node(t)) * d + col, out);
+            const int node = places.node(t);
+            if (live && stores(node)) store_row<VEC>(M + static_cast<int64_t>(node) * d + col, out);
             lds.put_message(t, tl, out);
         }
     }
@@ -1504,14 +1506,14 @@ __device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, c
 // one level-1 sub-tree (grid.y) per workgroup
 template <int VEC, int B, typename TABLES>
 __global__ void __launch_bounds__(1024)
-tree_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, TreeLevels tree, int64_t d, int nq)
+tree_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, NodeBits stored, TreeLevels tree, int64_t d, int nq)
 {
     extern __shared__ __align__(16) char tree_lds[];
     const auto view = view_tables(tables, tree.threads, tree_lds);
     const TreeLds<VEC, B> lds(tree_lds + TABLES::kLdsBytes, tree.total, tree.leaves);
     const int q = blockIdx.x * B + threadIdx.x % B;
     const int64_t col = chunk_offset<VEC>(q, nq, static_cast<int>(d));       // lanes past the row repeat its last chunk and do not store
-    tree_messages<VEC, B>(tree, blockIdx.y, lds, view, G, M, d, col, q < nq);
+    tree_messages<VEC, B>(tree, blockIdx.y, lds, view, stored, G, M, d, col, q < nq);
 }
 
 // What one column contributes to the convergence measures of a gradient step: |w_new - w|^2, |w|^2, |w_new - w*|^2, |w*|^2.
@@ -1561,8 +1563,8 @@ __device__ __forceinline__ void put_gradient(const double (&acc)[VEC], float *g,
 // (3,4) tree, 6 500 columns 5.7 + 2.6 / 5.7; (2,12), s = 2, 24 576 columns 13.4 + 3.9 / 14.6, 73 728 columns 29.9 + 4.7 / 35.4.
 template <int VEC, int B, typename TABLES>
 __global__ void __launch_bounds__(1024)
-tree_decode_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, TreeLevels tree, float *__restrict__ g, GradientStep step,
-                   int64_t d, int nq)
+tree_decode_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, NodeBits stored, TreeLevels tree, float *__restrict__ g,
+                   GradientStep step, int64_t d, int nq)
 {
     extern __shared__ __align__(16) char tree_lds[];
     const auto view = view_tables(tables, tree.threads, tree_lds);
@@ -1571,7 +1573,7 @@ tree_decode_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES ta
     const int64_t col = chunk_offset<VEC>(q, nq, static_cast<int>(d));
     float w_old[VEC] = {}, w_star[VEC] = {};             // on their way from the start, not once the gradient is there
     if (threadIdx.x < B) load_step<VEC>(step, col, w_old, w_star);
-    tree_messages<VEC, B>(tree, 0, lds, view, G, M, d, col, q < nq);
+    tree_messages<VEC, B>(tree, 0, lds, view, stored, G, M, d, col, q < nq);
     __syncthreads();
     if (threadIdx.x >= B) return;
     double sum[4] = {0.0, 0.0, 0.0, 0.0};
@@ -2021,7 +2023,7 @@ hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int n
 
 namespace {
 constexpr size_t kTreeLdsBytes = size_t(60) << 10;          // 64 KB with ArgumentTables' copy
-static_assert(sizeof(ArgumentTables) <= 3776 && sizeof(DeviceTables) <= 3776 && sizeof(TreeLevels) + sizeof(GradientStep) + 64 <= 256, "4 KB of kernel arguments");
+static_assert(sizeof(ArgumentTables) <= 3776 && sizeof(DeviceTables) <= 3776 && sizeof(TreeLevels) + sizeof(GradientStep) + sizeof(NodeBits) + 64 <= 320, "4 KB of kernel arguments");
 
 // the nodes of one level-1 sub-tree, or of all of them
 TreeLevels tree_levels(int n, int L, bool whole)
@@ -2061,34 +2063,34 @@ template <int B, typename TABLES> int tree_threads(int nodes, int groups, int le
 }
 
 template <int VEC, int B, typename TABLES>
-hipError_t launch_tree_shape(const float *G, float *M, const TABLES &tables, TreeLevels tree, int64_t d, hipStream_t stream)
+hipError_t launch_tree_shape(const float *G, float *M, const TABLES &tables, const NodeBits &stored, TreeLevels tree, int64_t d, hipStream_t stream)
 {
     const int nq = static_cast<int>((d + VEC - 1) / VEC), groups = (nq + B - 1) / B;
     const size_t lds = TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves);
     tree.threads = tree_threads<B, TABLES>(tree.total, groups * tree.n, 256);
-    tree_kernel<VEC, B><<<dim3(groups, tree.n), tree.threads, lds, stream>>>(G, M, tables, tree, d, nq);
+    tree_kernel<VEC, B><<<dim3(groups, tree.n), tree.threads, lds, stream>>>(G, M, tables, stored, tree, d, nq);
     return hipGetLastError();
 }
 
 template <typename TABLES>
-hipError_t launch_tree(const float *G, float *M, const TABLES &tables, int n, int L, int64_t d, hipStream_t stream)
+hipError_t launch_tree(const float *G, float *M, const TABLES &tables, const NodeBits &stored, int n, int L, int64_t d, hipStream_t stream)
 {
     const TreeLevels tree = tree_levels(n, L, false);
-    if (d < 4) return launch_tree_shape<1, 16>(G, M, tables, tree, d, stream);
+    if (d < 4) return launch_tree_shape<1, 16>(G, M, tables, stored, tree, d, stream);
     // 64 chunks: longer pieces of a slab.  Sub-trees of two levels have the workgroups for it from half as many columns on (us, 16 chunks / 64:
     // (2,20), 16 385 columns 27.9 / 22.1, 32 768 45.0 / 35.2; (2,4) 16 385 7.7 / 7.8, 24 576 8.8 / 7.9; (3,4) 24 576 13.0 / 12.1, (3,6) 22.6 / 32.9)
-    if (d > (L == 2 ? kTreeNarrowColumns / 2 : kTreeNarrowColumns) && tree_fits<4, 64>(tree)) return launch_tree_shape<4, 64>(G, M, tables, tree, d, stream);
-    return launch_tree_shape<4, 16>(G, M, tables, tree, d, stream);
+    if (d > (L == 2 ? kTreeNarrowColumns / 2 : kTreeNarrowColumns) && tree_fits<4, 64>(tree)) return launch_tree_shape<4, 64>(G, M, tables, stored, tree, d, stream);
+    return launch_tree_shape<4, 16>(G, M, tables, stored, tree, d, stream);
 }
 
 template <int VEC, int B, typename TABLES>
-hipError_t launch_tree_decode_shape(const float *G, float *M, const TABLES &tables, TreeLevels tree, float *g, const GradientStep &step, int64_t d,
-                                    hipStream_t stream)
+hipError_t launch_tree_decode_shape(const float *G, float *M, const TABLES &tables, const NodeBits &stored, TreeLevels tree, float *g,
+                                    const GradientStep &step, int64_t d, hipStream_t stream)
 {
     const int nq = static_cast<int>((d + VEC - 1) / VEC), groups = (nq + B - 1) / B;
     const size_t lds = TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves);
     tree.threads = tree_threads<B, TABLES>(tree.total, groups, 512);
-    tree_decode_kernel<VEC, B><<<groups, tree.threads, lds, stream>>>(G, M, tables, tree, g, step, d, nq);
+    tree_decode_kernel<VEC, B><<<groups, tree.threads, lds, stream>>>(G, M, tables, stored, tree, g, step, d, nq);
     return hipGetLastError();
 }
 
@@ -2102,15 +2104,15 @@ int tree_decode_chunks(const TreeLevels &tree, int64_t d)
 }
 
 template <typename TABLES>
-hipError_t launch_tree_decode(const float *G, float *M, const TABLES &tables, int n, int L, float *g, const GradientStep &step, int64_t d,
-                              hipStream_t stream)
+hipError_t launch_tree_decode(const float *G, float *M, const TABLES &tables, const NodeBits &stored, int n, int L, float *g,
+                              const GradientStep &step, int64_t d, hipStream_t stream)
 {
     const TreeLevels tree = tree_levels(n, L, true);
-    if (d < 4) return launch_tree_decode_shape<1, 8>(G, M, tables, tree, g, step, d, stream);
+    if (d < 4) return launch_tree_decode_shape<1, 8>(G, M, tables, stored, tree, g, step, d, stream);
     const int chunks = tree_decode_chunks(tree, d);
-    if (chunks == 16) return launch_tree_decode_shape<4, 16>(G, M, tables, tree, g, step, d, stream);
-    if (chunks == 4) return launch_tree_decode_shape<4, 4>(G, M, tables, tree, g, step, d, stream);
-    return launch_tree_decode_shape<4, 8>(G, M, tables, tree, g, step, d, stream);
+    if (chunks == 16) return launch_tree_decode_shape<4, 16>(G, M, tables, stored, tree, g, step, d, stream);
+    if (chunks == 4) return launch_tree_decode_shape<4, 4>(G, M, tables, stored, tree, g, step, d, stream);
+    return launch_tree_decode_shape<4, 8>(G, M, tables, stored, tree, g, step, d, stream);
 }
 }  // namespace
 
@@ -2161,26 +2163,26 @@ int tree_decode_groups(int n, int L, int64_t d)
     return static_cast<int>((chunks + per - 1) / per);
 }
 
-hipError_t launch_tree_encode(const float *G, float *M, const DeviceTables &tables, int n, int L, int64_t d, hipStream_t stream)
+hipError_t launch_tree_encode(const float *G, float *M, const DeviceTables &tables, const NodeBits &stored, int n, int L, int64_t d, hipStream_t stream)
 {
-    return launch_tree(G, M, tables, n, L, d, stream);
+    return launch_tree(G, M, tables, stored, n, L, d, stream);
 }
 
-hipError_t launch_tree_encode(const float *G, float *M, const ArgumentTables &tables, int n, int L, int64_t d, hipStream_t stream)
+hipError_t launch_tree_encode(const float *G, float *M, const ArgumentTables &tables, const NodeBits &stored, int n, int L, int64_t d, hipStream_t stream)
 {
-    return launch_tree(G, M, tables, n, L, d, stream);
+    return launch_tree(G, M, tables, stored, n, L, d, stream);
 }
 
-hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, int n, int L, float *g, const GradientStep &step,
-                                     int64_t d, hipStream_t stream)
+hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, const NodeBits &stored, int n, int L, float *g,
+                                     const GradientStep &step, int64_t d, hipStream_t stream)
 {
-    return launch_tree_decode(G, M, tables, n, L, g, step, d, stream);
+    return launch_tree_decode(G, M, tables, stored, n, L, g, step, d, stream);
 }
 
-hipError_t launch_tree_encode_decode(const float *G, float *M, const ArgumentTables &tables, int n, int L, float *g, const GradientStep &step,
-                                     int64_t d, hipStream_t stream)
+hipError_t launch_tree_encode_decode(const float *G, float *M, const ArgumentTables &tables, const NodeBits &stored, int n, int L, float *g,
+                                     const GradientStep &step, int64_t d, hipStream_t stream)
 {
-    return launch_tree_decode(G, M, tables, n, L, g, step, d, stream);
+    return launch_tree_decode(G, M, tables, stored, n, L, g, step, d, stream);
 }
 
 int decode_groups(int64_t d)
@@ -2283,7 +2285,7 @@ __global__ void __launch_bounds__(256) program_kernel(ProgramTables out, Program
     for (int i = threadIdx.x; i < block.terms; i += 256) {
         const uint64_t t = block.word[block.coefs + i];
         out.slab[block.first + i] = static_cast<int32_t>(t & 4095);
-        out.row[block.first + i] = static_cast<int32_t>(t >> 12 & 4095);
+        out.row[block.first + i] = static_cast<int32_t>(t >> 12 & 4095) ^ -static_cast<int32_t>(t >> 52 & 1);      // ~row: not stored
         out.level[block.first + i] = static_cast<int32_t>(t >> 24 & 15);
         out.coef[block.first + i] = __longlong_as_double(static_cast<int64_t>(block.word[t >> 28 & 4095]));
         out.acoef[block.first + i] = __longlong_as_double(static_cast<int64_t>(block.word[t >> 40 & 4095]));
@@ -2319,10 +2321,11 @@ hipError_t launch_program(const ProgramTables &out, const ProgramTables &host, i
         };
         while (first + count < terms && coefs + count + 3 <= ProgramBlock::kWords) {     // room for a term and two new coefficients
             const int t = first + count;
-            if ((host.slab[t] | host.row[t]) >> 12 || host.level[t] >> 4) return hipErrorInvalidValue;
+            const int32_t row = host.row[t] < 0 ? ~host.row[t] : host.row[t];
+            if ((host.slab[t] | row) >> 12 || host.level[t] >> 4) return hipErrorInvalidValue;
             const uint64_t c = place(host.coef[t]), a = place(host.acoef[t]);
-            packed[count++] = static_cast<uint64_t>(host.slab[t]) | static_cast<uint64_t>(host.row[t]) << 12 |
-                              static_cast<uint64_t>(host.level[t]) << 24 | c << 28 | a << 40;
+            packed[count++] = static_cast<uint64_t>(host.slab[t]) | static_cast<uint64_t>(row) << 12 | static_cast<uint64_t>(host.level[t]) << 24 |
+                              c << 28 | a << 40 | static_cast<uint64_t>(host.row[t] < 0) << 52;
         }
         std::memcpy(block.word + coefs, packed, static_cast<size_t>(count) * 8);
         block.first = first;
