@@ -1460,7 +1460,8 @@ __device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, c
                                               const float *G, float *M, int64_t d, int64_t col, bool live)
 {
     const int TEAMS = tree.threads / B;
-    const int team = threadIdx.x / B, tl = threadIdx.x % B;
+    // 64 lanes: the team is a wavefront, and what it reads of the tables is the same for all lanes
+    const int team = B == 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / 64) : threadIdx.x / B, tl = threadIdx.x % B;
     const TreePlaces places{tree, sub};
     auto stores = [&](int node) { return (stored.word[node >> 5] >> (node & 31) & 1u) != 0; };
     for (int t = team; t < tree.total; t += TEAMS) {
@@ -2051,15 +2052,15 @@ TreeLevels tree_levels(int n, int L, bool whole)
 template <int VEC, int B> bool tree_fits(const TreeLevels &tree) { return TreeLds<VEC, B>::bytes(tree.total, tree.leaves) <= kTreeLdsBytes; }
 
 // Threads of a workgroup that has `nodes` nodes and B lanes for each: the more nodes have a team of their own the fewer fetches follow
-// one another, as long as all workgroups are on the chip at once (us of the kernel, 256 threads / more): (3,6), s = 2, 1 024 columns
-// 8.2 / 6.5 (704), 4 096 9.5 / 8.0, 6 500 10.9 / 10.7 (512) / 12.4 (704, two rounds), 16 384 13.5 / 18.9 (512, two rounds); (3,4) 6 500 6.9 /
-// 6.1 (384), 16 384 7.8 / 9.2; encode and decode together, (2,12), s = 2, 512 / 1 024: 12 288 columns 12.0 / 10.0, 24 576 14.1 / 16.8.
+// one another, as long as the workgroups that LDS leaves room for are on the chip at once (us of the kernel, 256 threads / more): (3,6), s = 2,
+// 1 024 columns 8.2 / 6.5 (704), 40 000, three workgroups per unit for their LDS, 28.0 / 24.6 (384); (3,4) 50 008, five, 10.6 / 12.3 (512);
+// encode and decode together, (2,12), s = 2, 512 / 1 024: 12 288 columns 12.0 / 10.0, 24 576, two per unit, 14.1 / 16.8.
 // Fewer threads where there are fewer nodes: (1,64) 16 384 columns 10.8 (256) / 7.5 (64).
-template <int B, typename TABLES> int tree_threads(int nodes, int groups, int least)
+template <int B, typename TABLES> int tree_threads(int nodes, int groups, size_t lds)
 {
-    constexpr int kUnits = 256, kWavefronts = std::is_same_v<TABLES, DeviceTables> ? 20 : 16;      // of a compute unit, by their registers
-    const int wanted = std::min(1024, (nodes * B + 63) / 64 * 64), fit = kWavefronts / ((groups + kUnits - 1) / kUnits) * 64;
-    return std::min(wanted, std::max(least, fit));
+    constexpr int kUnits = 256, kWavefronts = B == 64 || std::is_same_v<TABLES, DeviceTables> ? 20 : 16;      // of a compute unit, by their registers
+    const int resident = std::max(1, std::min((groups + kUnits - 1) / kUnits, static_cast<int>((size_t(160) << 10) / lds)));
+    return std::min({1024, (nodes * B + 63) / 64 * 64, std::max(256, kWavefronts / resident * 64)});
 }
 
 template <int VEC, int B, typename TABLES>
@@ -2067,7 +2068,7 @@ hipError_t launch_tree_shape(const float *G, float *M, const TABLES &tables, con
 {
     const int nq = static_cast<int>((d + VEC - 1) / VEC), groups = (nq + B - 1) / B;
     const size_t lds = TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves);
-    tree.threads = tree_threads<B, TABLES>(tree.total, groups * tree.n, 256);
+    tree.threads = tree_threads<B, TABLES>(tree.total, groups * tree.n, lds);
     tree_kernel<VEC, B><<<dim3(groups, tree.n), tree.threads, lds, stream>>>(G, M, tables, stored, tree, d, nq);
     return hipGetLastError();
 }
@@ -2077,9 +2078,11 @@ hipError_t launch_tree(const float *G, float *M, const TABLES &tables, const Nod
 {
     const TreeLevels tree = tree_levels(n, L, false);
     if (d < 4) return launch_tree_shape<1, 16>(G, M, tables, stored, tree, d, stream);
-    // 64 chunks: longer pieces of a slab.  Sub-trees of two levels have the workgroups for it from half as many columns on (us, 16 chunks / 64:
-    // (2,20), 16 385 columns 27.9 / 22.1, 32 768 45.0 / 35.2; (2,4) 16 385 7.7 / 7.8, 24 576 8.8 / 7.9; (3,4) 24 576 13.0 / 12.1, (3,6) 22.6 / 32.9)
-    if (d > (L == 2 ? kTreeNarrowColumns / 2 : kTreeNarrowColumns) && tree_fits<4, 64>(tree)) return launch_tree_shape<4, 64>(G, M, tables, stored, tree, d, stream);
+    // 64 chunks: the team is a wavefront, whose tables and base addresses are scalars, and pieces of a slab are four times as long.  Short
+    // vectors only where every node then has a wavefront (us, 16 chunks / 64: (4,2), 15 nodes, 300 columns 6.9 / 5.2, 16 384 7.2 / 5.7; (2,12), 13,
+    // 2 048 5.5 / 5.0, 12 288 9.8 / 8.4; (3,5), s = 1, 31 nodes, 1 024 6.3 / 7.0, 4 096 7.1 / 7.1, 12 288 9.9 / 8.1; (3,4), 21, 16 384 7.6 / 6.3;
+    // (2,17) 6 500 14.5 / 8.7; (1,64) 8 192 5.7 / 3.5, 32 768 14.5 / 6.9)
+    if ((tree.total <= 16 || d > 3072) && tree_fits<4, 64>(tree)) return launch_tree_shape<4, 64>(G, M, tables, stored, tree, d, stream);
     return launch_tree_shape<4, 16>(G, M, tables, stored, tree, d, stream);
 }
 
@@ -2089,7 +2092,7 @@ hipError_t launch_tree_decode_shape(const float *G, float *M, const TABLES &tabl
 {
     const int nq = static_cast<int>((d + VEC - 1) / VEC), groups = (nq + B - 1) / B;
     const size_t lds = TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves);
-    tree.threads = tree_threads<B, TABLES>(tree.total, groups, 512);
+    tree.threads = tree_threads<B, TABLES>(tree.total, groups, lds);
     tree_decode_kernel<VEC, B><<<groups, tree.threads, lds, stream>>>(G, M, tables, stored, tree, g, step, d, nq);
     return hipGetLastError();
 }
