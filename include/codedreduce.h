@@ -185,7 +185,7 @@ int cr_bind_workspace(cr_plan_t *plan, void *dev_ptr, size_t bytes, void *hip_st
  *   Stragglers write no message (their row of M keeps stale data); all other nodes do, also below a straggler.
  *   CR_E_UNDECODABLE, before anything is enqueued and with no state change, if any group has more than s stragglers.
  *   On trees of at most 448 workers whose level-1 sub-trees' messages fit a workgroup's LDS (all but some of more than six levels) and with
- *   vectors of up to 32768 columns, 40000 to 81920 depending on the tree, all it enqueues is one kernel launch, with what the mask
+ *   vectors of up to 32768 columns, 40000 to 163840 depending on the tree, all it enqueues is one kernel launch, with what the mask
  *   decides as kernel arguments; else the mask's encode program travels in a copy from pinned memory first.  (The tree's tables are read
  *   from the workspace with stage 1's slabs, from 1 MB that the library keeps for bound plans with the caller's; while that is all in
  *   use they travel with the call, in a copy where they do not fit the arguments.)
@@ -232,7 +232,7 @@ int cr_aggregate_run(cr_plan_t *plan, const float *G_dev, int64_t G_step_stride,
  * itself (CR_STATIC_SCRATCH_BYTES; each GPU the library runs on holds one until the process ends).  The plan needs no workspace.
  * The call allocates and frees nothing on the device or in pinned memory and records no copy: what the kernels need reaches the device
  * as kernel arguments, so all it enqueues on hip_stream is kernel launches: one for encode and decode where the tree's tables and the
- * mask's coefficients fit the arguments and d <= 32768, two up to 81920 columns depending on the tree, else a few small ones that write
+ * mask's coefficients fit the arguments and d <= 32768, two up to 163840 columns depending on the tree, else a few small ones that write
  * the program out, encode and decode.  (Trees of up to some 150 workers fit; whether one near that border does depends on how many
  * different coefficients the mask calls for.)
  *   plan        any plan; its model is not consulted (no stage 1 runs)

@@ -1366,8 +1366,9 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
     bool sent = false;
     for (int t0 = 0; t0 < steps; t0 += kProgramSlots) {
         const int count = std::min(kProgramSlots, steps - t0);
-        // one mask: the nodes side by side need no copy of a program
-        const bool alone = cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kCopy) && count == 1;
+        // one mask: the nodes side by side need no copy of a program; beyond 81 920 columns one launch for everything makes up for it
+        const bool alone = count == 1 && cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kCopy) &&
+                           (p->d <= 81920 || in_order || !cr::encode_in_steps(p->shape, p->d, 1));
         const bool in_steps = !in_order && !alone && cr::encode_in_steps(p->shape, p->d, count);
         const bool side_by_side = alone || cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kBatch);
         auto stores = [&](int i) { return Stores{among_messages ? Stores::kAll : t0 + i, !in_steps && !together}; };

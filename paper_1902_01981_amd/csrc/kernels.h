@@ -192,7 +192,7 @@ hipError_t launch_encode_steps(const float *G, int64_t G_stride, float *M, const
                                float *g, int64_t g_stride, int64_t d, hipStream_t stream);
 // The encode of trees of at most NodeCoefs::kNodes nodes and vectors of at most kTreeColumns columns (tree_side_by_side): a workgroup
 // per level-1 sub-tree and 16 or 64 chunks of columns.  The tables travel with the launch or are on the device.
-constexpr int64_t kTreeColumns = 81920, kTreeNarrowColumns = 32768;
+constexpr int64_t kTreeColumns = 163840, kTreeNarrowColumns = 32768;
 // What the encode would take instead: a copy of one program, a program written out by launches, a program of which 16 share a copy.
 enum class Otherwise { kCopy, kLaunches, kBatch };
 bool tree_side_by_side(const TreeShape &tree, int64_t d, Otherwise otherwise);

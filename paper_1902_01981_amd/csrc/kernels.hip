@@ -1467,6 +1467,7 @@ __device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, c
     for (int t = team; t < tree.total; t += TEAMS) {
         const int node = places.node(t);
         const double a = view.coef_of(node);
+        const bool put_down = stores(node);
         const int begin = view.begin(node), end = view.begin(node + 1);
         if (tl == 0) lds.coef[t] = a;
         if (!sends(a)) continue;
@@ -1478,7 +1479,7 @@ __device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, c
             float out[VEC];
 #pragma unroll
             for (int v = 0; v < VEC; ++v) out[v] = static_cast<float>(acc[v]);
-            if (live && stores(node)) store_row<VEC>(M + static_cast<int64_t>(node) * d + col, out);
+            if (live && put_down) store_row<VEC>(M + static_cast<int64_t>(node) * d + col, out);
             lds.put_message(t, tl, out);
         } else {
 #pragma unroll
@@ -1490,6 +1491,8 @@ __device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, c
         const int first = tree.first[l - 1], end = l > 1 ? tree.first[l - 2] : tree.total;
         for (int t = first + team; t < end; t += TEAMS) {
             if (!sends(lds.coef[t])) continue;
+            const int node = places.node(t);
+            const bool put_down = stores(node);
             double pend[VEC];
 #pragma unroll
             for (int v = 0; v < VEC; ++v) pend[v] = 0.0;
@@ -1497,8 +1500,7 @@ __device__ __forceinline__ void tree_messages(const TreeLevels &tree, int sub, c
             float out[VEC];
 #pragma unroll
             for (int v = 0; v < VEC; ++v) out[v] = static_cast<float>(lds.own[((t - tree.leaves) * VEC + v) * B + tl] + pend[v]);
-            const int node = places.node(t);
-            if (live && stores(node)) store_row<VEC>(M + static_cast<int64_t>(node) * d + col, out);
+            if (live && put_down) store_row<VEC>(M + static_cast<int64_t>(node) * d + col, out);
             lds.put_message(t, tl, out);
         }
     }
@@ -2056,11 +2058,12 @@ template <int VEC, int B> bool tree_fits(const TreeLevels &tree) { return TreeLd
 // 1 024 columns 8.2 / 6.5 (704), 40 000, three workgroups per unit for their LDS, 28.0 / 24.6 (384); (3,4) 50 008, five, 10.6 / 12.3 (512);
 // encode and decode together, (2,12), s = 2, 512 / 1 024: 12 288 columns 12.0 / 10.0, 24 576, two per unit, 14.1 / 16.8.
 // Fewer threads where there are fewer nodes: (1,64) 16 384 columns 10.8 (256) / 7.5 (64).
-template <int B, typename TABLES> int tree_threads(int nodes, int groups, size_t lds)
+template <int B> int tree_threads(int nodes, int groups, size_t lds)
 {
-    constexpr int kUnits = 256, kWavefronts = B == 64 || std::is_same_v<TABLES, DeviceTables> ? 20 : 16;      // of a compute unit, by their registers
+    constexpr int kUnits = 256, kWavefronts = B == 64 ? 20 : 16;      // of a compute unit, by their registers
     const int resident = std::max(1, std::min((groups + kUnits - 1) / kUnits, static_cast<int>((size_t(160) << 10) / lds)));
-    return std::min({1024, (nodes * B + 63) / 64 * 64, std::max(256, kWavefronts / resident * 64)});
+    const int teams = std::min(1024, std::max(256, kWavefronts / resident * 64)) / B, rounds = (nodes + teams - 1) / teams;
+    return ((nodes + rounds - 1) / rounds * B + 63) / 64 * 64;         // no more than it takes for as few rounds
 }
 
 template <int VEC, int B, typename TABLES>
@@ -2068,7 +2071,7 @@ hipError_t launch_tree_shape(const float *G, float *M, const TABLES &tables, con
 {
     const int nq = static_cast<int>((d + VEC - 1) / VEC), groups = (nq + B - 1) / B;
     const size_t lds = TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves);
-    tree.threads = tree_threads<B, TABLES>(tree.total, groups * tree.n, lds);
+    tree.threads = tree_threads<B>(tree.total, groups * tree.n, lds);
     tree_kernel<VEC, B><<<dim3(groups, tree.n), tree.threads, lds, stream>>>(G, M, tables, stored, tree, d, nq);
     return hipGetLastError();
 }
@@ -2092,7 +2095,7 @@ hipError_t launch_tree_decode_shape(const float *G, float *M, const TABLES &tabl
 {
     const int nq = static_cast<int>((d + VEC - 1) / VEC), groups = (nq + B - 1) / B;
     const size_t lds = TABLES::kLdsBytes + TreeLds<VEC, B>::bytes(tree.total, tree.leaves);
-    tree.threads = tree_threads<B, TABLES>(tree.total, groups, lds);
+    tree.threads = tree_threads<B>(tree.total, groups, lds);
     tree_decode_kernel<VEC, B><<<groups, tree.threads, lds, stream>>>(G, M, tables, stored, tree, g, step, d, nq);
     return hipGetLastError();
 }
@@ -2122,30 +2125,39 @@ hipError_t launch_tree_decode(const float *G, float *M, const TABLES &tables, co
 // Up to 32 768 columns the nodes side by side are ahead of a walk on every tree.  Beyond, it depends on what the walk's program costs, on
 // the wavefronts that the LDS of 64 chunks leaves in flight (32 KB: five workgroups per compute unit), and on whether slabs and
 // messages in use leave room in the last-level cache, past which the walk reads.  us of a whole iteration on few rows, walk / side by side:
-//   a copy each      32 KB        (2,12), s = 2, 40 001 columns 75.4 / 53.9, 81 920 (164 MB in use) 111 / 104; (2,17) 40 001 (141 MB) 169 / 159,
-//                                 57 344 (202 MB) 222 / 238; (2,12), s = 5, 65 536 (160 MB) 125 / 123, 73 728 (180 MB) 142 / 145
-//                    60 KB        (3,6), s = 2, 40 001 117 / 104, 49 152 128 / 139; (3,5), s = 1, 40 001 (64 MB) 82.4 / 84.7, 57 344 (92 MB)
-//                                 96 / 102; s = 4, 49 152 (37 MB) 77.9 / 67.1, 65 536 (49 MB) 103 / 95
-//                    more         (4,3) 45 001 69.0 / 65.3, 57 344 71.0 / 75.2; (6,2) 40 001 55.7 / 55.6, 65 536 70.5 / 73.4; (3,7) 36 001
-//                                 (146 MB) 190 / 204
-//   16 in a copy     one level    (1,64), 40 001 columns 46.5 / 42.8, 81 920 64.2 / 59.1; (1,10) 28.7 / 28.4, 32.8 / 33.7
-//                    8 to 16      (2,8), s = 2, 40 001 54.8 / 52.0, 49 152 55.9 / 57.3; (2,12), s = 5, 70.3 / 64.8, 79.6 / 80.5
-//                    else         (2,4) 40 001 27.9 / 29.3; (4,2) 26.8 / 29.7; (2,17) 152 / 159; (3,4) 41.2 / 41.3; (3,6) 100 / 105
-//   launches         32 KB        (2,12), s = 2, 40 001 22.7 / 22.3, (1,10) 14.5 / 9.6; beside the arguments' copy (3,4), 31 KB, 65 536 16.9 / 15.7,
-//                                 81 920 19.7 / 22.3, (4,2), 29 KB, 14.8 / 13.1
-//                    more         40 001 (3,5), s = 4, 16.0 / 19.4, (5,2) 18.1 / 19.5
+//   a copy each      32 KB        (2,12), s = 2, 40 001 columns 75.1 / 53.7, 98 304 (188 MB in use) 136 / 129, 117 706 (225 MB) 172 / 173; s = 5,
+//                                 81 920 (190 MB) 139 / 129; (3,4) 65 536 53.4 / 49.4, 160 001 (106 MB) 101 / 95; (2,8) 117 706 (108 MB)
+//                                 113 / 105, 160 001 (146 MB) 149 / 155; (1,64) 98 304 75.3 / 47.4
+//                    60 KB        (3,6), s = 2, 49 152 (127 MB) 118 / 102, 65 536 (169 MB) 147 / 150; (3,5), s = 1, 73 728 (112 MB) 108 / 106, 98 304
+//                                 (150 MB) 137 / 142; s = 4, 65 536 92.1 / 79.1
+//                    more         (5,2) 49 152 44.2 / 39.0, 57 344 46.8 / 46.6; (4,3) 40 001 65.1 / 61.9, 57 344 72.5 / 72.6
+//   16 in a copy     21 KB        (2,12), s = 2, 73 728 (141 MB) 86.3 / 85.5, 98 304 (188 MB) 111 / 119; s = 5, 57 344 (133 MB) 84.4 / 83.5, 65 536 (152 MB)
+//                                 95.9 / 103; (2,4) 49 152 26.0 / 23.4, 160 001 47.8 / 46.9; (1,10) 65 536 28.4 / 25.1; (2,17) 40 001 (134 MB) 123 / 121
+//                    32 KB        (3,4) 40 001 42.1 / 38.6, 81 920 57.3 / 57.3, 98 304 63.5 / 66.5; (4,2) 73 728 31.3 / 30.6
+//                    more         (3,6) 40 001 85.2 / 83.1, 57 344 107 / 119; (3,5), s = 4, 40 001 55.7 / 55.7, 65 536 74.6 / 79.1; (5,2) 40 001 41.9 / 37.6;
+//                                 (4,3) 59.9 / 60.4; (6,2) 54.8 / 55.6
+//   launches         10 KB        (2,4) 40 001 20.6 / 16.0, 160 001 18.9 / 15.5; (1,64) 160 001 48.4 / 40.6
+//                    32 KB        (2,8) 65 536 21.1 / 17.0, 81 920 19.4 / 20.2; (2,12), s = 5, 40 001 26.2 / 23.3, 81 920 39.0 / 38.4; beside the
+//                                 arguments' copy (3,4), 31 KB, 65 536 20.0 / 16.7, 73 728 19.4 / 19.9
+//                    60 KB        (3,5), s = 4, 40 001 19.6 / 17.3, 65 536 19.2 / 20.0; s = 1, 40 001 25.1 / 23.5, 57 344 24.1 / 27.2
+//                    more         (4,3) 33 001 21.7 / 24.2
 bool tree_side_by_side(const TreeShape &tree, int64_t d, Otherwise otherwise)
 {
     const TreeLevels sub = tree.nodes <= NodeCoefs::kNodes ? tree_levels(tree.n, tree.L, false) : TreeLevels();
     if (tree.nodes > NodeCoefs::kNodes || d > kTreeColumns || !tree_fits<4, 16>(sub)) return false;
     if (d <= kTreeNarrowColumns) return true;
-    if (otherwise == Otherwise::kBatch) return tree.L == 1 || (tree.L == 2 && tree.n >= 8 && tree.n <= 16 && d <= 45056);
-    const size_t lds = TreeLds<4, 64>::bytes(sub.total, sub.leaves);
-    if (otherwise == Otherwise::kLaunches) return lds <= size_t(d <= 65536 ? 32 : 30) << 10;
-    const int64_t in_use = (tree.slabs + tree.nodes) * d * 4 / tree.n * (tree.n - tree.s);
-    if (lds <= size_t(32) << 10) return in_use <= int64_t(164) << 20;
-    if (in_use > int64_t(140) << 20) return false;
-    return tree_fits<4, 64>(sub) ? d <= 40960 || in_use <= int64_t(64) << 20 : d <= 49152;
+    const size_t lds = TreeLds<4, 64>::bytes(sub.total, sub.leaves), kb = size_t(1) << 10;
+    const int64_t in_use = (tree.slabs + tree.nodes) * d * 4 / tree.n * (tree.n - tree.s), mb = int64_t(1) << 20;
+    switch (otherwise) {
+    case Otherwise::kBatch:
+        return lds <= 32 * kb ? in_use <= 141 * mb && (lds <= 21 * kb || d <= 81920) : d <= 40960;
+    case Otherwise::kLaunches:
+        return lds <= 10 * kb || (lds <= 30 * kb && d <= 81920) || (lds <= 32 * kb && d <= 65536) || (tree_fits<4, 64>(sub) && d <= 40960);
+    case Otherwise::kCopy:
+        if (lds <= 32 * kb) return in_use <= 190 * mb && (d <= 131072 || in_use <= 120 * mb);
+        return tree_fits<4, 64>(sub) ? in_use <= 130 * mb : d <= 49152;
+    }
+    return false;
 }
 
 // From 8 192 columns on, where the whole tree's messages do not fit LDS for 16 chunks, the launch has twice the workgroups, of eight chunks,

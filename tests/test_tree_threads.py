@@ -6,9 +6,11 @@ import pytest
 import paper_1902_01981_amd as cr
 
 # four chunks per workgroup up to 2 048 columns (and not on small trees), one, two and three workgroups per compute unit (16 chunks: 256 * 64
-# columns each), fewer threads than 64, more nodes than teams
+# columns each), fewer threads than 64, more nodes than teams, 64 chunks from 3 073 columns on or where every node has a wavefront, the
+# lines between nodes side by side and a walk
 CASES = [(2, 12, 2, d) for d in (4, 5, 2_047, 2_048, 2_049, 16_384, 16_385, 32_767)] + [(3, 6, 2, d) for d in (9, 2_048, 2_053, 4_097)] + \
-        [(2, 3, 1, 2_047), (1, 64, 1, 1_023), (1, 2, 1, 12), (3, 5, 1, 1_031), (5, 2, 1, 6_501), (2, 17, 1, 2_048)]
+        [(3, 4, 1, 163_840), (3, 4, 1, 163_841), (2, 8, 2, 131_073), (1, 10, 4, 163_843), (3, 6, 2, 40_961), (4, 3, 1, 49_153), (2, 12, 2, 98_305)] + \
+        [(3, 5, 1, 3_072), (3, 5, 1, 3_073), (4, 2, 1, 300), (2, 3, 1, 2_047), (1, 64, 1, 1_023), (1, 2, 1, 12), (3, 5, 1, 1_031), (5, 2, 1, 6_501), (2, 17, 1, 2_048)]
 
 
 @pytest.mark.gpu
