@@ -135,6 +135,7 @@ struct cr_plan_s {
     uint64_t *d_crew_slots = nullptr;              // `crew`: what its kernel exchanges in
     uint32_t *d_crew_state = nullptr;
     int num_sums = 0;
+    int64_t rows_summed = 0;                       // by all of them
     uint32_t *d_placement = nullptr;               // kPlacementSlots words: where the workgroups of a probe launch ran
     char *d_program = nullptr;                     // kProgramSlots encode programs
     int32_t *d_node_begin = nullptr;               // slabs of every node, their coefficients: what the tree kernels read
@@ -886,6 +887,8 @@ try {
         put(p->at_team_piece_begin, p->split.team_piece_begin);
     }
     p->num_sums = static_cast<int>(sums.size());
+    p->rows_summed = 0;
+    for (const cr::DevSum &sum : sums) p->rows_summed += sum.row_end - sum.row_begin;
     put(p->at_sums, sums);
     put(p->at_dst, dst);
     put(p->at_node_begin, p->node_slab_begin);
@@ -946,7 +949,7 @@ int cr_partial_grads(cr_plan_t *p, const void *X, const float *y, const float *w
     }
     if (p->num_sums > 0) {
         LaunchTimer t(p, CR_K_REDUCE_PIECES, ((p->rows_once ? p->work.partials : P) + S) * p->d * 4);
-        CR_HIP(cr::launch_sum_rows(p->d_G, p->d_sums, p->num_sums, p->d_dst, p->d, p->stream));
+        CR_HIP(cr::launch_sum_rows(p->d_G, p->d_sums, p->num_sums, p->rows_summed, p->d_dst, p->d, p->stream));
         t.done();
     }
     p->G_src = p->d_G;

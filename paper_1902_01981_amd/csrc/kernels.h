@@ -183,7 +183,8 @@ constexpr int kWideColumnChunks = 256;
 hipError_t launch_wide_once(int x_dtype, const void *X, const float *y, const float *w, float *residuals, int64_t m, const DevRun *parts, int num_parts,
                             const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int logistic, int64_t cached_from, int units,
                             hipStream_t stream);
-hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, const int32_t *dst, int64_t d, hipStream_t stream);
+// summed: rows that the sums add up, all together
+hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, int64_t summed, const int32_t *dst, int64_t d, hipStream_t stream);
 hipError_t launch_encode(const float *G, float *M, const EncProgram &prog, int num_sub, int L, int64_t d, hipStream_t stream);
 // Encode and decode of `steps` masks, one after the other, in one launch (where encode_in_steps says so); the programs lie prog_stride
 // bytes apart.

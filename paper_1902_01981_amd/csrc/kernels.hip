@@ -1187,6 +1187,37 @@ sum_rows_kernel(float *__restrict__ rows, const DevSum *__restrict__ sums, const
     for (int j = s->dst_begin + wave; j < s->dst_end; j += WAVES) store_row<VEC>(rows + static_cast<int64_t>(table(dst)[j]) * d + col, out);
 }
 
+// The same for many sums of few rows (see launch_sum_rows): a wavefront per 64 chunks of columns takes all rows of a sum, in their order, where
+// the workgroup above would have wavefronts without a row and eight times the workgroups.
+__global__ void __launch_bounds__(256)
+sum_few_rows_kernel(float *__restrict__ rows, const DevSum *__restrict__ sums, const int32_t *__restrict__ dst, int64_t d, int nq)
+{
+    constexpr int VEC = 4, U = 8;
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    const int64_t col = chunk_offset<VEC>(min(q, nq - 1), nq, static_cast<int>(d));
+    const table_t<DevSum> s = table(sums) + blockIdx.y;
+    const int row_begin = s->row_begin, row_end = s->row_end, dst_begin = s->dst_begin, dst_end = s->dst_end;
+    double acc[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
+    for (int j0 = row_begin; j0 < row_end; j0 += U) {
+        float xv[U][VEC];
+#pragma unroll
+        for (int u = 0; u < U; ++u) load_row<VEC>(rows + static_cast<int64_t>(min(j0 + u, row_end - 1)) * d + col, xv[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (j0 + u < row_end) {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[v] += static_cast<double>(xv[u][v]);
+            }
+    }
+    if (q >= nq) return;
+    float out[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) out[v] = static_cast<float>(acc[v]);
+    for (int j = dst_begin; j < dst_end; ++j) store_row<VEC>(rows + static_cast<int64_t>(table(dst)[j]) * d + col, out);
+}
+
 // ---- encode ---------------------------------------------------------------------------------------------------------
 // One thread owns C chunks of VEC columns and runs the whole sub-tree of one level-1 node for them: a post-order list of terms
 // (own += coef * G[slab]) in which the last term of a node finishes it: message = own + pending[level], stored (rounded to fp32,
@@ -1946,12 +1977,22 @@ hipError_t launch_wide_once(int x_dtype, const void *X, const float *y, const fl
     return wide_once<1, 8>(X, y, w, residuals, m, parts, num_parts, runs, dst, rows, d, logistic, cached_from, units, stream);
 }
 
-hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, const int32_t *dst, int64_t d, hipStream_t stream)
+hipError_t launch_sum_rows(float *rows, const DevSum *sums, int num_sums, int64_t summed, const int32_t *dst, int64_t d, hipStream_t stream)
 {
     constexpr int kMaxGridY = 65535;
     const int nq = static_cast<int>(d >= 4 ? (d + 3) / 4 : d);
+    // A wavefront for all rows of a sum where there are wavefronts enough to make up for the longer chain: 48 times the rows of a sum.  us, a
+    // workgroup / a wavefront, by wavefronts per row of a sum: (2,12), s = 1, 5 001 columns (390) 9.9 / 7.8, 50 008 bf16 33.6 / 17.4; (3,6), s = 2,
+    // 20 001 31.7 / 21.3; (2,4) 50 008 bf16 (700) 11.2 / 8.0; (3,4) 20 001 (190) 15.0 / 12.4, 6 500 (62) 8.4 / 8.3, 5 001 (48) 7.9 / 8.2; (2,4) 20 001
+    // (34) 10.6 / 12.0, 5 001 (9) 7.0 / 10.0; (3,6) 1 024 (17) 7.5 / 10.3; (1,10), s = 4, 20 001 (6) 9.5 / 9.9
+    const int64_t wavefronts = static_cast<int64_t>((nq + 63) / 64) * num_sums;
+    const bool few = d >= 4 && num_sums > 0 && wavefronts >= 256 && wavefronts * num_sums > 48 * summed;
     for (int lo = 0; lo < num_sums; lo += kMaxGridY) {
         const dim3 grid((nq + 63) / 64, num_sums - lo < kMaxGridY ? num_sums - lo : kMaxGridY);
+        if (few) {
+            sum_few_rows_kernel<<<dim3((nq + 255) / 256, grid.y), 256, 0, stream>>>(rows, sums + lo, dst, d, nq);
+            continue;
+        }
         if (d >= 4) sum_rows_kernel<4><<<grid, 512, 0, stream>>>(rows, sums + lo, dst, d, nq);
         else sum_rows_kernel<1><<<grid, 512, 0, stream>>>(rows, sums + lo, dst, d, nq);
     }

@@ -93,7 +93,7 @@ def test_vectors_among_the_messages():
     n, d, steps = 4, 40, 3
     plan = cr.cr_plan_ex(1, n, 1, 8, d, model=cr.CR_AGGREGATE_ONLY)
     ws = cr.Workspace(plan)
-    G = torch.randn(steps, cr.cr_plan_info(plan).num_slabs * d, device="cuda")
+    G = torch.randn(steps, cr.cr_plan_info(plan).num_slabs * d, generator=torch.Generator(device="cuda").manual_seed(d), device="cuda")
     masks = np.zeros((steps, n), np.uint8)
     masks[0, 0] = masks[1, 1] = masks[2, 2] = 1
     M, g = ws.messages(), torch.empty(d, device="cuda")
