@@ -1388,13 +1388,14 @@ encode_steps_kernel(const float *__restrict__ G, int64_t G_stride, float *__rest
 __device__ __forceinline__ bool sends(double a) { return __double_as_longlong(a) != kStraggler; }
 
 // A workgroup's view of the tables: read in place where they are on the device ...
-struct DeviceView {
-    const DeviceTables &t;
+template <typename TABLES> struct DeviceView {
+    const TABLES &t;
     __device__ __forceinline__ double coef_of(int node) const { return t.coefs.a[node]; }
     __device__ __forceinline__ int begin(int node) const { return t.node_begin[node]; }
     __device__ __forceinline__ double slab_coef_of(int s) const { return t.slab_coef[s]; }
 };
-__device__ __forceinline__ DeviceView view_tables(const DeviceTables &t, int, char *) { return {t}; }
+__device__ __forceinline__ DeviceView<DeviceTables> view_tables(const DeviceTables &t, int, char *) { return {t}; }
+__device__ __forceinline__ DeviceView<SmallDeviceTables> view_tables(const SmallDeviceTables &t, int, char *) { return {t}; }
 // ... and copied to LDS first where they are arguments, since a coefficient is two dependent fetches away.
 struct ArgumentView {
     const double *value;
@@ -1403,7 +1404,7 @@ struct ArgumentView {
     __device__ __forceinline__ int begin(int node) const { return first[node]; }
     __device__ __forceinline__ double slab_coef_of(int s) const { return value[slab[s]]; }
 };
-__device__ __forceinline__ ArgumentView view_tables(const ArgumentTables &t, int threads, char *lds)
+template <typename TABLES> __device__ __forceinline__ ArgumentView view_arguments(const TABLES &t, int threads, char *lds)
 {
     uint64_t *copy = reinterpret_cast<uint64_t *>(lds);
     for (int i = threadIdx.x; i < t.used; i += threads) copy[i] = t.word[i];
@@ -1411,6 +1412,8 @@ __device__ __forceinline__ ArgumentView view_tables(const ArgumentTables &t, int
     const uint16_t *half = reinterpret_cast<const uint16_t *>(lds);
     return {reinterpret_cast<const double *>(lds), half + t.at_begin, half + t.at_coef, half + t.at_slab};
 }
+__device__ __forceinline__ ArgumentView view_tables(const ArgumentTables &t, int threads, char *lds) { return view_arguments(t, threads, lds); }
+__device__ __forceinline__ ArgumentView view_tables(const SmallArgumentTables &t, int threads, char *lds) { return view_arguments(t, threads, lds); }
 
 // The places of a workgroup's nodes, leaves first, then level by level up; sub: which level-1 sub-tree (0 where it has them all).
 struct TreePlaces {
@@ -2219,26 +2222,50 @@ int tree_decode_groups(int n, int L, int64_t d)
     return static_cast<int>((chunks + per - 1) / per);
 }
 
+namespace {
+// f(tables), with as short an argument as they fit
+template <typename F> hipError_t with_short(const DeviceTables &tables, int nodes, F f)
+{
+    if (nodes > SmallDeviceTables::kNodes) return f(tables);
+    SmallDeviceTables small = {tables.node_begin, tables.slab_coef, {}};
+    std::copy(tables.coefs.a, tables.coefs.a + nodes, small.coefs.a);
+    return f(small);
+}
+template <typename F> hipError_t with_short(const ArgumentTables &tables, int, F f)
+{
+    if (tables.used > SmallArgumentTables::kWords) return f(tables);
+    SmallArgumentTables small = {tables.at_begin, tables.at_coef, tables.at_slab, tables.used, {}};
+    std::copy(tables.word, tables.word + tables.used, small.word);
+    return f(small);
+}
+int nodes_of(int n, int L)
+{
+    int nodes = 0;
+    for (int l = 0; l < L; ++l) nodes = (nodes + 1) * n;
+    return nodes;
+}
+}  // namespace
+
 hipError_t launch_tree_encode(const float *G, float *M, const DeviceTables &tables, const NodeBits &stored, int n, int L, int64_t d, hipStream_t stream)
 {
-    return launch_tree(G, M, tables, stored, n, L, d, stream);
+    return with_short(tables, nodes_of(n, L), [&](const auto &t) { return launch_tree(G, M, t, stored, n, L, d, stream); });
 }
 
 hipError_t launch_tree_encode(const float *G, float *M, const ArgumentTables &tables, const NodeBits &stored, int n, int L, int64_t d, hipStream_t stream)
 {
-    return launch_tree(G, M, tables, stored, n, L, d, stream);
+    return with_short(tables, nodes_of(n, L), [&](const auto &t) { return launch_tree(G, M, t, stored, n, L, d, stream); });
 }
 
 hipError_t launch_tree_encode_decode(const float *G, float *M, const DeviceTables &tables, const NodeBits &stored, int n, int L, float *g,
                                      const GradientStep &step, int64_t d, hipStream_t stream)
 {
-    return launch_tree_decode(G, M, tables, stored, n, L, g, step, d, stream);
+    return with_short(tables, nodes_of(n, L), [&](const auto &t) { return launch_tree_decode(G, M, t, stored, n, L, g, step, d, stream); });
 }
 
 hipError_t launch_tree_encode_decode(const float *G, float *M, const ArgumentTables &tables, const NodeBits &stored, int n, int L, float *g,
                                      const GradientStep &step, int64_t d, hipStream_t stream)
 {
-    return launch_tree_decode(G, M, tables, stored, n, L, g, step, d, stream);
+    return with_short(tables, nodes_of(n, L), [&](const auto &t) { return launch_tree_decode(G, M, t, stored, n, L, g, step, d, stream); });
 }
 
 int decode_groups(int64_t d)
