@@ -73,3 +73,44 @@ def test_rows_that_are_not_finite_stay_with_their_slabs(bf16):
     assert finite == [True, False, True]
     del ws
     cr.cr_plan_destroy(plan)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,bf16", [(50_001, 0), (60_000, 0), (80_003, 0), (57_347, 1), (50_008, 1), (172_032, 1)])
+@pytest.mark.parametrize("patience", [None, 0])
+def test_infinities_in_the_last_chunk_of_a_slice(d, bf16, patience):
+    """sigmoid(+-inf) is 0 or 1, so that an infinite entry reaches its own column only, wherever the columns are cut into slices: an entry in
+    the last chunk of every slice that 2 to 16 workgroups can have, first and last column of the chunk.  The infinite products of a row have one
+    sign.  Fewer than 80 rows of these widths are always shared."""
+    import torch
+
+    vec = 8 if bf16 else 4
+    nq = (d + vec - 1) // vec
+    cols = sorted({c for members in range(2, 17) for j in range(1, members + 1) for q in [nq * j // members - 1]
+                   for c in (min(q * vec, d - vec), min(q * vec, d - vec) + vec - 1, min(q * vec + vec - 1, d - 1))})
+    m = 79
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    X = torch.randn(m, d, generator=gen, device="cuda").to(torch.bfloat16 if bf16 else torch.float32)
+    w = torch.randn(d, generator=gen, device="cuda") / d ** 0.5
+    y = torch.full((m,), 0.25, device="cuda")
+    for i, c in enumerate(cols):
+        X[i % m, c] = torch.copysign(torch.tensor(float("inf")), w[c].cpu() * (1 if i % m % 3 else -1))
+    plan = cr.cr_plan_ex(1, 3, 1, m, d, model=cr.CR_LOGISTIC, x_dtype=bf16)
+    if patience is not None:
+        assert cr.load_library().cr_testing_patience(ctypes.c_void_p(plan), patience) == 0
+    ws = cr.Workspace(plan)
+    cr.cr_partial_grads(plan, X, y, w)
+    cr.cr_synchronize(plan)
+    rb, re_, _, _ = cr.cr_plan_get_segments(plan)
+    for q in range(len(rb)):
+        lo, hi = int(rb[q]), int(re_[q])
+        z = X[lo:hi].double() @ w.double()
+        assert not bool(torch.isnan(z).any())
+        res = torch.sigmoid(z) - y[lo:hi].double()
+        got = ws.slab_grads()[q].double()
+        whole = torch.isfinite(X[lo:hi]).all(0)
+        assert torch.equal(torch.isfinite(got), whole)
+        ref = X[lo:hi].double().nan_to_num(posinf=0.0, neginf=0.0).T @ res
+        assert float(((got - ref)[whole]).abs().max() / ref[whole].pow(2).mean().sqrt()) <= 3e-6
+    del ws
+    cr.cr_plan_destroy(plan)
