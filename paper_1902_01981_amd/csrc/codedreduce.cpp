@@ -361,7 +361,12 @@ void make_wide_once(cr_plan_t *p, int64_t rows_per_run)
     cr::CrewVariant crew;
     if (!cr::select_once_wide(p->x_dtype, p->d) && cr::select_crew(p->x_dtype, p->d, p->units, &crew) && crew_pays(p, crew)) {
         p->crew = std::make_unique<cr::CrewVariant>(crew);
-        return cr::once_equal_parts(p->slabs, p->m, crew_parts(p, crew), rows_per_run, p->work, kWideCopies);
+        cr::once_equal_parts(p->slabs, p->m, crew_parts(p, crew), rows_per_run, p->work, kWideCopies);
+        int64_t longest = 0;
+        for (size_t b = 0; b + 1 < p->work.part_run_begin.size(); ++b)
+            longest = std::max(longest, p->work.runs[p->work.part_run_begin[b + 1] - 1].row_end - p->work.runs[p->work.part_run_begin[b]].row_begin);
+        p->crew->ring_steps = cr::crew_ring_steps(crew, longest);
+        return;
     }
     cr::once_equal_parts(p->slabs, p->m, wide_two_pass_parts(p), rows_per_run, p->work);
 }

@@ -169,12 +169,14 @@ hipError_t launch_rows_once(const OnceVariant &v, const void *X, const float *y,
 struct CrewVariant {
     int xd, vec, k, rows_per_step;
     int members;                     // workgroups per row
+    int ring_steps;                  // steps of a part whose slots are kept: a power of two
     const void *fn[2];               // plain loads, loads with the non-temporal hint
 };
 constexpr int kCrewMembers = 16;     // at most
 constexpr int kCrewThreads = 448;    // that hold a member's slice of a row
-constexpr int kCrewPatience = 64;    // polls for the others' part of a dot product, some 0.7 us each, before it is worked out again
+constexpr int kCrewPatience = 64;    // polls for the others' part of a dot product, some 0.7 us each, before it is worked out again (8 to 64: the same)
 bool select_crew(int x_dtype, int64_t d, int units, CrewVariant *v);       // units: compute units of the device
+int crew_ring_steps(const CrewVariant &v, int64_t longest_part);           // rows
 int64_t crew_exchange_words(const CrewVariant &v);
 hipError_t launch_rows_once_crew(const CrewVariant &v, const void *X, const float *y, const float *w, const DevRun *parts, int num_parts,
                                  const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int logistic, bool stream_past_caches,

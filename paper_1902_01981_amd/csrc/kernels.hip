@@ -706,7 +706,11 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
 // has no rows of its own to wait for, so the exchange (about 1 us) passes behind the loads and the arithmetic of the other seven.
 // The members of a crew are 8 workgroup ids apart: on one die where workgroups are dealt to the dies in turn, which is worth a shorter
 // exchange and nothing else.  No member depends on another one running: what has not arrived after `patience` polls a member's eighth
-// wavefront works out itself, from the rest of the row, in the same order (the same bits), and from then on it looks once per step only.
+// wavefront works out itself, from the rest of the row, in the same order (the same bits), and puts it in the other's slot, where the rest
+// of the crew finds it: each member begins with another row.  It waits again once a step's answers are all there at first sight.  Slots are kept
+// for all steps, so that a member that starts when the others are done finds their answers.  With 1, 8 or 32 compute units held by another
+// stream 4 000 x 50 008 bf16 takes 127 to 134 us with sums (600 to 1 006 with a slot ring of 16 steps, one load in flight and no waiting after
+// the first late answer; 133 to 137 in two passes), 20 000 rows 540 to 548 (1 900 to 4 700; 624 to 628).
 // A tag is the launch's number and the step's, so that what a slot held before is never taken for an answer: a launch writes every slot
 // that it reads, and its number, kept in state[0], is counted up by the last workgroup to finish (state[1] counts those).
 // What bounds it is the read of X, 6.5 TB/s over long parts (20 000 x 50 008 bf16, 2 GB, 301 us), and some 10 us to fill the chip and put
@@ -714,12 +718,11 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
 // What it took: the exchange in a wavefront of its own (loads return in order, so that polls behind a wavefront's own rows wait for
 // those: 113 us), two steps for it instead of one (100), rows per step times chunks per thread near eight (two rows instead of four 88),
 // no re-reading of the last row at the part's end (82).  Twice the wavefronts with half the chunks each: 107.
-constexpr int kCrewRing = 16;                            // steps; a member is at most two ahead of the others' answers unless they are late
 template <int XD, int VEC, int K, int R, bool NT>
 __global__ void __launch_bounds__(kCrewThreads + 64)
 rows_once_crew_kernel(const void *__restrict__ X, const float *__restrict__ y, const float *__restrict__ w, const DevRun *__restrict__ parts,
                       const DevRun *__restrict__ runs, const int32_t *__restrict__ dst, float *__restrict__ rows, int d, int nq, int logistic,
-                      int num_parts, int members, uint64_t *slots, uint32_t *state, int patience)
+                      int num_parts, int members, uint64_t *slots, int ring_steps, uint32_t *state, int patience)
 {
     using C = Chunk<XD, VEC>;
     constexpr int TS = kCrewThreads, WAVES = TS / 64, SETS = 4, LAG = 2;
@@ -750,13 +753,46 @@ rows_once_crew_kernel(const void *__restrict__ X, const float *__restrict__ y, c
 
     if (wave == WAVES) {
         const uint32_t launch = __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        uint64_t *const ring = slots + static_cast<int64_t>(crew) * kCrewRing * members * R;
+        uint64_t *const ring = slots + static_cast<int64_t>(crew) * ring_steps * members * R;
         auto targets = [&](int row) { return y[part_begin + min(row + lane, total - 1)]; };
         float y_now = targets(0), y_ahead = targets(64); // of 64 rows each: a load per step would be waited for with the polls
         int y_row = 0;
+        // member j's part of the dot product of a row, as its wavefronts form it; as many chunks in flight as there are registers for
+        auto part_of_row = [&](int r, int j) {
+            constexpr int N = WAVES * K, U = K > 2 ? (N + 1) / 2 : N;
+            const int from_q = slice(j), to_q = slice(j + 1);
+            const void *row = row_ptr<XD>(X, part_begin + min(r, total - 1), d);
+            float p = 0.f, t[2] = {0.f, 0.f};
+            auto at = [&](int n) { return from_q + n / K * 64 + lane + n % K * TS; };
+#pragma unroll
+            for (int n0 = 0; n0 < N; n0 += U) {
+                typename C::raw_t x[U];
+                float wt[U][VEC];
+#pragma unroll
+                for (int u = 0; u < U && n0 + u < N; ++u) {
+                    const int k = (n0 + u) % K, e = k < K - 1 ? at(n0 + u) * VEC : chunk_offset<VEC>(min(at(n0 + u), to_q - 1), nq, d);
+                    x[u] = C::load(row, e);
+                    load_row<VEC>(w + e, wt[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < U && n0 + u < N; ++u) {
+                    const int q = at(n0 + u), k = (n0 + u) % K;
+                    float xv[VEC];
+                    C::widen(k < K - 1 ? x[u] : only(x[u], owned(q, to_q)), xv);
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v)
+                        t[k & 1] = fmaf(xv[v], k < K - 1 || (q < to_q && chunk_owns<VEC>(q, v, nq, d)) ? wt[u][v] : 0.f, t[k & 1]);
+                    if (k < K - 1) continue;
+                    p += group_sum<64>(t[0] + t[1]);
+                    t[0] = t[1] = 0.f;
+                }
+            }
+            return p;
+        };
+        int polls = patience;                            // left for what is late
         for (int i = 0; i < steps + LAG; ++i) {
             auto tag = [&](int step) { return launch << 20 | (static_cast<uint32_t>(step) & 0xfffffu); };
-            auto slot = [&](int step) { return ring + step % kCrewRing * members * R; };
+            auto slot = [&](int step) { return ring + (step & (ring_steps - 1)) * members * R; };
             __syncthreads();                             // the wavefronts' parts of step i are in red
             if (i < steps && lane < R) {
                 float p = 0.f;
@@ -766,38 +802,28 @@ rows_once_crew_kernel(const void *__restrict__ X, const float *__restrict__ y, c
             }
             const int step = i - (LAG - 1);
             if (step < 0 || step >= steps) continue;
-            const bool mine = lane < members * R;
-            uint64_t word = 0, late;
-            bool here = !mine;
-            for (int polls = 0;; ++polls) {
+            uint64_t word = 0;
+            bool here = lane >= members * R;
+            auto look = [&] {                            // which slots are still empty
                 if (!here) word = __hip_atomic_load(slot(step) + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 here = here || static_cast<uint32_t>(word >> 32) == tag(step);
-                late = __ballot(!here);
-                if (!late || polls >= patience) break;
-            }
-            float part_of = __uint_as_float(static_cast<uint32_t>(word));
-            if (late) patience = 0;
-            for (; late; late &= late - 1) {
-                const int at = __builtin_ctzll(late), from_q = slice(at / R), to_q = slice(at / R + 1);
-                const void *row = row_ptr<XD>(X, part_begin + min(step * R + at % R, total - 1), d);
-                float p = 0.f;
-                for (int i = 0; i < WAVES; ++i) {
-                    float t[2] = {0.f, 0.f};
-#pragma unroll 1
-                    for (int k = 0; k < K; ++k) {
-                        const int q = from_q + i * 64 + lane + k * TS, e = chunk_offset<VEC>(min(q, to_q - 1), nq, d);
-                        float xv[VEC], wt[VEC], sum = k & 1 ? t[1] : t[0];
-                        C::widen(only(C::load(row, e), owned(q, to_q)), xv);
-                        load_row<VEC>(w + e, wt);
-#pragma unroll
-                        for (int v = 0; v < VEC; ++v) sum = fmaf(xv[v], q < to_q && chunk_owns<VEC>(q, v, nq, d) ? wt[v] : 0.f, sum);
-                        if (k & 1) t[1] = sum;
-                        else t[0] = sum;
-                    }
-                    p += group_sum<64>(t[0] + t[1]);
+                return __ballot(!here);
+            };
+            uint64_t late = look();
+            if (!late) polls = patience;
+            for (; late && polls > 0; --polls) late = look();
+            for (; late; late = look()) {                // what another member has worked out meanwhile is in its slot
+                uint64_t choice = late;
+                for (int skip = member % __builtin_popcountll(late); skip > 0; --skip) choice &= choice - 1;
+                const int at = __builtin_ctzll(choice);
+                const float p = part_of_row(step * R + at % R, at / R);
+                if (lane == at) {
+                    word = static_cast<uint64_t>(tag(step)) << 32 | __float_as_uint(p);
+                    here = true;
+                    __hip_atomic_store(slot(step) + at, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-                if (lane == at) part_of = p;
             }
+            const float part_of = __uint_as_float(static_cast<uint32_t>(word));
             float z = 0.f;
             for (int j = 0; j < members; ++j) z += __shfl(part_of, j * R + (lane < R ? lane : 0), 64);
             const int at = step * R + (lane < R ? lane : 0) - y_row;
@@ -872,7 +898,7 @@ rows_once_crew_kernel(const void *__restrict__ X, const float *__restrict__ y, c
         for (int r = 0; r < R; ++r) finite = fmaf(p[r], 0.f, finite);
         // Lanes that count nothing of their last chunk, or not all of it, have weights of zero there, and infinity times zero is no number: once
         // more without.  Four rows at a time: 4 000 x 50 008 bf16 with sums 77.3 us; looked at after every row 82.5, bits masked on every row 78.6.
-        if (!whole && finite != 0.f) {
+        if (__builtin_expect(!whole && finite != 0.f, 0)) {
             unsigned at = off;
             asm volatile("" : "+v"(at));                 // worked out here: there are no registers to keep it from step to step
             const bits_t keep = owned(static_cast<int>(at / VEC) + (K - 1) * TS, q_end);
@@ -1826,7 +1852,7 @@ const OnceVariant kOnceVariantsWide[] = {
 };
 // several workgroups per row
 #define CR_OC(XD, VEC, K, R)                                                                            \
-    {XD, VEC, K, R, 0,                                                                                  \
+    {XD, VEC, K, R, 0, 0,                                                                               \
      {reinterpret_cast<const void *>(&rows_once_crew_kernel<XD, VEC, K, R, false>),                     \
       reinterpret_cast<const void *>(&rows_once_crew_kernel<XD, VEC, K, R, true>)}}
 const CrewVariant kCrewVariants[] = {
@@ -1909,14 +1935,22 @@ bool select_crew(int x_dtype, int64_t d, int units, CrewVariant *v)
     return best > 0.0;
 }
 
-int64_t crew_exchange_words(const CrewVariant &v) { return static_cast<int64_t>(kCrewRing) * v.members * v.rows_per_step; }
+// Steps whose slots are kept: all of a part's, so that a member that starts late finds every answer (4 000 rows: 32 steps, 512 KB of slots), or
+// the last 1 024 (some 2 ms of work).
+int crew_ring_steps(const CrewVariant &v, int64_t longest_part)
+{
+    int steps = 16;
+    while (steps < 1024 && static_cast<int64_t>(steps) * v.rows_per_step < longest_part) steps *= 2;
+    return steps;
+}
+int64_t crew_exchange_words(const CrewVariant &v) { return static_cast<int64_t>(v.ring_steps) * v.members * v.rows_per_step; }
 
 hipError_t launch_rows_once_crew(const CrewVariant &v, const void *X, const float *y, const float *w, const DevRun *parts, int num_parts,
                                  const DevRun *runs, const int32_t *dst, float *rows, int64_t d, int logistic, bool stream_past_caches,
                                  uint64_t *slots, uint32_t *state, int patience, hipStream_t stream)
 {
-    int di = static_cast<int>(d), nq = static_cast<int>((d + v.vec - 1) / v.vec), members = v.members;
-    void *args[] = {&X, &y, &w, &parts, &runs, &dst, &rows, &di, &nq, &logistic, &num_parts, &members, &slots, &state, &patience};
+    int di = static_cast<int>(d), nq = static_cast<int>((d + v.vec - 1) / v.vec), members = v.members, ring_steps = v.ring_steps;
+    void *args[] = {&X, &y, &w, &parts, &runs, &dst, &rows, &di, &nq, &logistic, &num_parts, &members, &slots, &ring_steps, &state, &patience};
     return hipLaunchKernel(v.fn[stream_past_caches ? 1 : 0], dim3((num_parts + 7) / 8 * 8 * members), dim3(kCrewThreads + 64), args, 0, stream);
 }
 
