@@ -1309,8 +1309,13 @@ int cr_gd_run(cr_plan_t *p, const void *X, const float *y, float *w, float *g, c
     if (rc != CR_OK) return rc;
     const int32_t N = p->tree.N;
     const bool side_by_side = cr::tree_side_by_side(p->shape, p->d, cr::Otherwise::kBatch);
-    const bool together = cr::tree_and_decode_together(p->shape, p->d) && !overlap(g, p->d, p->d_G, static_cast<int64_t>(p->slabs.size()) * p->d);
-    const bool among_messages = overlap(g, p->d, p->d_M, N * p->d) || overlap(w, p->d, p->d_M, N * p->d);
+    // vectors of the caller's that lie among the messages: everything in its place and in launches of its own, as the separate calls leave it
+    auto lies_there = [&](const void *x, int64_t floats) { return x && overlap(static_cast<const float *>(x), floats, p->d_M, N * p->d); };
+    const bool among_messages = lies_there(g, p->d) || lies_there(w, p->d) || lies_there(w_star, p->d) || lies_there(y, p->m) ||
+                                lies_there(X, (p->m * p->d * elem_size(p) + 3) / 4) || lies_there(metrics, 2 * static_cast<int64_t>(steps));
+    const bool one_for_two = overlap(w, p->d, g, p->d) || (w_star && (overlap(w_star, p->d, w, p->d) || overlap(w_star, p->d, g, p->d)));
+    const bool together = cr::tree_and_decode_together(p->shape, p->d) && !among_messages && !one_for_two &&
+                          !overlap(g, p->d, p->d_G, static_cast<int64_t>(p->slabs.size()) * p->d);
     note_last_sends(p, masks, steps);
     ProgramCounts counts[kProgramSlots];
     MaskTables tables;
@@ -1362,12 +1367,12 @@ int cr_aggregate_run(cr_plan_t *p, const float *G, int64_t G_step_stride, const 
     if (steps > 0) p->slabs_here = false;
     const int64_t more = std::max(0, steps - 1);
     const bool in_place = overlap(g, p->d + more * g_step_stride, G, static_cast<int64_t>(p->slabs.size()) * p->d + more * G_step_stride);
-    // one launch for several masks leaves the order in which workgroups decode open: vectors that overlap in part need it
-    const bool in_order = in_place || (g_step_stride > 0 && g_step_stride < p->d);
-    const bool together = cr::tree_and_decode_together(p->shape, p->d) && !in_place;
-    // vectors of the caller's that lie among the messages: everything in its place, as the separate calls leave it
+    // vectors of the caller's that lie among the messages: everything in its place and in launches of its own, as the separate calls leave it
     const bool among_messages = overlap(g, p->d + more * g_step_stride, p->d_M, N * p->d) ||
                                 overlap(G, static_cast<int64_t>(p->slabs.size()) * p->d + more * G_step_stride, p->d_M, N * p->d);
+    // one launch for several masks leaves the order in which workgroups decode open: vectors that overlap in part need it
+    const bool in_order = in_place || among_messages || (g_step_stride > 0 && g_step_stride < p->d);
+    const bool together = cr::tree_and_decode_together(p->shape, p->d) && !in_place && !among_messages;
     note_last_sends(p, masks, steps);
     ProgramCounts counts[kProgramSlots];
     MaskTables tables;

@@ -114,3 +114,78 @@ def test_vectors_among_the_messages():
     assert torch.equal(left[0], left[1])
     del ws
     cr.cr_plan_destroy(plan)
+
+
+# where the vector lies among the messages: a first-level row, a row of a worker further down, between two rows
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,n,s,d", [(2, 3, 1, 100), (2, 3, 1, 4_003), (1, 4, 1, 20_000), (2, 12, 2, 33_004)])
+@pytest.mark.parametrize("place", ["first", "below", "between"])
+def test_models_among_the_messages(L, n, s, d, place):
+    """The model of a training run lies where messages are written: the steps start from what the separate calls would find there."""
+    import torch
+
+    if L == 1 and place != "first":
+        pytest.skip("one level")
+    N, steps = sum(n ** l for l in range(1, L + 1)), 3
+    plan = cr.cr_plan_ex(L, n, s, 3 * N, d)
+    ws = cr.Workspace(plan)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    X, y, w0 = (torch.randn(shape, generator=gen, device="cuda") for shape in ((3 * N, d), (3 * N,), (d,)))
+    masks = _masks(np.random.default_rng(d), steps, N // n, n, s)
+    at = {"first": d, "below": (N - 2) * d, "between": (N - 2) * d + d // 2 // 4 * 4}[place]
+    w, g, left = ws.messages().view(-1)[at:at + d], torch.empty(d, device="cuda"), []
+    for run in (False, True):
+        ws.messages().fill_(7.0)
+        w.copy_(w0)
+        if run:
+            cr.cr_gd_run(plan, X, y, w, g, masks, 1e-6)
+        else:
+            for t in range(steps):
+                cr.cr_partial_grads(plan, X, y, w)
+                cr.cr_encode_tree(plan, masks[t])
+                cr.cr_decode_root(plan, g)
+                cr.cr_gd_update(plan, w, g, 1e-6)
+        cr.cr_synchronize(plan)
+        left.append((ws.messages().clone(), g.clone()))
+    assert torch.equal(left[0][0], left[1][0]) and torch.equal(left[0][1], left[1][1])
+    del ws, w
+    cr.cr_plan_destroy(plan)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("L,n,s,d", [(2, 3, 1, 100), (2, 3, 1, 4_003), (2, 12, 2, 33_001)])
+def test_one_vector_for_two(L, n, s, d):
+    """The reference model, the model and the gradient may be one vector: the values are those of a launch each for decode, step and measures."""
+    import torch
+
+    N, steps, lr = sum(n ** l for l in range(1, L + 1)), 3, 1e-6
+    plan = cr.cr_plan_ex(L, n, s, 3 * N, d)
+    ws = cr.Workspace(plan)
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    X, y, w0 = (torch.randn(shape, generator=gen, device="cuda") for shape in ((3 * N, d), (3 * N,), (d,)))
+    masks = _masks(np.random.default_rng(d), steps, N // n, n, s)
+    metrics = torch.empty(steps, 2, device="cuda")
+    for g_is_w, star in ((True, None), (False, "w"), (False, "g"), (True, "w")):
+        want_w = w0.clone()
+        want_g = want_w if g_is_w else torch.empty(d, device="cuda")
+        want = []
+        for t in range(steps):
+            cr.cr_partial_grads(plan, X, y, want_w)
+            cr.cr_encode_tree(plan, masks[t])
+            cr.cr_decode_root(plan, want_g)
+            cr.cr_synchronize(plan)
+            before = want_w.double()
+            cr.cr_gd_update(plan, want_w, want_g, lr)
+            cr.cr_synchronize(plan)
+            after = want_w.double()
+            ref = {None: None, "w": after, "g": want_g.double()}[star]
+            want.append([float((after - before).norm() ** 2 / before.norm() ** 2), -1.0 if ref is None else float((after - ref).norm() ** 2 / ref.norm() ** 2)])
+        w = w0.clone()
+        g = w if g_is_w else torch.empty(d, device="cuda")
+        cr.cr_gd_run(plan, X, y, w, g, masks, lr, {None: None, "w": w, "g": g}[star], metrics)
+        cr.cr_synchronize(plan)
+        assert torch.equal(w, want_w) and torch.equal(g, want_g), (g_is_w, star)
+        # sums of d squares in 64 bits, rounded to fp32 once
+        assert np.allclose(metrics.cpu().numpy(), np.array(want), rtol=1e-6, atol=0.0), (g_is_w, star)
+    del ws
+    cr.cr_plan_destroy(plan)
