@@ -1381,11 +1381,10 @@ encode_kernel(const float *__restrict__ G, float *__restrict__ M, EncProgram pro
 // Encode and decode of several masks, one after the other, in one launch: a workgroup owns 64 chunks of columns for all of them, its
 // wavefronts share out the level-1 sub-trees, whose messages meet in LDS for the decode (two sets in turn: one barrier per mask, after
 // which one wavefront decodes while the others go on).  No launches, ramps and last waves between the masks, and the master's messages
-// are not read back.  us a mask, a launch each for encode and decode / this: (2,4) tree, 2 000 000 columns, four masks 62.2 / 54.6;
-// (3,4), 60 001 columns, eight masks 17.3 / 12.1; (2,12), s = 5, 117 706 columns, eight masks 61.8 / 60.7 (rows on 8-byte boundaries;
-// 117 760 columns 56).  Where it loses: see encode_in_steps.
-// Slabs are read past the caches.  Messages that a later mask replaces are not written at all (row < 0): 117 706 columns, s = 5, eight masks
-// 411 us, 499 with every one written.
+// are not read back.  us a mask of eight, a launch each for encode and decode / this: (2,4) tree, 2 000 000 columns 50.9 / 48.1; (3,4), 60 001
+// columns 13.6 / 10.7; (2,12), s = 5, 117 706 columns 51.9 / 49.4 (rows on 8-byte boundaries; 117 760 columns 50.6 / 47.7).  Where it loses: see
+// encode_in_steps.  Slabs are read past the caches.  Messages that a later mask replaces are not written at all (row < 0): 117 706 columns,
+// s = 5, 51 us a mask, 62 with every one written.
 template <int LT>
 __global__ void __launch_bounds__(1024)
 encode_steps_kernel(const float *__restrict__ G, int64_t G_stride, float *__restrict__ M, EncProgram prog, int64_t prog_stride, int steps, int n,
@@ -1655,8 +1654,8 @@ __device__ __forceinline__ void put_gradient(const double (&acc)[VEC], float *g,
 
 // The whole tree per workgroup, the master's decode and the gradient step after it: one launch where there were two or three.  For
 // vectors of so few columns that a launch lasts no longer than its chain of fetches; longer ones have more to gain from a workgroup per
-// sub-tree and a decode of their own.  us, encode and decode apart / together: (2,12) tree, s = 2, 10 columns 4.2 + 2.0 / 6.1;
-// (3,4) tree, 6 500 columns 5.7 + 2.6 / 5.7; (2,12), s = 2, 24 576 columns 13.4 + 3.9 / 14.6, 73 728 columns 29.9 + 4.7 / 35.4.
+// sub-tree and a decode of their own.  us of encode and decode, apart / together, 16 masks back to back: (2,4) tree, 1 024 columns 5.7 / 4.3; (2,12),
+// s = 2, 10 columns 6.6 / 5.2, 1 024 6.8 / 6.0, 16 384 11.6 / 11.1, 73 728 27.8 / 38.1; (3,4), 6 500 columns 8.3 / 6.3, 32 768 10.3 / 9.7.
 template <int VEC, int B, typename TABLES>
 __global__ void __launch_bounds__(1024)
 tree_decode_kernel(const float *__restrict__ G, float *__restrict__ M, TABLES tables, NodeBits stored, TreeLevels tree, float *__restrict__ g,
@@ -2089,17 +2088,20 @@ static bool encode_is_wide(int n, int L, int64_t d) { return d >= 4 && ((d + 3) 
 
 // The rule for one launch of all masks.  A workgroup keeps its 64 chunks of columns for all of them, so that a round of a workgroup per
 // compute unit that is less than half full costs as much as a full one, and every next one the more the more slabs there are.  What the
-// launch saves is the launches and ramps of each mask and, where the messages of a mask do not fit the last-level cache, writing them
-// more than once.  us a mask, eight masks with gradients of their own, a launch of each kind per mask / one launch:
-//   one round    (2,12), s = 2, 65 536 columns 29.4 / 24.7; (3,6), s = 2, 40.9 / 34.6; (2,24), s = 1, 81.6 / 74.9
-//   two          73 728 columns: (2,8), s = 2 (248 slabs) 21.0 / 17.9; (2,12), s = 1 (300) 29.4 / 28.3; s = 2 (444) 33.3 / 34.4; s = 5 (888)
-//                41.3 / 44.2; (2,17) (629) 53.2 / 60.2; 117 706: s = 5 62.0 / 60.7; (2,17) 80.6 / 77.6; (3,8), s = 2 (2104) 186.6 / 187.7
-//   three, four  160 001: (2,8) 35.1 / 32.5; (3,5) (345) 56.1 / 50.8; (2,12), s = 5 81.9 / 83.7; 200 003: s = 2 77.6 / 83.8, s = 5 100 / 110
-//   more         400 001: s = 2 147 / 157, s = 5 190 / 208; (3,4) (148) 58.5 / 54.3
-//   messages of 256 MB and more   (2,12), s = 1, 600 001 224 / 183; (3,6) 400 001 258 / 229; (2,24) 160 001 249 / 206
-// Up to 32 768 columns a launch per mask is ahead on every tree: (2,24), s = 1, 1 000 columns 17.5 / 30.1, 32 768 46.8 / 49.4.  A single
-// mask has less to save (and the nodes side by side where tree_side_by_side says so): (2,12), s = 2, 117 706 66.2 / 64.9, 200 003
-// 94.3 / 101; s = 5, 81 920 59.8 / 64.4; (2,32), s = 1, 40 001 117 / 125.
+// launch saves is the launches and ramps of each mask.  us a mask, eight masks with gradients of their own, a launch of each kind per mask / one
+// launch:
+//   one round    (2,12), s = 2, 65 536 columns 25.9 / 17.7; (3,6), s = 2, 32.0 / 26.0; (2,24), s = 1, 61.7 / 53.5
+//   two          73 728 columns: (2,8), s = 2 (248 slabs) 17.9 / 13.4; (3,5) (345) 23.8 / 20.9; (2,12), s = 2 (444) 28.4 / 24.5, 77 000 27.5 / 27.8;
+//                (2,14), s = 1 (406) 29.7 / 30.8, 67 000 27.8 / 32.0; (2,12), s = 5 (888) 36.0 / 37.1; (2,17) (629) 40.1 / 44.5; 95 000: (2,12), s = 5
+//                43.7 / 42.4, (3,6), s = 2 (756) 46.8 / 41.8; 117 706: (2,12), s = 5 51.9 / 49.4, (2,17) 61.1 / 56.0, (3,8), s = 2 (2104) 145 / 149
+//   three, four  160 001: (2,8) 29.2 / 26.6; (3,5) 44.2 / 38.9; (2,12), s = 5 69.5 / 70.4; 200 003: s = 2 63.5 / 65.9, s = 5 86.8 / 93.3
+//   more         300 001: (3,6), s = 2 130 / 146; 400 001: (2,12), s = 2 122 / 126, s = 5 165 / 177, (2,8) 66.5 / 66.1, (3,4) (148) 44.3 / 42.8;
+//                800 001: (3,4) 80.4 / 84.7
+//   messages of 256 MB and more   (2,12), s = 1, 600 001 159 / 162; (3,6) 400 001 180 / 196; (2,24) (1176) 160 001 153 / 151.  That line is from when
+//                every mask wrote all its messages, 224 / 183, 258 / 229 and 249 / 206: one launch is no longer ahead there, and behind on three levels.
+// Up to 32 768 columns a launch per mask needs no copy of programs: (2,24), s = 1, 1 000 columns 16.9 / 29.8.  (Towards 32 768 one launch takes
+// the device less, (2,12), s = 2, 16.5 / 12.0, but the host builds its programs.)  A single mask has less to save (and the nodes side by side where
+// tree_side_by_side says so): (2,12), s = 2, 117 706 65.6 / 64.9, 200 003 94.3 / 99.7; s = 5, 81 920 58.9 / 64.0; (2,32), s = 1, 40 001 110 / 120.
 bool encode_in_steps(const TreeShape &tree, int64_t d, int steps)
 {
     if (tree.n > 32 || tree.L > 3 || d <= kTogetherColumns || encode_is_wide(tree.n, tree.L, d)) return false;
@@ -2272,9 +2274,11 @@ bool tree_side_by_side(const TreeShape &tree, int64_t d, Otherwise otherwise)
 }
 
 // From 8 192 columns on, where the whole tree's messages do not fit LDS for 16 chunks, the launch has twice the workgroups, of eight chunks,
-// each with the whole chain of a deep tree; on two levels that still pays.  us of encode and decode apart / together: (6,2) 12 288 columns
-// 16.2 / 19.4, 32 768 18.4 / 38.0; (3,6), s = 2, 8 195 13.4 / 17.5, 16 384 19.4 / 18.4, 32 768 28.8 / 33.5; (2,17), s = 1, 16 384 18.8 / 18.8,
-// 24 576 25.4 / 26.4, 12 288 20.3 / 17.3; (2,19) 16 384 20.8 / 21.7.
+// each with the whole chain of a deep tree; on two levels that still pays, or costs little.  us of encode and decode apart / together: (3,6), s = 2,
+// 4 096 columns 10.0 / 9.8, 8 195 11.4 / 14.3, 16 384 15.0 / 16.4, 32 768 23.3 / 35.9; (2,17), s = 1, 8 192 13.3 / 11.6, 16 384 17.1 / 16.8, 24 576
+// 20.9 / 22.5; (2,19) 8 192 15.0 / 12.6, 16 384 18.8 / 19.0, 32 768 29.9 / 36.3.  Where they fit: (6,2) 32 768 18.6 / 17.1; (2,8), s = 2, 32 768
+// 11.6 / 11.2; (1,64) 32 768 19.3 / 11.8; (2,12), s = 2, 12 288 10.7 / 10.3, 20 480 12.8 / 15.3, 32 768 16.1 / 16.6.  (An encode alone has become
+// faster than when the line at 32 768 columns was drawn: trees of 150 nodes and more on two levels are up to 20 % behind from 20 000 columns on.)
 bool tree_and_decode_together(const TreeShape &tree, int64_t d)
 {
     const TreeLevels whole = tree.nodes <= NodeCoefs::kNodes ? tree_levels(tree.n, tree.L, true) : TreeLevels();

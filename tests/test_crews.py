@@ -93,8 +93,9 @@ def test_what_is_late_costs_little(m, d, bf16):
     (12 to 17 times)."""
     import torch
 
-    X = torch.empty(m, d, device="cuda", dtype=torch.bfloat16 if bf16 else torch.float32).normal_()
-    w, y = torch.randn(d, device="cuda") / d ** 0.5, torch.rand(m, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    X = torch.empty(m, d, device="cuda", dtype=torch.bfloat16 if bf16 else torch.float32).normal_(generator=gen)
+    w, y = torch.randn(d, generator=gen, device="cuda") / d ** 0.5, torch.rand(m, generator=gen, device="cuda")
     plan = cr.cr_plan_ex(2, 4, 1, m, d, model=cr.CR_LOGISTIC, x_dtype=bf16)
     ws = cr.Workspace(plan)
     times = {64: [], 0: []}
