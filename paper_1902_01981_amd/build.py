@@ -29,7 +29,8 @@ def build(verbose: bool = False) -> str:
         cmd += ["-c", os.path.join(CSRC, src), "-o", obj]
         _run(cmd, verbose)
         objs.append(obj)
-    _run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB] + objs, verbose)
+    # the interface and nothing else: helpers with plain names would meet a program's own
+    _run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-Wl,--version-script=" + os.path.join(CSRC, "exports.map"), "-o", LIB] + objs, verbose)
     return LIB
 
 

@@ -18,6 +18,7 @@
 #include "gc_design.h"
 #include "kernels.h"
 #include "latency_model.h"
+#include "testing.h"
 #include "tree_plan.h"
 
 namespace {
@@ -1569,7 +1570,6 @@ int cr_synchronize(cr_plan_t *p)
     return CR_OK;
 }
 
-// Not part of the interface: how often a workgroup of a crew asks for what another has not published yet.  Tests take the waiting away.
 int cr_testing_patience(cr_plan_t *p, int polls)
 {
     if (!p || polls < 0) return CR_E_INVAL;
