@@ -133,7 +133,9 @@ int cr_plan_decode_row(const cr_plan_t *plan, const uint8_t *flags /* host, n */
  *                          hold it, and adds a run up in fp64 (all but the up to four rows it has in hand at a time).  Rows of more
  *                          than 24576 columns take one pass where their weights fit LDS (34816 columns fp32, 36864 bf16), X is
  *                          large against the rows that its parts put away (48 MB at least) and `value` is at most a compute unit's
- *                          share of the rows; else two passes, the second cut into parts of rows and blocks of columns.
+ *                          share of the rows.  Wider ones, up to 114688 columns fp32 and 172032 bf16, take one pass too, shared by 2 to
+ *                          16 workgroups, a part per crew of them (but for some small X); else two passes, the second cut into parts of
+ *                          rows and blocks of columns.
  *                          CR_ROWS_WHOLE_RANGES as value (d <= 24576): a workgroup per distinct slab range, which it adds up whole; rows
  *                          of ranges that overlap are then formed once per range.
  * With the first two every holder of a row does its own arithmetic on it, as separate workers would: they are there to measure what
@@ -166,7 +168,9 @@ int cr_simulate_iteration(const cr_plan_t *plan, double a, double mu, double t_c
  * The workspace holds the device tables, 16 encode programs (for trees and vectors whose encode takes programs), the stage-1 partial rows, the slab gradients
  * G[S][d] (not for CR_AGGREGATE_ONLY) and the messages M[N][d], all fp32 rows of d floats.  dev_ptr must be 256-byte aligned and stay valid while the plan
  * is used; hip_stream is a hipStream_t (NULL = the default stream).  cr_bind_workspace copies the tables synchronously, in one copy.
- * The tables of stage 1 must stay as bound.  A call on slab gradients of the caller's (cr_load_partial_grads, cr_aggregate_run) relies on
+ * The tables of stage 1 must stay as bound.  Beside them lies, where workgroups share rows, what they exchange in and the number of the
+ * launch: every cr_partial_grads changes it and the next one relies on it, so nobody else writes there between binding and the last call,
+ * and a program that saves the block and puts it back does so with all of it, between calls.  A call on slab gradients of the caller's (cr_load_partial_grads, cr_aggregate_run) relies on
  * nothing that the workspace held before it, so aggregation-only plans may take turns in one block. */
 int cr_workspace_bytes(cr_plan_t *plan, size_t *bytes);
 int cr_bind_workspace(cr_plan_t *plan, void *dev_ptr, size_t bytes, void *hip_stream);
@@ -207,6 +211,8 @@ int cr_gd_update(cr_plan_t *plan, float *w_dev, const float *g_dev, float lr);
  *   masks_host      steps x N bytes, one straggler mask per step; all are checked first: CR_E_UNDECODABLE before anything is enqueued
  *   w_dev, g_dev    d floats each; w is updated in place, g holds the last decoded gradient
  *   w_star_or_null  d floats (device): the reference model of the normalised error rate, or NULL
+ *                   (w, g and w* may be one vector, or lie among the messages: the values are those of the separate calls, and encode and
+ *                   decode take launches of their own then)
  *   metrics_or_null device, steps x 2 floats: [2t] = ||w_t+1 - w_t||^2 / ||w_t||^2 (relative error rate, eq. (6)),
  *                   [2t+1] = ||w_t+1 - w*||^2 / ||w*||^2 (normalised error rate, eq. (8); -1 without w*); NULL = not wanted.  The sums
  *                   behind them are formed by the launch that makes the step, the quotients by one launch per 16 steps */
@@ -221,7 +227,7 @@ int cr_gd_run(cr_plan_t *plan, const void *X_dev, const float *y_dev, float *w_d
  *   G_dev          device, S x d floats per step, 16-byte aligned; G_step_stride in floats (a multiple of 4): 0 = the same slabs every step
  *   masks_host     steps x N bytes; all are checked first: CR_E_UNDECODABLE before anything is enqueued
  *   g_dev          device, d floats per step; g_step_stride in floats: 0 = every step overwrites the same vector.  The vectors may lie
- *                  among the slabs or overlap in part: the steps then take launches of their own, in order
+ *                  among the slabs or the messages or overlap in part: the steps then take launches of their own, in order
  * Afterwards the plan is in the state the last step's three calls would have left (messages of the last mask). */
 int cr_aggregate_run(cr_plan_t *plan, const float *G_dev, int64_t G_step_stride, const uint8_t *masks_host, int steps, float *g_dev,
                      int64_t g_step_stride);
