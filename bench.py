@@ -65,9 +65,10 @@ def split_signature(info) -> str:
     return f"{kind}:{info.split_value}:team{info.stage1_team_size}x{info.stage1_teams_per_group}:staged{info.stage1_staged}"
 
 
-def load_traffic(workload: str, signature: str):
+def load_traffic(workload: str, signature: str, algorithmic=None):
     """HBM bytes per launch of the dominant kernel from the committed rocprofv3 --pmc summary, if it was taken with this kernel
-    and work split (else None and the reason)."""
+    and work split (else None and the reason).  algorithmic: this run's algorithmic bytes per launch, where they depend on how its
+    steps divide into calls (a call of several masks writes the messages of the last ones only): the record is scaled to them."""
     path = os.path.join(ROOT, "profiles", "hbm_traffic.json")
     if not os.path.exists(path):
         return None, "no traffic record"
@@ -77,7 +78,10 @@ def load_traffic(workload: str, signature: str):
         return None, "no traffic record for this workload"
     if entry.get("split_signature") not in (None, signature):
         return None, f"traffic record is for {entry.get('split_signature')}, this run uses {signature}"
-    return entry.get("bytes_per_launch"), entry.get("source")
+    traffic = entry.get("bytes_per_launch")
+    if traffic and algorithmic and entry.get("algorithmic_bytes_per_launch"):
+        traffic = round(traffic * algorithmic / entry["algorithmic_bytes_per_launch"])
+    return traffic, entry.get("source")
 
 
 def stats(ms: np.ndarray) -> dict:
@@ -283,7 +287,7 @@ def run_workload(name: str, steps: int, warmup: int, cpu_budget: float, args) ->
     dk = kernels[dominant]
     avg_s = dk["ms"]["avg"] * 1e-3
     signature = split_signature(info) if not aggregate else "encode"
-    traffic, traffic_source = load_traffic(name, signature)
+    traffic, traffic_source = load_traffic(name, signature, dk["algorithmic_bytes_per_launch"] if aggregate else None)
     holder_ms = every_holder_ms(cfg, X_dev, y_dev, w_dev) if not aggregate and s > 0 else None
     # yardstick: what a plain streaming read of the same buffer reaches on this device right now
     big = G_dev if aggregate else X_dev
