@@ -173,3 +173,66 @@ def test_infinities_in_the_last_chunk_of_a_slice(d, bf16, patience):
         assert float(((got - ref)[whole]).abs().max() / ref[whole].pow(2).mean().sqrt()) <= 3e-6
     del ws
     cr.cr_plan_destroy(plan)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,d,bf16", [(61, 50_001, 0), (700, 57_347, 1)])
+def test_replays_of_a_captured_launch(m, d, bf16):
+    """The number of a launch is kept on the device: replays, with other weights each and calls outside the graph in between, give the bits of
+    plain calls."""
+    import torch
+
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    X = torch.empty(m, d, device="cuda", dtype=torch.bfloat16 if bf16 else torch.float32).normal_(generator=gen)
+    y = torch.randn(m, generator=gen, device="cuda")
+    ws_of_seed = [torch.randn(d, generator=gen, device="cuda") / d ** 0.5 for _ in range(4)]
+    w, stream = torch.empty(d, device="cuda"), torch.cuda.Stream()
+    plan = cr.cr_plan_ex(1, 3, 1, m, d, x_dtype=bf16)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        ws = cr.Workspace(plan)
+        want = []
+        for v in ws_of_seed:
+            w.copy_(v)
+            cr.cr_partial_grads(plan, X, y, w)
+            want.append(ws.slab_grads().clone())
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            cr.cr_partial_grads(plan, X, y, w)
+        for i in (0, 1, 2, 3, 1, 0):
+            w.copy_(ws_of_seed[i])
+            ws.slab_grads().fill_(float("nan"))
+            graph.replay()
+            stream.synchronize()
+            assert torch.equal(ws.slab_grads(), want[i])
+            if i % 2:
+                cr.cr_partial_grads(plan, X, y, w)
+                cr.cr_synchronize(plan)
+                assert torch.equal(ws.slab_grads(), want[i])
+    del graph, ws
+    cr.cr_plan_destroy(plan)
+
+
+@pytest.mark.gpu
+def test_more_launches_than_numbers():
+    """A tag has 12 bits for the launch: around the 4 096th launch, with other weights each, nothing of an earlier launch is taken for an answer."""
+    import torch
+
+    m, d = 12, 50_001
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    X, y = torch.randn(m, d, generator=gen, device="cuda"), torch.randn(m, generator=gen, device="cuda")
+    w = [torch.randn(d, generator=gen, device="cuda") / d ** 0.5 for _ in range(3)]
+    plan = cr.cr_plan_ex(1, 3, 1, m, d)
+    ws = cr.Workspace(plan)
+    want = []
+    for v in w:
+        cr.cr_partial_grads(plan, X, y, v)
+        want.append(ws.slab_grads().clone())
+    for i in range(4_110):
+        cr.cr_partial_grads(plan, X, y, w[i % 3])
+        if i > 4_080:
+            cr.cr_synchronize(plan)
+            assert torch.equal(ws.slab_grads(), want[i % 3]), i
+    del ws
+    cr.cr_plan_destroy(plan)
