@@ -181,7 +181,8 @@ int cr_bind_workspace(cr_plan_t *plan, void *dev_ptr, size_t bytes, void *hip_st
  *   One pass over X as long as a row fits the registers of a workgroup (d <= 24576, whether or not d is a multiple of the 16-byte
  *   chunk) or its weights LDS beside them (34816 fp32, 36864 bf16, X of 48 MB or more
  *   depending on the tree), or the registers of up to 16 workgroups (114688 fp32, 172032 bf16, but for some
- *   small X); other rows take two passes.  Every slab of every worker is written; what the workers that hold a row have in common is
+ *   small X); other rows take two passes.  With CR_LOGISTIC an infinite entry of X reaches its own column of the slabs and no other
+ *   (sigmoid(+-inf) is 0 or 1), but under the splits that do every holder's arithmetic.  Every slab of every worker is written; what the workers that hold a row have in common is
  *   formed once for all of them unless the split says otherwise (see cr_plan_set_split).
  * cr_load_partial_grads: use caller-supplied slab gradients G_dev[S][d] (fp32, 16-byte aligned) in place of stage 1;
  *   the buffer is read in place by cr_encode_tree and must stay valid until then.

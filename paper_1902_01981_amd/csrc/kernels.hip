@@ -109,6 +109,12 @@ template <int VEC> __device__ __forceinline__ bool chunk_owns(int q, int v, int 
     return q < nq - 1 || (q == nq - 1 && d - VEC + v >= (nq - 1) * VEC);
 }
 
+// Element v of chunk q if it belongs to it alone.  The dot products meet the others, which another lane counts, with weights of zero, which
+// is right for every number.  Infinity times zero is none: where a logistic dot product is not a number it is formed once more from these, by
+// the run where a wavefront forms its rows alone, by the step where a workgroup shares them (1 200 x 100, 20 steps 223 us with and without,
+// launches of 8 us up to 0.2 us more, 252 000 x 4 096 602 / 604).  The kernels that do every holder's rows separately leave it at the weights.
+template <int VEC> __device__ __forceinline__ float counted(float x, int q, int v, int nq, int d) { return chunk_owns<VEC>(q, v, nq, d) ? x : 0.f; }
+
 // ---- how a chunk of a row of X is fetched and widened to fp32 -------------------------------------------------
 // load(row, e): the chunk at element e of the row that starts at `row` (a wave-uniform pointer; e differs per lane);
 // load_once: the same for rows nobody else reads, with the non-temporal hint, so that they stream past the caches
@@ -464,10 +470,6 @@ rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const 
         const float *yb = y + run.row_begin;
         const int n = run.nrows;
         double acc[K][VEC];
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[k][v] = 0.0;
         // rows past the end of the run re-read its last row; they count for nothing
         auto load = [&](Step &s, int r0) {
 #pragma unroll
@@ -481,7 +483,7 @@ rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const 
                 for (int k = 0; k < K; ++k) s.x[r][k] = NT ? C::load_once(row, rel + off[k]) : C::load(row, rel + off[k]);
             }
         };
-        auto compute = [&](const Step &s, int r0) {
+        auto compute = [&](const Step &s, int r0, auto only_counted) {
             float z[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -491,7 +493,8 @@ rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const 
                     float xv[VEC];
                     C::widen(s.x[r][k], xv);
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) t = fmaf(xv[v], wv[k][v], t);
+                    for (int v = 0; v < VEC; ++v)
+                        t = fmaf(decltype(only_counted)::value ? counted<VEC>(xv[v], tl + k * LPR, v, nq, d) : xv[v], wv[k][v], t);
                 }
                 z[r] = group_sum<LPR>(t);
             }
@@ -543,16 +546,25 @@ rows_once_kernel(const void *__restrict__ X, const float *__restrict__ y, const 
                 }
             }
         };
-        Step a, b;
-        load(a, 0);
-        for (int r0 = 0;;) {
-            load(b, r0 + STEP);
-            compute(a, r0);
-            if ((r0 += STEP) >= n) break;
-            load(a, r0 + STEP);
-            compute(b, r0);
-            if ((r0 += STEP) >= n) break;
-        }
+        auto form = [&](auto only_counted) {
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) acc[k][v] = 0.0;
+            Step a, b;
+            load(a, 0);
+            for (int r0 = 0;;) {
+                load(b, r0 + STEP);
+                compute(a, r0, only_counted);
+                if ((r0 += STEP) >= n) break;
+                load(a, r0 + STEP);
+                compute(b, r0, only_counted);
+                if ((r0 += STEP) >= n) break;
+            }
+        };
+        form(std::false_type{});
+        // see counted(): a dot product that is not a number leaves no sum of its lane one
+        if (__builtin_expect(logistic && !__all(acc[0][0] == acc[0][0]), 0)) form(std::true_type{});
         store();
         if (next >= more) break;
         run = read_run(table(runs) + next++);
@@ -600,6 +612,7 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
             for (int i = 0; i < VEC / 4; ++i) wl[k][i][tl] = f4a{t[4 * i], t[4 * i + 1], t[4 * i + 2], t[4 * i + 3]};
     }
 
+    const bool ragged = logistic && d != K * TS * VEC;   // elements that no lane counts, or two have: see counted()
     struct Step {
         typename C::raw_t x[R][K];
         float yy[R];
@@ -628,7 +641,8 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
                 }
             }
         };
-        auto compute = [&](const Step &s, int r0) {
+        // the wavefronts' parts of the dot products of a step go to LDS
+        auto dots = [&](const Step &s, auto only_counted) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 float t[2] = {0.f, 0.f};                 // two chains: a multiply-add need not wait for the one before it
@@ -636,6 +650,9 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
                 for (int k = 0; k < K; ++k) {
                     float xv[VEC];
                     C::widen(s.x[r][k], xv);
+                    if (decltype(only_counted)::value && k == K - 1)
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) xv[v] = counted<VEC>(xv[v], tl + k * TS, v, nq, d);
                     if constexpr (WL) {
 #pragma unroll
                         for (int i = 0; i < VEC / 4; ++i) {
@@ -654,14 +671,32 @@ rows_once_team_kernel(const void *__restrict__ X, const float *__restrict__ y, c
                 if ((tl & 63) == 0) red[buf][r][wave] = dot;
             }
             __syncthreads();
+        };
+        auto compute = [&](const Step &s, int r0) {
+            dots(s, std::false_type{});
+            float z[R];
+            auto sums = [&] {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    z[r] = 0.f;
+#pragma unroll
+                    for (int i = 0; i < WAVES; ++i) z[r] += red[buf][r][i];
+                }
+            };
+            sums();
+            if (ragged) {
+                float finite = 0.f;                      // the same for all threads
+#pragma unroll
+                for (int r = 0; r < R; ++r) finite = fmaf(z[r], 0.f, finite);
+                if (__builtin_expect(__builtin_amdgcn_readfirstlane(finite != 0.f), 0)) {
+                    __syncthreads();                     // the sums have been read
+                    dots(s, std::true_type{});
+                    sums();
+                }
+            }
             float res[R];
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                float z = 0.f;
-#pragma unroll
-                for (int i = 0; i < WAVES; ++i) z += red[buf][r][i];
-                res[r] = r0 + r < n ? residual(z, s.yy[r], logistic) : 0.f;
-            }
+            for (int r = 0; r < R; ++r) res[r] = r0 + r < n ? residual(z[r], s.yy[r], logistic) : 0.f;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 float xv[R][VEC];
